@@ -3,7 +3,6 @@
 #include "dsa_internal.h"
 #include "attention_api.h"
 #include "predict_api.h"
-#include "predict_stream_api.h"
 #include "project_api.h"
 #include "threshold_api.h"
 

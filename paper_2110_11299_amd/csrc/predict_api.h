@@ -1,4 +1,4 @@
-// Host-side launchers of predict.hip (tiled predictor, row-max contraction, MFMA yardstick): each validates nothing (the ABI layer did) and enqueues kernels.
+// Host-side launchers of predict.hip and predict_split_*.hip (mask predictor, row-max contraction, MFMA yardstick): each validates nothing (the ABI layer did) and enqueues kernels.
 #pragma once
 
 #include "dsa_internal.h"
@@ -11,6 +11,12 @@ size_t predict_workspace_bytes(const dsa_shape &sh);
 hipError_t launch_rowmax(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *rowmax,
                          hipStream_t st);
 hipError_t launch_mfma_i8_stream(int blocks, int iters, int32_t *sink, hipStream_t st);
+// predict_split, one translation unit per projection dimension.
+hipError_t launch_split_k16(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
+hipError_t launch_split_k32(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
+hipError_t launch_split_k48(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
+hipError_t launch_split_k64(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
+hipError_t launch_split_any(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
 // Largest L the predict kernels accept.
 int predict_max_L();
 

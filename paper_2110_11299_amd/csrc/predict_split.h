@@ -1,0 +1,751 @@
+// The mask predictor (paper section 3.1: approximate scores S~ = Q~ K~^T and the per-unit top-k that becomes the mask;
+// section 5.1: a unit is a query row, or a group of 4 / 8 rows whose scores are summed).  Scores are exact integers, so
+// the selection is exact: larger score first, lower key index among equals, list ascending.  No score is ever stored:
+// the int8 contraction is cheap enough on the matrix cores to be swept twice.
+//
+// One workgroup of W wavefronts owns 16 * UT units of one head and the wavefronts split its keys.  Keys are the rows
+// (A operand), units the columns (B operand) of v_mfma_i32_16x16x64_i8; the key range is cut into 4 W lane ranges of
+// 32 * NW keys, and lane (c = lane % 16, g = lane / 16) of wavefront w holds, for unit c, the scores of range 4 w + g.
+//
+//   sweep 1    every lane keeps up to 32 maxima over disjoint key sets ("buckets").
+//   bounds     from a histogram of a unit's maxima in LDS two thresholds tl < th are read off, such that the keep-th
+//              largest score lies between them almost surely: the number of buckets that the x largest keys fall into
+//              is known to a few per cent (section "targets" on the host side).  For short ranges a bucket is one key
+//              and the bounds are certain.
+//   sweep 2    the keys are swept again with -tl and with -th as accumulator inputs: the signs that come out are two
+//              bitmaps, which stay in registers (NW words per lane and bitmap), and their counts.
+//   check      count(>= th) <= keep <= count(>= tl), and few enough keys between (the "band"): else the bracket is
+//              moved or cut in three and swept again.  This ends for any scores: the bracket shrinks until it holds a
+//              single score value, and a plateau of equal scores needs no score at all (its first keys are taken).
+//   band       only the keys between the thresholds (about 50 of 4096) get their scores recomputed, from K~ rows, 16
+//              lanes per unit; the exact threshold is found by bisection, ties go to the lower key.
+//   emission   every lane turns its words into key indices at its place in the unit's row, in LDS; the rows leave as
+//              one contiguous block.
+//
+// What bounds it: vector-ALU issue (half an operation per score in sweep 1, two in sweep 2, about 25 per candidate).
+// Splitting the keys rather than giving a wavefront whole units keeps the bitmaps in registers, needs a quarter of the
+// bucket registers per lane and gives every shape, the shortest included, four times the wavefronts.
+#pragma once
+
+#include "dsa_internal.h"
+#include "predict_api.h"
+#include "key_stream.h"
+
+#include <math.h>
+
+namespace dsa {
+namespace {
+
+constexpr int kTile = 16;               // units of one matrix instruction
+constexpr int kBins = 128;              // histogram bins per unit
+constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' bins start in different banks
+constexpr int kBandCap = 384;           // keys of one unit's band that are scored (INT4 codes: two plateaus of about 120 equal scores)
+constexpr int kBandSlots = kBandCap / 16;
+constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
+
+struct SplitArgs {
+    const int8_t *Qt, *Kt;
+    int32_t *idx;
+    int L, k, keep, vec;
+    int NW;                             // bitmap words per lane: a lane range is 32 * NW keys
+    int wgs_per_head;
+    int target_l, target_h;             // buckets that reach tl / th
+    int direct;                         // the rows do not fit LDS: indices go straight to memory
+};
+
+// LDS of a workgroup, in bytes from the start (every part a multiple of 16).
+struct SplitLds {
+    unsigned tot, q, hist, list, bytes;
+    __host__ __device__ SplitLds(int W, int UT, int NW, int k, bool group, int keep, bool direct)
+    {
+        const unsigned U = kTile * UT;
+        tot = 6 * U * 4;                                        // [6][U]: tl, th, need, band count, and two spare
+        q = tot + 2 * W * U * 4;                                // [2][W][U]
+        hist = q + U * (group ? 2 : 1) * (k + 16);              // [U][parts][k + 16]
+        const unsigned h = U * kBinStride * 4, s = UT * NW * W * kWave * 4;
+        list = hist + (h > s ? h : s);                          // [U][bins], later the selected band bits [UT][NW][threads]
+        bytes = list + U * kBandCap * 2;                        // [U][kBandCap]
+        const unsigned rows = hist + (direct ? 0 : (U * keep * 2 + 16 + 15) / 16 * 16);   // image of the index rows, last
+        if (rows > bytes) bytes = rows;
+    }
+};
+
+// Sum / maximum over the 16 lanes of a row (DPP).
+__device__ __forceinline__ int row_sum(int x)
+{
+    x += dpp_move<kDppXor1>(x);
+    x += dpp_move<kDppXor2>(x);
+    x += dpp_move<kDppHalfMirror>(x);
+    return x + dpp_move<kDppMirror>(x);
+}
+__device__ __forceinline__ int row_max(int x)
+{
+    x = max(x, dpp_move<kDppXor1>(x));
+    x = max(x, dpp_move<kDppXor2>(x));
+    x = max(x, dpp_move<kDppHalfMirror>(x));
+    return max(x, dpp_move<kDppMirror>(x));
+}
+// Sum of x over the lanes above this one in its row of 16.
+__device__ __forceinline__ int row_sum_above(int x)
+{
+    int s = x;
+    s += __builtin_amdgcn_update_dpp(0, s, 0x101, 0xF, 0xF, true);   // row_shl:1
+    s += __builtin_amdgcn_update_dpp(0, s, 0x102, 0xF, 0xF, true);   // row_shl:2
+    s += __builtin_amdgcn_update_dpp(0, s, 0x104, 0xF, 0xF, true);   // row_shl:4
+    s += __builtin_amdgcn_update_dpp(0, s, 0x108, 0xF, 0xF, true);   // row_shl:8
+    return s - x;
+}
+
+// K: the projection dimension (16, 32, 48, 64), or 0 for any other (up to 128, two contraction steps).
+// GROUP: units are groups of vec rows.  NWM: most bitmap words per lane.
+template <int K, bool GROUP, int UT, int NWM>
+__global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitArgs a)
+{
+    constexpr int R = K == 16 ? 4 : K == 32 ? 2 : 1;     // keys side by side in a matrix row = tiles per row operand
+    constexpr int STEPS = K ? 1 : 2;                     // contraction steps of 64
+    constexpr int NS = 8 / R;                            // row operands of a group of 8 tiles (32 keys per lane range)
+    constexpr int NSB = NS < 4 ? NS : 4;                 // row operands of one batch of requests
+    constexpr int BPG = NS / NSB;                        // batches per group
+    constexpr int TB = NSB * R;                          // tiles per batch
+    constexpr int PARTS = GROUP ? 2 : 1;
+    constexpr int U = kTile * UT;
+    extern __shared__ __align__(16) unsigned char lds[];
+
+    const int k = K ? K : a.k;
+    const int L = a.L, keep = a.keep, NW = a.NW, Lr = 32 * NW;
+    const int T = blockDim.x, W = T / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int c = lane & 15, g = lane >> 4, h = 4 * wv + g;
+    const SplitLds at(W, UT, NW, k, GROUP, keep, a.direct);
+    int *s_tl = reinterpret_cast<int *>(lds), *s_th = s_tl + U, *s_need = s_th + U, *s_nb = s_need + U;
+    int *s_totl = reinterpret_cast<int *>(lds + at.tot), *s_toth = s_totl + W * U;       // [W][U] each
+    unsigned char *s_q = lds + at.q;
+    const int qstride = PARTS * (k + 16);
+    unsigned *hist = reinterpret_cast<unsigned *>(lds + at.hist);
+    uint16_t *list = reinterpret_cast<uint16_t *>(lds + at.list);
+
+    const unsigned wg = xcd_contiguous(blockIdx.x, gridDim.x);
+    const unsigned n = wg / (unsigned)a.wgs_per_head;
+    const int u0 = (int)(wg % (unsigned)a.wgs_per_head) * U;
+    const int G = GROUP ? L / a.vec : L;
+    const int nu = min(U, G - u0);
+    const int8_t *Kh = a.Kt + (size_t)n * L * k;
+    const int8_t *Qh = a.Qt + (size_t)n * L * k;
+
+    // ---- query side of every unit into LDS: the row, or the sum of the unit's rows as 128 hi + lo -----------------
+    for (int e = tid; e < U * (k / 4); e += T) {
+        const int u = e / (k / 4), c4 = e - u * (k / 4);
+        int lo = 0, hi = 0;
+        if (u < nu) {
+            if (GROUP) {
+                const int *row = reinterpret_cast<const int *>(Qh + (size_t)(u0 + u) * (a.vec * k)) + c4;
+                int sum[4] = {0, 0, 0, 0};
+                for (int r = 0; r < a.vec; ++r) add_bytes(sum, row[r * (k / 4)]);
+                split_sums(sum, lo, hi);
+            } else {
+                lo = reinterpret_cast<const int *>(Qh + (size_t)(u0 + u) * k)[c4];
+            }
+        }
+        int *dst = reinterpret_cast<int *>(s_q + u * qstride) + c4;
+        dst[0] = lo;
+        if (GROUP) dst[(k + 16) / 4] = hi;
+    }
+    for (int e = tid; e < U * kBinStride / 4; e += T) reinterpret_cast<v4i *>(hist)[e] = v4i{0, 0, 0, 0};
+
+    // ---- key rows: lane (r = lane % 16, kb = lane / 16) fetches 16 bytes of matrix row r ---------------------------
+    const int sub = R == 4 ? g : R == 2 ? g >> 1 : 0, part = R == 4 ? 0 : R == 2 ? g & 1 : g;
+    int poff[STEPS];
+    bool plive[STEPS];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        plive[s] = 64 * s + 16 * part < k;
+        poff[s] = plive[s] ? 64 * s + 16 * part : 0;
+    }
+    unsigned row0 = (unsigned)((4 * wv + (c >> 2)) * Lr + 4 * sub + (c & 3)) * (unsigned)k;
+    const unsigned row_last = (unsigned)(L - 1) * (unsigned)k;
+    const unsigned slot_step = 4u * R * (unsigned)k;
+    const int batches = NW * BPG;
+    auto request = [&](v4i (&dst)[NSB][STEPS], int b) {          // rows beyond L (and batches beyond the range) read real ones
+        const unsigned first = row0 + (unsigned)(min(b, batches - 1) * NSB) * slot_step;
+#pragma unroll
+        for (int sl = 0; sl < NSB; ++sl) {
+            const unsigned row = min(first + sl * slot_step, row_last);
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) dst[sl][s] = *reinterpret_cast<const v4i *>(Kh + row + poff[s]);
+        }
+    };
+    v4i rows[2][NSB][STEPS];
+    request(rows[0], 0);
+    __syncthreads();
+
+    // unit operands: 16 bytes of the unit's query side where this lane's part of the key row is, zero in the tiles of
+    // the row operand that belong to other keys
+    v4i q[UT][PARTS][R][STEPS];
+#pragma unroll
+    for (int t = 0; t < UT; ++t)
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p)
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                const v4i piece = *reinterpret_cast<const v4i *>(s_q + (kTile * t + c) * qstride + p * (k + 16) + poff[s]);
+#pragma unroll
+                for (int i = 0; i < R; ++i) q[t][p][i][s] = (sub == i && plive[s]) ? piece : v4i{0, 0, 0, 0};
+            }
+
+    // scores of tile j of the batch against the units of operand t, each plus b
+    auto tile_scores = [&](const v4i (&buf)[NSB][STEPS], int j, int t, int b) -> v4i {
+        v4i acc = v4i{b, b, b, b};
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(buf[j / R][s], q[t][0][j % R][s], acc, 0, 0, 0);
+        if (GROUP) {
+            v4i top = v4i{0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) top = __builtin_amdgcn_mfma_i32_16x16x64_i8(buf[j / R][s], q[t][PARTS - 1][j % R][s], top, 0, 0, 0);
+            acc += top << 7;
+        }
+        return acc;
+    };
+
+    int nv = max(0, min(L - h * Lr, Lr));                          // real keys of this lane's range
+    const int nv_all = max(0, min(L - (4 * wv + 3) * Lr, Lr));           // of the wavefront's last range: the fewest
+
+    // ---- sweep 1: bucket maxima --------------------------------------------------------------------------------------
+    // A range of one group (NWM == 1) keeps every score; else tiles j and j ^ 2 share a bucket, and so do groups of the
+    // same parity: two scores per v_max3.
+    int bm[UT][32];
+#pragma unroll
+    for (int t = 0; t < UT; ++t)
+#pragma unroll
+        for (int b = 0; b < 32; ++b) bm[t][b] = INT32_MIN;
+    auto maxima = [&](const v4i (&buf)[NSB][STEPS], int w, auto par, auto half, auto masked) {
+        constexpr int PAR = decltype(par)::value, J0 = decltype(half)::value * TB;
+#pragma unroll
+        for (int t = 0; t < UT; ++t)
+#pragma unroll
+            for (int jb = 0; jb < TB; jb += 4)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int j = jb + e;
+                    v4i x = tile_scores(buf, j, t, 0), y = tile_scores(buf, j + 2, t, 0);
+                    if (decltype(masked)::value) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            x[i] = mask_beyond(x[i], 32 * w + 4 * (J0 + j) + i, nv);
+                            y[i] = mask_beyond(y[i], 32 * w + 4 * (J0 + j + 2) + i, nv);
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (NWM == 1) {
+                            bm[t][(4 * (J0 + j) + i) % 32] = x[i];
+                            bm[t][(4 * (J0 + j + 2) + i) % 32] = y[i];
+                        } else {
+                            int &m = bm[t][16 * PAR + ((J0 + jb) / 4 % 2) * 8 + 4 * e + i];
+                            m = max(max(x[i], y[i]), m);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+    };
+    {
+        auto group = [&](int w, auto par) {
+            constexpr int PAR = decltype(par)::value;
+            auto batch = [&](auto half) {
+                constexpr int HB = decltype(half)::value, P = BPG == 2 ? HB : PAR;
+                request(rows[P ^ 1], w * BPG + HB + 1);
+                if (32 * (w + 1) <= nv_all) maxima(rows[P], w, par, half, std::false_type{});
+                else maxima(rows[P], w, par, half, std::true_type{});
+            };
+            batch(std::integral_constant<int, 0>{});
+            if constexpr (BPG == 2) batch(std::integral_constant<int, 1>{});
+        };
+        if (NWM == 1) {
+            group(0, std::integral_constant<int, 0>{});
+        } else {
+            for (int w = 0; w < NW; w += 2) {
+                group(w, std::integral_constant<int, 0>{});
+                if (w + 1 < NW) group(w + 1, std::integral_constant<int, 1>{});
+            }
+        }
+    }
+    request(rows[0], 0);         // sweep 2 starts with what is on its way during the bounds
+
+    // ---- bounds -------------------------------------------------------------------------------------------------------
+    // The histogram's range is [smallest maximum, it + 3 * (mean - it)]: high-norm keys put a few maxima far above the
+    // others and would otherwise stretch the bins; they go to the last one.
+    int lo[UT], shift[UT];
+    {
+        float *s_sum = reinterpret_cast<float *>(s_toth);
+#pragma unroll
+        for (int t = 0; t < UT; ++t) {
+            int mn = INT32_MAX;
+            float sum = 0.f;
+#pragma unroll
+            for (int b = 0; b < 32; ++b) {
+                const bool real = bm[t][b] != INT32_MIN;
+                mn = real ? min(mn, bm[t][b]) : mn;
+                sum += real ? (float)bm[t][b] : 0.f;
+            }
+            mn = min(mn, __shfl_xor(mn, 16, kWave));
+            mn = min(mn, __shfl_xor(mn, 32, kWave));
+            sum += __shfl_xor(sum, 16, kWave);
+            sum += __shfl_xor(sum, 32, kWave);
+            if (g == 0) {
+                s_totl[wv * U + kTile * t + c] = mn;
+                s_sum[wv * U + kTile * t + c] = sum;
+            }
+        }
+        __syncthreads();
+        // buckets that hold a key: 32 (or min(nv, 32) single keys) per full range; the mean only places the range's end
+        const float per_bucket = NWM == 1 ? (float)min(L, 32 * 4 * W) : 32.f * fminf((float)(4 * W), (float)L / (float)Lr);
+#pragma unroll
+        for (int t = 0; t < UT; ++t) {
+            int mn = INT32_MAX;
+            float sum = 0.f;
+            for (int x = 0; x < W; ++x) {
+                mn = min(mn, s_totl[x * U + kTile * t + c]);
+                sum += s_sum[x * U + kTile * t + c];
+            }
+            lo[t] = mn;
+            const float range = fminf(fmaxf(3.f * (sum / per_bucket - (float)mn), 1.f), 1.0e9f);
+            shift[t] = max(0, 25 - (int)__clz((int)((unsigned)range | 1u)));     // range >> shift < kBins
+            unsigned *uh = hist + (kTile * t + c) * kBinStride;
+#pragma unroll
+            for (int b = 0; b < 32; ++b) {
+                const unsigned bin = min((unsigned)(max(bm[t][b], mn) - mn) >> shift[t], (unsigned)(kBins - 1));
+                if (bm[t][b] != INT32_MIN) atomicAdd(&uh[bin], 1u);
+            }
+            if (wv == 0 && g == 0) {
+                s_tl[kTile * t + c] = mn;
+                s_th[kTile * t + c] = shift[t];
+            }
+        }
+        __syncthreads();
+        // 16 lanes per unit, 8 bins each: th is the lowest bin edge that at most target_h maxima reach, tl the highest
+        // that at least target_l reach
+        for (int b4 = wv; b4 < 4 * UT; b4 += W) {
+            const int u = 4 * b4 + g;
+            const unsigned *uh = hist + u * kBinStride + 8 * c;
+            const v4i x = *reinterpret_cast<const v4i *>(uh), y = *reinterpret_cast<const v4i *>(uh + 4);
+            const int bins[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+            int suffix = row_sum_above(((bins[0] + bins[1]) + (bins[2] + bins[3])) + ((bins[4] + bins[5]) + (bins[6] + bins[7])));
+            int edge_h = kBins, edge_l = -1;             // in this lane: lowest edge with suffix <= target_h, highest with >= target_l
+#pragma unroll
+            for (int e = 7; e >= 0; --e) {
+                suffix += bins[e];                        // maxima in bins >= 8 c + e
+                if (suffix <= a.target_h) edge_h = 8 * c + e;
+                if (suffix >= a.target_l && edge_l < 0) edge_l = 8 * c + e;
+            }
+            edge_h = -row_max(-edge_h);
+            edge_l = row_max(edge_l);
+            const int base = s_tl[u], sh = s_th[u];
+            const int top = (GROUP ? a.vec : 1) * k * 16384 + 1;             // above every score
+            if (c == 0) {
+                s_tl[u] = base + (max(edge_l, 0) << sh);
+                s_th[u] = edge_h == kBins ? top : base + (edge_h << sh);
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- sweep 2: bitmaps of score >= tl and score >= th, until every unit's bracket is good ---------------------------
+    const int smax = (GROUP ? a.vec : 1) * k * 16384;
+    int tl[UT], th[UT], blo[UT], bhi[UT], nblo[UT], nbhi[UT];
+#pragma unroll
+    for (int t = 0; t < UT; ++t) {
+        tl[t] = s_tl[kTile * t + c];
+        th[t] = max(s_th[kTile * t + c], tl[t] + 1);
+        blo[t] = -smax;
+        nblo[t] = L;
+        bhi[t] = smax + 1;
+        nbhi[t] = 0;
+    }
+    unsigned wl[UT][NWM], wh[UT][NWM];
+    int nl[UT], nh[UT], band0[UT];                 // counts of the unit; band keys in the ranges before this lane's
+    for (int tries = 0;; ++tries) {
+        int cl[UT], ch[UT];
+#pragma unroll
+        for (int t = 0; t < UT; ++t) cl[t] = ch[t] = 0;
+        // the sweep's addresses and masks are the same in every round: computed ahead for all words they would fill the
+        // registers, so the compiler is kept from seeing it
+        asm volatile("" : "+v"(row0), "+v"(nv));
+#pragma unroll
+        for (int w = 0; w < NWM; ++w) {
+            if (w < NW) {
+#pragma unroll
+                for (int t = 0; t < UT; ++t) wl[t][w] = wh[t][w] = 0u;
+#pragma unroll
+                for (int hb = 0; hb < BPG; ++hb) {
+                    constexpr int two = BPG == 2 ? 1 : 0;
+                    const int P = two ? hb : w & 1;
+                    request(rows[P ^ 1], w * BPG + hb + 1);
+#pragma unroll
+                    for (int j = 0; j < TB; ++j)
+#pragma unroll
+                        for (int t = 0; t < UT; ++t) {
+                            const v4i x = tile_scores(rows[P], j, t, -tl[t]);
+                            v4i y;
+                            if (GROUP) {
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) y[i] = x[i] - (th[t] - tl[t]);
+                            } else {
+                                y = tile_scores(rows[P], j, t, -th[t]);
+                            }
+                            shift_in_signs(wl[t][w], x);
+                            shift_in_signs(wh[t][w], y);
+                            if (j % 2 == 1) __builtin_amdgcn_sched_barrier(0);      // else every tile's scores live at once
+                        }
+                }
+                const int left = nv - 32 * w;                            // real keys of this word
+                const unsigned real = left >= 32 ? ~0u : left <= 0 ? 0u : (1u << left) - 1u;
+#pragma unroll
+                for (int t = 0; t < UT; ++t) {
+                    wl[t][w] = ~__brev(wl[t][w]) & real;                 // the first key of the word was shifted in first
+                    wh[t][w] = ~__brev(wh[t][w]) & real;
+                    cl[t] += __popc(wl[t][w]);
+                    ch[t] += __popc(wh[t][w]);
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < UT; ++t) wl[t][w] = wh[t][w] = 0u;
+            }
+        }
+        request(rows[0], 0);
+#pragma unroll
+        for (int t = 0; t < UT; ++t) {
+            // (count(>= tl) << 16 | count(>= th)) of the unit's ranges in this wavefront: at most 8192 each
+            const int mine = cl[t] << 16 | ch[t];
+            int all;
+            const int before = unit_excl_scan(mine, g, &all);
+            band0[t] = (before >> 16) - (before & 0xffff);
+            if (g == 0) s_totl[wv * U + kTile * t + c] = all;
+        }
+        __syncthreads();
+        bool again = false;
+#pragma unroll
+        for (int t = 0; t < UT; ++t) {
+            nl[t] = nh[t] = 0;
+            for (int x = 0; x < W; ++x) {
+                const int v = s_totl[x * U + kTile * t + c];
+                const int vl = v >> 16, vh = v & 0xffff;
+                nl[t] += vl;
+                nh[t] += vh;
+                band0[t] += x < wv ? vl - vh : 0;
+            }
+            const bool good = nh[t] == keep || (nh[t] < keep && nl[t] >= keep && (nl[t] - nh[t] <= kBandCap || th[t] - tl[t] == 1));
+            if (!good) {
+                again = true;
+                const int width = th[t] - tl[t];
+                const bool low = nl[t] < keep, high = nh[t] > keep;      // T lies below tl / at or above th
+                if (low) { bhi[t] = tl[t]; nbhi[t] = nl[t]; }
+                else if (high) { blo[t] = th[t]; nblo[t] = nh[t]; }
+                else { blo[t] = tl[t]; nblo[t] = nl[t]; bhi[t] = th[t]; nbhi[t] = nh[t]; }
+                const int span = bhi[t] - blo[t];
+                if (span == 1 || nblo[t] - nbhi[t] <= kBandCap) {
+                    tl[t] = blo[t];
+                    th[t] = bhi[t];
+                } else if (tries < 2 && low) {           // just missed: a bracket of four times the width beside it
+                    th[t] = bhi[t];
+                    tl[t] = max(blo[t], th[t] - 4 * min(width, 1 << 24));
+                } else if (tries < 2 && high) {
+                    tl[t] = blo[t];
+                    th[t] = min(bhi[t], tl[t] + 4 * min(width, 1 << 24));
+                } else {                                 // the middle third (at least one value): T's bracket shrinks whatever comes out
+                    tl[t] = blo[t] + span / 3;
+                    th[t] = tl[t] + max(1, span / 3);
+                }
+            }
+        }
+        // every wavefront sees all units: the same outcome everywhere
+        if (__ballot(again) == 0) break;
+        __syncthreads();
+    }
+
+    // ---- band list: keys between the thresholds, in key order -----------------------------------------------------------
+    // A unit whose bracket is one score value wide takes its first keys of that value and needs no scores.
+    bool scored[UT];
+#pragma unroll
+    for (int t = 0; t < UT; ++t) {
+        scored[t] = nh[t] < keep && th[t] - tl[t] != 1;
+        uint16_t *ul = list + (kTile * t + c) * kBandCap;
+        int pos = band0[t];
+#pragma unroll
+        for (int w = 0; w < NWM; ++w) {
+            if (w < NW) {
+                unsigned m = scored[t] ? wl[t][w] & ~wh[t][w] : 0u;
+                const int code1 = (h << kPosBits) + 32 * w - 1;
+                while (__ballot(m != 0u) != 0) {
+                    if (m) ul[pos] = (uint16_t)(code1 + __ffs(m));       // pos < nl - nh <= kBandCap
+                    pos += m != 0u;
+                    m &= m - 1u;
+                }
+            }
+        }
+        if (wv == 0 && g == 0) {
+            s_tl[kTile * t + c] = tl[t];
+            s_th[kTile * t + c] = th[t];
+            s_need[kTile * t + c] = keep - nh[t];
+            s_nb[kTile * t + c] = scored[t] ? nl[t] - nh[t] : 0;
+        }
+    }
+    unsigned *sel = hist;                          // [UT][NW][T] band keys that are kept: the histogram is dead
+    for (int e = tid; e < UT * NW * T / 4; e += T) reinterpret_cast<v4i *>(sel)[e] = v4i{0, 0, 0, 0};
+    __syncthreads();
+
+    // ---- band scores and exact threshold: 16 lanes per unit, four units at a time per wavefront -------------------------
+    for (int b4 = wv; b4 < 4 * UT; b4 += W) {
+        const int u = 4 * b4 + g;                  // this lane's unit here; c is its place in the row of 16
+        const int nb = s_nb[u], need = s_need[u], ulo = s_tl[u];
+        const int most = max(max(__builtin_amdgcn_readlane(nb, 0), __builtin_amdgcn_readlane(nb, 16)),
+                             max(__builtin_amdgcn_readlane(nb, 32), __builtin_amdgcn_readlane(nb, 48)));
+        if (most == 0) continue;
+        const uint16_t *ul = list + u * kBandCap;
+        const unsigned char *uq = s_q + u * qstride;
+        int sc[kBandSlots];
+        int peak = INT32_MIN;
+#pragma unroll
+        for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
+            if (16 * i0 < most) {
+                const int8_t *kr[4];
+                int s[4], sh[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned code = ul[max(min(c + 16 * (i0 + i), nb - 1), 0)];
+                    const int key = (int)(code >> kPosBits) * Lr + (int)(code & ((1u << kPosBits) - 1));
+                    kr[i] = Kh + (size_t)((unsigned)min(key, L - 1) * (unsigned)k);
+                    s[i] = sh[i] = 0;
+                }
+                auto piece = [&](int p) {
+                    v4i kk[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) kk[i] = *reinterpret_cast<const v4i *>(kr[i] + 16 * p);
+                    const v4i ql = *reinterpret_cast<const v4i *>(uq + 16 * p);
+                    const v4i qh = *reinterpret_cast<const v4i *>(uq + (GROUP ? k + 16 : 0) + 16 * p);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            s[i] = __builtin_amdgcn_sdot4(ql[x], kk[i][x], s[i], false);
+                            if (GROUP) sh[i] = __builtin_amdgcn_sdot4(qh[x], kk[i][x], sh[i], false);
+                        }
+                    if (K > 32) __builtin_amdgcn_sched_barrier(0);       // the rows of four keys do not fit the registers
+                };
+                if constexpr (K != 0) {
+#pragma unroll
+                    for (int p = 0; p < K / 16; ++p) piece(p);
+                } else {
+                    for (int p = 0; p < k / 16; ++p) piece(p);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int v = s[i] + 128 * sh[i];
+                    sc[i0 + i] = c + 16 * (i0 + i) < nb ? v : INT32_MIN;
+                    peak = max(peak, sc[i0 + i]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sc[i0 + i] = INT32_MIN;
+            }
+        }
+        // the need-th largest of the band: all its scores are >= tl and at least need of them exist
+        int lo_ = ulo, hi_ = nb ? max(row_max(peak), ulo) : ulo;
+        while (__ballot(lo_ < hi_) != 0) {
+            const int mid = (lo_ + hi_ + 1) >> 1;         // |scores| < 2^27
+            int cnt = 0;
+#pragma unroll
+            for (int i0 = 0; i0 < kBandSlots; i0 += 4)
+                if (16 * i0 < most) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) cnt += sc[i0 + i] >= mid;
+                }
+            const bool ge = row_sum(cnt) >= need;
+            lo_ = ge ? mid : lo_;
+            hi_ = ge ? hi_ : mid - 1;
+        }
+        const int Tx = lo_;
+        int gt = 0;
+#pragma unroll
+        for (int i = 0; i < kBandSlots; ++i) gt += sc[i] > Tx;
+        const int need_eq = need - row_sum(gt);
+        int eq_before = 0;
+        const unsigned below = (1u << c) - 1u;
+#pragma unroll
+        for (int i = 0; i < kBandSlots; ++i) {
+            if (16 * i < most) {
+                const bool eq = sc[i] == Tx && c + 16 * i < nb;
+                const unsigned meq = (unsigned)(__ballot(eq) >> (16 * g)) & 0xffffu;
+                const bool take = c + 16 * i < nb && (sc[i] > Tx || (eq && eq_before + __popc(meq & below) < need_eq));
+                eq_before += __popc(meq);
+                if (take) {
+                    const unsigned code = ul[c + 16 * i], hh = code >> kPosBits, pos = code & ((1u << kPosBits) - 1);
+                    const unsigned thread = (hh >> 2) * kWave + (hh & 3) * 16 + (u & 15);
+                    atomicOr(&sel[((u >> 4) * NW + (pos >> 5)) * T + thread], 1u << (pos & 31));
+                }
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- emission -----------------------------------------------------------------------------------------------------
+    int out0[UT];
+#pragma unroll
+    for (int t = 0; t < UT; ++t) {
+        const bool tie = nh[t] < keep && !scored[t];
+        int quota = max(0, keep - nh[t] - band0[t]);                 // ties this lane may still keep
+        int mine = 0;
+#pragma unroll
+        for (int w = 0; w < NWM; ++w) {
+            if (w < NW) {
+                const unsigned band = wl[t][w] & ~wh[t][w];
+                unsigned more = sel[(t * NW + w) * T + tid];
+                if (tie) {
+                    more = lowest_set_bits(band, quota);
+                    quota -= __popc(more);
+                }
+                wl[t][w] = wh[t][w] | more;
+                mine += __popc(wl[t][w]);
+            }
+        }
+        int all;
+        out0[t] = unit_excl_scan(mine, g, &all);
+        if (g == 0) s_totl[wv * U + kTile * t + c] = all;
+    }
+    __syncthreads();
+    uint16_t *image = reinterpret_cast<uint16_t *>(lds + at.hist);      // [U * keep] and a spare slot; everything there is dead
+    int32_t *out = a.idx + ((size_t)n * G + u0) * keep;
+#pragma unroll
+    for (int t = 0; t < UT; ++t) {
+        for (int x = 0; x < wv; ++x) out0[t] += s_totl[x * U + kTile * t + c];
+        const bool live = kTile * t + c < nu;
+        int pos = (kTile * t + c) * keep + out0[t];
+#pragma unroll
+        for (int w = 0; w < NWM; ++w) {
+            if (w < NW) {
+                unsigned m = live ? wl[t][w] : 0u;
+                const int key1 = h * Lr + 32 * w - 1;
+                if (!a.direct) {
+                    while (__ballot(m != 0u) != 0) {
+#pragma unroll
+                        for (int twice = 0; twice < 2; ++twice) {
+                            image[m != 0u ? pos : U * keep] = (uint16_t)(key1 + __ffs(m));
+                            pos += m != 0u;
+                            m &= m - 1u;
+                        }
+                    }
+                } else {
+                    while (m) {
+                        out[pos++] = key1 + __ffs(m);
+                        m &= m - 1u;
+                    }
+                }
+            }
+        }
+    }
+    if (a.direct) return;
+    __syncthreads();
+    const int total = nu * keep;
+    for (int e = 4 * tid; e < total; e += 4 * T) {
+        const uint2 four = *reinterpret_cast<const uint2 *>(image + e);
+        const int v[4] = {(int)(four.x & 0xffffu), (int)(four.x >> 16), (int)(four.y & 0xffffu), (int)(four.y >> 16)};
+        if (e + 4 <= total) {
+            *reinterpret_cast<int4 *>(out + e) = make_int4(v[0], v[1], v[2], v[3]);
+        } else {
+            for (int i = 0; e + i < total; ++i) out[e + i] = v[i];
+        }
+    }
+}
+
+// ---- host side -----------------------------------------------------------------------------------------------------------
+
+struct SplitPlan { int W, NW, target_l, target_h; };
+
+// Targets.  If a share p of a unit's keys lies above a threshold, a bucket of s keys reaches it with probability
+// 1 - (1 - p)^s; the number of buckets that reach it, given the number x of keys that do, has the mean D(x) below and a
+// variance that is the binomial one less what x explains.  tl is put where keep + z sigma keys are expected above it,
+// th where keep - z sigma are: with z = 3.5 a unit misses in about one case of 2000 (and is then swept again).
+inline void split_targets(int L, int keep, int W, int NW, int *target_l, int *target_h)
+{
+    if (NW == 1) {                       // every key is its own bucket
+        *target_l = keep;
+        *target_h = keep - 1;
+        return;
+    }
+    const int Lr = 32 * NW;
+    const double p = (double)keep / L, vx = L * p * (1.0 - p);
+    // two bucket sizes (group parity), each in `ranges` full lane ranges
+    const double ranges = (double)L / Lr;
+    const double size[2] = {2.0 * ((NW + 1) / 2), 2.0 * (NW / 2)}, count = 16.0 * ranges;
+    double binomial = 0, cov = 0;
+    for (double s : size) {
+        const double miss = pow(1.0 - p, s);
+        binomial += count * miss * (1.0 - miss);
+        cov += count * s * p * miss;
+    }
+    auto buckets = [&](double x) {
+        const double share = fmin(fmax(x / L, 0.0), 1.0);
+        double d = 0;
+        for (double s : size) d += count * (1.0 - pow(1.0 - share, s));
+        return d;
+    };
+    const double slope = vx > 0 ? fmax(cov / vx, 1e-6) : 1.0;
+    const double sigma = sqrt(fmax(binomial - (vx > 0 ? cov * cov / vx : 0.0), 0.0)) / slope;
+    const double reach = 3.5 * sigma + 1.0;
+    int l = (int)ceil(buckets(keep + reach)), h = (int)floor(buckets(keep - reach));
+    if (keep - reach < 1.0) h = 0;
+    const int most = (int)(2.0 * count);
+    l = l > most ? most : l < 1 ? 1 : l;
+    h = h > l - 1 ? l - 1 : h;
+    *target_l = l;
+    *target_h = h;
+}
+
+inline SplitPlan split_plan(const dsa_shape &sh)
+{
+    SplitPlan p{};
+    const long long tiles = (long long)sh.B * sh.H * ((sh.L / sh.vec + kTile - 1) / kTile);
+    p.W = sh.L <= 128 ? 1 : sh.L <= 256 ? 2 : sh.L <= 4096 ? 4 : sh.L <= 16384 ? 8 : 16;
+    if (p.W == 4 && sh.L > 512 && 4 * tiles < 4096) p.W = 8;
+    p.NW = (sh.L + 128 * p.W - 1) / (128 * p.W);
+    split_targets(sh.L, sh.keep, p.W, p.NW, &p.target_l, &p.target_h);
+    return p;
+}
+
+template <int K, bool GROUP, int UT, int NWM>
+hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t *Qt, const int8_t *Kt, int32_t *idx,
+                          hipStream_t st)
+{
+    SplitArgs a{};
+    a.Qt = Qt; a.Kt = Kt; a.idx = idx;
+    a.L = sh.L; a.k = sh.k; a.keep = sh.keep; a.vec = sh.vec;
+    a.NW = p.NW;
+    a.wgs_per_head = (sh.L / sh.vec + kTile * UT - 1) / (kTile * UT);
+    a.target_l = p.target_l;
+    a.target_h = p.target_h;
+    a.direct = (size_t)kTile * UT * sh.keep * 2 > 128 * 1024;
+    const size_t lds = SplitLds(p.W, UT, p.NW, sh.k, GROUP, sh.keep, a.direct != 0).bytes;
+    auto kern = predict_split<K, GROUP, UT, NWM>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds)) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)sh.B * sh.H * a.wgs_per_head), dim3(p.W * kWave), lds, st, a);
+    return hipGetLastError();
+}
+
+template <int K, bool GROUP>
+hipError_t launch_split_g(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st)
+{
+    const SplitPlan p = split_plan(sh);
+    if (p.NW == 1) return launch_split_t<K, GROUP, 1, 1>(sh, p, Qt, Kt, idx, st);
+    if (p.NW <= 4) return launch_split_t<K, GROUP, 1, 4>(sh, p, Qt, Kt, idx, st);
+    if (p.NW <= 8) return launch_split_t<K, GROUP, 1, 8>(sh, p, Qt, Kt, idx, st);
+    return launch_split_t<K, GROUP, 1, 16>(sh, p, Qt, Kt, idx, st);
+}
+
+template <int K>
+hipError_t launch_split_k(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st)
+{
+    if (sh.vec == 1) return launch_split_g<K, false>(sh, Qt, Kt, idx, st);
+    return launch_split_g<K, true>(sh, Qt, Kt, idx, st);
+}
+
+}  // namespace
+}  // namespace dsa

@@ -1,0 +1,76 @@
+"""The key-splitting mask predictor at the sizes where its plan changes (one key group per lane range, odd numbers of
+groups, 1 to 16 wavefronts), at the edges of keep, and on score orders for which its first guess of the threshold
+bracket is wrong, so that it has to sweep again.  Masks are whole numbers: every one is compared exactly."""
+import numpy as np
+import pytest
+
+import dsa_inputs as di
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dsa():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("these tests need the MI355X: run them with -m gpu on the GPU box")
+    import paper_2110_11299_amd as pkg
+    pkg.binding.lib()
+    return pkg
+
+
+def check(dsa, oracle, Qt, Kt, keep, vec, label):
+    import torch
+    B, H, L, k = Qt.shape
+    print(f"[split] {label} B={B} H={H} L={L} k={k} vec={vec} keep={keep}", flush=True)
+    sh = dsa.make_shape(B, H, L, 64, k, keep, vec, dsa.DSA_F32, 0.125)
+    got = dsa.dsa_predict_mask(sh, torch.from_numpy(Qt).cuda(), torch.from_numpy(Kt).cuda()).cpu().numpy().reshape(-1, keep)
+    units = np.unique(np.linspace(0, got.shape[0] - 1, min(got.shape[0], max(32, (1 << 24) // L)), dtype=np.int64))
+    want = oracle.predict_mask(Qt, Kt, keep, vec, units=units)
+    bad = int((got[units] != want).any(axis=1).sum())
+    assert bad == 0, f"{bad} of {len(units)} units differ"
+    assert (np.diff(got, axis=1) > 0).all() and got.min() >= 0 and got.max() < L
+
+
+# one key group per range (1, 2, 4, 8 wavefronts), one key more; 3 groups; 8 and 16 groups, a ragged last range
+@pytest.mark.parametrize("L", [127, 128, 129, 256, 257, 511, 512, 513, 1025, 1537, 4095, 4097, 8193, 16385])
+@pytest.mark.parametrize("k", [16, 32, 48, 64, 96])
+def test_lengths(dsa, oracle, L, k):
+    Qt, Kt = di.random_int8_case(L + k, 1, 2, L, k)
+    check(dsa, oracle, Qt, Kt, max(1, L // 20), 1, "length")
+    for vec in (4, 8):
+        Lv = L // vec * vec
+        check(dsa, oracle, np.ascontiguousarray(Qt[:, :, :Lv]), np.ascontiguousarray(Kt[:, :, :Lv]), max(1, Lv // 33), vec, "length")
+
+
+@pytest.mark.parametrize("L", [96, 512, 1600, 4096, 9000])
+def test_keep_edges(dsa, oracle, L):
+    Qt, Kt = di.random_int8_case(L, 1, 1, L, 32)
+    for keep in sorted({1, 2, 15, 16, 17, L // 3, L // 2, L - 1, L}):
+        check(dsa, oracle, Qt, Kt, keep, 1, "keep")
+
+
+@pytest.mark.parametrize("L,keep", [(700, 60), (4096, 205), (4096, 1500), (12000, 120)])
+def test_score_orders(dsa, oracle, L, keep):
+    """Scores that rise or fall with the key (the largest ones fill few buckets), a block of large ones, two values
+    per key parity, and one outlier far above the rest (the histogram's range)."""
+    k = 32
+    pos = np.arange(L)
+    orders = {
+        "rising": pos * 254 // L - 127,
+        "falling": 127 - pos * 254 // L,
+        "block": np.where((pos > L // 2) & (pos < L // 2 + 2 * keep), 100, -20),
+        "parity": np.where(pos % 2 == 0, 3, -3),
+        "outlier": np.where(pos == L // 3, 127, (pos * 7919) % 5),
+    }
+    rng = np.random.Generator(np.random.Philox(L + keep))
+    for name, v in orders.items():
+        Kt = np.zeros((1, 1, L, k), np.int8)
+        Kt[..., 0] = v
+        Kt[..., 1] = rng.integers(-2, 3, size=L)
+        Qt = np.zeros((1, 1, L, k), np.int8)
+        Qt[..., 0] = np.where(pos % 3 == 0, 127, np.where(pos % 3 == 1, -127, 1))
+        Qt[..., 1] = rng.integers(-1, 2, size=L)
+        for vec in (1, 8):
+            Lv = L // vec * vec
+            check(dsa, oracle, np.ascontiguousarray(Qt[:, :, :Lv]), np.ascontiguousarray(Kt[:, :, :Lv]), keep, vec, name)
