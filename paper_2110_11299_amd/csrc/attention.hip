@@ -407,24 +407,21 @@ __global__ __launch_bounds__(kRowWaves *kWave) void gather_probe(const T *__rest
     if (live) sink[(size_t)r * kWave + lane] = acc;
 }
 
-// Group kernel for the vector-wise mask with bfloat16 inputs.  The 8 query rows of a group share
-// one key list, so each gathered key / value row serves 8 rows and the products become small
-// dense contractions for the bf16 matrix cores (v_mfma_f32_16x16x32_bf16, fp32 accumulate).  One
-// wavefront owns one group.
-//   Scores: the gathered key rows are the A operand (16 keys per tile, loaded straight from
-//   global memory as 16-byte pieces: lane (r = lane%16, g = lane/16) holds key r, elements
-//   [8g, 8g+8) of each 32-element step), the 8 query rows (padded to 16) the B operand.  Lane
-//   (c, g) then owns, for query c, keys 4g..4g+3 of the tile.  Scaled scores go to LDS.
-//   Output: weights stay in the lane that owns them.  Over a 32-key step lane group g owns keys
-//   {4g+i} of the first tile and {16+4g+i} of the second: these 8 are its slots of the step's
-//   contraction index, so its packed bf16 weights ARE the A operand (query c, slots of g).  The
-//   32 gathered value rows go through LDS once and come back transposed as the B operand with
-//   the same slot order (lane (c, g): column c of the rows that are g's slots).
-// The weights are rounded to bfloat16 for the second product (relative 2^-9, inside the 2e-2
-// budget of bfloat16 inputs); scores, softmax statistics and accumulation are fp32.
+// Group kernel for the staged entry points (SDDMM, SpMM) of the vector-wise mask with bfloat16 inputs.  The 8 query rows of
+// a group share one key list, so each gathered key / value row serves 8 rows and the products become small dense
+// contractions for the bf16 matrix cores (v_mfma_f32_16x16x32_bf16, fp32 accumulate).  One wavefront owns one group.
+//   Scores: the gathered key rows are the A operand (16 keys per tile: lane (r = lane%16, g = lane/16) holds key r,
+//   elements [8g, 8g+8) of each 32-element step), the 8 query rows (padded to 16) the B operand.  Lane (c, g) then owns,
+//   for query c, keys 4g..4g+3 of the tile.  Scaled scores go to LDS and leave as whole rows.
+//   Output: over a 32-key step lane group g owns keys {4g+i} of the first tile and {16+4g+i} of the second: the weights of
+//   these 8, rounded to bfloat16 (relative 2^-9, inside the 2e-2 budget), are the A operand (query c, slots of g).  The
+//   32 gathered value rows go through LDS once and come back transposed (ds_read_tr16_b64) as the B operand with the same
+//   slot order (lane (c, g): column c of the rows that are g's slots).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 constexpr int kGroupWaves = 4;
 
@@ -432,7 +429,7 @@ constexpr int kGroupWaves = 4;
 // (The launch bound is twice the launched size: with at most 256 registers per lane the compiler
 // gives the matrix core plain VGPR destinations instead of accumulation registers that every
 // other instruction would have to copy from.)
-// MODE kFused: Q,K,V,idx -> O.  kSddmm: Q,K,idx -> S (scaled scores of the 8 rows).  kSpmm: Pin,V,idx -> O.
+// MODE kSddmm: Q,K,idx -> S (scaled scores of the 8 rows).  kSpmm: Pin,V,idx -> O.
 template <int D, int MODE>
 __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
@@ -473,16 +470,14 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
     for (int t = lane; t < keep_pad; t += kWave) sl[t] = min(max(list[min(t, keep - 1)], 0), L - 1);
     wave_lds_fence();
 
-    // scores of all kept keys -> LDS, running maximum per query.  The key rows of a step (32 keys) are
-    // gathered the way the value rows are below: D / 8 neighbouring lanes fetch one row as 16-byte pieces
-    // (whole cache lines per row, which is what the vector memory path serves best; fetched straight
-    // into the operand layout, 16 lanes take 16 bytes of 16 different rows each and the same bytes come
-    // at a third of the rate), pass through the value tile's LDS and come back as the first operand of
+    // scores of all kept keys -> LDS.  The key rows of a step (32 keys) are gathered the way the value rows are below:
+    // D / 8 neighbouring lanes fetch one row as 16-byte pieces (whole cache lines per row, which is what the vector memory
+    // path serves best; fetched straight into the operand layout, 16 lanes take 16 bytes of 16 different rows each and the
+    // same bytes come at a third of the rate), pass through the value tile's LDS and come back as the first operand of
     // the matrix instruction.  The rows of step t + 1 are requested before step t is consumed.
-    float mx = -INFINITY;
     constexpr int VP = 32 / RPI;           // load instructions per step of 32 rows
     const int vrow = lane / LPR, vpiece = lane % LPR;
-    if (MODE != kSpmm) {
+    if (MODE == kSddmm) {
         v4u kring[VP];
 #pragma unroll
         for (int rr = 0; rr < VP; ++rr)
@@ -505,18 +500,12 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
                     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qop[s], acc, 0, 0, 0);
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc[i] = tile + 4 * g + i < keep ? acc[i] * scale : -INFINITY;
-                    mx = fmaxf(mx, acc[i]);
-                }
+                for (int i = 0; i < 4; ++i) acc[i] *= scale;
                 if (c < 8) *reinterpret_cast<v4f *>(sS + c * keep_pad + tile + 4 * g) = acc;
             }
             wave_lds_fence();       // the next step overwrites the tile
         }
-    }
-    if (MODE == kSddmm) {
         // the 8 rows of scores leave through LDS: consecutive lanes write consecutive entries of a row
-        wave_lds_fence();
         if (live) {
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
@@ -526,86 +515,228 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
         }
         return;
     }
-    if (MODE == kSpmm) {
-        // the given weights come in the same way (0 beyond the list)
+    // the given weights come in the same way (0 beyond the list)
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const float *src = Pin + ((size_t)n * L + u * 8 + r) * keep;
-            for (int t = lane; t < keep_pad; t += kWave) sS[r * keep_pad + t] = t < keep ? src[t] : 0.f;
-        }
+    for (int r = 0; r < 8; ++r) {
+        const float *src = Pin + ((size_t)n * L + u * 8 + r) * keep;
+        for (int t = lane; t < keep_pad; t += kWave) sS[r * keep_pad + t] = t < keep ? src[t] : 0.f;
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
     wave_lds_fence();
 
     v4f o[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) o[ct] = v4f{0.f, 0.f, 0.f, 0.f};
-    float z = 0.f;
     const float *srow = sS + (c & 7) * keep_pad + 4 * g;
-    // value rows of a step: 32 / RPI pieces of 16 bytes per lane; a ring of VF steps is kept in flight
-    constexpr int VF = 1;
-    v4u vring[VF][VP];
+    const char *block = sV + (4 * g + (c >> 2)) * VROW + 8 * (c & 3);      // what a lane contributes to a transposing read
+    v4u vring[VP];
 #pragma unroll
-    for (int f = 0; f < VF; ++f)
+    for (int rr = 0; rr < VP; ++rr) vring[rr] = *reinterpret_cast<const v4u *>(Vh + (size_t)sl[rr * RPI + vrow] * D + vpiece * 8);
+    for (int t0 = 0; t0 < keep_pad; t0 += 32) {
+        // 32 gathered value rows -> LDS, and the request for the rows of the next step
+#pragma unroll
+        for (int rr = 0; rr < VP; ++rr) *reinterpret_cast<v4u *>(sV + (rr * RPI + vrow) * VROW + vpiece * 16) = vring[rr];
+        const int tn = min(t0 + 32, keep_pad - 32);
 #pragma unroll
         for (int rr = 0; rr < VP; ++rr)
-            vring[f][rr] = *reinterpret_cast<const v4u *>(
-                Vh + (size_t)sl[min(32 * f, keep_pad - 32) + rr * RPI + vrow] * D + vpiece * 8);
-    for (int t1 = 0; t1 < keep_pad; t1 += 32 * VF) {
+            vring[rr] = *reinterpret_cast<const v4u *>(Vh + (size_t)sl[tn + rr * RPI + vrow] * D + vpiece * 8);
+        // weights of this lane's 8 slots
+        const v4f s0 = *reinterpret_cast<const v4f *>(srow + t0);
+        const v4f s1 = *reinterpret_cast<const v4f *>(srow + t0 + 16);
+        bf16x8 pa;
 #pragma unroll
-        for (int f = 0; f < VF; ++f) {
-            const int t0 = t1 + 32 * f;
-            if (t0 < keep_pad) {
-                // 32 gathered value rows -> LDS, and the request for the rows of step t0 + VF
+        for (int i = 0; i < 4; ++i) {
+            pa[i] = (__bf16)s0[i];
+            pa[4 + i] = (__bf16)s1[i];
+        }
+        wave_lds_fence();
 #pragma unroll
-                for (int rr = 0; rr < VP; ++rr)
-                    *reinterpret_cast<v4u *>(sV + (rr * RPI + vrow) * VROW + vpiece * 16) = vring[f][rr];
-                const int tn = min(t0 + 32 * VF, keep_pad - 32);
+        for (int ct = 0; ct < CT; ++ct) {
+            union { s16x4 half[2]; bf16x8 all; } vb;
+            vb.half[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(block + 32 * ct));
+            vb.half[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(block + 16 * VROW + 32 * ct));
+            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, vb.all, o[ct], 0, 0, 0);
+        }
+        wave_lds_fence();       // the next step overwrites the value tile
+    }
+    // lane (c, g) holds O[query 4g+i][16 ct + c]
+    if (live && g < 2) {
 #pragma unroll
-                for (int rr = 0; rr < VP; ++rr)
-                    vring[f][rr] = *reinterpret_cast<const v4u *>(
-                        Vh + (size_t)sl[tn + rr * RPI + vrow] * D + vpiece * 8);
-                // weights of this lane's 8 slots
-                const v4f s0 = *reinterpret_cast<const v4f *>(srow + t0);
-                const v4f s1 = *reinterpret_cast<const v4f *>(srow + t0 + 16);
-                bf16x8 pa;
+        for (int i = 0; i < 4; ++i) {
+            float *out = O + ((size_t)n * L + u * 8 + 4 * g + i) * D + c;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float p0 = MODE == kSpmm ? s0[i] : __expf(s0[i] - mx);
-                    const float p1 = MODE == kSpmm ? s1[i] : __expf(s1[i] - mx);
-                    z += p0 + p1;
-                    pa[i] = (__bf16)p0;
-                    pa[4 + i] = (__bf16)p1;
-                }
-                wave_lds_fence();
+            for (int ct = 0; ct < CT; ++ct) out[16 * ct] = o[ct][i];
+        }
+    }
+}
+
+// The fused mode for units of VEC rows (8 or 4) with bfloat16 inputs, one wavefront per unit, in one pass over the unit's
+// keys: key and value rows of a step of 32 keys are gathered together, one step ahead, and pass through one tile in LDS, the
+// keys first.  Scores as in attention_groups_bf16, but they stay in the lane that owns them (query c, keys 4g..4g+3 of both
+// tiles), which is where the second product wants its weights: neither scores nor weights pass through LDS.  The
+// exponentials are taken relative to a running reference that is moved only when a score exceeds it by a factor of
+// 2^kUnitSlack, so that a step needs no reduction across lanes.
+// Every list length fits (the list takes 4 bytes per key, 128 KB at most for D = 128).
+//
+// What bounds it: LDS (145 cycles per step and wavefront, two thirds of them the writes of the gathered rows; active 69 % of
+// the time at N = 64, L = 2000, keep = 200, VEC = 4), next to it the latency of list -> gather -> tile for short lists.
+// Measured (kernel alone): that shape 213 -> 94 us against one row per wavefront (attention_rows), which gathers the four
+// times 3.3 GB; VEC = 8, N = 16, L = 4096, keep = 205: 44.7 -> 29 us, N = 64, L = 2048, keep = 102: 51 -> 35 us, D = 128,
+// N = 16, L = 8192, keep = 82: 72.6 -> 55 us against two passes with the scores in LDS.  A key and a value tile side by side
+// cost occupancy at D = 128 (59 us); rows padded to 16 bytes more instead of swizzled: 96 us at the first shape.
+// The error against 64 bits at the shapes below is 2e-6 (two-norm), 4e-4 to 1.3e-3 before with weights of one bf16.
+constexpr float kUnitSlack = 16.f;
+
+// Where the 16-byte pieces of tile row r are: piece p at p ^ unit_swizzle(r).  Eight rows of one piece (the score operand)
+// and four rows of two neighbouring pieces (a transposing read) both fall on different banks.
+__device__ __forceinline__ unsigned unit_swizzle(unsigned r) { return (r & 3u) << 1 | (r >> 2 & 1u); }
+
+template <int D> constexpr int unit_tile_bytes() { return 32 * 2 * D; }        // key rows, then value rows
+
+template <int D, int VEC>
+__global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
+    const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
+    const int32_t *__restrict__ idx, float *__restrict__ O, int L, int keep, int keep_pad, float scale, unsigned total_units)
+{
+    constexpr int KS = D / 32, CT = D / 16;
+    constexpr int ROW = D * 2;             // bytes of a row in LDS
+    constexpr int LPR = D / 8, RPI = kWave / LPR, VP = 32 / RPI;
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int c = lane & 15, g = lane >> 4;
+    char *tile = lds_raw + wave * (unit_tile_bytes<D>() + keep_pad * 4);
+    unsigned *sl = reinterpret_cast<unsigned *>(tile + unit_tile_bytes<D>());        // [keep_pad] byte offsets of the rows
+
+    const unsigned unit = xcd_contiguous(blockIdx.x, gridDim.x) * kGroupWaves + wave;
+    if (unit >= total_units) return;       // the whole wavefront: nothing below is shared
+    const unsigned G = L / VEC, n = unit / G, u = unit % G;
+    const int32_t *list = idx + (size_t)unit * keep;
+    const char *Kh = reinterpret_cast<const char *>(K + (size_t)n * L * D);
+    const char *Vh = reinterpret_cast<const char *>(V + (size_t)n * L * D);
+    for (int t = lane; t < keep_pad; t += kWave) sl[t] = (unsigned)min(max(list[min(t, keep - 1)], 0), L - 1) * (D * 2u);
+
+    // the sign of the scale goes into the query rows, its size into the exponential
+    const float factor = fabsf(scale) * 1.44269504088896340736f;
+    bf16x8 qop[KS];
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    bf16x8 vb;
-                    const char *col = sV + (16 * ct + c) * 2;
+    for (int s = 0; s < KS; ++s) {
+        uint4 raw = make_uint4(0, 0, 0, 0);
+        if (c < VEC) raw = *reinterpret_cast<const uint4 *>(Q + ((size_t)n * L + u * VEC + c) * D + 32 * s + 8 * g);
+        if (scale < 0.f) raw = Piece<uint16_t>::negate(raw);
+        qop[s] = __builtin_bit_cast(bf16x8, raw);
+    }
+    wave_lds_fence();
+
+    // gathers: lane (r = lane / LPR, p = lane % LPR) takes piece p of list entries VP r .. VP r + VP - 1 of the step, which
+    // are also the tile's rows: the entries come as one or two 16-byte reads
+    const int first = lane / LPR * VP;
+    const unsigned piece = lane % LPR;
+    v4u kring[VP], vring[VP];
+    auto gather = [&](v4u (&ring)[VP], const char *head, int t0) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        vb[i] = *reinterpret_cast<const __bf16 *>(col + (4 * g + i) * VROW);
-                        vb[4 + i] = *reinterpret_cast<const __bf16 *>(col + (16 + 4 * g + i) * VROW);
-                    }
-                    o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, vb, o[ct], 0, 0, 0);
-                }
-                wave_lds_fence();       // the next step overwrites the value tile
+        for (int r = 0; r < VP; r += 4) {
+            const v4u at = *reinterpret_cast<const v4u *>(sl + t0 + first + r);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ring[r + i] = *reinterpret_cast<const v4u *>(head + (at[i] + 16u * piece));
+        }
+    };
+    auto put = [&](const v4u (&ring)[VP]) {
+#pragma unroll
+        for (int r = 0; r < VP; ++r)
+            *reinterpret_cast<v4u *>(tile + (first + r) * ROW + 16u * (piece ^ unit_swizzle(first + r))) = ring[r];
+    };
+    // operands: row c (and 16 + c) of the key rows; of the value rows, the 4 x 4 block that ds_read_tr16_b64 takes from a lane
+    const unsigned vrow = 4 * g + (c >> 2), vswz = unit_swizzle(vrow);       // the same for row 16 + vrow
+    auto key_piece = [&](int half, int s) {
+        return *reinterpret_cast<const bf16x8 *>(tile + (16 * half + c) * ROW + 16u * ((4 * s + g) ^ unit_swizzle(c)));
+    };
+    auto value_block = [&](int half, int ct) {
+        return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_s16x4 *)(tile + (16 * half + vrow) * ROW + 16u * ((2 * ct + (c >> 1 & 1)) ^ vswz) + 8 * (c & 1)));
+    };
+
+    v4f o[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) o[ct] = v4f{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, z = 0.f;
+    gather(kring, Kh, 0);
+    gather(vring, Vh, 0);
+    for (int t0 = 0; t0 < keep_pad; t0 += 32) {
+        const int t1 = min(t0 + 32, keep_pad - 32);
+        put(kring);
+        gather(kring, Kh, t1);
+        wave_lds_fence();
+        v4f s2[2];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            s2[half] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                s2[half] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(key_piece(half, s), qop[s], s2[half], 0, 0, 0);
             }
         }
+        wave_lds_fence();
+        put(vring);
+        gather(vring, Vh, t1);
+        float mx = fmaxf(s2[0][0], s2[1][0]);
+#pragma unroll
+        for (int i = 1; i < 4; ++i) mx = fmaxf(fmaxf(s2[0][i], s2[1][i]), mx);
+        // (compared with >: nothing moves for scores that are not numbers, they reach the sums by themselves)
+        if (__ballot(m == -INFINITY ? mx > -INFINITY : (mx - m) * factor > kUnitSlack) != 0) {
+            mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+            const float to = fmaxf(m, mx);
+            const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - to) * factor);
+            m = to;
+            z *= f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float fi = __shfl(f, 4 * g + i, kWave);          // lane (query, 0): the sums of query 4 g + i
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) o[ct][i] *= fi;
+            }
+        }
+        const float m0 = m == -INFINITY ? 0.f : m;
+        float p[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f((s2[i / 4][i % 4] - m0) * factor);
+        if (t0 + 32 > keep) {              // the padding repeats the last key: it may set the reference, but has no weight
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (t0 + 16 * (i / 4) + 4 * g + i % 4 >= keep) p[i] = 0.f;
+        }
+        // A weight is the sum of two bf16 (relative 2^-17): one alone would be rounded at 2^-9, the largest one too, whose
+        // weight is not 1 here.  hi is p cut off, and lo is not zero where p is not (the factor is 1 + 2^-23), so that both
+        // products with an infinite value have its sign.
+        unsigned cut[8];
+        bf16x8 lo;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            z += p[i];
+            cut[i] = __float_as_uint(p[i]) & 0xffff0000u;
+            lo[i] = (__bf16)fmaf(p[i], 1.00000012f, -__uint_as_float(cut[i]));
+        }
+        const bf16x8 hi = __builtin_bit_cast(bf16x8, v4u{cut[0] >> 16 | cut[1], cut[2] >> 16 | cut[3], cut[4] >> 16 | cut[5], cut[6] >> 16 | cut[7]});
+        wave_lds_fence();
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            union { s16x4 half[2]; bf16x8 all; } vb;
+            vb.half[0] = value_block(0, ct);
+            vb.half[1] = value_block(1, ct);
+            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, vb.all, o[ct], 0, 0, 0);
+            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, vb.all, o[ct], 0, 0, 0);
+        }
+        wave_lds_fence();                  // the next step overwrites the tile
     }
     z += __shfl_xor(z, 16, kWave);
     z += __shfl_xor(z, 32, kWave);
     // lane (c, g) holds O[query 4g+i][16 ct + c]; the sum of query q sits in the lanes with column q
-    if (live) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float inv = MODE == kSpmm ? 1.f : 1.f / __shfl(z, (4 * g + i) & 7, kWave);
-            if (g < 2) {
-                float *out = O + ((size_t)n * L + u * 8 + 4 * g + i) * D + c;
+    for (int i = 0; i < 4; ++i) {
+        const float inv = 1.f / __shfl(z, 4 * g + i, kWave);
+        if (4 * g + i < VEC) {
+            float *out = O + ((size_t)n * L + u * VEC + 4 * g + i) * D + c;
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) out[16 * ct] = o[ct][i] * inv;
-            }
+            for (int ct = 0; ct < CT; ++ct) out[16 * ct] = o[ct][i] * inv;
         }
     }
 }
@@ -706,13 +837,27 @@ hipError_t launch_groups(const dsa_shape &sh, const void *Q, const void *K, cons
     return hipGetLastError();
 }
 
+template <int D, int VEC>
+hipError_t launch_units(const dsa_shape &sh, const void *Q, const void *K, const void *V, const int32_t *idx, float *O,
+                        hipStream_t st)
+{
+    const unsigned units = (unsigned)sh.B * sh.H * (sh.L / VEC);
+    const int keep_pad = (sh.keep + 31) / 32 * 32;
+    const size_t lds = kGroupWaves * (unit_tile_bytes<D>() + keep_pad * sizeof(unsigned));
+    auto kern = attention_units_bf16<D, VEC>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds)) return e;
+    hipLaunchKernelGGL(kern, dim3((units + kGroupWaves - 1) / kGroupWaves), dim3(kGroupWaves * kWave), lds, st,
+                       static_cast<const uint16_t *>(Q), static_cast<const uint16_t *>(K),
+                       static_cast<const uint16_t *>(V), idx, O, sh.L, sh.keep, keep_pad, sh.scale, units);
+    return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_groups_d(AttnMode mode, const dsa_shape &sh, const void *Q, const void *K, const void *V,
                            const int32_t *idx, const float *Pin, float *S, float *O, hipStream_t st)
 {
     if (mode == kSddmm) return launch_groups<D, kSddmm>(sh, Q, K, V, idx, Pin, S, O, st);
-    if (mode == kSpmm) return launch_groups<D, kSpmm>(sh, Q, K, V, idx, Pin, S, O, st);
-    return launch_groups<D, kFused>(sh, Q, K, V, idx, Pin, S, O, st);
+    return launch_groups<D, kSpmm>(sh, Q, K, V, idx, Pin, S, O, st);
 }
 
 }  // namespace
@@ -729,6 +874,11 @@ hipError_t launch_attention(AttnMode mode, const dsa_shape &sh, const void *Q, c
     if (sh.dtype == DSA_F32) {
         if (sh.d == 64) return launch_rows<float, 64>(mode, sh, Q, K, V, idx, Pin, S, O, st);
         return launch_rows<float, 128>(mode, sh, Q, K, V, idx, Pin, S, O, st);
+    }
+    if (sh.vec > 1 && mode == kFused) {
+        if (sh.vec == 8)
+            return sh.d == 64 ? launch_units<64, 8>(sh, Q, K, V, idx, O, st) : launch_units<128, 8>(sh, Q, K, V, idx, O, st);
+        return sh.d == 64 ? launch_units<64, 4>(sh, Q, K, V, idx, O, st) : launch_units<128, 4>(sh, Q, K, V, idx, O, st);
     }
     if (sh.vec == 8 && groups_lds_bytes(sh) <= 144 * 1024) {
         if (sh.d == 64) return launch_groups_d<64>(mode, sh, Q, K, V, idx, Pin, S, O, st);

@@ -1,0 +1,88 @@
+"""Fused attention of vector-wise units (8 or 4 rows share a list, bfloat16) at the edges of its steps of 32 keys and of its
+workgroups of four units, up to the longest list, with scores that outgrow its running reference, and with scales of any
+sign.  Against the oracle, with the bound for bf16 inputs that the other tests use: weights rounded to bf16 (2^-9) of
+values of about 1."""
+import numpy as np
+import pytest
+
+import dsa_inputs as di
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+
+
+@pytest.fixture(scope="module")
+def dsa():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("these tests need the MI355X: run them with -m gpu on the GPU box")
+    import paper_2110_11299_amd as pkg
+    pkg.binding.lib()
+    return pkg
+
+
+def case(H, L, d, vec, keep):
+    x = di.make_inputs(di.custom_config("units", B=1, H=H, L=L, d=d, dtype="bf16", rank=8, k=16, vec=vec, keep=keep, seed=L + keep))
+    rng = np.random.Generator(np.random.Philox(L + keep + vec))
+    idx = np.stack([np.sort(rng.choice(L, keep, replace=False)) for _ in range(H * (L // vec))]).astype(np.int32)
+    return [np.ascontiguousarray(a) for a in (x.Q, x.K, x.V)], idx
+
+
+def run(dsa, qkv, idx, vec, scale):
+    import torch
+    _, H, L, d = qkv[0].shape
+    keep = idx.shape[-1]
+    print(f"[units] H={H} L={L} d={d} vec={vec} keep={keep} scale={scale}", flush=True)
+    sh = dsa.make_shape(1, H, L, d, 16, keep, vec, dsa.DSA_BF16, scale)
+    dev = [torch.from_numpy(a).cuda().bfloat16() for a in qkv]
+    O = dsa.dsa_masked_attention(sh, *dev, torch.from_numpy(idx.reshape(1, H, L // vec, keep)).cuda())
+    return O.cpu().numpy().reshape(-1, d)
+
+
+def check(dsa, oracle, qkv, idx, vec, scale):
+    want = oracle.masked_attention(*qkv, idx, scale, vec).reshape(-1, qkv[0].shape[-1])
+    assert np.abs(run(dsa, qkv, idx, vec, scale) - want).max() <= TOL
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("vec", [4, 8])
+@pytest.mark.parametrize("L,keep", [(8, 1), (40, 31), (40, 32), (72, 33), (136, 64), (264, 65), (264, 264), (1000, 97)])
+def test_edges(dsa, oracle, d, vec, L, keep):
+    qkv, idx = case(3, L, d, vec, keep)
+    for scale in (0.125, -0.125, 0.0):
+        check(dsa, oracle, qkv, idx, vec, scale)
+
+
+@pytest.mark.parametrize("d,vec", [(64, 8), (128, 4)])
+def test_longest_list(dsa, oracle, d, vec):
+    qkv, _ = case(1, 64, d, vec, 1)
+    L, keep = 4200, 4096
+    rng = np.random.Generator(np.random.Philox(d))
+    qkv = [np.ascontiguousarray(np.concatenate([a] * 66, axis=2)[:, :, :L]) for a in qkv]
+    idx = np.stack([np.sort(rng.choice(L, keep, replace=False)) for _ in range(L // vec)]).astype(np.int32)
+    check(dsa, oracle, qkv, idx, vec, 0.125)
+
+
+@pytest.mark.parametrize("vec", [4, 8])
+@pytest.mark.parametrize("order", [1, -1])
+def test_scores_that_grow(dsa, oracle, vec, order):
+    """Scores from 0 to 88, rising or falling along the list, in one query of the unit only."""
+    qkv, idx = case(1, 640, 64, vec, 320)
+    Q, K, _ = qkv
+    Q[0, 0, ::vec] = 1.0
+    K[...] = (np.arange(640)[::order] // 54).astype(np.float32)[None, None, :, None]
+    check(dsa, oracle, qkv, idx, vec, 0.125)
+
+
+@pytest.mark.parametrize("vec", [4, 8])
+def test_values_that_are_not_finite(dsa, oracle, vec):
+    """They reach the rows that keep their key, with their sign, and no others."""
+    qkv, idx = case(2, 600, 64, vec, 96)                # no padding: it would repeat the last key with a zero weight
+    V = qkv[2]
+    V[0, 0, 5, 3], V[0, 0, 70, 7], V[0, 1, 590, 63], V[0, 1, 64, 0] = np.inf, np.nan, -np.inf, np.inf
+    want = oracle.masked_attention(*qkv, idx, 0.125, vec).reshape(-1, 64)
+    got = run(dsa, qkv, idx, vec, 0.125)
+    ok = np.isfinite(want)
+    assert 0 < (~ok).sum() < want.size
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert np.abs(got[ok] - want[ok]).max() <= TOL
