@@ -7,7 +7,7 @@
 // (A operand), units the columns (B operand) of v_mfma_i32_16x16x64_i8; the key range is cut into 4 W lane ranges of
 // 32 * NW keys, and lane (c = lane % 16, g = lane / 16) of wavefront w holds, for unit c, the scores of range 4 w + g.
 //
-//   sweep 1    every lane keeps up to 32 maxima over disjoint key sets ("buckets").
+//   sweep 1    every lane keeps up to NB = 32 or 16 maxima over disjoint key sets ("buckets").
 //   bounds     from a histogram of a unit's maxima in LDS two thresholds tl < th are read off, such that the keep-th
 //              largest score lies between them almost surely: the number of buckets that the x largest keys fall into
 //              is known to a few per cent (section "targets" on the host side).  For short ranges a bucket is one key
@@ -97,9 +97,10 @@ __device__ __forceinline__ int row_sum_above(int x)
 }
 
 // K: the projection dimension (16, 32, 48, 64), or 0 for any other (up to 128, two contraction steps).
-// GROUP: units are groups of vec rows.  NWM: most bitmap words per lane.
-template <int K, bool GROUP, int UT, int NWM>
-__global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitArgs a)
+// GROUP: units are groups of vec rows.  UT: tiles of 16 units per workgroup.  NB: buckets per lane and unit (32, or 16 if a
+// range has several groups).  NWM: most bitmap words per lane.
+template <int K, bool GROUP, int UT, int NB, int NWM>
+__global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitArgs a)
 {
     constexpr int R = K == 16 ? 4 : K == 32 ? 2 : 1;     // keys side by side in a matrix row = tiles per row operand
     constexpr int STEPS = K ? 1 : 2;                     // contraction steps of 64
@@ -211,13 +212,13 @@ __global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitAr
     const int nv_all = max(0, min(L - (4 * wv + 3) * Lr, Lr));           // of the wavefront's last range: the fewest
 
     // ---- sweep 1: bucket maxima --------------------------------------------------------------------------------------
-    // A range of one group (NWM == 1) keeps every score; else tiles j and j ^ 2 share a bucket, and so do groups of the
-    // same parity: two scores per v_max3.
-    int bm[UT][32];
+    // A range of one group (NWM == 1) keeps every score; else tiles j and j ^ 2 share a bucket, and so do all groups (of
+    // the same parity, if there are 32): two scores per v_max3.
+    int bm[UT][NB];
 #pragma unroll
     for (int t = 0; t < UT; ++t)
 #pragma unroll
-        for (int b = 0; b < 32; ++b) bm[t][b] = INT32_MIN;
+        for (int b = 0; b < NB; ++b) bm[t][b] = INT32_MIN;
     auto maxima = [&](const v4i (&buf)[NSB][STEPS], int w, auto par, auto half, auto masked) {
         constexpr int PAR = decltype(par)::value, J0 = decltype(half)::value * TB;
 #pragma unroll
@@ -238,10 +239,10 @@ __global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitAr
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         if (NWM == 1) {
-                            bm[t][(4 * (J0 + j) + i) % 32] = x[i];
-                            bm[t][(4 * (J0 + j + 2) + i) % 32] = y[i];
+                            bm[t][(4 * (J0 + j) + i) % NB] = x[i];
+                            bm[t][(4 * (J0 + j + 2) + i) % NB] = y[i];
                         } else {
-                            int &m = bm[t][16 * PAR + ((J0 + jb) / 4 % 2) * 8 + 4 * e + i];
+                            int &m = bm[t][(NB == 32 ? 16 * PAR : 0) + ((J0 + jb) / 4 % 2) * 8 + 4 * e + i];
                             m = max(max(x[i], y[i]), m);
                         }
                     }
@@ -274,19 +275,27 @@ __global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitAr
     // ---- bounds -------------------------------------------------------------------------------------------------------
     // The histogram's range is [smallest maximum, it + 3 * (mean - it)]: high-norm keys put a few maxima far above the
     // others and would otherwise stretch the bins; they go to the last one.
-    int lo[UT], shift[UT];
+    const bool full = nv_all == Lr;               // every bucket of the wavefront holds a key
     {
         float *s_sum = reinterpret_cast<float *>(s_toth);
 #pragma unroll
         for (int t = 0; t < UT; ++t) {
-            int mn = INT32_MAX;
-            float sum = 0.f;
+            int mn = INT32_MAX, all = 0;                 // 32 scores below 2^24 each
+            if (full) {
 #pragma unroll
-            for (int b = 0; b < 32; ++b) {
-                const bool real = bm[t][b] != INT32_MIN;
-                mn = real ? min(mn, bm[t][b]) : mn;
-                sum += real ? (float)bm[t][b] : 0.f;
+                for (int b = 0; b < NB; ++b) {
+                    mn = min(mn, bm[t][b]);
+                    all += bm[t][b];
+                }
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const bool real = bm[t][b] != INT32_MIN;
+                    mn = real ? min(mn, bm[t][b]) : mn;
+                    all += real ? bm[t][b] : 0;
+                }
             }
+            float sum = (float)all;
             mn = min(mn, __shfl_xor(mn, 16, kWave));
             mn = min(mn, __shfl_xor(mn, 32, kWave));
             sum += __shfl_xor(sum, 16, kWave);
@@ -297,8 +306,8 @@ __global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitAr
             }
         }
         __syncthreads();
-        // buckets that hold a key: 32 (or min(nv, 32) single keys) per full range; the mean only places the range's end
-        const float per_bucket = NWM == 1 ? (float)min(L, 32 * 4 * W) : 32.f * fminf((float)(4 * W), (float)L / (float)Lr);
+        // buckets that hold a key: NB (or min(nv, 32) single keys) per full range; the mean only places the range's end
+        const float per_bucket = NWM == 1 ? (float)min(L, 32 * 4 * W) : (float)NB * fminf((float)(4 * W), (float)L / (float)Lr);
 #pragma unroll
         for (int t = 0; t < UT; ++t) {
             int mn = INT32_MAX;
@@ -307,18 +316,21 @@ __global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitAr
                 mn = min(mn, s_totl[x * U + kTile * t + c]);
                 sum += s_sum[x * U + kTile * t + c];
             }
-            lo[t] = mn;
             const float range = fminf(fmaxf(3.f * (sum / per_bucket - (float)mn), 1.f), 1.0e9f);
-            shift[t] = max(0, 25 - (int)__clz((int)((unsigned)range | 1u)));     // range >> shift < kBins
+            const int shift = max(0, 25 - (int)__clz((int)((unsigned)range | 1u)));     // range >> shift < kBins
             unsigned *uh = hist + (kTile * t + c) * kBinStride;
+            auto count = [&](int x) { atomicAdd(&uh[min((unsigned)(x - mn) >> shift, (unsigned)(kBins - 1))], 1u); };
+            if (full) {
 #pragma unroll
-            for (int b = 0; b < 32; ++b) {
-                const unsigned bin = min((unsigned)(max(bm[t][b], mn) - mn) >> shift[t], (unsigned)(kBins - 1));
-                if (bm[t][b] != INT32_MIN) atomicAdd(&uh[bin], 1u);
+                for (int b = 0; b < NB; ++b) count(bm[t][b]);
+            } else {
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    if (bm[t][b] != INT32_MIN) count(bm[t][b]);
             }
             if (wv == 0 && g == 0) {
                 s_tl[kTile * t + c] = mn;
-                s_th[kTile * t + c] = shift[t];
+                s_th[kTile * t + c] = shift;
             }
         }
         __syncthreads();
@@ -548,10 +560,15 @@ __global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitAr
                 for (int i = 0; i < 4; ++i) sc[i0 + i] = INT32_MIN;
             }
         }
-        // the need-th largest of the band: all its scores are >= tl and at least need of them exist
-        int lo_ = ulo, hi_ = nb ? max(row_max(peak), ulo) : ulo;
-        while (__ballot(lo_ < hi_) != 0) {
-            const int mid = (lo_ + hi_ + 1) >> 1;         // |scores| < 2^27
+        // The need-th largest of the band: all its scores are >= tl and at least need of them exist.  The interval is cut
+        // where it would be cut for evenly spread scores and in the middle in turn, until a cut leaves exactly need.
+        int lo_ = ulo, hi_ = nb ? max(row_max(peak), ulo) : ulo, cnt_lo = nb, cnt_hi = 0;   // counts >= lo_ and > hi_
+        for (bool even = true; __ballot(lo_ < hi_) != 0; even = !even) {
+            const int width = hi_ - lo_;                  // |scores| < 2^27
+            int step = (width + 1) >> 1;
+            if (even)
+                step = min(max((int)((float)width * (float)(cnt_lo - need) * __builtin_amdgcn_rcpf((float)(cnt_lo - cnt_hi))), 1), width);
+            const int mid = lo_ + step;
             int cnt = 0;
 #pragma unroll
             for (int i0 = 0; i0 < kBandSlots; i0 += 4)
@@ -559,14 +576,23 @@ __global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitAr
 #pragma unroll
                     for (int i = 0; i < 4; ++i) cnt += sc[i0 + i] >= mid;
                 }
-            const bool ge = row_sum(cnt) >= need;
-            lo_ = ge ? mid : lo_;
-            hi_ = ge ? hi_ : mid - 1;
+            cnt = row_sum(cnt);
+            if (lo_ < hi_) {
+                const bool ge = cnt >= need;
+                lo_ = ge ? mid : lo_;
+                cnt_lo = ge ? cnt : cnt_lo;
+                hi_ = !ge ? mid - 1 : cnt == need ? mid : hi_;
+                cnt_hi = ge ? cnt_hi : cnt;
+            }
         }
         const int Tx = lo_;
         int gt = 0;
 #pragma unroll
-        for (int i = 0; i < kBandSlots; ++i) gt += sc[i] > Tx;
+        for (int i0 = 0; i0 < kBandSlots; i0 += 4)
+            if (16 * i0 < most) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) gt += sc[i0 + i] > Tx;
+            }
         const int need_eq = need - row_sum(gt);
         int eq_before = 0;
         const unsigned below = (1u << c) - 1u;
@@ -658,13 +684,13 @@ __global__ __launch_bounds__(NWM > 8 ? 1024 : 512, 4) void predict_split(SplitAr
 
 // ---- host side -----------------------------------------------------------------------------------------------------------
 
-struct SplitPlan { int W, NW, target_l, target_h; };
+struct SplitPlan { int W, NW, UT, NB, target_l, target_h; };
 
 // Targets.  If a share p of a unit's keys lies above a threshold, a bucket of s keys reaches it with probability
 // 1 - (1 - p)^s; the number of buckets that reach it, given the number x of keys that do, has the mean D(x) below and a
 // variance that is the binomial one less what x explains.  tl is put where keep + z sigma keys are expected above it,
 // th where keep - z sigma are: with z = 3.5 a unit misses in about one case of 2000 (and is then swept again).
-inline void split_targets(int L, int keep, int W, int NW, int *target_l, int *target_h)
+inline void split_targets(int L, int keep, int NW, int NB, int *target_l, int *target_h)
 {
     if (NW == 1) {                       // every key is its own bucket
         *target_l = keep;
@@ -673,9 +699,9 @@ inline void split_targets(int L, int keep, int W, int NW, int *target_l, int *ta
     }
     const int Lr = 32 * NW;
     const double p = (double)keep / L, vx = L * p * (1.0 - p);
-    // two bucket sizes (group parity), each in `ranges` full lane ranges
+    // one bucket size, or two (group parity), 16 of each in `ranges` full lane ranges
     const double ranges = (double)L / Lr;
-    const double size[2] = {2.0 * ((NW + 1) / 2), 2.0 * (NW / 2)}, count = 16.0 * ranges;
+    const double size[2] = {NB == 32 ? 2.0 * ((NW + 1) / 2) : 2.0 * NW, NB == 32 ? 2.0 * (NW / 2) : 0.0}, count = 16.0 * ranges;
     double binomial = 0, cov = 0;
     for (double s : size) {
         const double miss = pow(1.0 - p, s);
@@ -693,25 +719,42 @@ inline void split_targets(int L, int keep, int W, int NW, int *target_l, int *ta
     const double reach = 3.5 * sigma + 1.0;
     int l = (int)ceil(buckets(keep + reach)), h = (int)floor(buckets(keep - reach));
     if (keep - reach < 1.0) h = 0;
-    const int most = (int)(2.0 * count);
+    const int most = (int)(count * NB / 16);
     l = l > most ? most : l < 1 ? 1 : l;
     h = h > l - 1 ? l - 1 : h;
     *target_l = l;
     *target_h = h;
 }
 
-inline SplitPlan split_plan(const dsa_shape &sh)
+// Wavefronts: ranges of 32 to 512 keys, and at least four where there are few tiles (the band step takes four units per
+// wavefront at a time: L = 256, 32 tiles, 12.6 -> 10.5 us).
+// Two tiles per workgroup halve the key rows that come from L2 per unit (at L = 16384, k = 64 every workgroup streams 1 MB
+// twice: 627 -> 472 us; L = 8192 in groups of 8: 95 -> 82 us).  It takes the unit operands of both in registers, which only
+// a contraction that fills its 64 slots leaves room for (k = 32 keeps two half-empty copies of each: 139 -> 171 us), 16
+// buckets per lane instead of 32, so keep at most 4/5 of their number, and enough units to fill the chip with half the
+// workgroups.
+inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
 {
     SplitPlan p{};
-    const long long tiles = (long long)sh.B * sh.H * ((sh.L / sh.vec + kTile - 1) / kTile);
+    const long long units = sh.L / sh.vec, heads = (long long)sh.B * sh.H;
+    const long long tiles = heads * ((units + kTile - 1) / kTile);
+    p.UT = 1;
+    p.NB = 32;
     p.W = sh.L <= 128 ? 1 : sh.L <= 256 ? 2 : sh.L <= 4096 ? 4 : sh.L <= 16384 ? 8 : 16;
+    if (p.W < 4 && tiles <= 1024) p.W = 4;
     if (p.W == 4 && sh.L > 512 && 4 * tiles < 4096) p.W = 8;
+    const int W2 = sh.L <= 8192 ? 8 : 16;
+    if (pairs && sh.L > 1024 && sh.L <= 16384 && heads * ((units + 31) / 32) * W2 >= 4096 && 5 * sh.keep <= 4 * 64 * W2) {
+        p.UT = 2;
+        p.NB = 16;
+        p.W = W2;
+    }
     p.NW = (sh.L + 128 * p.W - 1) / (128 * p.W);
-    split_targets(sh.L, sh.keep, p.W, p.NW, &p.target_l, &p.target_h);
+    split_targets(sh.L, sh.keep, p.NW, p.NB, &p.target_l, &p.target_h);
     return p;
 }
 
-template <int K, bool GROUP, int UT, int NWM>
+template <int K, bool GROUP, int UT, int NB, int NWM>
 hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t *Qt, const int8_t *Kt, int32_t *idx,
                           hipStream_t st)
 {
@@ -724,7 +767,7 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
     a.target_h = p.target_h;
     a.direct = (size_t)kTile * UT * sh.keep * 2 > 128 * 1024;
     const size_t lds = SplitLds(p.W, UT, p.NW, sh.k, GROUP, sh.keep, a.direct != 0).bytes;
-    auto kern = predict_split<K, GROUP, UT, NWM>;
+    auto kern = predict_split<K, GROUP, UT, NB, NWM>;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds)) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)sh.B * sh.H * a.wgs_per_head), dim3(p.W * kWave), lds, st, a);
     return hipGetLastError();
@@ -733,11 +776,16 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
 template <int K, bool GROUP>
 hipError_t launch_split_g(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st)
 {
-    const SplitPlan p = split_plan(sh);
-    if (p.NW == 1) return launch_split_t<K, GROUP, 1, 1>(sh, p, Qt, Kt, idx, st);
-    if (p.NW <= 4) return launch_split_t<K, GROUP, 1, 4>(sh, p, Qt, Kt, idx, st);
-    if (p.NW <= 8) return launch_split_t<K, GROUP, 1, 8>(sh, p, Qt, Kt, idx, st);
-    return launch_split_t<K, GROUP, 1, 16>(sh, p, Qt, Kt, idx, st);
+    constexpr bool pairs = K == 48 || K == 64;
+    const SplitPlan p = split_plan(sh, pairs);
+    if constexpr (pairs) {
+        if (p.UT == 2 && p.NW <= 4) return launch_split_t<K, GROUP, 2, 16, 4>(sh, p, Qt, Kt, idx, st);
+        if (p.UT == 2) return launch_split_t<K, GROUP, 2, 16, 8>(sh, p, Qt, Kt, idx, st);
+    }
+    if (p.NW == 1) return launch_split_t<K, GROUP, 1, 32, 1>(sh, p, Qt, Kt, idx, st);
+    if (p.NW <= 4) return launch_split_t<K, GROUP, 1, 32, 4>(sh, p, Qt, Kt, idx, st);
+    if (p.NW <= 8) return launch_split_t<K, GROUP, 1, 32, 8>(sh, p, Qt, Kt, idx, st);
+    return launch_split_t<K, GROUP, 1, 32, 16>(sh, p, Qt, Kt, idx, st);
 }
 
 template <int K>

@@ -74,3 +74,13 @@ def test_score_orders(dsa, oracle, L, keep):
         for vec in (1, 8):
             Lv = L // vec * vec
             check(dsa, oracle, np.ascontiguousarray(Qt[:, :, :Lv]), np.ascontiguousarray(Kt[:, :, :Lv]), keep, vec, name)
+
+
+# two tiles of units per workgroup (projection dimensions of 48 and 64, enough units): a tile that is partly or wholly
+# beyond the head, ranges of 2, 3 and 8 groups, keep at the edge of what its 16 buckets per lane take
+@pytest.mark.parametrize("H,L,vec", [(16, 1025, 1), (15, 1100, 1), (60, 1104, 4), (8, 2049, 1), (30, 8200, 8)])
+@pytest.mark.parametrize("k", [48, 64])
+def test_pairs_of_tiles(dsa, oracle, H, L, vec, k):
+    Qt, Kt = di.random_int8_case(L + H, 1, H, L, k)
+    for keep in (1, 30, 409, 410):
+        check(dsa, oracle, Qt, Kt, keep, vec, "pairs")
