@@ -135,6 +135,70 @@ __device__ __forceinline__ void wave_lds_fence()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The two gather loops of the row kernels, over `n` entries in LDS (a multiple of kRowPad) that hold the byte offsets of the
+// rows inside the head.  Four gathers are in flight per lane while full trips last.
+constexpr int kRowGathers = 4;
+
+template <int STEP, typename F> __device__ __forceinline__ void row_trips(int n, F &&trip)
+{
+    int t0 = 0;
+    for (; t0 + kRowGathers * STEP <= n; t0 += kRowGathers * STEP) trip(t0, std::integral_constant<int, kRowGathers>{});
+    for (; t0 < n; t0 += STEP) trip(t0, std::integral_constant<int, 1>{});
+}
+
+// q . k of every entry to sc; returns the maximum over this lane group's entries.
+template <typename T, int D>
+__device__ __forceinline__ float row_scores(const T *Kh, typename Piece<T>::raw_t q, const unsigned *sl, float *sc, int n, int sub, int grp)
+{
+    typedef Piece<T> P;
+    constexpr int LPR = D / P::N, RPI = kWave / LPR;
+    static_assert(kRowPad % RPI == 0, "n is a whole number of single trips");
+    const unsigned piece_at = sub * P::N * (unsigned)sizeof(T);
+    float m = -INFINITY;
+    row_trips<RPI>(n, [&](int t0, auto uu) {
+        constexpr int UU = decltype(uu)::value;
+        typename P::raw_t kv[UU];
+#pragma unroll
+        for (int u = 0; u < UU; ++u)
+            kv[u] = P::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(Kh) + (size_t)(sl[t0 + u * RPI + grp] + piece_at)));
+        float acc[UU];
+#pragma unroll
+        for (int u = 0; u < UU; ++u) acc[u] = piece_sum<LPR>(P::dot(q, kv[u]));
+#pragma unroll
+        for (int u = 0; u < UU; ++u) {
+            m = fmaxf(m, acc[u]);
+            sc[t0 + u * RPI + grp] = acc[u];      // every lane of the group writes the same value
+        }
+    });
+    return m;
+}
+
+// o += weight * value row and z += weight over the entries of this lane group.
+template <typename T, int D>
+__device__ __forceinline__ void row_values(const T *Vh, const unsigned *sl, const unsigned *sw, int n, int sub, int grp,
+                                           float (&o)[Piece<T>::N], float &z)
+{
+    typedef Piece<T> P;
+    constexpr int LPR = D / P::N, RPI = kWave / LPR;
+    const unsigned piece_at = sub * P::N * (unsigned)sizeof(T);
+    row_trips<RPI>(n, [&](int t0, auto uu) {
+        constexpr int UU = decltype(uu)::value;
+        typename P::raw_t vv[UU];
+        unsigned w[UU];
+#pragma unroll
+        for (int u = 0; u < UU; ++u) {
+            const int t = t0 + u * RPI + grp;
+            vv[u] = P::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(Vh) + (size_t)(sl[t] + piece_at)));
+            w[u] = sw[t];
+        }
+#pragma unroll
+        for (int u = 0; u < UU; ++u) {
+            z = P::wsum(z, w[u]);
+            P::axpy(o, w[u], vv[u]);
+        }
+    });
+}
+
 // MODE kFused: Q,K,V,idx -> O.  kSddmm: Q,K,idx -> S.  kSpmm: Pin,V,idx -> O.
 template <typename T, int D, int MODE>
 __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
@@ -162,19 +226,12 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
     // (or from the start, when the weights are given) its weights.  The list is padded to keep_pad, a multiple of the keys one
     // trip of the loops below takes, with its last key: a padded entry has the score of a real one (no
     // effect on the maximum) and gets the weight 0, so the loops test nothing.
-    constexpr unsigned kRowBytes = D * sizeof(T), kPieceBytes = E * sizeof(T);
+    constexpr unsigned kRowBytes = D * sizeof(T);
     unsigned *sl = reinterpret_cast<unsigned *>(lds_scores) + wave * 2 * keep_pad;
     float *sc = reinterpret_cast<float *>(sl + keep_pad);
     unsigned *sw = reinterpret_cast<unsigned *>(sc);      // the same words once they hold weights
     for (int t = lane; t < keep_pad; t += kWave) sl[t] = (unsigned)min(max(list[min(t, keep - 1)], 0), L - 1) * kRowBytes;
     wave_lds_fence();
-    constexpr int U = 4;                  // independent gathers in flight per lane
-    static_assert(kRowPad % RPI == 0, "keep_pad is a whole number of single trips");
-    const unsigned piece_at = sub * kPieceBytes;
-    auto piece_of = [&](const T *head, unsigned row_at) {
-        return P::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(head) + (size_t)(row_at + piece_at)));
-    };
-
     float m = -INFINITY;
     // fused mode: the scores are kept as sign(scale) * q.k and the factor |scale| waits for the exponential
     const bool flip = MODE == kFused && scale < 0.f;
@@ -183,25 +240,7 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
         typename P::raw_t q = P::load(Q + (size_t)r * D + sub * E);
         if (flip) q = P::negate(q);
         const T *Kh = K + (size_t)n * L * D;
-        // UU gathers in flight per lane: trips of U while they fit, single ones for the rest
-        auto scores_of = [&](int t0, auto uu) {
-            constexpr int UU = decltype(uu)::value;
-            typename P::raw_t kv[UU];
-#pragma unroll
-            for (int u = 0; u < UU; ++u) kv[u] = piece_of(Kh, sl[t0 + u * RPI + grp]);
-            float acc[UU];
-#pragma unroll
-            for (int u = 0; u < UU; ++u) acc[u] = piece_sum<LPR>(P::dot(q, kv[u]));
-#pragma unroll
-            for (int u = 0; u < UU; ++u) {
-                const int t = t0 + u * RPI + grp;
-                if (MODE != kSddmm) m = fmaxf(m, acc[u]);
-                sc[t] = acc[u];               // every lane of the group writes the same value
-            }
-        };
-        int t0 = 0;
-        for (; t0 + U * RPI <= keep_pad; t0 += U * RPI) scores_of(t0, std::integral_constant<int, U>{});
-        for (; t0 < keep_pad; t0 += RPI) scores_of(t0, std::integral_constant<int, 1>{});
+        m = row_scores<T, D>(Kh, q, sl, sc, keep_pad, sub, grp);
         if (MODE == kSddmm) {
             // the row of scores leaves in one piece: consecutive lanes, consecutive entries
             wave_lds_fence();
@@ -226,27 +265,7 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = 0.f;
     const T *Vh = V + (size_t)n * L * D;
-    auto values_of = [&](int t0, auto uu) {
-        constexpr int UU = decltype(uu)::value;
-        typename P::raw_t vv[UU];
-        unsigned w[UU];
-#pragma unroll
-        for (int u = 0; u < UU; ++u) {
-            const int t = t0 + u * RPI + grp;
-            vv[u] = piece_of(Vh, sl[t]);
-            w[u] = sw[t];
-        }
-#pragma unroll
-        for (int u = 0; u < UU; ++u) {
-            z = P::wsum(z, w[u]);
-            P::axpy(o, w[u], vv[u]);
-        }
-    };
-    {
-        int t0 = 0;
-        for (; t0 + U * RPI <= keep_pad; t0 += U * RPI) values_of(t0, std::integral_constant<int, U>{});
-        for (; t0 < keep_pad; t0 += RPI) values_of(t0, std::integral_constant<int, 1>{});
-    }
+    row_values<T, D>(Vh, sl, sw, keep_pad, sub, grp, o, z);
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = groups_sum<LPR>(o[e]);
     if (MODE == kFused) {
@@ -264,10 +283,13 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
 }
 
 // Row kernel for masks in CSR form (threshold masks, section 3.1: the count per row varies).  Same
-// wavefront-per-row scheme as attention_rows, fused only; a row's list is taken in chunks of
+// wavefront-per-row scheme and the same gather loops as attention_rows, fused only; a row's list is taken in chunks of
 // kCsrChunk keys with a running maximum, so that any count fits the same LDS: when a later chunk
-// raises the maximum, the sums so far are rescaled by exp(m_old - m_new).
-constexpr int kCsrChunk = 1024;
+// raises the maximum, the sums so far are rescaled by exp(m_old - m_new).  4 KB of LDS per row leave room for eight rows
+// per SIMD, and most lists are one chunk.  N = 16, L = 2048, about 102 keys a row: 91 -> 54 us against tests per key,
+// a conversion per weight and gather, and 8 KB per row.
+constexpr int kCsrChunk = 512;
+static_assert(kCsrChunk % kRowPad == 0, "a full chunk needs no padding");
 
 template <typename T, int D>
 __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows_csr(
@@ -276,8 +298,9 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows_csr(
     float scale, unsigned total_rows)
 {
     typedef Piece<T> P;
-    constexpr int E = P::N, LPR = D / E, RPI = kWave / LPR, U = 4;
-    __shared__ int lists[kRowWaves][kCsrChunk];
+    constexpr int E = P::N, LPR = D / E;
+    constexpr unsigned kRowBytes = D * sizeof(T);
+    __shared__ unsigned lists[kRowWaves][kCsrChunk];
     __shared__ float scores[kRowWaves][kCsrChunk];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -288,60 +311,36 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows_csr(
     const size_t u = (size_t)n * (L / vec) + i / vec;
     const int beg = row_ptr[u];
     const int cnt = max(row_ptr[u + 1] - beg, 0);
-    int *sl = lists[wave];
+    unsigned *sl = lists[wave];
     float *sc = scores[wave];
-    const typename P::raw_t q = P::load(Q + (size_t)row * D + sub * E);
+    unsigned *sw = reinterpret_cast<unsigned *>(sc);      // the same words once they hold weights
+    // the scores are kept as sign(scale) * q.k and the factor |scale| waits for the exponential
+    typename P::raw_t q = P::load(Q + (size_t)row * D + sub * E);
+    if (scale < 0.f) q = P::negate(q);
+    const float factor = fabsf(scale);
     const T *Kh = K + (size_t)n * L * D, *Vh = V + (size_t)n * L * D;
 
     float m = -INFINITY, z = 0.f, o[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = 0.f;
     for (int c0 = 0; c0 < cnt; c0 += kCsrChunk) {
-        const int nk = min(kCsrChunk, cnt - c0);
-        for (int t = lane; t < nk; t += kWave) sl[t] = min(max(col[beg + c0 + t], 0), L - 1);
+        const int nk = min(kCsrChunk, cnt - c0), pad = (nk + kRowPad - 1) / kRowPad * kRowPad;
+        const int32_t *list = col + beg + c0;
+        for (int t = lane; t < pad; t += kWave) sl[t] = (unsigned)min(max(list[min(t, nk - 1)], 0), L - 1) * kRowBytes;
         wave_lds_fence();
-        float mc = -INFINITY;
-        for (int t0 = 0; t0 < nk; t0 += U * RPI) {
-            typename P::raw_t kv[U];
+        const float m_new = fmaxf(m, groups_max<LPR>(row_scores<T, D>(Kh, q, sl, sc, pad, sub, grp)));
+        if (c0 > 0) {
+            const float f = __expf(factor * (m - m_new));
+            z *= f;
 #pragma unroll
-            for (int x = 0; x < U; ++x) kv[x] = P::load(Kh + (unsigned)(sl[min(t0 + x * RPI + grp, nk - 1)] * D + sub * E));
-#pragma unroll
-            for (int x = 0; x < U; ++x) {
-                const int t = t0 + x * RPI + grp;
-                const float acc = piece_sum<LPR>(P::dot(q, kv[x])) * scale;
-                if (t < nk) {
-                    mc = fmaxf(mc, acc);
-                    if (sub == 0) sc[t] = acc;
-                }
-            }
+            for (int e = 0; e < E; ++e) o[e] *= f;
         }
-        mc = groups_max<LPR>(mc);
-        const float m_new = fmaxf(m, mc);
-        const float f = __expf(m - m_new);               // 0 for the first chunk (m = -inf)
-        z *= f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) o[e] *= f;
         m = m_new;
         wave_lds_fence();
-        for (int t = lane; t < nk; t += kWave) sc[t] = __expf(sc[t] - m);
+        for (int t = lane; t < pad; t += kWave) sw[t] = t < nk ? P::weight(__expf(factor * (sc[t] - m))) : 0u;
         wave_lds_fence();
-        for (int t0 = 0; t0 < nk; t0 += U * RPI) {
-            typename P::raw_t vv[U];
-            float p[U];
-#pragma unroll
-            for (int x = 0; x < U; ++x) {
-                const int t = t0 + x * RPI + grp;
-                const int tt = min(t, nk - 1);
-                vv[x] = P::load(Vh + (unsigned)(sl[tt] * D + sub * E));
-                p[x] = t < nk ? sc[tt] : 0.f;
-            }
-#pragma unroll
-            for (int x = 0; x < U; ++x) {
-                z += p[x];
-                P::axpy(o, P::weight(p[x]), vv[x]);
-            }
-        }
-        wave_lds_fence();                                  // the next chunk overwrites list and scores
+        row_values<T, D>(Vh, sl, sw, pad, sub, grp, o, z);
+        wave_lds_fence();                                  // the next chunk overwrites list and weights
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = groups_sum<LPR>(o[e]);
