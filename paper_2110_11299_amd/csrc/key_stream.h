@@ -175,9 +175,10 @@ __device__ __forceinline__ int mask_beyond(int v, int key, int L)
 
 // One bitmap word of a threshold sweep: 8 tiles, 32 consecutive keys of this lane's quarter, bit = score
 // reaches the threshold.  The stream was restarted with bias = -threshold, so a score misses the
-// threshold iff its sign bit is set, and one funnel shift per score moves that bit into the word.
+// threshold iff its sign bit is set, and one funnel shift per score moves that bit into the word.  *top: the largest of the
+// 32 and what it was.
 template <bool SAFE, int PAR, class Stream>
-__device__ __forceinline__ unsigned pass2_word(Stream &ks, int t8)
+__device__ __forceinline__ unsigned pass2_word(Stream &ks, int t8, int *top)
 {
     const unsigned next = ks.template begin_group<PAR>(t8);
     unsigned word = 0;
@@ -185,6 +186,8 @@ __device__ __forceinline__ unsigned pass2_word(Stream &ks, int t8)
     for (int j = 0; j < 8; ++j) {
         const v4i cur = ks.template next_tile<SAFE>(t8, j, next);
         shift_in_signs(word, cur);
+        *top = max(max(cur[0], cur[1]), *top);
+        *top = max(max(cur[2], cur[3]), *top);
         __builtin_amdgcn_sched_barrier(0);
     }
     ks.end_group();

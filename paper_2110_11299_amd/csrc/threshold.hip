@@ -5,12 +5,14 @@
 // which is what the paper's equal-count constraint avoids (section 5.2), so the mask is CSR:
 // row_ptr [units + 1], col [nnz], keys ascending per unit.
 //
-//   sweep   one wavefront per 16 units streams the keys once (the key stream of the fine-grained
-//           predictor): every score is compared with theta, the outcomes are the unit's bitmap,
-//           which goes to the workspace together with the unit's count.
-//   scan    exclusive prefix sum of the counts: blocks of 1024 units, then the block totals.
-//   fill    one wavefront per unit turns its bitmap into keys at row_ptr[u]; a unit without a key
-//           finds its best key with packed dot products.
+//   sweep   one wavefront per task of 16 units streams the keys once: every score is compared with theta, the outcomes are
+//           the units' bitmaps, which go to the workspace together with the task's count.  The largest score per lane and
+//           the word it lies in are kept beside it (half an operation per score): a unit without a key scores the 32 keys of
+//           that word again and keeps the best.
+//   scan    only for more than kDirectTasks tasks: exclusive prefix sum of the counts, blocks of 1024 tasks, then the block
+//           totals.
+//   fill    one workgroup per task: the task's place in col (the sum of the counts before it, unless the scan has it), row_ptr,
+//           and the bitmaps as keys, which leave through LDS as consecutive entries.
 #include "dsa_internal.h"
 #include "threshold_api.h"
 #include "key_stream.h"
@@ -18,13 +20,16 @@
 namespace dsa {
 namespace {
 
-constexpr int kScanBlock = 1024;        // units per block of the prefix sum
+constexpr int kScanBlock = 1024;        // tasks per block of the prefix sum
+// Up to here every fill workgroup adds up the counts before its own (16 KB at most, from L2) instead of two more launches:
+// 2048 tasks of L = 2048, N = 16: sweep, scan and fill together 39.2 us with the scan, 32.3 without.
+constexpr unsigned kDirectTasks = 4096;
 
 // Bitmap in the workspace: word w of lane l of task t at (t * NWL + w) * 64 + l (what a wavefront
 // stores with one instruction is contiguous).
 template <int K, int VEC>
 __global__ __launch_bounds__(kWave, 4) void threshold_sweep(const int8_t *__restrict__ Qt, const int8_t *__restrict__ Kt,
-                                                           unsigned *__restrict__ bitmap, int32_t *__restrict__ cnt,
+                                                           unsigned *__restrict__ bitmap, int32_t *__restrict__ task_count,
                                                            int L, int theta, int tasks_per_head)
 {
     const int lane = threadIdx.x;
@@ -44,37 +49,61 @@ __global__ __launch_bounds__(kWave, 4) void threshold_sweep(const int8_t *__rest
 
     KeyStream<K, VEC> ks;
     // no score lies beyond the limits
-    ks.start(Kh, Qh + (size_t)min(u0 + c, G - 1) * (VEC * K), unit_live, lane, Lq, L,
-             -max(-kSweepLimit, min(theta, kSweepLimit)));
+    const int8_t *Qu = Qh + (size_t)min(u0 + c, G - 1) * (VEC * K);
+    const int limit = max(-kSweepLimit, min(theta, kSweepLimit));
+    ks.start(Kh, Qu, unit_live, lane, Lq, L, -limit);
     unsigned *words = bitmap + (size_t)task * NWL * kWave + lane;
-    int mine = 0;
+    int mine = 0, best = INT32_MIN, best_word = 0;       // best: largest score - limit so far, in word g * NWL + best_word
     for (int w = 0; w < NWL; ++w) {
         unsigned word;
+        int top = INT32_MIN;
+        const int nv = key_lim - (key_lo + 32 * w);      // real keys in this word
         if (8 * w + 8 + decltype(ks)::kLookahead <= tfull) {
-            word = pass2_word<false, 0>(ks, 8 * w);
+            word = pass2_word<false, 0>(ks, 8 * w, &top);
         } else {
-            word = pass2_word<true, 0>(ks, 8 * w);
-            const int nv = key_lim - (key_lo + 32 * w);      // real keys in this word
+            word = pass2_word<true, 0>(ks, 8 * w, &top);
             word = nv >= 32 ? word : nv <= 0 ? 0u : word & ((1u << nv) - 1u);
         }
         words[(size_t)w * kWave] = word;
         mine += __popc(word);
+        // (keys beyond L score like the last one, which shares their word if there is a real key in it)
+        if (nv > 0 && top > best) { best = top; best_word = w; }
     }
     mine += __shfl_xor(mine, 16, kWave);
     mine += __shfl_xor(mine, 32, kWave);
-    if (g == 0 && unit_live) cnt[(size_t)n * G + u0 + c] = max(mine, 1);      // an empty unit keeps one key
+    const bool empty = unit_live && mine == 0;
+    if (__ballot(empty) != 0) {
+        // the unit keeps its best key (largest score, lower index among equals): lane g takes 8 of the 32 keys
+        int at = g * NWL + best_word;                    // word of the unit
+#pragma unroll
+        for (int off = 16; off < kWave; off <<= 1) {
+            const int b2 = __shfl_xor(best, off, kWave), at2 = __shfl_xor(at, off, kWave);
+            if (b2 > best || (b2 == best && at2 < at)) { best = b2; at = at2; }
+        }
+        int first = INT32_MAX;
+#pragma unroll
+        for (int i = 7; i >= 0; --i) {
+            const int key = 32 * at + 8 * g + i;
+            const int s = unit_key_score(reinterpret_cast<const int *>(Qu), Kh + (size_t)min(key, L - 1) * K, VEC, K / 4);
+            if (key < L && s - limit == best) first = key;
+        }
+        first = min(first, __shfl_xor(first, 16, kWave));
+        first = min(first, __shfl_xor(first, 32, kWave));
+        if (empty && g == at / NWL) words[(size_t)(at % NWL) * kWave] = 1u << (first & 31);      // this lane's own word
+    }
+    const int all = wave_sum(g == 0 && unit_live ? max(mine, 1) : 0);
+    if (lane == 0) task_count[task] = all;
 }
 
-// Exclusive prefix sums inside blocks of kScanBlock counts (into row_ptr) and the block totals.
-__global__ __launch_bounds__(256) void scan_blocks(const int32_t *__restrict__ cnt, int32_t *__restrict__ row_ptr,
-                                                   int32_t *__restrict__ block_total, unsigned units)
+// Exclusive prefix sums inside blocks of kScanBlock counts (in place) and the block totals.
+__global__ __launch_bounds__(256) void scan_blocks(int32_t *__restrict__ count, int32_t *__restrict__ block_total, unsigned tasks)
 {
     __shared__ int part[256];
     const unsigned base = blockIdx.x * kScanBlock + threadIdx.x * 4;
     int v[4], s = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        v[i] = base + i < units ? cnt[base + i] : 0;
+        v[i] = base + i < tasks ? count[base + i] : 0;
         s += v[i];
     }
     part[threadIdx.x] = s;
@@ -88,15 +117,14 @@ __global__ __launch_bounds__(256) void scan_blocks(const int32_t *__restrict__ c
     int run = part[threadIdx.x] - s;                     // exclusive
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        if (base + i < units) row_ptr[base + i] = run;
+        if (base + i < tasks) count[base + i] = run;
         run += v[i];
     }
     if (threadIdx.x == 255) block_total[blockIdx.x] = part[255];
 }
 
 // Exclusive prefix sum of the block totals, in place: one workgroup walks them 256 at a time.
-__global__ __launch_bounds__(256) void scan_totals(int32_t *__restrict__ block_total, unsigned blocks,
-                                                   int32_t *__restrict__ row_ptr, unsigned units)
+__global__ __launch_bounds__(256) void scan_totals(int32_t *__restrict__ block_total, unsigned blocks)
 {
     __shared__ int part[256];
     __shared__ int carry;
@@ -118,60 +146,90 @@ __global__ __launch_bounds__(256) void scan_totals(int32_t *__restrict__ block_t
         if (threadIdx.x == 255) carry += part[255];
         __syncthreads();
     }
-    if (threadIdx.x == 0) row_ptr[units] = carry;        // nnz
 }
 
-// One wavefront per unit: final row_ptr[u] and the unit's keys.
-template <int K>
-__global__ __launch_bounds__(256) void threshold_fill(const int8_t *__restrict__ Qt, const int8_t *__restrict__ Kt,
-                                                      const unsigned *__restrict__ bitmap,
+constexpr int kFillWaves = 8;
+constexpr int kFillRow = kWave + 1;     // words of LDS for one stored word of all lanes: a unit's words then lie on different banks
+
+// LDS: [NWL][kFillRow] the task's bitmap, then per wavefront the keys of 64 of a unit's words.
+__host__ __device__ inline size_t fill_lds_bytes(int NWL)
+{
+    return ((size_t)NWL * kFillRow * 4 + 15) / 16 * 16 + kFillWaves * 32 * kWave * sizeof(uint16_t);
+}
+
+__global__ __launch_bounds__(kFillWaves *kWave) void threshold_fill(const unsigned *__restrict__ bitmap,
+                                                      const int32_t *__restrict__ task_count,
                                                       const int32_t *__restrict__ block_total,
                                                       int32_t *__restrict__ row_ptr, int32_t *__restrict__ col,
                                                       long long col_capacity, int L, int vec, int tasks_per_head,
                                                       unsigned units)
 {
-    const int lane = threadIdx.x & (kWave - 1);
-    const unsigned u = xcd_contiguous(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
-    if (u >= units) return;
+    extern __shared__ __align__(16) unsigned words[];
+    __shared__ int s_count[16], s_part[kFillWaves];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const unsigned task = xcd_contiguous(blockIdx.x, gridDim.x);
     const int G = L / vec;
-    const unsigned n = u / (unsigned)G;
-    const int i = (int)(u % (unsigned)G);
+    const unsigned n = task / (unsigned)tasks_per_head;
+    const int u0 = (int)(task % (unsigned)tasks_per_head) * 16, nu = min(16, G - u0);
     const int Lq = stream_quarter(L), NWL = Lq / 32, NW = 4 * NWL;
-    const unsigned task = n * (unsigned)tasks_per_head + (unsigned)(i >> 4);
-    const int c = i & 15;
-    const unsigned *words = bitmap + (size_t)task * NWL * kWave + c;
-    const long long start = (long long)row_ptr[u] + block_total[u / kScanBlock];
-    if (lane == 0) row_ptr[u] = (int32_t)start;
-    int32_t *out = col + start;
-    int base = 0;
-    // word W of the unit in key order: quarter W / NWL, word W % NWL of lane 16 * quarter + c
-    for (int W0 = 0; W0 < NW; W0 += kWave) {
-        const int W = W0 + lane;
-        const int q = W / NWL, w = W - q * NWL;
-        unsigned m = W < NW ? words[(size_t)w * kWave + 16 * q] : 0u;
-        const int cc = __popc(m);
-        int total;
-        int rank = base + wave_incl_scan(cc, lane, &total) - cc;
-        base += total;
-        const int key1 = q * Lq + 32 * w - 1;
-        while (m) {
-            if (start + rank < col_capacity) out[rank] = key1 + __ffs(m);
-            ++rank;
-            m &= m - 1u;
-        }
+    uint16_t *keys = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(words) + fill_lds_bytes(NWL)) -
+                     (kFillWaves - wave) * 32 * kWave;
+    const unsigned *stored = bitmap + (size_t)task * NWL * kWave;
+    for (int e = tid; e < NWL * kWave; e += kFillWaves * kWave) words[(e / kWave) * kFillRow + lane] = stored[e];
+    // entries before the task's
+    int before = 0;
+    if (block_total) {
+        before = task_count[task] + block_total[task / kScanBlock];
+    } else {
+        for (unsigned t = tid; t < task; t += kFillWaves * kWave) before += task_count[t];
+        before = wave_sum(before);
+        if (lane == 0) s_part[wave] = before;
     }
-    if (base == 0) {
-        // no key reached theta: the unit keeps its best key (largest score, lower index among equals)
-        const int *qu = reinterpret_cast<const int *>(Qt + ((size_t)n * L + (size_t)i * vec) * K);
-        const int8_t *Kh = Kt + (size_t)n * L * K;
-        int best = INT32_MIN, at = 0;
-        for (int j = lane; j < L; j += kWave) {
-            const int s = unit_key_score(qu, Kh + (size_t)j * K, vec, K / 4);
-            if (s > best) { best = s; at = j; }          // ascending j per lane: the first maximum stays
+    __syncthreads();
+    if (!block_total) {
+        before = 0;
+#pragma unroll
+        for (int w = 0; w < kFillWaves; ++w) before += s_part[w];
+    }
+    // word W of unit c in key order: quarter W / NWL, word W % NWL of lane 16 * quarter + c
+    auto word_of = [&](int c, int W) -> unsigned {
+        const int q = W / NWL, w = W - q * NWL;
+        return W < NW ? words[w * kFillRow + 16 * q + c] : 0u;
+    };
+    for (int c = wave; c < 16; c += kFillWaves) {
+        int count = 0;
+        for (int W = lane; W < NW; W += kWave) count += __popc(word_of(c, W));
+        count = wave_sum(count);
+        if (lane == 0) s_count[c] = count;
+    }
+    __syncthreads();
+    for (int c = wave; c < nu; c += kFillWaves) {
+        long long start = before;
+        for (int x = 0; x < c; ++x) start += s_count[x];
+        const unsigned u = n * (unsigned)G + u0 + c;
+        if (lane == 0) {
+            row_ptr[u] = (int32_t)start;
+            if (u + 1 == units) row_ptr[units] = (int32_t)(start + s_count[c]);       // nnz
         }
-        const int top = wave_max(best);
-        const int first = wave_min(best == top ? at : INT32_MAX);
-        if (lane == 0 && start < col_capacity) out[0] = first;
+        int32_t *out = col + start;
+        const long long room = col_capacity - start;      // entries beyond the capacity are left out
+        int done = 0;
+        for (int W0 = 0; W0 < NW; W0 += kWave) {
+            const int W = W0 + lane;
+            unsigned m = word_of(c, W);
+            int total;
+            int rank = wave_incl_scan(__popc(m), lane, &total) - __popc(m);
+            const int key1 = 32 * W - 1;
+            while (m) {
+                keys[rank++] = (uint16_t)(key1 + __ffs(m));
+                m &= m - 1u;
+            }
+            wave_lds_sync();
+            for (int t = lane; t < total; t += kWave)
+                if (done + t < room) out[done + t] = keys[t];
+            wave_lds_sync();
+            done += total;
+        }
     }
 }
 
@@ -182,16 +240,20 @@ hipError_t launch_threshold_kv(const dsa_shape &sh, const int8_t *Qt, const int8
     const int tasks_per_head = (sh.L / VEC + 15) / 16;
     const unsigned tasks = (unsigned)sh.B * sh.H * tasks_per_head;
     const unsigned units = (unsigned)sh.B * sh.H * (sh.L / VEC);
-    const unsigned blocks = (units + kScanBlock - 1) / kScanBlock;
     const size_t bitmap_words = (size_t)tasks * (stream_quarter(sh.L) / 32) * kWave;
     unsigned *bitmap = static_cast<unsigned *>(ws);
-    int32_t *cnt = reinterpret_cast<int32_t *>(bitmap + bitmap_words);
-    int32_t *block_total = cnt + units;
-    hipLaunchKernelGGL((threshold_sweep<K, VEC>), dim3(tasks), dim3(kWave), 0, st, Qt, Kt, bitmap, cnt, sh.L, theta,
+    int32_t *task_count = reinterpret_cast<int32_t *>(bitmap + bitmap_words);
+    int32_t *block_total = tasks > kDirectTasks ? task_count + tasks : nullptr;
+    hipLaunchKernelGGL((threshold_sweep<K, VEC>), dim3(tasks), dim3(kWave), 0, st, Qt, Kt, bitmap, task_count, sh.L, theta,
                        tasks_per_head);
-    hipLaunchKernelGGL(scan_blocks, dim3(blocks), dim3(256), 0, st, cnt, row_ptr, block_total, units);
-    hipLaunchKernelGGL(scan_totals, dim3(1), dim3(256), 0, st, block_total, blocks, row_ptr, units);
-    hipLaunchKernelGGL(threshold_fill<K>, dim3((units + 3) / 4), dim3(256), 0, st, Qt, Kt, bitmap, block_total, row_ptr,
+    if (block_total) {
+        const unsigned blocks = (tasks + kScanBlock - 1) / kScanBlock;
+        hipLaunchKernelGGL(scan_blocks, dim3(blocks), dim3(256), 0, st, task_count, block_total, tasks);
+        hipLaunchKernelGGL(scan_totals, dim3(1), dim3(256), 0, st, block_total, blocks);
+    }
+    const size_t lds = fill_lds_bytes(stream_quarter(sh.L) / 32);
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(threshold_fill), lds)) return e;
+    hipLaunchKernelGGL(threshold_fill, dim3(tasks), dim3(kFillWaves * kWave), lds, st, bitmap, task_count, block_total, row_ptr,
                        col, col_capacity, sh.L, VEC, tasks_per_head, units);
     return hipGetLastError();
 }

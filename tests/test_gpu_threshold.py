@@ -153,3 +153,14 @@ def test_threshold_errors_launch_nothing(dsa):
     big = b.make_shape(1, 64, 8192, 64, 32, 1, 1, b.DSA_F32, 0.125)       # 64 * 8192 * 8192 > 2^31 - 1
     assert lib.dsa_predict_mask_threshold(ctypes.byref(big), fake, fake, 0, fake, fake, 10, fake, 1 << 40, None) == 3
     assert lib.dsa_masked_attention_csr(ctypes.byref(sh), fake, fake, fake, None, fake, fake, None) == 1
+
+
+@pytest.mark.parametrize("H,L,vec", [(520, 130, 1), (700, 200, 4)])
+def test_threshold_many_tasks(dsa, oracle, H, L, vec):
+    """More tasks of 16 units than the fill adds up by itself."""
+    Qt, Kt = di.random_int8_case(L, 1, H, L, 16)
+    x = di.DsaInputs(di.custom_config(B=1, H=H, L=L, d=64, dtype="f32", rank=4, k=16, vec=vec, keep=1, seed=3),
+                     None, None, None, Qt, Kt, None, None, None)
+    for fraction in (0.001, 0.1):
+        run_case(dsa, oracle, x, theta_for(oracle, x, fraction), "many tasks", check_attention=False)
+    run_case(dsa, oracle, x, theta_for(oracle, x, 0.1), "many tasks, capacity", capacity=5000, check_attention=False)
