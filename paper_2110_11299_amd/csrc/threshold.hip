@@ -151,10 +151,11 @@ __global__ __launch_bounds__(256) void scan_totals(int32_t *__restrict__ block_t
 constexpr int kFillWaves = 8;
 constexpr int kFillRow = kWave + 1;     // words of LDS for one stored word of all lanes: a unit's words then lie on different banks
 
-// LDS: [NWL][kFillRow] the task's bitmap, then per wavefront the keys of 64 of a unit's words.
+// LDS: [NWL][kFillRow] the task's bitmap, then per wavefront the keys of 64 of a unit's words, then the units' counts and a
+// sum per wavefront.
 __host__ __device__ inline size_t fill_lds_bytes(int NWL)
 {
-    return ((size_t)NWL * kFillRow * 4 + 15) / 16 * 16 + kFillWaves * 32 * kWave * sizeof(uint16_t);
+    return ((size_t)NWL * kFillRow * 4 + 15) / 16 * 16 + kFillWaves * 32 * kWave * sizeof(uint16_t) + (16 + kFillWaves) * sizeof(int);
 }
 
 __global__ __launch_bounds__(kFillWaves *kWave) void threshold_fill(const unsigned *__restrict__ bitmap,
@@ -165,15 +166,15 @@ __global__ __launch_bounds__(kFillWaves *kWave) void threshold_fill(const unsign
                                                       unsigned units)
 {
     extern __shared__ __align__(16) unsigned words[];
-    __shared__ int s_count[16], s_part[kFillWaves];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const unsigned task = xcd_contiguous(blockIdx.x, gridDim.x);
     const int G = L / vec;
     const unsigned n = task / (unsigned)tasks_per_head;
     const int u0 = (int)(task % (unsigned)tasks_per_head) * 16, nu = min(16, G - u0);
     const int Lq = stream_quarter(L), NWL = Lq / 32, NW = 4 * NWL;
-    uint16_t *keys = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(words) + fill_lds_bytes(NWL)) -
-                     (kFillWaves - wave) * 32 * kWave;
+    int *s_count = reinterpret_cast<int *>(reinterpret_cast<char *>(words) + fill_lds_bytes(NWL)) - (16 + kFillWaves);
+    int *s_part = s_count + 16;
+    uint16_t *keys = reinterpret_cast<uint16_t *>(s_count) - (kFillWaves - wave) * 32 * kWave;
     const unsigned *stored = bitmap + (size_t)task * NWL * kWave;
     for (int e = tid; e < NWL * kWave; e += kFillWaves * kWave) words[(e / kWave) * kFillRow + lane] = stored[e];
     // entries before the task's

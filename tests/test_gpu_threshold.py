@@ -155,9 +155,9 @@ def test_threshold_errors_launch_nothing(dsa):
     assert lib.dsa_masked_attention_csr(ctypes.byref(sh), fake, fake, fake, None, fake, fake, None) == 1
 
 
-@pytest.mark.parametrize("H,L,vec", [(520, 130, 1), (700, 200, 4)])
-def test_threshold_many_tasks(dsa, oracle, H, L, vec):
-    """More tasks of 16 units than the fill adds up by itself."""
+@pytest.mark.parametrize("H,L,vec", [(520, 130, 1), (700, 200, 4), (1, 9000, 8), (1, 16384, 8)])
+def test_threshold_many_tasks_and_long_bitmaps(dsa, oracle, H, L, vec):
+    """More tasks of 16 units than the fill adds up by itself; bitmaps of a task that take more than 48 KB of LDS."""
     Qt, Kt = di.random_int8_case(L, 1, H, L, 16)
     x = di.DsaInputs(di.custom_config(B=1, H=H, L=L, d=64, dtype="f32", rank=4, k=16, vec=vec, keep=1, seed=3),
                      None, None, None, Qt, Kt, None, None, None)
