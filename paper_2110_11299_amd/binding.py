@@ -143,16 +143,32 @@ def _check(status: int, where: str):
         raise DsaError(status, where)
 
 
+# The argument types of the library turn integers and None into pointers.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = None
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle, without a Stream object around it where torch offers that."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        torch.cuda.current_stream()                # initialises CUDA
+        get, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
+        _raw_stream = (lambda: get(device())) if get else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _raw_stream()
 
 
 def _dev(t, dtype, shape):
+    # a call checks up to seven tensors: the cheap form first, everything it does not accept goes on to the full one
+    try:
+        if t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+            return t
+    except AttributeError:
+        pass
     import torch
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype
             and tuple(t.shape) == tuple(shape)):
