@@ -514,50 +514,49 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
         if (most == 0) continue;
         const uint16_t *ul = list + u * kBandCap;
         const unsigned char *uq = s_q + u * qstride;
+        // (the loops over slots leave where the band ends: one taken branch, not one per slot that is skipped)
         int sc[kBandSlots];
         int peak = INT32_MIN;
 #pragma unroll
+        for (int i = 0; i < kBandSlots; ++i) sc[i] = INT32_MIN;
+#pragma unroll
         for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
-            if (16 * i0 < most) {
-                const int8_t *kr[4];
-                int s[4], sh[4];
+            if (16 * i0 >= most) break;
+            const int8_t *kr[4];
+            int s[4], sh[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const unsigned code = ul[max(min(c + 16 * (i0 + i), nb - 1), 0)];
-                    const int key = (int)(code >> kPosBits) * Lr + (int)(code & ((1u << kPosBits) - 1));
-                    kr[i] = Kh + (size_t)((unsigned)min(key, L - 1) * (unsigned)k);
-                    s[i] = sh[i] = 0;
-                }
-                auto piece = [&](int p) {
-                    v4i kk[4];
+            for (int i = 0; i < 4; ++i) {
+                const unsigned code = ul[max(min(c + 16 * (i0 + i), nb - 1), 0)];
+                const int key = (int)(code >> kPosBits) * Lr + (int)(code & ((1u << kPosBits) - 1));
+                kr[i] = Kh + (size_t)((unsigned)min(key, L - 1) * (unsigned)k);
+                s[i] = sh[i] = 0;
+            }
+            auto piece = [&](int p) {
+                v4i kk[4];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) kk[i] = *reinterpret_cast<const v4i *>(kr[i] + 16 * p);
-                    const v4i ql = *reinterpret_cast<const v4i *>(uq + 16 * p);
-                    const v4i qh = *reinterpret_cast<const v4i *>(uq + (GROUP ? k + 16 : 0) + 16 * p);
+                for (int i = 0; i < 4; ++i) kk[i] = *reinterpret_cast<const v4i *>(kr[i] + 16 * p);
+                const v4i ql = *reinterpret_cast<const v4i *>(uq + 16 * p);
+                const v4i qh = *reinterpret_cast<const v4i *>(uq + (GROUP ? k + 16 : 0) + 16 * p);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                        for (int x = 0; x < 4; ++x) {
-                            s[i] = __builtin_amdgcn_sdot4(ql[x], kk[i][x], s[i], false);
-                            if (GROUP) sh[i] = __builtin_amdgcn_sdot4(qh[x], kk[i][x], sh[i], false);
-                        }
-                    if (K > 32) __builtin_amdgcn_sched_barrier(0);       // the rows of four keys do not fit the registers
-                };
-                if constexpr (K != 0) {
+                    for (int x = 0; x < 4; ++x) {
+                        s[i] = __builtin_amdgcn_sdot4(ql[x], kk[i][x], s[i], false);
+                        if (GROUP) sh[i] = __builtin_amdgcn_sdot4(qh[x], kk[i][x], sh[i], false);
+                    }
+                if (K > 32) __builtin_amdgcn_sched_barrier(0);       // the rows of four keys do not fit the registers
+            };
+            if constexpr (K != 0) {
 #pragma unroll
-                    for (int p = 0; p < K / 16; ++p) piece(p);
-                } else {
-                    for (int p = 0; p < k / 16; ++p) piece(p);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int v = s[i] + 128 * sh[i];
-                    sc[i0 + i] = c + 16 * (i0 + i) < nb ? v : INT32_MIN;
-                    peak = max(peak, sc[i0 + i]);
-                }
+                for (int p = 0; p < K / 16; ++p) piece(p);
             } else {
+                for (int p = 0; p < k / 16; ++p) piece(p);
+            }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) sc[i0 + i] = INT32_MIN;
+            for (int i = 0; i < 4; ++i) {
+                const int v = s[i] + 128 * sh[i];
+                sc[i0 + i] = c + 16 * (i0 + i) < nb ? v : INT32_MIN;
+                peak = max(peak, sc[i0 + i]);
             }
         }
         // The need-th largest of the band: all its scores are >= tl and at least need of them exist.  The interval is cut
@@ -571,11 +570,11 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
             const int mid = lo_ + step;
             int cnt = 0;
 #pragma unroll
-            for (int i0 = 0; i0 < kBandSlots; i0 += 4)
-                if (16 * i0 < most) {
+            for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
+                if (16 * i0 >= most) break;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) cnt += sc[i0 + i] >= mid;
-                }
+                for (int i = 0; i < 4; ++i) cnt += sc[i0 + i] >= mid;
+            }
             cnt = row_sum(cnt);
             if (lo_ < hi_) {
                 const bool ge = cnt >= need;
@@ -588,26 +587,25 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
         const int Tx = lo_;
         int gt = 0;
 #pragma unroll
-        for (int i0 = 0; i0 < kBandSlots; i0 += 4)
-            if (16 * i0 < most) {
+        for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
+            if (16 * i0 >= most) break;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) gt += sc[i0 + i] > Tx;
-            }
+            for (int i = 0; i < 4; ++i) gt += sc[i0 + i] > Tx;
+        }
         const int need_eq = need - row_sum(gt);
         int eq_before = 0;
         const unsigned below = (1u << c) - 1u;
 #pragma unroll
         for (int i = 0; i < kBandSlots; ++i) {
-            if (16 * i < most) {
-                const bool eq = sc[i] == Tx && c + 16 * i < nb;
-                const unsigned meq = (unsigned)(__ballot(eq) >> (16 * g)) & 0xffffu;
-                const bool take = c + 16 * i < nb && (sc[i] > Tx || (eq && eq_before + __popc(meq & below) < need_eq));
-                eq_before += __popc(meq);
-                if (take) {
-                    const unsigned code = ul[c + 16 * i], hh = code >> kPosBits, pos = code & ((1u << kPosBits) - 1);
-                    const unsigned thread = (hh >> 2) * kWave + (hh & 3) * 16 + (u & 15);
-                    atomicOr(&sel[((u >> 4) * NW + (pos >> 5)) * T + thread], 1u << (pos & 31));
-                }
+            if (16 * i >= most) break;
+            const bool eq = sc[i] == Tx && c + 16 * i < nb;
+            const unsigned meq = (unsigned)(__ballot(eq) >> (16 * g)) & 0xffffu;
+            const bool take = c + 16 * i < nb && (sc[i] > Tx || (eq && eq_before + __popc(meq & below) < need_eq));
+            eq_before += __popc(meq);
+            if (take) {
+                const unsigned code = ul[c + 16 * i], hh = code >> kPosBits, pos = code & ((1u << kPosBits) - 1);
+                const unsigned thread = (hh >> 2) * kWave + (hh & 3) * 16 + (u & 15);
+                atomicOr(&sel[((u >> 4) * NW + (pos >> 5)) * T + thread], 1u << (pos & 31));
             }
         }
     }
