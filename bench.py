@@ -277,13 +277,13 @@ def main() -> int:
     dom = stages["C4f"]
     scores_per_launch = float(cf.N) * cf.L * cf.L
     achieved_alu = scores_per_launch / (dom["predict_ms"] * 1e-3) / 1e12
-    roofline = dict(kernel="predict_split<32, false, 1, 8> (fine-grained dsa_predict_mask at C4: a1 + b)", bound="alu",
+    roofline = dict(kernel="predict_split<32, false, 1, 32, 8> (fine-grained dsa_predict_mask at C4: a1 + b)", bound="alu",
                     achieved=achieved_alu, peak=ALU_PEAK_LANE_OPS / 1e12, unit="Tlane-op/s",
                     frac=achieved_alu / (ALU_PEAK_LANE_OPS / 1e12),
-                    traffic=profiled_traffic_bytes("predict_split<32, false, 1, 8>"),
+                    traffic=profiled_traffic_bytes("predict_split<32, false, 1, 32, 8>"),
                     traffic_source="profiles/bench_C4_hbm_traffic.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, not measured in this run)",
-                    valu_busy=profiled_ratio("vector ALU busy", "predict_split<32, false, 1, 8>"),
-                    mfma_busy=profiled_ratio("matrix-core busy", "predict_split<32, false, 1, 8>"),
+                    valu_busy=profiled_ratio("vector ALU busy", "predict_split<32, false, 1, 32, 8>"),
+                    mfma_busy=profiled_ratio("matrix-core busy", "predict_split<32, false, 1, 32, 8>"),
                     busy_source="profiles/bench_C4_pmc_counters.md (share of the launch in which the vector ALUs / the matrix cores issue; not measured in this run)",
                     algorithmic_ops=scores_per_launch, algorithmic_unit="score inspections (N*L*L), one lane operation each",
                     avg_launch_ms=dom["predict_ms"], int8_TOPS=dom["predict_int8_TOPS"],

@@ -268,8 +268,7 @@ dsa_status dsa_predict_mask_bits(const dsa_shape *sh, int32_t bits, const void *
     int8_t *q8 = static_cast<int8_t *>(ws), *k8 = q8 + codes;
     void *pws = k8 + codes;
     hipStream_t st = (hipStream_t)stream;
-    if (hipError_t e = dsa::launch_unpack_codes(bits, Qt, q8, n_codes, st)) return from_hip(e);
-    if (hipError_t e = dsa::launch_unpack_codes(bits, Kt, k8, n_codes, st)) return from_hip(e);
+    if (hipError_t e = dsa::launch_unpack_codes(bits, Qt, Kt, q8, k8, n_codes, st)) return from_hip(e);
     return from_hip(dsa::launch_predict(*sh, q8, k8, idx, pws, st));
 }
 
