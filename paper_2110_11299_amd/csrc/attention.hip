@@ -574,7 +574,7 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
 // tiles), which is where the second product wants its weights: neither scores nor weights pass through LDS.  The
 // exponentials are taken relative to a running reference that is moved only when a score exceeds it by a factor of
 // 2^kUnitSlack, so that a step needs no reduction across lanes.
-// Every list length fits (the list takes 4 bytes per key, 128 KB at most for D = 128).
+// Every list length fits (4 bytes per key and wavefront; 96 KB of LDS with 4096 keys at D = 128).
 //
 // What bounds it: LDS (145 cycles per step and wavefront, two thirds of them the writes of the gathered rows; active 69 % of
 // the time at N = 64, L = 2000, keep = 200, VEC = 4), next to it the latency of list -> gather -> tile for short lists.
