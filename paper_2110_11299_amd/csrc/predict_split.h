@@ -39,8 +39,11 @@ namespace {
 constexpr int kTile = 16;               // units of one matrix instruction
 constexpr int kBins = 128;              // histogram bins per unit
 constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' bins start in different banks
-constexpr int kBandCap = 384;           // keys of one unit's band that are scored (INT4 codes: two plateaus of about 120 equal scores)
-constexpr int kBandSlots = kBandCap / 16;
+// Keys of one unit's band that are scored, 16 per slot.  Few-level codes make bands of whole plateaus of equal scores: with 24
+// slots INT4 codes at L = 4096, keep = 205 sweep 1.47 times on average, with 32 the kernel takes 154 us instead of 168.  Where
+// that does not pay (short ranges, whose bands are one bucket, and units of several rows, which have many levels) or the
+// registers are short (two tiles), it is 24: L = 256, 9.5 us against 10.4.
+template <bool GROUP, int UT, int NWM> constexpr int band_slots() { return !GROUP && UT == 1 && NWM >= 4 ? 32 : 24; }
 constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
 
 struct SplitArgs {
@@ -56,7 +59,7 @@ struct SplitArgs {
 // LDS of a workgroup, in bytes from the start (every part a multiple of 16).
 struct SplitLds {
     unsigned tot, q, hist, list, bytes;
-    __host__ __device__ SplitLds(int W, int UT, int NW, int k, bool group, int keep, bool direct)
+    __host__ __device__ SplitLds(int W, int UT, int NW, int k, bool group, int keep, bool direct, int slots)
     {
         const unsigned U = kTile * UT;
         tot = 6 * U * 4;                                        // [6][U]: tl, th, need, band count, and two spare
@@ -64,7 +67,7 @@ struct SplitLds {
         hist = q + U * (group ? 2 : 1) * (k + 16);              // [U][parts][k + 16]
         const unsigned h = U * kBinStride * 4, s = UT * NW * W * kWave * 4;
         list = hist + (h > s ? h : s);                          // [U][bins], later the selected band bits [UT][NW][threads]
-        bytes = list + U * kBandCap * 2;                        // [U][kBandCap]
+        bytes = list + U * slots * 16 * 2;                      // [U][16 slots]
         const unsigned rows = hist + (direct ? 0 : (U * keep * 2 + 16 + 15) / 16 * 16);   // image of the index rows, last
         if (rows > bytes) bytes = rows;
     }
@@ -110,6 +113,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
     constexpr int TB = NSB * R;                          // tiles per batch
     constexpr int PARTS = GROUP ? 2 : 1;
     constexpr int U = kTile * UT;
+    constexpr int kBandSlots = band_slots<GROUP, UT, NWM>(), kBandCap = 16 * kBandSlots;
     extern __shared__ __align__(16) unsigned char lds[];
 
     const int k = K ? K : a.k;
@@ -118,7 +122,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int c = lane & 15, g = lane >> 4, h = 4 * wv + g;
-    const SplitLds at(W, UT, NW, k, GROUP, keep, a.direct);
+    const SplitLds at(W, UT, NW, k, GROUP, keep, a.direct, kBandSlots);
     int *s_tl = reinterpret_cast<int *>(lds), *s_th = s_tl + U, *s_need = s_th + U, *s_nb = s_need + U;
     int *s_totl = reinterpret_cast<int *>(lds + at.tot), *s_toth = s_totl + W * U;       // [W][U] each
     unsigned char *s_q = lds + at.q;
@@ -764,7 +768,7 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
     a.target_l = p.target_l;
     a.target_h = p.target_h;
     a.direct = (size_t)kTile * UT * sh.keep * 2 > 128 * 1024;
-    const size_t lds = SplitLds(p.W, UT, p.NW, sh.k, GROUP, sh.keep, a.direct != 0).bytes;
+    const size_t lds = SplitLds(p.W, UT, p.NW, sh.k, GROUP, sh.keep, a.direct != 0, band_slots<GROUP, UT, NWM>()).bytes;
     auto kern = predict_split<K, GROUP, UT, NB, NWM>;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds)) return e;
     hipLaunchKernelGGL(kern, dim3((unsigned)sh.B * sh.H * a.wgs_per_head), dim3(p.W * kWave), lds, st, a);
