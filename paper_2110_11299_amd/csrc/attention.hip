@@ -173,8 +173,8 @@ __device__ __forceinline__ float row_scores(const T *Kh, typename Piece<T>::raw_
     return m;
 }
 
-// o += weight * value row and z += weight over the entries of this lane group.
-template <typename T, int D>
+// o += weight * value row over the entries of this lane group, and z += weight if SUM.
+template <typename T, int D, bool SUM>
 __device__ __forceinline__ void row_values(const T *Vh, const unsigned *sl, const unsigned *sw, int n, int sub, int grp,
                                            float (&o)[Piece<T>::N], float &z)
 {
@@ -193,7 +193,7 @@ __device__ __forceinline__ void row_values(const T *Vh, const unsigned *sl, cons
         }
 #pragma unroll
         for (int u = 0; u < UU; ++u) {
-            z = P::wsum(z, w[u]);
+            if (SUM) z = P::wsum(z, w[u]);
             P::axpy(o, w[u], vv[u]);
         }
     });
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = 0.f;
     const T *Vh = V + (size_t)n * L * D;
-    row_values<T, D>(Vh, sl, sw, keep_pad, sub, grp, o, z);
+    row_values<T, D, MODE == kFused>(Vh, sl, sw, keep_pad, sub, grp, o, z);
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = groups_sum<LPR>(o[e]);
     if (MODE == kFused) {
@@ -288,6 +288,7 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
 // raises the maximum, the sums so far are rescaled by exp(m_old - m_new).  4 KB of LDS per row leave room for eight rows
 // per SIMD, and most lists are one chunk.  N = 16, L = 2048, about 102 keys a row: 91 -> 54 us against tests per key,
 // a conversion per weight and gather, and 8 KB per row.
+// The weights are summed in fp32 as they are made; only the products take them rounded, if T is bfloat16.
 constexpr int kCsrChunk = 512;
 static_assert(kCsrChunk % kRowPad == 0, "a full chunk needs no padding");
 
@@ -337,14 +338,18 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows_csr(
         }
         m = m_new;
         wave_lds_fence();
-        for (int t = lane; t < pad; t += kWave) sw[t] = t < nk ? P::weight(__expf(factor * (sc[t] - m))) : 0u;
+        for (int t = lane; t < pad; t += kWave) {
+            const float p = t < nk ? __expf(factor * (sc[t] - m)) : 0.f;
+            z += p;
+            sw[t] = P::weight(p);
+        }
         wave_lds_fence();
-        row_values<T, D>(Vh, sl, sw, pad, sub, grp, o, z);
+        row_values<T, D, false>(Vh, sl, sw, pad, sub, grp, o, z);
         wave_lds_fence();                                  // the next chunk overwrites list and weights
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) o[e] = groups_sum<LPR>(o[e]);
-    z = groups_sum<LPR>(z);
+    z = wave_all_sum(z);
     const float inv = cnt > 0 ? 1.f / z : 0.f;            // a row without keys (not made by the predictor) gives 0
     if (grp == 0) {
         float *out = O + (size_t)row * D + sub * E;

@@ -164,3 +164,29 @@ def test_threshold_many_tasks_and_long_bitmaps(dsa, oracle, H, L, vec):
     for fraction in (0.001, 0.1):
         run_case(dsa, oracle, x, theta_for(oracle, x, fraction), "many tasks", check_attention=False)
     run_case(dsa, oracle, x, theta_for(oracle, x, 0.1), "many tasks, capacity", capacity=5000, check_attention=False)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [2, 41, 700])
+def test_csr_normaliser_is_summed_in_fp32(dsa, oracle, d, n):
+    """One key of every row has the weight 1, which no rounding changes, and the only value that is not 0, so a row's output
+    is 1 / (sum of its weights).  Summed in fp32 that is good to the errors of an exponential and of 700 additions (2^-24
+    each, of either sign); a sum of weights rounded to bfloat16 (2^-8) is off by about 1e-3.  n = 700: two chunks."""
+    import torch
+    L = 768
+    rng = np.random.Generator(np.random.Philox(n + d))
+    Q, K, V = (np.zeros((1, 1, L, d), np.float32) for _ in range(3))
+    Q[..., 0] = 0.5 + (np.arange(L) % 190) / 128.0          # below 2: bfloat16 holds these
+    K[0, 0, 384, 0] = 1.0
+    V[0, 0, 384, 1] = 1.0
+    others = np.delete(np.arange(L), 384)
+    lists = [np.sort(np.append(rng.choice(others, n - 1, replace=False), 384)) for _ in range(L)]
+    ptr, col = (np.arange(L + 1) * n).astype(np.int32), np.concatenate(lists).astype(np.int32)
+    print(f"[csr normaliser] d={d} n={n}", flush=True)
+    sh = dsa.make_shape(1, 1, L, d, 16, 1, 1, dsa.DSA_BF16, 1.0)
+    dev = [torch.from_numpy(a).cuda().bfloat16() for a in (Q, K, V)]
+    got = dsa.dsa_masked_attention_csr(sh, *dev, torch.from_numpy(ptr).cuda(), torch.from_numpy(col).cuda()).cpu().numpy()
+    want = oracle.masked_attention_csr(Q, K, V, ptr, col, 1.0).reshape(L, d)
+    err = np.abs(got.reshape(L, d)[:, 1] / want[:, 1] - 1.0).max()
+    print(f"    max relative error {err:.3e}", flush=True)
+    assert err <= 1e-5
