@@ -662,6 +662,7 @@ __global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) o[ct] = v4f{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, z = 0.f;
+    const float share = 1.f / (float)(keep_pad - keep + 1);      // the list is filled up with copies of its last key
     gather(kring, Kh, 0);
     gather(vring, Vh, 0);
     for (int t0 = 0; t0 < keep_pad; t0 += 32) {
@@ -703,10 +704,10 @@ __global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
         float p[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f((s2[i / 4][i % 4] - m0) * factor);
-        if (t0 + 32 > keep) {              // the padding repeats the last key: it may set the reference, but has no weight
+        if (t0 + 32 > keep) {              // the copies of the last key share its weight: 0 would make NaN of an infinite value
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (t0 + 16 * (i / 4) + 4 * g + i % 4 >= keep) p[i] = 0.f;
+                if (t0 + 16 * (i / 4) + 4 * g + i % 4 >= keep - 1) p[i] *= share;
         }
         // A weight is the sum of two bf16 (relative 2^-17): one alone would be rounded at 2^-9, the largest one too, whose
         // weight is not 1 here.  hi is p cut off, and lo is not zero where p is not (the factor is 1 + 2^-23), so that both

@@ -86,3 +86,21 @@ def test_values_that_are_not_finite(dsa, oracle, vec):
     assert 0 < (~ok).sum() < want.size
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
     assert np.abs(got[ok] - want[ok]).max() <= TOL
+
+
+@pytest.mark.parametrize("d,vec", [(64, 4), (64, 8), (128, 4), (128, 8)])
+@pytest.mark.parametrize("keep", [1, 31, 33, 200])
+def test_infinite_value_at_the_end_of_a_list(dsa, oracle, d, vec, keep):
+    """The step of 32 keys that a list ends in is filled up with its last key: an infinite value there stays infinite."""
+    qkv, idx = case(2, 600, d, vec, keep)
+    V = qkv[2]
+    V[0, 0, 599, 3], V[0, 1, 598, d - 1] = np.inf, -np.inf
+    idx[::3, -1] = 599
+    idx[1::3, -1] = 598
+    idx[:, :-1] = np.minimum(idx[:, :-1], 597)              # (a key may then be listed twice: it counts twice)
+    want = oracle.masked_attention(*qkv, idx, 0.125, vec).reshape(-1, d)
+    got = run(dsa, qkv, idx, vec, 0.125)
+    ok = np.isfinite(want)
+    assert 0 < (~ok).sum() < want.size and not np.isnan(want).any()
+    assert np.array_equal(got[~ok], want[~ok])
+    assert np.abs(got[ok] - want[ok]).max() <= TOL
