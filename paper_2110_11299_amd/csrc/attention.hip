@@ -596,22 +596,18 @@ __device__ __forceinline__ unsigned unit_swizzle(unsigned r) { return (r & 3u) <
 
 template <int D> constexpr int unit_tile_bytes() { return 32 * 2 * D; }        // key rows, then value rows
 
+// The unit from its list to its rows of O, with a reference that may lag the maximum by a factor of 2^slack.  Returns whether
+// every sum was finite.
 template <int D, int VEC>
-__global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
-    const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
-    const int32_t *__restrict__ idx, float *__restrict__ O, int L, int keep, int keep_pad, float scale, unsigned total_units)
+__device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, const uint16_t *V, const int32_t *idx, float *O, int L,
+                                          int keep, int keep_pad, float scale, unsigned unit, int lane, char *tile, float slack)
 {
     constexpr int KS = D / 32, CT = D / 16;
     constexpr int ROW = D * 2;             // bytes of a row in LDS
     constexpr int LPR = D / 8, RPI = kWave / LPR, VP = 32 / RPI;
-    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
-    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int c = lane & 15, g = lane >> 4;
-    char *tile = lds_raw + wave * (unit_tile_bytes<D>() + keep_pad * 4);
     unsigned *sl = reinterpret_cast<unsigned *>(tile + unit_tile_bytes<D>());        // [keep_pad] byte offsets of the rows
 
-    const unsigned unit = xcd_contiguous(blockIdx.x, gridDim.x) * kGroupWaves + wave;
-    if (unit >= total_units) return;       // the whole wavefront: nothing below is shared
     const unsigned G = L / VEC, n = unit / G, u = unit % G;
     const int32_t *list = idx + (size_t)unit * keep;
     const char *Kh = reinterpret_cast<const char *>(K + (size_t)n * L * D);
@@ -686,7 +682,7 @@ __global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
 #pragma unroll
         for (int i = 1; i < 4; ++i) mx = fmaxf(fmaxf(s2[0][i], s2[1][i]), mx);
         // (compared with >: nothing moves for scores that are not numbers, they reach the sums by themselves)
-        if (__ballot(m == -INFINITY ? mx > -INFINITY : (mx - m) * factor > kUnitSlack) != 0) {
+        if (__ballot(m == -INFINITY ? mx > -INFINITY : (mx - m) * factor > slack) != 0) {
             mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
             mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
             const float to = fmaxf(m, mx);
@@ -743,6 +739,31 @@ __global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) out[16 * ct] = o[ct][i] * inv;
         }
+    }
+    float odd = 0.f;                       // NaN if a sum is not finite
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) odd = fmaf(o[ct][i], 0.f, odd);
+    return __ballot(odd != 0.f) == 0;
+}
+
+template <int D, int VEC>
+__global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
+    const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
+    const int32_t *__restrict__ idx, float *__restrict__ O, int L, int keep, int keep_pad, float scale, unsigned total_units)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds_raw[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    char *tile = lds_raw + wave * (unit_tile_bytes<D>() + keep_pad * 4);
+    const unsigned unit = xcd_contiguous(blockIdx.x, gridDim.x) * kGroupWaves + wave;
+    if (unit >= total_units) return;       // the whole wavefront: nothing below is shared
+    // Weights above 1 may take large values beyond fp32 (from 2^111 / keep on) that weights of at most 1 would not: then once
+    // more with a reference that is the maximum.  (That from the start costs up to 13 % of the kernel.)
+    for (float slack = kUnitSlack;; slack = 0.f) {
+        int lane = threadIdx.x & (kWave - 1);
+        asm volatile("" : "+v"(lane));     // nothing of a round is computed ahead of the loop: that would delay the first gathers
+        if (unit_rows<D, VEC>(Q, K, V, idx, O, L, keep, keep_pad, scale, unit, lane, tile, slack) || slack == 0.f) break;
     }
 }
 

@@ -104,3 +104,22 @@ def test_infinite_value_at_the_end_of_a_list(dsa, oracle, d, vec, keep):
     assert 0 < (~ok).sum() < want.size and not np.isnan(want).any()
     assert np.array_equal(got[~ok], want[~ok])
     assert np.abs(got[ok] - want[ok]).max() <= TOL
+
+
+@pytest.mark.parametrize("d,vec", [(64, 4), (64, 8), (128, 4), (128, 8)])
+@pytest.mark.parametrize("keep", [64, 75])
+def test_large_values_with_scores_that_grow(dsa, oracle, d, vec, keep):
+    """Scores that exceed those of the first 32 keys by 10 (a factor of 2^14.4 between the weights), values of 2^118 and
+    2^119: sums of up to 75 of them with weights of at most 1 stay below 2^126.  Every value is positive, so the relative
+    error is that of a weight (2^-16)."""
+    qkv, idx = case(2, 320, d, vec, keep)
+    Q, K, V = qkv
+    Q[...], K[...] = 0.0, 0.0
+    Q[..., 0] = 1.0
+    K[:, :, 160:, 0] = 10.0
+    V[...] = np.where(V > 0, 2.0 ** 119, 2.0 ** 118)
+    idx[:, :32] = np.sort(idx[:, :32] % 160, axis=1)
+    idx[:, 32:] = np.sort(160 + idx[:, 32:] % 160, axis=1)
+    want = oracle.masked_attention(*qkv, idx, 1.0, vec).reshape(-1, d)
+    got = run(dsa, qkv, idx, vec, 1.0)
+    assert np.abs(got / want - 1.0).max() <= 2.0 ** -15
