@@ -162,14 +162,16 @@ def _stream():
     return _raw_stream()
 
 
+_tensor = ()          # torch.Tensor, once a call has imported torch
+
+
 def _dev(t, dtype, shape):
+    global _tensor
     # a call checks up to seven tensors: the cheap form first, everything it does not accept goes on to the full one
-    try:
-        if t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
-            return t
-    except AttributeError:
-        pass
+    if isinstance(t, _tensor) and t.is_cuda and t.dtype is dtype and t.shape == shape and t.is_contiguous():
+        return t
     import torch
+    _tensor = torch.Tensor
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and t.dtype == dtype
             and tuple(t.shape) == tuple(shape)):
         raise ValueError(f"expected a contiguous CUDA tensor {dtype} {tuple(shape)}, got "

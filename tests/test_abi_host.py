@@ -120,6 +120,24 @@ def test_binding_refuses_cpu_tensors(b):
         b.dsa_predict_mask(sh, t, t)
 
 
+def test_binding_takes_tensors_only(b):
+    """An object that looks like a CUDA tensor is refused, before and after torch's class is known to the check."""
+    import torch
+
+    class Alike:
+        is_cuda, dtype, shape = True, torch.int8, (2, 2, 256, 32)
+
+        def is_contiguous(self):
+            return True
+
+        def data_ptr(self):
+            return P
+
+    for _ in range(2):
+        with pytest.raises(ValueError):
+            b._dev(Alike(), torch.int8, (2, 2, 256, 32))
+
+
 def test_noalloc_rejects_masks_beyond_its_array_on_the_host(b):
     """The size check of dsa_attention_fwd_noalloc comes before any device work."""
     lib = b.lib()
