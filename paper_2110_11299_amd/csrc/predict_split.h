@@ -108,9 +108,10 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
     constexpr int R = K == 16 ? 4 : K == 32 ? 2 : 1;     // keys side by side in a matrix row = tiles per row operand
     constexpr int STEPS = K ? 1 : 2;                     // contraction steps of 64
     constexpr int NS = 8 / R;                            // row operands of a group of 8 tiles (32 keys per lane range)
-    constexpr int NSB = NS < 4 ? NS : 4;                 // row operands of one batch of requests
+    constexpr int NSB = STEPS == 2 ? 2 : NS < 4 ? NS : 4;    // row operands of one batch of requests (8 registers each if two steps)
     constexpr int BPG = NS / NSB;                        // batches per group
     constexpr int TB = NSB * R;                          // tiles per batch
+    constexpr int PAIR = TB >= 4 ? 2 : 1;                // tiles j and j + PAIR share a bucket
     constexpr int PARTS = GROUP ? 2 : 1;
     constexpr int U = kTile * UT;
     constexpr int kBandSlots = band_slots<GROUP, UT, NWM>(), kBandCap = 16 * kBandSlots;
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
     const int nv_all = max(0, min(L - (4 * wv + 3) * Lr, Lr));           // of the wavefront's last range: the fewest
 
     // ---- sweep 1: bucket maxima --------------------------------------------------------------------------------------
-    // A range of one group (NWM == 1) keeps every score; else tiles j and j ^ 2 share a bucket, and so do all groups (of
+    // A range of one group (NWM == 1) keeps every score; else tiles j and j + PAIR share a bucket, and so do all groups (of
     // the same parity, if there are 32): two scores per v_max3.
     int bm[UT][NB];
 #pragma unroll
@@ -228,25 +229,25 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
 #pragma unroll
         for (int t = 0; t < UT; ++t)
 #pragma unroll
-            for (int jb = 0; jb < TB; jb += 4)
+            for (int jb = 0; jb < TB; jb += 2 * PAIR)
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
+                for (int e = 0; e < PAIR; ++e) {
                     const int j = jb + e;
-                    v4i x = tile_scores(buf, j, t, 0), y = tile_scores(buf, j + 2, t, 0);
+                    v4i x = tile_scores(buf, j, t, 0), y = tile_scores(buf, j + PAIR, t, 0);
                     if (decltype(masked)::value) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
                             x[i] = mask_beyond(x[i], 32 * w + 4 * (J0 + j) + i, nv);
-                            y[i] = mask_beyond(y[i], 32 * w + 4 * (J0 + j + 2) + i, nv);
+                            y[i] = mask_beyond(y[i], 32 * w + 4 * (J0 + j + PAIR) + i, nv);
                         }
                     }
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         if (NWM == 1) {
                             bm[t][(4 * (J0 + j) + i) % NB] = x[i];
-                            bm[t][(4 * (J0 + j + 2) + i) % NB] = y[i];
+                            bm[t][(4 * (J0 + j + PAIR) + i) % NB] = y[i];
                         } else {
-                            int &m = bm[t][(NB == 32 ? 16 * PAR : 0) + ((J0 + jb) / 4 % 2) * 8 + 4 * e + i];
+                            int &m = bm[t][(NB == 32 ? 16 * PAR : 0) + 4 * ((J0 + jb) / 2 + e) + i];
                             m = max(max(x[i], y[i]), m);
                         }
                     }
@@ -257,13 +258,17 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
         auto group = [&](int w, auto par) {
             constexpr int PAR = decltype(par)::value;
             auto batch = [&](auto half) {
-                constexpr int HB = decltype(half)::value, P = BPG == 2 ? HB : PAR;
+                constexpr int HB = decltype(half)::value, P = BPG == 1 ? PAR : HB & 1;
                 request(rows[P ^ 1], w * BPG + HB + 1);
                 if (32 * (w + 1) <= nv_all) maxima(rows[P], w, par, half, std::false_type{});
                 else maxima(rows[P], w, par, half, std::true_type{});
             };
             batch(std::integral_constant<int, 0>{});
-            if constexpr (BPG == 2) batch(std::integral_constant<int, 1>{});
+            if constexpr (BPG >= 2) batch(std::integral_constant<int, 1>{});
+            if constexpr (BPG == 4) {
+                batch(std::integral_constant<int, 2>{});
+                batch(std::integral_constant<int, 3>{});
+            }
         };
         if (NWM == 1) {
             group(0, std::integral_constant<int, 0>{});
@@ -393,8 +398,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
                 for (int t = 0; t < UT; ++t) wl[t][w] = wh[t][w] = 0u;
 #pragma unroll
                 for (int hb = 0; hb < BPG; ++hb) {
-                    constexpr int two = BPG == 2 ? 1 : 0;
-                    const int P = two ? hb : w & 1;
+                    const int P = BPG == 1 ? w & 1 : hb & 1;
                     request(rows[P ^ 1], w * BPG + hb + 1);
 #pragma unroll
                     for (int j = 0; j < TB; ++j)
@@ -548,12 +552,13 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
                         s[i] = __builtin_amdgcn_sdot4(ql[x], kk[i][x], s[i], false);
                         if (GROUP) sh[i] = __builtin_amdgcn_sdot4(qh[x], kk[i][x], sh[i], false);
                     }
-                if (K > 32) __builtin_amdgcn_sched_barrier(0);       // the rows of four keys do not fit the registers
+                if (K == 0 || K > 32) __builtin_amdgcn_sched_barrier(0);       // the rows of four keys do not fit the registers
             };
             if constexpr (K != 0) {
 #pragma unroll
                 for (int p = 0; p < K / 16; ++p) piece(p);
             } else {
+#pragma unroll 1
                 for (int p = 0; p < k / 16; ++p) piece(p);
             }
 #pragma unroll

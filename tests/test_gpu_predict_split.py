@@ -84,3 +84,14 @@ def test_pairs_of_tiles(dsa, oracle, H, L, vec, k):
     Qt, Kt = di.random_int8_case(L + H, 1, H, L, k)
     for keep in (1, 30, 409, 410):
         check(dsa, oracle, Qt, Kt, keep, vec, "pairs")
+
+
+# two contraction steps, the second one partly empty (112) or not (128), in every number of groups per range that has a kernel
+# of its own
+@pytest.mark.parametrize("H,L", [(2, 130), (2, 1025), (4, 4096), (1, 8193), (1, 16385)])
+@pytest.mark.parametrize("k", [112, 128])
+def test_two_steps(dsa, oracle, H, L, k):
+    Qt, Kt = di.random_int8_case(L + k, 1, H, L, k)
+    for vec in (1, 4, 8):
+        Lv = L // vec * vec
+        check(dsa, oracle, np.ascontiguousarray(Qt[:, :, :Lv]), np.ascontiguousarray(Kt[:, :, :Lv]), max(1, L // 50), vec, "two steps")
