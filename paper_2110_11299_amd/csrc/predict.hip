@@ -145,6 +145,7 @@ hipError_t launch_predict(const dsa_shape &sh, const int8_t *Qt, const int8_t *K
     case 32: return launch_split_k32(sh, Qt, Kt, idx, st);
     case 48: return launch_split_k48(sh, Qt, Kt, idx, st);
     case 64: return launch_split_k64(sh, Qt, Kt, idx, st);
+    case 128: return launch_split_k128(sh, Qt, Kt, idx, st);
     default: return launch_split_any(sh, Qt, Kt, idx, st);
     }
 }

@@ -16,6 +16,7 @@ hipError_t launch_split_k16(const dsa_shape &sh, const int8_t *Qt, const int8_t 
 hipError_t launch_split_k32(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
 hipError_t launch_split_k48(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
 hipError_t launch_split_k64(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
+hipError_t launch_split_k128(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
 hipError_t launch_split_any(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st);
 // Largest L the predict kernels accept.
 int predict_max_L();

@@ -99,14 +99,18 @@ __device__ __forceinline__ int row_sum_above(int x)
     return s - x;
 }
 
-// K: the projection dimension (16, 32, 48, 64), or 0 for any other (up to 128, two contraction steps).
+// K: the projection dimension (16, 32, 48, 64, 128), or 0 for any other (up to 112, two contraction steps).
 // GROUP: units are groups of vec rows.  UT: tiles of 16 units per workgroup.  NB: buckets per lane and unit (32, or 16 if a
 // range has several groups).  NWM: most bitmap words per lane.
 template <int K, bool GROUP, int UT, int NB, int NWM>
 __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitArgs a)
 {
     constexpr int R = K == 16 ? 4 : K == 32 ? 2 : 1;     // keys side by side in a matrix row = tiles per row operand
-    constexpr int STEPS = K ? 1 : 2;                     // contraction steps of 64
+    constexpr int STEPS = K && K <= 64 ? 1 : 2;          // contraction steps of 64
+    // Rows of 128 bytes: the four rows that neighbouring lanes read 16 bytes of lie at the same place of their cache lines, and
+    // the L1 takes them one after the other.  Odd rows fetch their second half first, and the halves change places in front
+    // of the matrix instruction.  L = 4096, keep = 41, N = 8: 251 -> 143 us (k = 112, whose rows spread by themselves: 111).
+    constexpr bool CROSS = K == 128;
     constexpr int NS = 8 / R;                            // row operands of a group of 8 tiles (32 keys per lane range)
     constexpr int NSB = STEPS == 2 ? 2 : NS < 4 ? NS : 4;    // row operands of one batch of requests (8 registers each if two steps)
     constexpr int BPG = NS / NSB;                        // batches per group
@@ -168,6 +172,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
         plive[s] = 64 * s + 16 * part < k;
         poff[s] = plive[s] ? 64 * s + 16 * part : 0;
     }
+    const bool crossed = CROSS && (c & 1);
     unsigned row0 = (unsigned)((4 * wv + (c >> 2)) * Lr + 4 * sub + (c & 3)) * (unsigned)k;
     const unsigned row_last = (unsigned)(L - 1) * (unsigned)k;
     const unsigned slot_step = 4u * R * (unsigned)k;
@@ -178,7 +183,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
         for (int sl = 0; sl < NSB; ++sl) {
             const unsigned row = min(first + sl * slot_step, row_last);
 #pragma unroll
-            for (int s = 0; s < STEPS; ++s) dst[sl][s] = *reinterpret_cast<const v4i *>(Kh + row + poff[s]);
+            for (int s = 0; s < STEPS; ++s) dst[sl][s] = *reinterpret_cast<const v4i *>(Kh + row + poff[crossed ? STEPS - 1 - s : s]);
         }
     };
     v4i rows[2][NSB][STEPS];
@@ -201,13 +206,18 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
 
     // scores of tile j of the batch against the units of operand t, each plus b
     auto tile_scores = [&](const v4i (&buf)[NSB][STEPS], int j, int t, int b) -> v4i {
+        v4i key[STEPS];
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) key[s][i] = CROSS && crossed ? buf[j / R][STEPS - 1 - s][i] : buf[j / R][s][i];
         v4i acc = v4i{b, b, b, b};
 #pragma unroll
-        for (int s = 0; s < STEPS; ++s) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(buf[j / R][s], q[t][0][j % R][s], acc, 0, 0, 0);
+        for (int s = 0; s < STEPS; ++s) acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(key[s], q[t][0][j % R][s], acc, 0, 0, 0);
         if (GROUP) {
             v4i top = v4i{0, 0, 0, 0};
 #pragma unroll
-            for (int s = 0; s < STEPS; ++s) top = __builtin_amdgcn_mfma_i32_16x16x64_i8(buf[j / R][s], q[t][PARTS - 1][j % R][s], top, 0, 0, 0);
+            for (int s = 0; s < STEPS; ++s) top = __builtin_amdgcn_mfma_i32_16x16x64_i8(key[s], q[t][PARTS - 1][j % R][s], top, 0, 0, 0);
             acc += top << 7;
         }
         return acc;

@@ -1,4 +1,4 @@
-// predict_split for projection dimensions above 64 (two contraction steps).
+// predict_split for projection dimensions of 80, 96 and 112 (two contraction steps).
 #include "predict_split.h"
 
 namespace dsa {

@@ -1,0 +1,11 @@
+// predict_split for a projection dimension of 128.
+#include "predict_split.h"
+
+namespace dsa {
+
+hipError_t launch_split_k128(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st)
+{
+    return launch_split_k<128>(sh, Qt, Kt, idx, st);
+}
+
+}  // namespace dsa

@@ -86,8 +86,8 @@ def test_pairs_of_tiles(dsa, oracle, H, L, vec, k):
         check(dsa, oracle, Qt, Kt, keep, vec, "pairs")
 
 
-# two contraction steps, the second one partly empty (112) or not (128), in every number of groups per range that has a kernel
-# of its own
+# two contraction steps: 112 (the second one partly empty) and 128 (its halves of odd rows change places), in every number of
+# groups per range that has a kernel of its own
 @pytest.mark.parametrize("H,L", [(2, 130), (2, 1025), (4, 4096), (1, 8193), (1, 16385)])
 @pytest.mark.parametrize("k", [112, 128])
 def test_two_steps(dsa, oracle, H, L, k):
