@@ -9,10 +9,10 @@
 //           the units' bitmaps, which go to the workspace together with the task's count.  The largest score per lane and
 //           the word it lies in are kept beside it (half an operation per score): a unit without a key scores the 32 keys of
 //           that word again and keeps the best.
-//   scan    only for more than kDirectTasks tasks: exclusive prefix sum of the counts, blocks of 1024 tasks, then the block
+//   scan    only where that many tasks make it pay (kDirectTasks): exclusive prefix sum of the counts, blocks of 1024 tasks, then the block
 //           totals.
 //   fill    one workgroup per task: the task's place in col (the sum of the counts before it, unless the scan has it), row_ptr,
-//           and the bitmaps as keys, which leave through LDS as consecutive entries.
+//           and the bitmaps as keys, 64 words at a time, which leave through LDS as consecutive entries.
 #include "dsa_internal.h"
 #include "threshold_api.h"
 #include "key_stream.h"
@@ -21,9 +21,11 @@ namespace dsa {
 namespace {
 
 constexpr int kScanBlock = 1024;        // tasks per block of the prefix sum
-// Up to here every fill workgroup adds up the counts before its own (16 KB at most, from L2) instead of two more launches:
-// 2048 tasks of L = 2048, N = 16: sweep, scan and fill together 39.2 us with the scan, 32.3 without.
-constexpr unsigned kDirectTasks = 4096;
+// Up to here every fill workgroup adds up the counts before its own (16 KB at most, from L2) instead of two more launches: a
+// call with the scan and without, k = 32: 2048 tasks of L = 2048 32.0 and 28.5 us, 4096 46.7 and 45.8, 8192 80.1 and 92.7.
+// Short sequences have few wavefronts to add with: L = 128 (one), 1024 tasks 14.4 and 11.3, 2048 tasks 14.8 and 16.8; L = 256
+// (two), 2048 tasks 15.7 and 13.4, 4096 20.4 and 21.9; L = 512 (four), 4096 tasks 25.5 and 24.7, 8192 37.0 and 47.4.
+constexpr unsigned kDirectTasks = 4096, kDirectTasksPerWave = 1024;
 
 // Bitmap in the workspace: word w of lane l of task t at (t * NWL + w) * 64 + l (what a wavefront
 // stores with one instruction is contiguous).
@@ -148,18 +150,26 @@ __global__ __launch_bounds__(256) void scan_totals(int32_t *__restrict__ block_t
     }
 }
 
-// (4: 20.3 us for the fill at N = 16, L = 2048; 8: 17.6; 16, which leaves two workgroups per CU: 22.3)
+// The words of a task in the order of its keys in col (unit by unit, word by word) are cut into NWL chunks of 64, one lane per
+// word: a chunk is as much work whatever the length of a unit, so that short sequences take few wavefronts (8 of them, a unit at
+// a time: L = 128, 4096 tasks, sweep to fill, 32.4 us; one: 18.0; L = 512: 35.4 and 25.1).  At most 8 share a task: N = 16,
+// L = 2048: 20.3 us for the fill with 4, 17.6 with 8, 22.3 with 16, which leaves two workgroups per CU.
 constexpr int kFillWaves = 8;
+// Above this length one workgroup's LDS leaves no room for a second one on the CU: N = 1, L = 32768, a call with 8 wavefronts
+// 555 us, with 16 437.
+constexpr int kFillLong = 184, kFillWavesLong = 16;
 constexpr int kFillRow = kWave + 1;     // words of LDS for one stored word of all lanes: a unit's words then lie on different banks
 
-// LDS: [NWL][kFillRow] the task's bitmap, then per wavefront the keys of 64 of a unit's words, then the units' counts and a
-// sum per wavefront.
-__host__ __device__ inline size_t fill_lds_bytes(int NWL)
+inline int fill_waves(int NWL) { return NWL > kFillLong ? kFillWavesLong : NWL < kFillWaves ? NWL : kFillWaves; }
+
+// LDS: [NWL][kFillRow] the task's bitmap, then per wavefront the keys of a chunk, then a count per chunk and a sum per wavefront.
+__host__ __device__ inline size_t fill_bitmap_bytes(int NWL) { return ((size_t)NWL * kFillRow * 4 + 15) / 16 * 16; }
+inline size_t fill_lds_bytes(int NWL)
 {
-    return ((size_t)NWL * kFillRow * 4 + 15) / 16 * 16 + kFillWaves * 32 * kWave * sizeof(uint16_t) + (16 + kFillWaves) * sizeof(int);
+    return fill_bitmap_bytes(NWL) + fill_waves(NWL) * 32 * kWave * sizeof(uint16_t) + (NWL + fill_waves(NWL)) * sizeof(int);
 }
 
-__global__ __launch_bounds__(kFillWaves *kWave) void threshold_fill(const unsigned *__restrict__ bitmap,
+__global__ __launch_bounds__(kFillWavesLong *kWave) void threshold_fill(const unsigned *__restrict__ bitmap,
                                                       const int32_t *__restrict__ task_count,
                                                       const int32_t *__restrict__ block_total,
                                                       int32_t *__restrict__ row_ptr, int32_t *__restrict__ col,
@@ -168,69 +178,70 @@ __global__ __launch_bounds__(kFillWaves *kWave) void threshold_fill(const unsign
 {
     extern __shared__ __align__(16) unsigned words[];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int T = blockDim.x, waves = T / kWave;
     const unsigned task = xcd_contiguous(blockIdx.x, gridDim.x);
     const int G = L / vec;
     const unsigned n = task / (unsigned)tasks_per_head;
     const int u0 = (int)(task % (unsigned)tasks_per_head) * 16, nu = min(16, G - u0);
     const int Lq = stream_quarter(L), NWL = Lq / 32, NW = 4 * NWL;
-    int *s_count = reinterpret_cast<int *>(reinterpret_cast<char *>(words) + fill_lds_bytes(NWL)) - (16 + kFillWaves);
-    int *s_part = s_count + 16;
-    uint16_t *keys = reinterpret_cast<uint16_t *>(s_count) - (kFillWaves - wave) * 32 * kWave;
+    uint16_t *keys = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(words) + fill_bitmap_bytes(NWL));
+    int *s_count = reinterpret_cast<int *>(keys + waves * 32 * kWave);
+    int *s_part = s_count + NWL;
+    keys += wave * 32 * kWave;
     const unsigned *stored = bitmap + (size_t)task * NWL * kWave;
-    for (int e = tid; e < NWL * kWave; e += kFillWaves * kWave) words[(e / kWave) * kFillRow + lane] = stored[e];
+    for (int e = tid; e < NWL * kWave; e += T) words[(e / kWave) * kFillRow + lane] = stored[e];
     // entries before the task's
     int before = 0;
     if (block_total) {
         before = task_count[task] + block_total[task / kScanBlock];
     } else {
-        for (unsigned t = tid; t < task; t += kFillWaves * kWave) before += task_count[t];
+        for (unsigned t = tid; t < task; t += T) before += task_count[t];
         before = wave_sum(before);
         if (lane == 0) s_part[wave] = before;
     }
     __syncthreads();
     if (!block_total) {
         before = 0;
-#pragma unroll
-        for (int w = 0; w < kFillWaves; ++w) before += s_part[w];
+        for (int w = 0; w < waves; ++w) before += s_part[w];
     }
-    // word W of unit c in key order: quarter W / NWL, word W % NWL of lane 16 * quarter + c
+    // word e of the task: word W of unit c, which is quarter W / NWL, word W % NWL of lane 16 * quarter + c
+    // (quotients below 16 of numbers below 2^14: a product with the reciprocal is off by less than 2^-19, and (x + 1/2) / y is
+    // at least 2^-11 away from the next whole number)
+    const float per_unit = 1.f / (float)NW, per_quarter = 1.f / (float)NWL;
+    auto unit_of = [&](int e) { return (int)(((float)e + 0.5f) * per_unit); };
     auto word_of = [&](int c, int W) -> unsigned {
-        const int q = W / NWL, w = W - q * NWL;
-        return W < NW ? words[w * kFillRow + 16 * q + c] : 0u;
+        const int q = (int)(((float)W + 0.5f) * per_quarter), w = W - q * NWL;
+        return c < nu ? words[w * kFillRow + 16 * q + c] : 0u;
     };
-    for (int c = wave; c < 16; c += kFillWaves) {
-        int count = 0;
-        for (int W = lane; W < NW; W += kWave) count += __popc(word_of(c, W));
-        count = wave_sum(count);
-        if (lane == 0) s_count[c] = count;
+    for (int j = wave; j < NWL; j += waves) {
+        const int e = j * kWave + lane, c = unit_of(e);
+        const int count = wave_sum(__popc(word_of(c, e - c * NW)));
+        if (lane == 0) s_count[j] = count;
     }
     __syncthreads();
-    for (int c = wave; c < nu; c += kFillWaves) {
-        const long long start = before + wave_sum(lane < c ? s_count[lane] : 0);
+    for (int j = wave; j < NWL; j += waves) {
+        int sum = 0;
+        for (int i = lane; i < j; i += kWave) sum += s_count[i];
+        const long long start = before + wave_sum(sum);
+        const int e = j * kWave + lane, c = unit_of(e), W = e - c * NW;
+        unsigned m = word_of(c, W);
+        int total;
+        const int end = wave_incl_scan(__popc(m), lane, &total);
+        int rank = end - __popc(m);
         const unsigned u = n * (unsigned)G + u0 + c;
-        if (lane == 0) {
-            row_ptr[u] = (int32_t)start;
-            if (u + 1 == units) row_ptr[units] = (int32_t)(start + s_count[c]);       // nnz
+        if (c < nu && W == 0) row_ptr[u] = (int32_t)(start + rank);
+        if (c == nu - 1 && W == NW - 1 && u + 1 == units) row_ptr[units] = (int32_t)(start + end);       // nnz
+        const int key1 = 32 * W - 1;
+        while (m) {
+            keys[rank++] = (uint16_t)(key1 + __ffs(m));
+            m &= m - 1u;
         }
+        wave_lds_sync();
         int32_t *out = col + start;
         const long long room = col_capacity - start;      // entries beyond the capacity are left out
-        int done = 0;
-        for (int W0 = 0; W0 < NW; W0 += kWave) {
-            const int W = W0 + lane;
-            unsigned m = word_of(c, W);
-            int total;
-            int rank = wave_incl_scan(__popc(m), lane, &total) - __popc(m);
-            const int key1 = 32 * W - 1;
-            while (m) {
-                keys[rank++] = (uint16_t)(key1 + __ffs(m));
-                m &= m - 1u;
-            }
-            wave_lds_sync();
-            for (int t = lane; t < total; t += kWave)
-                if (done + t < room) out[done + t] = keys[t];
-            wave_lds_sync();
-            done += total;
-        }
+        for (int t = lane; t < total; t += kWave)
+            if (t < room) out[t] = keys[t];
+        wave_lds_sync();
     }
 }
 
@@ -244,7 +255,9 @@ hipError_t launch_threshold_kv(const dsa_shape &sh, const int8_t *Qt, const int8
     const size_t bitmap_words = (size_t)tasks * (stream_quarter(sh.L) / 32) * kWave;
     unsigned *bitmap = static_cast<unsigned *>(ws);
     int32_t *task_count = reinterpret_cast<int32_t *>(bitmap + bitmap_words);
-    int32_t *block_total = tasks > kDirectTasks ? task_count + tasks : nullptr;
+    const int NWL = stream_quarter(sh.L) / 32;
+    const unsigned direct = min(kDirectTasks, kDirectTasksPerWave * fill_waves(NWL));
+    int32_t *block_total = tasks > direct ? task_count + tasks : nullptr;
     hipLaunchKernelGGL((threshold_sweep<K, VEC>), dim3(tasks), dim3(kWave), 0, st, Qt, Kt, bitmap, task_count, sh.L, theta,
                        tasks_per_head);
     if (block_total) {
@@ -252,9 +265,9 @@ hipError_t launch_threshold_kv(const dsa_shape &sh, const int8_t *Qt, const int8
         hipLaunchKernelGGL(scan_blocks, dim3(blocks), dim3(256), 0, st, task_count, block_total, tasks);
         hipLaunchKernelGGL(scan_totals, dim3(1), dim3(256), 0, st, block_total, blocks);
     }
-    const size_t lds = fill_lds_bytes(stream_quarter(sh.L) / 32);
+    const size_t lds = fill_lds_bytes(NWL);
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(threshold_fill), lds)) return e;
-    hipLaunchKernelGGL(threshold_fill, dim3(tasks), dim3(kFillWaves * kWave), lds, st, bitmap, task_count, block_total, row_ptr,
+    hipLaunchKernelGGL(threshold_fill, dim3(tasks), dim3(fill_waves(NWL) * kWave), lds, st, bitmap, task_count, block_total, row_ptr,
                        col, col_capacity, sh.L, VEC, tasks_per_head, units);
     return hipGetLastError();
 }

@@ -166,6 +166,19 @@ def test_threshold_many_tasks_and_long_bitmaps(dsa, oracle, H, L, vec):
     run_case(dsa, oracle, x, theta_for(oracle, x, 0.1), "many tasks, capacity", capacity=5000, check_attention=False)
 
 
+# words per unit 4 to 800: 1, 2, 3, 7, 8, 9 chunks of 64 words (fewer wavefronts than 8, as many, a second round), the longest
+# form; 16 units of which the last task has 1, 15 or all; one wavefront with the sum and with the scan
+@pytest.mark.parametrize("H,L,vec", [(3, 17, 1), (2, 127, 1), (3, 129, 1), (2, 272, 1), (2, 896, 4), (1, 1020, 1), (1, 1028, 4),
+                                     (1, 25000, 8), (300, 40, 1), (400, 48, 1)])
+def test_threshold_fill_chunks(dsa, oracle, H, L, vec):
+    Qt, Kt = di.random_int8_case(L + H, 1, H, L, 32)
+    x = di.DsaInputs(di.custom_config(B=1, H=H, L=L, d=64, dtype="f32", rank=4, k=32, vec=vec, keep=1, seed=3),
+                     None, None, None, Qt, Kt, None, None, None)
+    for fraction in (0.01, 0.5):
+        run_case(dsa, oracle, x, theta_for(oracle, x, fraction), "chunks", check_attention=False)
+    run_case(dsa, oracle, x, -(1 << 27), "chunks, dense", check_attention=False)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n", [2, 41, 700])
 def test_csr_normaliser_is_summed_in_fp32(dsa, oracle, d, n):
