@@ -743,13 +743,47 @@ inline void split_targets(int L, int keep, int NW, int NB, int *target_l, int *t
     *target_h = h;
 }
 
-// Wavefronts: ranges of 32 to 512 keys, and at least four where there are few tiles (the band step takes four units per
-// wavefront at a time: L = 256, 32 tiles, 12.6 -> 10.5 us).
-// Two tiles per workgroup halve the key rows that come from L2 per unit (at L = 16384, k = 64 every workgroup streams 1 MB
-// twice: 627 -> 472 us; L = 8192 in groups of 8: 95 -> 82 us).  It takes the unit operands of both in registers, which only
-// a contraction that fills its 64 slots leaves room for (k = 32 keeps two half-empty copies of each: 139 -> 171 us), 16
-// buckets per lane instead of 32, so keep at most 4/5 of their number, and enough units to fill the chip with half the
-// workgroups.
+// Wavefronts.  A lane's range holds at most 512 keys, which four wavefronts reach up to L = 8192 and eight up to 16384.  More
+// than that pay where they fill an empty chip, and for long lists in long ranges, whose words are then too many for the
+// registers (times of both sides; k = 32 and 5 % unless said):
+//   4 or 8   L = 4608, N = 12: 112 and 166 us; 6144, N = 7: 111 and 129; 6000, N = 3, 10 %: 89 and 85; 8192, N = 4, 2 %: 92 and 101,
+//            N = 2, 10 %, k = 16: 81 and 76; k = 128, 8192: 398 and 362.
+//            Few tiles: L = 777, 294 tiles 12.7 and 11.8, 1024, 256 tiles 9.9 and 9.2, 512 12.2 and 13.3, 768, 672 tiles 15.4 and
+//            18.6; 1536, 96 tiles, k = 16, 7 %: 14.2 and 12.7, 288 tiles 13.5 and 16.6; 2048, 256 tiles 13.5 and 12.7, 512 15.7
+//            and 16.1; 3072, 336 tiles 27.2 and 28.5; 4096, 512 tiles 23.3 and 22.5, 1024 36.1 and 40.9; 8192, 512 38.9 and 36.1.
+//   1 or 4   L = 128, 10 %: 1024 tiles 14.3 and 13.1, 2048 24.1 and 23.4, 4096 36.7 and 40.9.
+//   2 or 4   L = 256, 10 %: 512 tiles 11.1 and 10.1, 1024 11.5 and 13.0; L = 192, 672 tiles 12.0 and 11.8, 1356 15.6 and 19.5.
+inline int split_waves(const dsa_shape &sh, long long tiles)
+{
+    if (sh.L <= 128) return tiles <= 2048 ? 4 : 1;
+    if (sh.L <= 256) return tiles <= 768 ? 4 : 2;
+    if (sh.L <= 512) return 4;
+    const bool four = sh.L <= 5120 || (sh.L <= 6144 && 16LL * sh.keep <= sh.L) || (sh.L <= 8192 && sh.k <= 64 && 40LL * sh.keep <= sh.L);
+    if (!four) return sh.L <= 16384 ? 8 : 16;
+    return tiles <= (sh.L <= 1024 ? 400 : sh.L < 2048 ? 128 : sh.L < 4096 ? 256 : sh.L / 8) ? 8 : 4;
+}
+
+// Two tiles per workgroup halve the key rows that come from L2 per unit.  They take the unit operands of both in registers, which
+// only a contraction that fills its 64 slots leaves room for (k = 32 keeps two half-empty copies of each: 139 -> 171 us), 16
+// buckets per lane instead of 32, whose bounds are worse the longer the list is, and a grid that is not left with half a round at
+// its end (waves between one and two per slot: L = 12288, N = 1, 88.6 us with one tile, 91.0 with two).  k = 64, N L^2 = 2^28,
+// one tile and two at 1, 2, 4, 8 %:
+//   rows         L = 1536 155 and 174, 161/182, 168/196, 195/232; 2048 158/148, 164/159, 174/177, 215/232; 3072 150/127, 153/139,
+//                173/165, 212/213; 4096 140/113, 148/127, 176/161, 211/209; 8192 139/107, 156/129, 181/157; 16384 145/116, 158/132,
+//                188/197.  Half a round is enough: L = 4096, N = 2, 27.1 and 23.4; L = 8192, N = 1, 47.1 and 37.7.
+//   groups of 8  (the operands do not fit: 31 and 50 registers go through scratch) 4096 123/126, 132/136, 148/160; 6144 153/157,
+//                164/177; 8192 146/136, 168/166, 200/218; 16384 157/144, 164/160, 197/195.  A quarter of a round: 49.2 and 67.5.
+//   k = 48 rows  4096 110/103, 120/114, 132/137; 7000, 5 % 194/167; 8192 96/90, 109/111, 134/129; 16384 99/96, 113/110, 134/135.
+//                In groups never (59 registers).
+inline bool split_pairs(const dsa_shape &sh, int W2, long long waves)
+{
+    if (sh.L < 2048 || sh.L > 16384) return false;
+    if (sh.vec > 1) return sh.L >= 8192 && 32LL * sh.keep <= sh.L && waves >= 4096;
+    if (waves < 2048 || (W2 == 16 && waves > 4096 && waves < 8192)) return false;
+    if (sh.k == 48 && (sh.L < 4096 || (sh.L <= 5120 && 50LL * sh.keep > sh.L))) return false;
+    return 5 * sh.keep <= 4 * 64 * W2 && sh.keep <= sh.L / (sh.L < 4096 ? 32 : 20) + 1;
+}
+
 inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
 {
     SplitPlan p{};
@@ -757,11 +791,9 @@ inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
     const long long tiles = heads * ((units + kTile - 1) / kTile);
     p.UT = 1;
     p.NB = 32;
-    p.W = sh.L <= 128 ? 1 : sh.L <= 256 ? 2 : sh.L <= 4096 ? 4 : sh.L <= 16384 ? 8 : 16;
-    if (p.W < 4 && tiles <= 1024) p.W = 4;
-    if (p.W == 4 && sh.L > 512 && 4 * tiles < 4096) p.W = 8;
+    p.W = split_waves(sh, tiles);
     const int W2 = sh.L <= 8192 ? 8 : 16;
-    if (pairs && sh.L > 1024 && sh.L <= 16384 && heads * ((units + 31) / 32) * W2 >= 4096 && 5 * sh.keep <= 4 * 64 * W2) {
+    if (pairs && split_pairs(sh, W2, heads * ((units + 2 * kTile - 1) / (2 * kTile)) * W2)) {
         p.UT = 2;
         p.NB = 16;
         p.W = W2;
@@ -793,7 +825,7 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
 template <int K, bool GROUP>
 hipError_t launch_split_g(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st)
 {
-    constexpr bool pairs = K == 48 || K == 64;
+    constexpr bool pairs = K == 64 || (K == 48 && !GROUP);
     const SplitPlan p = split_plan(sh, pairs);
     if constexpr (pairs) {
         if (p.UT == 2 && p.NW <= 4) return launch_split_t<K, GROUP, 2, 16, 4>(sh, p, Qt, Kt, idx, st);

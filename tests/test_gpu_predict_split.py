@@ -86,6 +86,23 @@ def test_pairs_of_tiles(dsa, oracle, H, L, vec, k):
         check(dsa, oracle, Qt, Kt, keep, vec, "pairs")
 
 
+# the same where the plan takes two tiles now: half a round of wavefronts, two rounds, long lists of a middling length, the two
+# lengths of a row that differ in wavefronts; and shapes on both sides of every line of the plan
+@pytest.mark.parametrize("H,L,vec,k,keep", [(2, 4100, 1, 64, 409), (2, 4100, 1, 48, 82), (16, 2050, 1, 64, 64), (1, 16384, 1, 64, 512),
+                                            (1, 16384, 1, 48, 327), (16, 8192, 8, 64, 256), (8, 8200, 4, 64, 256), (16, 8192, 8, 64, 257),
+                                            (4, 4100, 1, 64, 409), (64, 1040, 1, 64, 10), (16, 8192, 8, 48, 82)])
+def test_pairs_of_tiles_in_the_plan(dsa, oracle, H, L, vec, k, keep):
+    Qt, Kt = di.random_int8_case(L + H + keep, 1, H, L, k)
+    check(dsa, oracle, Qt, Kt, keep, vec, "pairs in the plan")
+
+
+@pytest.mark.parametrize("H,L", [(256, 128), (257, 128), (48, 256), (49, 256), (1, 2047), (1, 2048), (3, 4096), (4, 4096), (1, 8192), (2, 8192)])
+def test_wavefronts_of_the_plan(dsa, oracle, H, L):
+    for k in (32, 96):
+        Qt, Kt = di.random_int8_case(L + H, 1, H, L, k)
+        check(dsa, oracle, Qt, Kt, max(1, L // 40), 1, "wavefronts")
+
+
 # two contraction steps: 112 (the second one partly empty) and 128 (its halves of odd rows change places), in every number of
 # groups per range that has a kernel of its own
 @pytest.mark.parametrize("H,L", [(2, 130), (2, 1025), (4, 4096), (1, 8193), (1, 16385)])
