@@ -154,7 +154,7 @@ def test_mask_with_zero_query_rows(dsa, oracle, L, keep, vec):
     first `keep` keys).  keep is chosen so that the image of the index rows is the larger part of a
     wavefront's LDS and has an odd length; several launches, because such faults come and go."""
     import torch
-    B, H, k = (8, 8, 32) if vec == 8 else (2, 6, 32)       # vec = 8: enough units for the streaming kernel
+    B, H, k = (8, 8, 32) if vec == 8 else (2, 6, 32)       # vec = 8: as many units as the others have
     Qt, Kt = di.random_int8_case(900 + L, B, H, L, k)
     Qt = Qt.copy()
     for first in (0, 2, 15, 16 * 5 + 7):
@@ -175,8 +175,8 @@ def test_mask_with_zero_query_rows(dsa, oracle, L, keep, vec):
 @pytest.mark.parametrize("L", [4096, 2500])
 def test_mask_with_score_plateaus(dsa, oracle, L):
     """Scores that take three values only, on plateaus of several hundred keys: the kept set is
-    decided inside a plateau (all ties), at its edge, or needs more candidates than the fast
-    selection holds -- the strict-threshold pass, the ties-only answer and the recomputing path."""
+    decided inside a plateau (all ties, no score needed), at its edge, or in a bracket with more keys than a
+    band holds, which is swept again."""
     import torch
     B, H, k = 1, 2, 32
     rng = np.random.Generator(np.random.Philox(77 + L))

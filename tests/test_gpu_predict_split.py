@@ -76,6 +76,35 @@ def test_score_orders(dsa, oracle, L, keep):
             check(dsa, oracle, np.ascontiguousarray(Qt[:, :, :Lv]), np.ascontiguousarray(Kt[:, :, :Lv]), keep, vec, name)
 
 
+# the same orders in every kernel: all projection dimensions, 1, 4, 8 and 16 groups per range with one tile, 4 and 8 with two
+@pytest.mark.parametrize("H,L,vec,k,keep", [
+    (2, 512, 1, 16, 30), (2, 512, 8, 48, 30), (2, 512, 1, 128, 30), (2, 1600, 1, 48, 90), (2, 1600, 4, 64, 90), (2, 1600, 8, 96, 90),
+    (4, 4096, 1, 16, 205), (5, 4096, 1, 32, 205), (5, 4096, 8, 64, 205), (5, 4096, 1, 112, 205), (1, 12000, 1, 64, 600), (1, 12000, 4, 16, 120),
+    (1, 12000, 8, 128, 120), (16, 2050, 1, 64, 60), (2, 4100, 1, 48, 80), (1, 16384, 1, 64, 500), (16, 8192, 8, 64, 250)])
+def test_score_orders_in_every_kernel(dsa, oracle, H, L, vec, k, keep):
+    """As above, and tiles of 16 units that need no second sweep next to tiles that do (of a workgroup with two tiles one is good
+    while the other is swept again)."""
+    pos = np.arange(L)
+    orders = {
+        "rising": pos * 254 // L - 127,
+        "block": np.where((pos > L // 2) & (pos < L // 2 + 2 * keep), 100, -20),
+        "parity": np.where(pos % 2 == 0, 3, -3),
+        "outlier": np.where(pos == L // 3, 127, (pos * 7919) % 5),
+    }
+    rng = np.random.Generator(np.random.Philox(L + keep + k))
+    for name, v in orders.items():
+        Kt = np.zeros((1, H, L, k), np.int8)
+        Kt[..., 0] = v
+        Kt[..., 1] = rng.integers(-2, 3, size=L)
+        Kt[..., k - 2] = rng.integers(-127, 128, size=(1, H, L))          # what the even tiles see, and nothing else
+        tile = pos // (16 * vec) % 2
+        Qt = np.zeros((1, H, L, k), np.int8)
+        Qt[..., 0] = tile * np.where(pos // vec % 3 == 0, 127, np.where(pos // vec % 3 == 1, -127, 1))
+        Qt[..., 1] = tile * rng.integers(-1, 2, size=L)
+        Qt[..., k - 2] = (1 - tile) * rng.integers(1, 100, size=(1, H, L))
+        check(dsa, oracle, Qt, Kt, keep, vec, name)
+
+
 # two tiles of units per workgroup (projection dimensions of 48 and 64, enough units): a tile that is partly or wholly
 # beyond the head, ranges of 2, 3 and 8 groups, keep at the edge of what its 16 buckets per lane take
 @pytest.mark.parametrize("H,L,vec", [(16, 1025, 1), (15, 1100, 1), (60, 1104, 4), (8, 2049, 1), (30, 8200, 8)])

@@ -122,7 +122,7 @@ def test_threshold_extremes_and_capacity(dsa, oracle, workload):
     sc = oracle.approx_scores(x.Qt, x.Kt, 1)
     run_case(dsa, oracle, x, int(sc.max()) + 1, "no key reaches theta: best key per row")
     run_case(dsa, oracle, x, int(sc.min()), "every key reaches theta: dense")
-    # rows of more than one chunk of the CSR attention kernel (1024 keys)
+    # rows of more than one chunk of the CSR attention kernel (512 keys)
     cfg = di.custom_config(B=1, H=2, L=2600, d=64, dtype="bf16", rank=4, k=32, vec=1, keep=1, seed=77)
     y = di.make_inputs(cfg)
     run_case(dsa, oracle, y, theta_for(oracle, y, 0.7), "long rows")
