@@ -44,7 +44,7 @@ template <> struct Piece<float> {
     static __device__ __forceinline__ raw_t negate(raw_t a) { return make_float4(-a.x, -a.y, -a.z, -a.w); }
 };
 // bfloat16: v_dot2_f32_bf16 multiplies two packed pairs and accumulates in fp32, so no element is
-// ever unpacked.  For the weighted sum the weight is rounded to bfloat16 (relative 2^-9, inside the
+// ever unpacked.  For the weighted sum the weight is rounded to bfloat16 (relative 2^-8, inside the
 // 2e-2 budget of bfloat16 inputs) and paired with a zero: (v0, v1) . (p, 0) = p v0, (v0, v1) . (0, p) = p v1.
 template <> struct Piece<uint16_t> {
     static constexpr int N = 8;
@@ -209,7 +209,6 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
     typedef Piece<T> P;
     constexpr int E = P::N;               // elements per lane
     constexpr int LPR = D / E;            // lanes per row
-    constexpr int RPI = kWave / LPR;      // gathered rows per wavefront instruction
     extern __shared__ float lds_scores[];
 
     const int lane = threadIdx.x & (kWave - 1);
@@ -418,7 +417,7 @@ __global__ __launch_bounds__(kRowWaves *kWave) void gather_probe(const T *__rest
 //   elements [8g, 8g+8) of each 32-element step), the 8 query rows (padded to 16) the B operand.  Lane (c, g) then owns,
 //   for query c, keys 4g..4g+3 of the tile.  Scaled scores go to LDS and leave as whole rows.
 //   Output: over a 32-key step lane group g owns keys {4g+i} of the first tile and {16+4g+i} of the second: the weights of
-//   these 8, rounded to bfloat16 (relative 2^-9, inside the 2e-2 budget), are the A operand (query c, slots of g).  The
+//   these 8, rounded to bfloat16 (relative 2^-8, inside the 2e-2 budget), are the A operand (query c, slots of g).  The
 //   32 gathered value rows go through LDS once and come back transposed (ds_read_tr16_b64) as the B operand with the same
 //   slot order (lane (c, g): column c of the rows that are g's slots).
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -587,7 +586,8 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
 // times 3.3 GB; VEC = 8, N = 16, L = 4096, keep = 205: 44.7 -> 29 us, N = 64, L = 2048, keep = 102: 51 -> 35 us, D = 128,
 // N = 16, L = 8192, keep = 82: 72.6 -> 55 us against two passes with the scores in LDS.  A key and a value tile side by side
 // cost occupancy at D = 128 (59 us); rows padded to 16 bytes more instead of swizzled: 96 us at the first shape.
-// The error against 64 bits at the shapes below is 2e-6 (two-norm), 4e-4 to 1.3e-3 before with weights of one bf16.
+// The error against 64 bits (two-norm): L = 4096, keep = 205, VEC = 8 4.5e-6, L = 2000, keep = 200, VEC = 4 4.3e-6, D = 128,
+// L = 8192, keep = 82, VEC = 8 4.0e-6; 3.7e-4 to 4.2e-4 there with weights of one bf16.
 constexpr float kUnitSlack = 16.f;
 
 // Where the 16-byte pieces of tile row r are: piece p at p ^ unit_swizzle(r).  Eight rows of one piece (the score operand)
@@ -705,7 +705,7 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
             for (int i = 0; i < 8; ++i)
                 if (t0 + 16 * (i / 4) + 4 * g + i % 4 >= keep - 1) p[i] *= share;
         }
-        // A weight is the sum of two bf16 (relative 2^-17): one alone would be rounded at 2^-9, the largest one too, whose
+        // A weight is the sum of two bf16 (relative 2^-16): one alone would be rounded at 2^-8, the largest one too, whose
         // weight is not 1 here.  hi is p cut off, and lo is not zero where p is not (the factor is 1 + 2^-23), so that both
         // products with an infinite value have its sign.
         unsigned cut[8];

@@ -110,10 +110,8 @@ template <int K, int VEC = 1> struct KeyStream {
         }
     }
     // A group of 8 tiles starts (t8, its first tile, a multiple of 8): byte offset of the row operand
-    // that holds tile t8 + 8.  PAR, the group's index modulo 4, means nothing to this stream.
-    template <int PAR> __device__ __forceinline__ unsigned begin_group(int t8) const { return off0 + (unsigned)(t8 / R + NS) * kSlotStep; }
-    __device__ __forceinline__ void end_group() const {}
-    __device__ __forceinline__ void finish() const {}
+    // that holds tile t8 + 8.
+    __device__ __forceinline__ unsigned begin_group(int t8) const { return off0 + (unsigned)(t8 / R + NS) * kSlotStep; }
 
     // Starts the stream: operands of tiles 0..7, tiles 0 and 1 issued.  Rows beyond L read row L - 1.
     // Qunit: the unit's first (or only) row of Q~; its VEC rows are contiguous.
@@ -125,15 +123,10 @@ template <int K, int VEC = 1> struct KeyStream {
         off0 = (unsigned)((r >> 2) * Lq + 4 * sub + (r & 3)) * (unsigned)K + 16u * part;
         off_last = (unsigned)(L - 1) * (unsigned)K + 16u * part;
         unit_operands<K, VEC>(Qunit, unit_live, lane, qv, qh);
-        restart(b);
-    }
-    // Rewinds to tile 0; from here on every score comes out as score + b.
-    __device__ __forceinline__ void restart(int b)
-    {
         bias = v4i{b, b, b, b};
 #pragma unroll
         for (int sl = 0; sl < NS; ++sl) ring[sl] = load16(Kh + min(off0 + (unsigned)sl * kSlotStep, off_last));
-        const unsigned next = begin_group<0>(0);
+        const unsigned next = begin_group(0);
         issue<true>(0, 0, next);
         p0 = p1;
         if (VEC != 1) h0 = h1;
@@ -174,13 +167,13 @@ __device__ __forceinline__ int mask_beyond(int v, int key, int L)
 }
 
 // One bitmap word of a threshold sweep: 8 tiles, 32 consecutive keys of this lane's quarter, bit = score
-// reaches the threshold.  The stream was restarted with bias = -threshold, so a score misses the
+// reaches the threshold.  The stream was started with bias = -threshold, so a score misses the
 // threshold iff its sign bit is set, and one funnel shift per score moves that bit into the word.  *top: the largest of the
 // 32 and what it was.
-template <bool SAFE, int PAR, class Stream>
-__device__ __forceinline__ unsigned pass2_word(Stream &ks, int t8, int *top)
+template <bool SAFE, class Stream>
+__device__ __forceinline__ unsigned sweep_word(Stream &ks, int t8, int *top)
 {
-    const unsigned next = ks.template begin_group<PAR>(t8);
+    const unsigned next = ks.begin_group(t8);
     unsigned word = 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -190,7 +183,6 @@ __device__ __forceinline__ unsigned pass2_word(Stream &ks, int t8, int *top)
         *top = max(max(cur[2], cur[3]), *top);
         __builtin_amdgcn_sched_barrier(0);
     }
-    ks.end_group();
     return ~__brev(word);         // the first key of the word was shifted in first
 }
 

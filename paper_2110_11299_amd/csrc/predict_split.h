@@ -18,7 +18,7 @@
 //              moved or cut in three and swept again.  This ends for any scores: the bracket shrinks until it holds a
 //              single score value, and a plateau of equal scores needs no score at all (its first keys are taken).
 //   band       only the keys between the thresholds (about 50 of 4096) get their scores recomputed, from K~ rows, 16
-//              lanes per unit; the exact threshold is found by bisection, ties go to the lower key.
+//              lanes per unit; the exact threshold is found by interpolation and bisection in turn, ties go to the lower key.
 //   emission   every lane turns its words into key indices at its place in the unit's row, in LDS; the rows leave as
 //              one contiguous block.
 //

@@ -61,9 +61,9 @@ __global__ __launch_bounds__(kWave, 4) void threshold_sweep(const int8_t *__rest
         int top = INT32_MIN;
         const int nv = key_lim - (key_lo + 32 * w);      // real keys in this word
         if (8 * w + 8 + decltype(ks)::kLookahead <= tfull) {
-            word = pass2_word<false, 0>(ks, 8 * w, &top);
+            word = sweep_word<false>(ks, 8 * w, &top);
         } else {
-            word = pass2_word<true, 0>(ks, 8 * w, &top);
+            word = sweep_word<true>(ks, 8 * w, &top);
             word = nv >= 32 ? word : nv <= 0 ? 0u : word & ((1u << nv) - 1u);
         }
         words[(size_t)w * kWave] = word;
@@ -293,6 +293,7 @@ size_t threshold_workspace_bytes(const dsa_shape &sh)
     const size_t tasks = (size_t)sh.B * sh.H * ((sh.L / sh.vec + 15) / 16);
     const size_t units = (size_t)sh.B * sh.H * (sh.L / sh.vec);
     const size_t blocks = (units + kScanBlock - 1) / kScanBlock;
+    // (the counts are one per task; callers have been told to bring room for one per unit, and the figure stays)
     return sizeof(unsigned) * tasks * (stream_quarter(sh.L) / 32) * kWave + sizeof(int32_t) * (units + blocks);
 }
 

@@ -29,25 +29,6 @@ __device__ __forceinline__ int wave_sum(int x)
     return __builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16) +
            __builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48);
 }
-__device__ __forceinline__ int wave_max(int x)
-{
-    x = max(x, dpp_move<kDppXor1>(x));
-    x = max(x, dpp_move<kDppXor2>(x));
-    x = max(x, dpp_move<kDppHalfMirror>(x));
-    x = max(x, dpp_move<kDppMirror>(x));
-    return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
-               max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
-}
-__device__ __forceinline__ int wave_min(int x)
-{
-    x = min(x, dpp_move<kDppXor1>(x));
-    x = min(x, dpp_move<kDppXor2>(x));
-    x = min(x, dpp_move<kDppHalfMirror>(x));
-    x = min(x, dpp_move<kDppMirror>(x));
-    return min(min(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
-               min(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
-}
-
 // Inclusive prefix sum over the 64 lanes: Hillis-Steele inside each row of 16 lanes with DPP row
 // shifts (zero fill), then the totals of the lower rows through v_readlane.  *total = wavefront sum.
 __device__ __forceinline__ int wave_incl_scan(int x, int lane, int *total)
