@@ -331,6 +331,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
         for (int t = 0; t < UT; ++t) {
             int mn = INT32_MAX;
             float sum = 0.f;
+#pragma unroll 4
             for (int x = 0; x < W; ++x) {
                 mn = min(mn, s_totl[x * U + kTile * t + c]);
                 sum += s_sum[x * U + kTile * t + c];
@@ -456,6 +457,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
 #pragma unroll
         for (int t = 0; t < UT; ++t) {
             nl[t] = nh[t] = 0;
+#pragma unroll 4
             for (int x = 0; x < W; ++x) {
                 const int v = s_totl[x * U + kTile * t + c];
                 const int vl = v >> 16, vh = v & 0xffff;
@@ -659,6 +661,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
     int32_t *out = a.idx + ((size_t)n * G + u0) * keep;
 #pragma unroll
     for (int t = 0; t < UT; ++t) {
+#pragma unroll 4
         for (int x = 0; x < wv; ++x) out0[t] += s_totl[x * U + kTile * t + c];
         const bool live = kTile * t + c < nu;
         int pos = (kTile * t + c) * keep + out0[t];
