@@ -80,6 +80,33 @@ size_t round_up_256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 dsa_status from_hip(hipError_t e) { return e == hipSuccess ? DSA_OK : DSA_ERR_HIP; }
 
+// Packed codes of Q~ and K~ as int8 in a workspace.
+struct Codes {
+    size_t n;
+    int8_t *q, *k;
+    void *rest;                         // of the workspace
+    Codes(const dsa_shape &sh, void *ws) : n((size_t)sh.B * sh.H * sh.L * sh.k)
+    {
+        q = static_cast<int8_t *>(ws);
+        k = q + round_up_256(n);
+        rest = k + round_up_256(n);
+    }
+    hipError_t unpack(int bits, const void *Qt, const void *Kt, hipStream_t st) const
+    {
+        return dsa::launch_unpack_codes(bits, Qt, Kt, q, k, n, st);
+    }
+};
+
+// Mask and attention over it, from int8 codes: one launch, or two.
+dsa_status launch_forward(const dsa_shape &sh, const void *Q, const void *K, const void *V, const int8_t *Qt, const int8_t *Kt,
+                          float *O, int32_t *idx, void *pws, hipStream_t st)
+{
+    const dsa::AttendPtrs attend{Q, K, V, O};
+    bool attended = false;
+    if (hipError_t e = dsa::launch_predict(sh, Qt, Kt, idx, pws, &attend, &attended, st)) return from_hip(e);
+    return attended ? DSA_OK : from_hip(dsa::launch_attention(dsa::kFused, sh, Q, K, V, idx, nullptr, nullptr, O, st));
+}
+
 }  // namespace
 
 extern "C" {
@@ -108,7 +135,7 @@ dsa_status dsa_predict_mask(const dsa_shape *sh, const int8_t *Qt, const int8_t 
     if (!aligned16(Qt) || !aligned16(Kt) || !aligned16(idx) || !aligned16(ws)) return DSA_ERR_ALIGN;
     const size_t need = round_up_256(dsa::predict_workspace_bytes(*sh));
     if (need && (!ws || ws_bytes < need)) return DSA_ERR_WORKSPACE;
-    return from_hip(dsa::launch_predict(*sh, Qt, Kt, idx, ws, (hipStream_t)stream));
+    return from_hip(dsa::launch_predict(*sh, Qt, Kt, idx, ws, nullptr, nullptr, (hipStream_t)stream));
 }
 
 dsa_status dsa_sddmm(const dsa_shape *sh, const void *Q, const void *K, const int32_t *idx, float *S,
@@ -166,9 +193,7 @@ dsa_status dsa_attention_fwd(const dsa_shape *sh, const void *Q, const void *K, 
     if (need && (!ws || ws_bytes < need)) return DSA_ERR_WORKSPACE;
     int32_t *idx = idx_out ? idx_out : static_cast<int32_t *>(ws);
     void *pws = idx_out ? ws : static_cast<void *>(static_cast<char *>(ws) + mask_bytes);
-    hipStream_t st = (hipStream_t)stream;
-    if (hipError_t e = dsa::launch_predict(*sh, Qt, Kt, idx, pws, st)) return from_hip(e);
-    return from_hip(dsa::launch_attention(dsa::kFused, *sh, Q, K, V, idx, nullptr, nullptr, O, st));
+    return launch_forward(*sh, Q, K, V, Qt, Kt, O, idx, pws, (hipStream_t)stream);
 }
 
 size_t dsa_noalloc_max_mask_bytes(void) { return kStaticScratchBytes; }
@@ -188,9 +213,7 @@ dsa_status dsa_attention_fwd_noalloc(const dsa_shape *sh, const void *Q, const v
     if (static_scratch(&base) != hipSuccess) return DSA_ERR_HIP;
     int32_t *idx = static_cast<int32_t *>(base);
     void *pws = static_cast<char *>(base) + mask_bytes;
-    hipStream_t st = (hipStream_t)stream;
-    if (hipError_t e = dsa::launch_predict(*sh, Qt, Kt, idx, pws, st)) return from_hip(e);
-    return from_hip(dsa::launch_attention(dsa::kFused, *sh, Q, K, V, idx, nullptr, nullptr, O, st));
+    return launch_forward(*sh, Q, K, V, Qt, Kt, O, idx, pws, (hipStream_t)stream);
 }
 
 dsa_status dsa_approx_rowmax(const dsa_shape *sh, const int8_t *Qt, const int8_t *Kt, int32_t *rowmax,
@@ -261,15 +284,11 @@ dsa_status dsa_predict_mask_bits(const dsa_shape *sh, int32_t bits, const void *
                                 stream);
     if (dsa_status s = check_predict(sh)) return s;
     if (!aligned16(Qt) || !aligned16(Kt) || !aligned16(idx) || !aligned16(ws)) return DSA_ERR_ALIGN;
-    const size_t need = dsa_predict_workspace_bytes_bits(sh, bits);
-    if (!ws || ws_bytes < need) return DSA_ERR_WORKSPACE;
-    const size_t n_codes = (size_t)sh->B * sh->H * sh->L * sh->k;
-    const size_t codes = round_up_256(n_codes);
-    int8_t *q8 = static_cast<int8_t *>(ws), *k8 = q8 + codes;
-    void *pws = k8 + codes;
+    if (!ws || ws_bytes < dsa_predict_workspace_bytes_bits(sh, bits)) return DSA_ERR_WORKSPACE;
+    const Codes c(*sh, ws);
     hipStream_t st = (hipStream_t)stream;
-    if (hipError_t e = dsa::launch_unpack_codes(bits, Qt, Kt, q8, k8, n_codes, st)) return from_hip(e);
-    return from_hip(dsa::launch_predict(*sh, q8, k8, idx, pws, st));
+    if (hipError_t e = c.unpack(bits, Qt, Kt, st)) return from_hip(e);
+    return from_hip(dsa::launch_predict(*sh, c.q, c.k, idx, c.rest, nullptr, nullptr, st));
 }
 
 size_t dsa_workspace_bytes_bits(const dsa_shape *sh, int32_t bits)
@@ -291,11 +310,15 @@ dsa_status dsa_attention_fwd_bits(const dsa_shape *sh, int32_t bits, const void 
     const size_t mask_bytes = round_up_256(idx_bytes(*sh));
     const size_t need = (idx_out ? 0 : mask_bytes) + dsa_predict_workspace_bytes_bits(sh, bits);
     if (need && (!ws || ws_bytes < need)) return DSA_ERR_WORKSPACE;
+    if (!aligned16(Qt) || !aligned16(Kt)) return DSA_ERR_ALIGN;
     int32_t *idx = idx_out ? idx_out : static_cast<int32_t *>(ws);
     void *pws = idx_out ? ws : static_cast<void *>(static_cast<char *>(ws) + mask_bytes);
-    if (dsa_status s = dsa_predict_mask_bits(sh, bits, Qt, Kt, idx, pws, ws_bytes - (idx_out ? 0 : mask_bytes), stream))
-        return s;
-    return from_hip(dsa::launch_attention(dsa::kFused, *sh, Q, K, V, idx, nullptr, nullptr, O, (hipStream_t)stream));
+    hipStream_t st = (hipStream_t)stream;
+    if (bits == 8)
+        return launch_forward(*sh, Q, K, V, static_cast<const int8_t *>(Qt), static_cast<const int8_t *>(Kt), O, idx, pws, st);
+    const Codes c(*sh, pws);
+    if (hipError_t e = c.unpack(bits, Qt, Kt, st)) return from_hip(e);
+    return launch_forward(*sh, Q, K, V, c.q, c.k, O, idx, c.rest, st);
 }
 
 size_t dsa_threshold_workspace_bytes(const dsa_shape *sh)

@@ -1,203 +1,17 @@
 // Exact attention at the kept positions (paper section 3.4 / 5.1): SDDMM (equation 2 sampled at
 // the mask), softmax over the kept entries (equation 4) and SpMM (equation 3).
 //
-// Row kernel.  One 64-lane wavefront owns one query row.  A key / value row of d elements is
-// d*e bytes; it is read as 16-byte pieces by LPR = d*e/16 neighbouring lanes, so one wavefront
-// load instruction fetches 64/LPR complete, fully coalesced rows of the gather list.  The
-// kernel is bound by those gathers (about 1 flop per byte), so everything else stays on chip:
-// the row's scores go to LDS, the softmax statistics live in registers, and the weights are
-// recomputed from the LDS scores while the value rows stream in.  S and P never reach HBM in
-// the fused mode.
+// Row kernel.  One 64-lane wavefront owns one query row, with the loops of row_attend.h.  The kernel is bound by the gathers
+// (about 1 flop per byte), so everything else stays on chip: S and P never reach HBM in the fused mode.
 #include "dsa_internal.h"
 #include "attention_api.h"
-
-#include <type_traits>
+#include "row_attend.h"
 
 namespace dsa {
 namespace {
 
 constexpr int kRowWaves = 4;          // query rows (wavefronts) per workgroup
-constexpr int kRowPad = 8;            // the row kernel pads a key list to a multiple of this
 constexpr int kMaxKeep = 4096;        // list and scores of a row in LDS: 4 waves * 4096 * 8 B = 128 KB
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// 16 bytes of a row: how to load them, to take a dot product of two of them and to add p times one
-// of them to fp32 accumulators.
-template <typename T> struct Piece;
-template <> struct Piece<float> {
-    static constexpr int N = 4;
-    typedef float4 raw_t;
-    static __device__ __forceinline__ raw_t load(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-    static __device__ __forceinline__ float dot(raw_t a, raw_t b)
-    {
-        return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)));
-    }
-    // A weight as the word that is kept in LDS, the sum of weights, o += weight * b, and -a.
-    static __device__ __forceinline__ unsigned weight(float p) { return __float_as_uint(p); }
-    static __device__ __forceinline__ float wsum(float z, unsigned w) { return z + __uint_as_float(w); }
-    static __device__ __forceinline__ void axpy(float (&o)[4], unsigned w, raw_t b)
-    {
-        const float p = __uint_as_float(w);
-        o[0] = fmaf(p, b.x, o[0]); o[1] = fmaf(p, b.y, o[1]); o[2] = fmaf(p, b.z, o[2]); o[3] = fmaf(p, b.w, o[3]);
-    }
-    static __device__ __forceinline__ raw_t negate(raw_t a) { return make_float4(-a.x, -a.y, -a.z, -a.w); }
-};
-// bfloat16: v_dot2_f32_bf16 multiplies two packed pairs and accumulates in fp32, so no element is
-// ever unpacked.  For the weighted sum the weight is rounded to bfloat16 (relative 2^-8, inside the
-// 2e-2 budget of bfloat16 inputs) and paired with a zero: (v0, v1) . (p, 0) = p v0, (v0, v1) . (0, p) = p v1.
-template <> struct Piece<uint16_t> {
-    static constexpr int N = 8;
-    typedef uint4 raw_t;
-    static __device__ __forceinline__ raw_t load(const uint16_t *p) { return *reinterpret_cast<const uint4 *>(p); }
-    static __device__ __forceinline__ float dot2(unsigned a, unsigned b, float acc)
-    {
-        return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), acc, false);
-    }
-    static __device__ __forceinline__ float dot(raw_t a, raw_t b)
-    {
-        return dot2(a.w, b.w, dot2(a.z, b.z, dot2(a.y, b.y, dot2(a.x, b.x, 0.f))));
-    }
-    // The weight kept in LDS is the pair (p rounded to bfloat16, 0); the sum takes the rounded weights, the
-    // ones the products use.
-    static __device__ __forceinline__ unsigned weight(float p) { return __builtin_bit_cast(unsigned short, (__bf16)p); }
-    static __device__ __forceinline__ float wsum(float z, unsigned w) { return dot2(w, 0x3f803f80u, z); }
-    static __device__ __forceinline__ raw_t negate(raw_t a)
-    {
-        return make_uint4(a.x ^ 0x80008000u, a.y ^ 0x80008000u, a.z ^ 0x80008000u, a.w ^ 0x80008000u);
-    }
-    static __device__ __forceinline__ void axpy(float (&o)[8], unsigned lo, raw_t b)
-    {
-        const unsigned hi = lo << 16;
-        o[0] = dot2(b.x, lo, o[0]); o[1] = dot2(b.x, hi, o[1]);
-        o[2] = dot2(b.y, lo, o[2]); o[3] = dot2(b.y, hi, o[3]);
-        o[4] = dot2(b.z, lo, o[4]); o[5] = dot2(b.z, hi, o[5]);
-        o[6] = dot2(b.w, lo, o[6]); o[7] = dot2(b.w, hi, o[7]);
-    }
-};
-
-// Cross-lane moves inside a row of 16 lanes without LDS traffic (DPP).
-template <int CTRL> __device__ __forceinline__ float dpp_f(float x)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
-}
-// Sum over the LPR neighbouring lanes that hold one row (LPR = 8, 16 or 32); every one of them gets it.
-template <int LPR> __device__ __forceinline__ float piece_sum(float x)
-{
-    x += dpp_f<0xB1>(x);                          // lane ^ 1 (quad permute 1,0,3,2)
-    x += dpp_f<0x4E>(x);                          // lane ^ 2 (quad permute 2,3,0,1)
-    x += dpp_f<0x141>(x);                         // the other quad of the 8 (half-row mirror)
-    if (LPR >= 16) x += dpp_f<0x140>(x);          // the other half of the 16 (row mirror)
-    if (LPR >= 32) x += __shfl_xor(x, 16, kWave);
-    return x;
-}
-// Combine the 64/LPR row groups of a wavefront: lane (group, piece) with every (group', piece).
-template <int LPR> __device__ __forceinline__ float groups_sum(float x)
-{
-    if (LPR <= 8) x += dpp_f<0x128>(x);           // lane ^ 8 (row rotate by 8)
-#pragma unroll
-    for (int off = (LPR <= 8 ? 16 : LPR); off < kWave; off <<= 1) x += __shfl_xor(x, off, kWave);
-    return x;
-}
-template <int LPR> __device__ __forceinline__ float groups_max(float x)
-{
-    if (LPR <= 8) x = fmaxf(x, dpp_f<0x128>(x));
-#pragma unroll
-    for (int off = (LPR <= 8 ? 16 : LPR); off < kWave; off <<= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
-    return x;
-}
-
-// Reductions over all 64 lanes.
-__device__ __forceinline__ float wave_all_sum(float x)
-{
-    x = piece_sum<16>(x);
-    x += __shfl_xor(x, 16, kWave);
-    x += __shfl_xor(x, 32, kWave);
-    return x;
-}
-__device__ __forceinline__ float wave_all_max(float x)
-{
-    x = fmaxf(x, dpp_f<0xB1>(x));
-    x = fmaxf(x, dpp_f<0x4E>(x));
-    x = fmaxf(x, dpp_f<0x141>(x));
-    x = fmaxf(x, dpp_f<0x140>(x));
-    x = fmaxf(x, __shfl_xor(x, 16, kWave));
-    x = fmaxf(x, __shfl_xor(x, 32, kWave));
-    return x;
-}
-
-// Makes LDS writes of some lanes of a wavefront visible to reads of its other lanes.  Every LDS
-// region below belongs to one wavefront, so no workgroup barrier is ever needed.
-__device__ __forceinline__ void wave_lds_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// The two gather loops of the row kernels, over `n` entries in LDS (a multiple of kRowPad) that hold the byte offsets of the
-// rows inside the head.  Four gathers are in flight per lane while full trips last.
-constexpr int kRowGathers = 4;
-
-template <int STEP, typename F> __device__ __forceinline__ void row_trips(int n, F &&trip)
-{
-    int t0 = 0;
-    for (; t0 + kRowGathers * STEP <= n; t0 += kRowGathers * STEP) trip(t0, std::integral_constant<int, kRowGathers>{});
-    for (; t0 < n; t0 += STEP) trip(t0, std::integral_constant<int, 1>{});
-}
-
-// q . k of every entry to sc; returns the maximum over this lane group's entries.
-template <typename T, int D>
-__device__ __forceinline__ float row_scores(const T *Kh, typename Piece<T>::raw_t q, const unsigned *sl, float *sc, int n, int sub, int grp)
-{
-    typedef Piece<T> P;
-    constexpr int LPR = D / P::N, RPI = kWave / LPR;
-    static_assert(kRowPad % RPI == 0, "n is a whole number of single trips");
-    const unsigned piece_at = sub * P::N * (unsigned)sizeof(T);
-    float m = -INFINITY;
-    row_trips<RPI>(n, [&](int t0, auto uu) {
-        constexpr int UU = decltype(uu)::value;
-        typename P::raw_t kv[UU];
-#pragma unroll
-        for (int u = 0; u < UU; ++u)
-            kv[u] = P::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(Kh) + (size_t)(sl[t0 + u * RPI + grp] + piece_at)));
-        float acc[UU];
-#pragma unroll
-        for (int u = 0; u < UU; ++u) acc[u] = piece_sum<LPR>(P::dot(q, kv[u]));
-#pragma unroll
-        for (int u = 0; u < UU; ++u) {
-            m = fmaxf(m, acc[u]);
-            sc[t0 + u * RPI + grp] = acc[u];      // every lane of the group writes the same value
-        }
-    });
-    return m;
-}
-
-// o += weight * value row over the entries of this lane group, and z += weight if SUM.
-template <typename T, int D, bool SUM>
-__device__ __forceinline__ void row_values(const T *Vh, const unsigned *sl, const unsigned *sw, int n, int sub, int grp,
-                                           float (&o)[Piece<T>::N], float &z)
-{
-    typedef Piece<T> P;
-    constexpr int LPR = D / P::N, RPI = kWave / LPR;
-    const unsigned piece_at = sub * P::N * (unsigned)sizeof(T);
-    row_trips<RPI>(n, [&](int t0, auto uu) {
-        constexpr int UU = decltype(uu)::value;
-        typename P::raw_t vv[UU];
-        unsigned w[UU];
-#pragma unroll
-        for (int u = 0; u < UU; ++u) {
-            const int t = t0 + u * RPI + grp;
-            vv[u] = P::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(Vh) + (size_t)(sl[t] + piece_at)));
-            w[u] = sw[t];
-        }
-#pragma unroll
-        for (int u = 0; u < UU; ++u) {
-            if (SUM) z = P::wsum(z, w[u]);
-            P::axpy(o, w[u], vv[u]);
-        }
-    });
-}
 
 // MODE kFused: Q,K,V,idx -> O.  kSddmm: Q,K,idx -> S.  kSpmm: Pin,V,idx -> O.
 template <typename T, int D, int MODE>
@@ -207,77 +21,47 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
     float *__restrict__ O, int L, int keep, int keep_pad, int vec, float scale, unsigned total_rows)
 {
     typedef Piece<T> P;
+    typedef typename P::raw_t raw_t;
     constexpr int E = P::N;               // elements per lane
-    constexpr int LPR = D / E;            // lanes per row
-    extern __shared__ float lds_scores[];
+    extern __shared__ unsigned lds_words[];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int sub = lane % LPR, grp = lane / LPR;
+    const int sub = lane % RowShape<T, D>::LPR;
     const unsigned vblock = xcd_contiguous(blockIdx.x, gridDim.x);
     const unsigned row = vblock * kRowWaves + wave;                 // wavefront-uniform from here on
-    const bool live = row < total_rows;
-    const unsigned r = live ? row : total_rows - 1;      // dead waves shadow a real row, write nothing
-    const unsigned n = r / (unsigned)L, i = r % (unsigned)L;
+    if (row >= total_rows) return;                        // the whole wavefront: nothing below is shared
+    const unsigned n = row / (unsigned)L, i = row % (unsigned)L;
     const int32_t *list = idx + ((size_t)n * (L / vec) + i / vec) * keep;
     // per wavefront in LDS: the row's key list, as the byte offset of every key row inside its head
-    // (keys clamped into [0, L), so that no idx can send a gather outside K / V), and its scores, later
-    // (or from the start, when the weights are given) its weights.  The list is padded to keep_pad, a multiple of the keys one
-    // trip of the loops below takes, with its last key: a padded entry has the score of a real one (no
-    // effect on the maximum) and gets the weight 0, so the loops test nothing.
+    // (keys clamped into [0, L), so that no idx can send a gather outside K / V), filled up with its last key, and its scores,
+    // later (or from the start, when the weights are given) its weights
     constexpr unsigned kRowBytes = D * sizeof(T);
-    unsigned *sl = reinterpret_cast<unsigned *>(lds_scores) + wave * 2 * keep_pad;
-    float *sc = reinterpret_cast<float *>(sl + keep_pad);
-    unsigned *sw = reinterpret_cast<unsigned *>(sc);      // the same words once they hold weights
+    unsigned *sl = lds_words + wave * 2 * keep_pad, *sw = sl + keep_pad;
     for (int t = lane; t < keep_pad; t += kWave) sl[t] = (unsigned)min(max(list[min(t, keep - 1)], 0), L - 1) * kRowBytes;
-    wave_lds_fence();
-    float m = -INFINITY;
-    // fused mode: the scores are kept as sign(scale) * q.k and the factor |scale| waits for the exponential
-    const bool flip = MODE == kFused && scale < 0.f;
-    const float factor = MODE == kFused ? fabsf(scale) : scale;
-    if (MODE != kSpmm) {
-        typename P::raw_t q = P::load(Q + (size_t)r * D + sub * E);
-        if (flip) q = P::negate(q);
-        const T *Kh = K + (size_t)n * L * D;
-        m = row_scores<T, D>(Kh, q, sl, sc, keep_pad, sub, grp);
-        if (MODE == kSddmm) {
-            // the row of scores leaves in one piece: consecutive lanes, consecutive entries
-            wave_lds_fence();
-            if (live)
-                for (int t = lane; t < keep; t += kWave) S[(size_t)r * keep + t] = sc[t] * factor;
-            return;
-        }
-        m = groups_max<LPR>(m);
-        wave_lds_fence();
-        // unnormalised weights, computed once per kept key (the lanes that share a value row would
-        // otherwise each repeat the exponential), in the form the products take them
-        for (int t = lane; t < keep_pad; t += kWave) sw[t] = t < keep ? P::weight(__expf(factor * (sc[t] - m))) : 0u;
-        wave_lds_fence();
-    }
-
-    if (MODE == kSpmm) {
-        // the given weights come in the same way and wait in LDS in the form the products take them
-        for (int t = lane; t < keep_pad; t += kWave) sw[t] = t < keep ? P::weight(Pin[(size_t)r * keep + t]) : 0u;
-        wave_lds_fence();
-    }
-    float o[E], z = 0.f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = 0.f;
-    const T *Vh = V + (size_t)n * L * D;
-    row_values<T, D, MODE == kFused>(Vh, sl, sw, keep_pad, sub, grp, o, z);
-#pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = groups_sum<LPR>(o[e]);
+    auto at = [&](int, int t) { return sl[t]; };
+    const T *Kh = K + (size_t)n * L * D, *Vh = V + (size_t)n * L * D;
+    raw_t q[1];
+    if (MODE != kSpmm) q[0] = P::load(Q + (size_t)row * D + sub * E);
+    wave_lds_sync();
     if (MODE == kFused) {
-        z = groups_sum<LPR>(z);
-        const float inv = 1.f / z;
+        attend_rows<T, D, 1>(Kh, Vh, q, at, sw, keep_pad, keep, scale, {O + (size_t)row * D}, lane);
+    } else if (MODE == kSddmm) {
+        float m[1];
+        float *sc = reinterpret_cast<float *>(sw);
+        row_scores<T, D, 1>(Kh, q, at, sc, 0, keep, lane, m);
+        // the row of scores leaves in one piece: consecutive lanes, consecutive entries
+        wave_lds_sync();
+        for (int t = lane; t < keep; t += kWave) S[(size_t)row * keep + t] = sc[t] * scale;
+    } else {
+        // the given weights come in the same way and wait in LDS in the form the products take them
+        for (int t = lane; t < keep_pad; t += kWave) sw[t] = t < keep ? P::weight(Pin[(size_t)row * keep + t]) : 0u;
+        wave_lds_sync();
+        float o[1][E];
 #pragma unroll
-        for (int e = 0; e < E; ++e) o[e] *= inv;
-    }
-    if (live && grp == 0) {
-        float *out = O + (size_t)r * D + sub * E;
-#pragma unroll
-        for (int e = 0; e < E; e += 4)
-            *reinterpret_cast<float4 *>(out + e) = make_float4(o[e], o[e + 1], o[e + 2], o[e + 3]);
+        for (int e = 0; e < E; ++e) o[0][e] = 0.f;
+        row_values<T, D, 1>(Vh, at, sw, 0, keep, lane, o);
+        row_store<T, D>(O + (size_t)row * D, o[0], 1.f, lane);
     }
 }
 
@@ -298,64 +82,53 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows_csr(
     float scale, unsigned total_rows)
 {
     typedef Piece<T> P;
-    constexpr int E = P::N, LPR = D / E;
+    constexpr int E = P::N;
     constexpr unsigned kRowBytes = D * sizeof(T);
     __shared__ unsigned lists[kRowWaves][kCsrChunk];
-    __shared__ float scores[kRowWaves][kCsrChunk];
+    __shared__ unsigned weights[kRowWaves][kCsrChunk];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int sub = lane % LPR, grp = lane / LPR;
+    const int sub = lane % RowShape<T, D>::LPR;
     const unsigned row = xcd_contiguous(blockIdx.x, gridDim.x) * kRowWaves + wave;
     if (row >= total_rows) return;                        // the whole wavefront: nothing below is shared
     const unsigned n = row / (unsigned)L, i = row % (unsigned)L;
     const size_t u = (size_t)n * (L / vec) + i / vec;
     const int beg = row_ptr[u];
     const int cnt = max(row_ptr[u + 1] - beg, 0);
-    unsigned *sl = lists[wave];
-    float *sc = scores[wave];
-    unsigned *sw = reinterpret_cast<unsigned *>(sc);      // the same words once they hold weights
+    unsigned *sl = lists[wave], *sw = weights[wave];      // (scores, then weights)
     // the scores are kept as sign(scale) * q.k and the factor |scale| waits for the exponential
-    typename P::raw_t q = P::load(Q + (size_t)row * D + sub * E);
-    if (scale < 0.f) q = P::negate(q);
+    typename P::raw_t q[1] = {P::load(Q + (size_t)row * D + sub * E)};
+    if (scale < 0.f) q[0] = P::negate(q[0]);
     const float factor = fabsf(scale);
     const T *Kh = K + (size_t)n * L * D, *Vh = V + (size_t)n * L * D;
+    auto at = [&](int, int t) { return sl[t]; };
 
-    float m = -INFINITY, z = 0.f, o[E];
+    float m[1] = {-INFINITY}, z[1] = {0.f}, o[1][E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = 0.f;
+    for (int e = 0; e < E; ++e) o[0][e] = 0.f;
     for (int c0 = 0; c0 < cnt; c0 += kCsrChunk) {
         const int nk = min(kCsrChunk, cnt - c0), pad = (nk + kRowPad - 1) / kRowPad * kRowPad;
         const int32_t *list = col + beg + c0;
         for (int t = lane; t < pad; t += kWave) sl[t] = (unsigned)min(max(list[min(t, nk - 1)], 0), L - 1) * kRowBytes;
-        wave_lds_fence();
-        const float m_new = fmaxf(m, groups_max<LPR>(row_scores<T, D>(Kh, q, sl, sc, pad, sub, grp)));
+        wave_lds_sync();
+        float m_new[1];
+        row_scores<T, D, 1>(Kh, q, at, reinterpret_cast<float *>(sw), 0, nk, lane, m_new);
+        m_new[0] = fmaxf(m[0], wave_all_max(m_new[0]));
         if (c0 > 0) {
-            const float f = __expf(factor * (m - m_new));
-            z *= f;
+            const float f = __expf(factor * (m[0] - m_new[0]));
+            z[0] *= f;
 #pragma unroll
-            for (int e = 0; e < E; ++e) o[e] *= f;
+            for (int e = 0; e < E; ++e) o[0][e] *= f;
         }
-        m = m_new;
-        wave_lds_fence();
-        for (int t = lane; t < pad; t += kWave) {
-            const float p = t < nk ? __expf(factor * (sc[t] - m)) : 0.f;
-            z += p;
-            sw[t] = P::weight(p);
-        }
-        wave_lds_fence();
-        row_values<T, D, false>(Vh, sl, sw, pad, sub, grp, o, z);
-        wave_lds_fence();                                  // the next chunk overwrites list and weights
+        m[0] = m_new[0];
+        wave_lds_sync();
+        row_weights<T, 1, false>(sw, pad, nk, factor, m, lane, z);
+        wave_lds_sync();
+        row_values<T, D, 1>(Vh, at, sw, 0, nk, lane, o);
+        wave_lds_sync();                                   // the next chunk overwrites list and weights
     }
-#pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = groups_sum<LPR>(o[e]);
-    z = wave_all_sum(z);
-    const float inv = cnt > 0 ? 1.f / z : 0.f;            // a row without keys (not made by the predictor) gives 0
-    if (grp == 0) {
-        float *out = O + (size_t)row * D + sub * E;
-#pragma unroll
-        for (int e = 0; e < E; e += 4)
-            *reinterpret_cast<float4 *>(out + e) = make_float4(o[e] * inv, o[e + 1] * inv, o[e + 2] * inv, o[e + 3] * inv);
-    }
+    // a row without keys (not made by the predictor) gives 0
+    row_store<T, D>(O + (size_t)row * D, o[0], cnt > 0 ? 1.f / wave_all_sum(z[0]) : 0.f, lane);
 }
 
 // Measurement aid: the gathers of attention_rows and nothing else.  Same launch shape, same key list
@@ -370,12 +143,10 @@ __global__ __launch_bounds__(kRowWaves *kWave) void gather_probe(const T *__rest
                                                                  int keep_pad, int vec, unsigned total_rows)
 {
     typedef Piece<T> P;
-    constexpr int E = P::N, LPR = D / E, RPI = kWave / LPR, U = 4;
-    constexpr unsigned kRowBytes = D * sizeof(T), kPieceBytes = E * sizeof(T);
+    constexpr unsigned kRowBytes = D * sizeof(T);
     extern __shared__ float lds_scores[];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int sub = lane % LPR, grp = lane / LPR;
     const unsigned row = xcd_contiguous(blockIdx.x, gridDim.x) * kRowWaves + wave;
     const bool live = row < total_rows;
     const unsigned r = live ? row : total_rows - 1;
@@ -384,28 +155,24 @@ __global__ __launch_bounds__(kRowWaves *kWave) void gather_probe(const T *__rest
     // the same padded list of byte offsets as in attention_rows, the same address arithmetic
     unsigned *sl = reinterpret_cast<unsigned *>(lds_scores) + wave * keep_pad;
     for (int t = lane; t < keep_pad; t += kWave) sl[t] = (unsigned)min(max(list[min(t, keep - 1)], 0), L - 1) * kRowBytes;
-    wave_lds_fence();
-    const unsigned piece_at = sub * kPieceBytes;
+    wave_lds_sync();
     unsigned acc = 0;
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
         const T *Xh = (pass ? V : K) + (size_t)n * L * D;
-        auto gather = [&](int t0, auto uu) {
-            constexpr int UU = decltype(uu)::value;
-            typename P::raw_t x[UU];
+        row_trips<T, D>(keep, [&](int t0, auto tail) {
+            typename P::raw_t x[1][kRowGathers];
+            if (decltype(tail)::value) {
 #pragma unroll
-            for (int u = 0; u < UU; ++u)
-                x[u] = P::load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(Xh) +
-                                                           (size_t)(sl[t0 + u * RPI + grp] + piece_at)));
+                for (int u = decltype(tail)::value; u < kRowGathers; ++u) x[0][u] = typename P::raw_t{};
+            }
+            row_gather<T, D, 1, decltype(tail)::value>(x, Xh, [&](int, int t) { return sl[t]; }, t0, keep, lane);
 #pragma unroll
-            for (int u = 0; u < UU; ++u) {
-                const uint4 w = __builtin_bit_cast(uint4, x[u]);
+            for (int u = 0; u < kRowGathers; ++u) {
+                const uint4 w = __builtin_bit_cast(uint4, x[0][u]);
                 acc ^= (w.x ^ w.y) ^ (w.z ^ w.w);
             }
-        };
-        int t0 = 0;
-        for (; t0 + U * RPI <= keep_pad; t0 += U * RPI) gather(t0, std::integral_constant<int, U>{});
-        for (; t0 < keep_pad; t0 += RPI) gather(t0, std::integral_constant<int, 1>{});
+        });
     }
     if (live) sink[(size_t)r * kWave + lane] = acc;
 }
@@ -471,7 +238,7 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
     // the group's key list once into LDS, clamped into [0, L) (no idx can send a gather outside K / V)
     // and padded with its last entry
     for (int t = lane; t < keep_pad; t += kWave) sl[t] = min(max(list[min(t, keep - 1)], 0), L - 1);
-    wave_lds_fence();
+    wave_lds_sync();
 
     // scores of all kept keys -> LDS.  The key rows of a step (32 keys) are gathered the way the value rows are below:
     // D / 8 neighbouring lanes fetch one row as 16-byte pieces (whole cache lines per row, which is what the vector memory
@@ -492,7 +259,7 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
 #pragma unroll
             for (int rr = 0; rr < VP; ++rr)
                 kring[rr] = *reinterpret_cast<const v4u *>(Kh + (size_t)sl[tn + rr * RPI + vrow] * D + vpiece * 8);
-            wave_lds_fence();
+            wave_lds_sync();
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 const int tile = t0 + 16 * half;
@@ -506,7 +273,7 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
                 for (int i = 0; i < 4; ++i) acc[i] *= scale;
                 if (c < 8) *reinterpret_cast<v4f *>(sS + c * keep_pad + tile + 4 * g) = acc;
             }
-            wave_lds_fence();       // the next step overwrites the tile
+            wave_lds_sync();       // the next step overwrites the tile
         }
         // the 8 rows of scores leave through LDS: consecutive lanes write consecutive entries of a row
         if (live) {
@@ -524,7 +291,7 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
         const float *src = Pin + ((size_t)n * L + u * 8 + r) * keep;
         for (int t = lane; t < keep_pad; t += kWave) sS[r * keep_pad + t] = t < keep ? src[t] : 0.f;
     }
-    wave_lds_fence();
+    wave_lds_sync();
 
     v4f o[CT];
 #pragma unroll
@@ -551,7 +318,7 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
             pa[i] = (__bf16)s0[i];
             pa[4 + i] = (__bf16)s1[i];
         }
-        wave_lds_fence();
+        wave_lds_sync();
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
             union { s16x4 half[2]; bf16x8 all; } vb;
@@ -559,7 +326,7 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
             vb.half[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(block + 16 * VROW + 32 * ct));
             o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, vb.all, o[ct], 0, 0, 0);
         }
-        wave_lds_fence();       // the next step overwrites the value tile
+        wave_lds_sync();       // the next step overwrites the value tile
     }
     // lane (c, g) holds O[query 4g+i][16 ct + c]
     if (live && g < 2) {
@@ -624,7 +391,7 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
         if (scale < 0.f) raw = Piece<uint16_t>::negate(raw);
         qop[s] = __builtin_bit_cast(bf16x8, raw);
     }
-    wave_lds_fence();
+    wave_lds_sync();
 
     // gathers: lane (r = lane / LPR, p = lane % LPR) takes piece p of list entries VP r .. VP r + VP - 1 of the step, which
     // are also the tile's rows: the entries come as one or two 16-byte reads
@@ -665,7 +432,7 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
         const int t1 = min(t0 + 32, keep_pad - 32);
         put(kring);
         gather(kring, Kh, t1);
-        wave_lds_fence();
+        wave_lds_sync();
         v4f s2[2];
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
@@ -675,7 +442,7 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
                 s2[half] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(key_piece(half, s), qop[s], s2[half], 0, 0, 0);
             }
         }
-        wave_lds_fence();
+        wave_lds_sync();
         put(vring);
         gather(vring, Vh, t1);
         float mx = fmaxf(s2[0][0], s2[1][0]);
@@ -717,7 +484,7 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
             lo[i] = (__bf16)fmaf(p[i], 1.00000012f, -__uint_as_float(cut[i]));
         }
         const bf16x8 hi = __builtin_bit_cast(bf16x8, v4u{cut[0] >> 16 | cut[1], cut[2] >> 16 | cut[3], cut[4] >> 16 | cut[5], cut[6] >> 16 | cut[7]});
-        wave_lds_fence();
+        wave_lds_sync();
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
             union { s16x4 half[2]; bf16x8 all; } vb;
@@ -726,7 +493,7 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
             o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, vb.all, o[ct], 0, 0, 0);
             o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, vb.all, o[ct], 0, 0, 0);
         }
-        wave_lds_fence();                  // the next step overwrites the tile
+        wave_lds_sync();                  // the next step overwrites the tile
     }
     z += __shfl_xor(z, 16, kWave);
     z += __shfl_xor(z, 32, kWave);

@@ -138,15 +138,15 @@ int predict_max_L() { return 32768; }
 size_t predict_workspace_bytes(const dsa_shape &) { return 0; }
 
 hipError_t launch_predict(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, void *,
-                          hipStream_t st)
+                          const AttendPtrs *attend, bool *attended, hipStream_t st)
 {
     switch (sh.k) {
-    case 16: return launch_split_k16(sh, Qt, Kt, idx, st);
-    case 32: return launch_split_k32(sh, Qt, Kt, idx, st);
-    case 48: return launch_split_k48(sh, Qt, Kt, idx, st);
-    case 64: return launch_split_k64(sh, Qt, Kt, idx, st);
-    case 128: return launch_split_k128(sh, Qt, Kt, idx, st);
-    default: return launch_split_any(sh, Qt, Kt, idx, st);
+    case 16: return launch_split_k16(sh, Qt, Kt, idx, attend, attended, st);
+    case 32: return launch_split_k32(sh, Qt, Kt, idx, attend, attended, st);
+    case 48: return launch_split_k48(sh, Qt, Kt, idx, attend, attended, st);
+    case 64: return launch_split_k64(sh, Qt, Kt, idx, attend, attended, st);
+    case 128: return launch_split_k128(sh, Qt, Kt, idx, attend, attended, st);
+    default: return launch_split_any(sh, Qt, Kt, idx, attend, attended, st);
     }
 }
 

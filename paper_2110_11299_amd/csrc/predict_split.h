@@ -21,6 +21,7 @@
 //              lanes per unit; the exact threshold is found by interpolation and bisection in turn, ties go to the lower key.
 //   emission   every lane turns its words into key indices at its place in the unit's row, in LDS; the rows leave as
 //              one contiguous block.
+//   attention  where it pays, over the lists while they are in LDS (row_attend.h).
 //
 // What bounds it: vector-ALU issue (half an operation per score in sweep 1, two in sweep 2, about 25 per candidate).
 // Splitting the keys rather than giving a wavefront whole units keeps the bitmaps in registers, needs a quarter of the
@@ -30,8 +31,11 @@
 #include "dsa_internal.h"
 #include "predict_api.h"
 #include "key_stream.h"
+#include "row_attend.h"
 
 #include <math.h>
+
+#include <algorithm>
 
 namespace dsa {
 namespace {
@@ -46,6 +50,15 @@ constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' b
 template <bool GROUP, int UT, int NWM> constexpr int band_slots() { return !GROUP && UT == 1 && NWM >= 4 ? 32 : 24; }
 constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
 
+// The attention that a workgroup goes on with, over the lists it has just made (see attend_here).
+enum AttendKind { kAttendBf16x64, kAttendBf16x128, kAttendF32x64, kAttendF32x128 };
+struct AttendArgs {
+    const void *Q, *K, *V;
+    float *O;
+    float scale;
+    int kind, pad;                      // list length rounded up to kRowPad
+};
+
 struct SplitArgs {
     const int8_t *Qt, *Kt;
     int32_t *idx;
@@ -55,10 +68,12 @@ struct SplitArgs {
     int target_l, target_h;             // buckets that reach tl / th
     int direct;                         // the rows do not fit LDS: indices go straight to memory
 };
+struct SplitAttendArgs : SplitArgs { AttendArgs attend; };
 
 // LDS of a workgroup, in bytes from the start (every part a multiple of 16).
 struct SplitLds {
     unsigned tot, q, hist, list, bytes;
+    unsigned attend;                                            // what the attention needs, behind the image of the rows
     __host__ __device__ SplitLds(int W, int UT, int NW, int k, bool group, int keep, bool direct, int slots)
     {
         const unsigned U = kTile * UT;
@@ -70,6 +85,7 @@ struct SplitLds {
         bytes = list + U * slots * 16 * 2;                      // [U][16 slots]
         const unsigned rows = hist + (direct ? 0 : (U * keep * 2 + 16 + 15) / 16 * 16);   // image of the index rows, last
         if (rows > bytes) bytes = rows;
+        attend = rows;
     }
 };
 
@@ -99,11 +115,44 @@ __device__ __forceinline__ int row_sum_above(int x)
     return s - x;
 }
 
+// Rows a wavefront attends to at a time: a gather of each is as good as another gather of one, and the steps between the gathers
+// overlap.  bf16 1, 2, 4 rows, k = 32: N = 16, L = 4096, keep = 205 211.7, 202.2, 210.4 us, keep = 410 323, 307, 356; fp32 (a
+// quarter of the sums per row) 2 and 4, k = 16: N = 512, L = 256, keep = 26 113.7 and 103.8, N = 128, L = 1024, keep = 102 256 and 249.
+template <typename T> constexpr int attend_rows_at_once() { return sizeof(T) == 2 ? 2 : 4; }
+
+// The rows of the workgroup's nu units.  image: the units' lists; lds: room for attend_rows_at_once() * pad words per wavefront.
+template <typename T, int D>
+__device__ __forceinline__ void attend_block(const AttendArgs &a, const uint16_t *image, unsigned *lds, int L, int keep, int vec, unsigned n, int u0, int nu)
+{
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), W = blockDim.x / kWave;
+    constexpr int NR = attend_rows_at_once<T>(), LPR = RowShape<T, D>::LPR, E = Piece<T>::N;
+    const size_t head = (size_t)n * L * D;
+    const T *Kh = static_cast<const T *>(a.K) + head, *Vh = static_cast<const T *>(a.V) + head, *Qh = static_cast<const T *>(a.Q) + head;
+    lds += wv * NR * a.pad;
+    const int total = nu * vec;
+    for (int p = wv; NR * p < total; p += W) {
+        typename Piece<T>::raw_t q[NR];
+        const uint16_t *list[NR];
+        float *out[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int j = min(NR * p + r, total - 1);          // (a row that is there twice is written twice)
+            const size_t row = (size_t)(u0 * vec + j) * D;
+            q[r] = Piece<T>::load(Qh + row + lane % LPR * E);
+            list[r] = image + (vec == 1 ? j : j / vec) * keep;
+            out[r] = a.O + head + row;
+        }
+        auto at = [&](int r, int t) { return (unsigned)list[r][t] * (unsigned)(D * sizeof(T)); };
+        attend_rows<T, D, NR>(Kh, Vh, q, at, lds, a.pad, keep, a.scale, out, lane);
+    }
+}
+
 // K: the projection dimension (16, 32, 48, 64, 128), or 0 for any other (up to 112, two contraction steps).
 // GROUP: units are groups of vec rows.  UT: tiles of 16 units per workgroup.  NB: buckets per lane and unit (32, or 16 if a
 // range has several groups).  NWM: most bitmap words per lane.
-template <int K, bool GROUP, int UT, int NB, int NWM>
-__global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitArgs a)
+// ATTEND: goes on with the attention (an instance of its own: the other one is up to 3 % faster without that code).
+template <int K, bool GROUP, int UT, int NB, int NWM, bool ATTEND>
+__global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::conditional_t<ATTEND, SplitAttendArgs, SplitArgs> a)
 {
     constexpr int R = K == 16 ? 4 : K == 32 ? 2 : 1;     // keys side by side in a matrix row = tiles per row operand
     constexpr int STEPS = K && K <= 64 ? 1 : 2;          // contraction steps of 64
@@ -700,6 +749,18 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(SplitA
             for (int i = 0; e + i < total; ++i) out[e + i] = v[i];
         }
     }
+
+    // ---- attention over the lists -------------------------------------------------------------------------------------
+    if constexpr (ATTEND) {
+        unsigned *room = reinterpret_cast<unsigned *>(lds + at.attend);     // behind the image: nobody else reads or writes there any more
+        const int vec = GROUP ? a.vec : 1;
+        switch (a.attend.kind) {
+        case kAttendBf16x64: attend_block<uint16_t, 64>(a.attend, image, room, L, keep, vec, n, u0, nu); break;
+        case kAttendBf16x128: attend_block<uint16_t, 128>(a.attend, image, room, L, keep, vec, n, u0, nu); break;
+        case kAttendF32x64: attend_block<float, 64>(a.attend, image, room, L, keep, vec, n, u0, nu); break;
+        case kAttendF32x128: attend_block<float, 128>(a.attend, image, room, L, keep, vec, n, u0, nu); break;
+        }
+    }
 }
 
 // ---- host side -----------------------------------------------------------------------------------------------------------
@@ -806,11 +867,34 @@ inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
     return p;
 }
 
+inline size_t attend_lds_bytes(const dsa_shape &sh, int W, int pad)
+{
+    return (size_t)W * (sh.dtype == DSA_F32 ? attend_rows_at_once<float>() : attend_rows_at_once<uint16_t>()) * pad * sizeof(unsigned);
+}
+
+// Whether the workgroups that make the lists attend over them too.  One launch less, lists that need not come back from memory,
+// and while some workgroups select (vector issue) others gather (L2): N = 16, L = 4096, keep = 205, bf16, k = 32 250 -> 214 us.
+// Both launches are better (times of two launches and of one):
+//   - if few workgroups have many bytes to gather, where the rows by themselves spread over more CUs.  Up to 16 KB per wavefront:
+//     N = 2, L = 128, keep = 13 11.8 and 11.3; 26 KB, N = 1, L = 512, keep = 51 12.1 and 12.8, fp32, N = 2, L = 256, keep = 26, 11.6
+//     and 12.4; 53 KB, fp32, d = 128, N = 4, L = 512, keep = 26, 12.6 and 14.1.  From 2048 wavefronts on: N = 16, L = 512, keep = 51
+//     16.6 and 15.3; fp32, groups of 8, N = 16, L = 2048, keep = 102 69.5 and 67.4, but with 1024, N = 64, L = 512, 29.0 and 38.8;
+//   - if a CU does not hold two workgroups: 16 wavefronts, N = 8, L = 16384, keep = 164 1063 and 1106, or long lists, L = 8192,
+//     keep = 1229, N = 2 281 and 294; keep = 614, L = 4096, N = 8 (three workgroups instead of four) 252 and 229.
+// Units of several rows in bf16 have a kernel of their own (attention_units_bf16).
+inline bool attend_here(const dsa_shape &sh, int W, int units, long long wgs, size_t lds)
+{
+    if (sh.vec > 1 && sh.dtype == DSA_BF16) return false;
+    if (W > 8 || lds > 80 * 1024) return false;
+    const long long work = ((long long)sh.keep * sh.d * (sh.dtype == DSA_F32 ? 4 : 2) + 1536) * ((units * sh.vec + W - 1) / W);
+    return wgs * W >= 2048 || work <= 16 * 1024;
+}
+
 template <int K, bool GROUP, int UT, int NB, int NWM>
 hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t *Qt, const int8_t *Kt, int32_t *idx,
-                          hipStream_t st)
+                          const AttendPtrs *attend, bool *attended, hipStream_t st)
 {
-    SplitArgs a{};
+    SplitAttendArgs a{};
     a.Qt = Qt; a.Kt = Kt; a.idx = idx;
     a.L = sh.L; a.k = sh.k; a.keep = sh.keep; a.vec = sh.vec;
     a.NW = p.NW;
@@ -818,33 +902,49 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
     a.target_l = p.target_l;
     a.target_h = p.target_h;
     a.direct = (size_t)kTile * UT * sh.keep * 2 > 128 * 1024;
-    const size_t lds = SplitLds(p.W, UT, p.NW, sh.k, GROUP, sh.keep, a.direct != 0, band_slots<GROUP, UT, NWM>()).bytes;
-    auto kern = predict_split<K, GROUP, UT, NB, NWM>;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds)) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)sh.B * sh.H * a.wgs_per_head), dim3(p.W * kWave), lds, st, a);
-    return hipGetLastError();
+    const SplitLds at(p.W, UT, p.NW, sh.k, GROUP, sh.keep, a.direct != 0, band_slots<GROUP, UT, NWM>());
+    size_t lds = at.bytes;
+    bool attends = false;
+    if (attend && !a.direct) {
+        const int pad = (sh.keep + kRowPad - 1) / kRowPad * kRowPad;
+        const size_t all = at.attend + attend_lds_bytes(sh, p.W, pad);
+        if (attend_here(sh, p.W, kTile * UT, (long long)sh.B * sh.H * a.wgs_per_head, std::max(lds, all))) {
+            lds = std::max(lds, all);
+            a.attend = AttendArgs{attend->Q, attend->K, attend->V, attend->O, sh.scale,
+                                  (sh.dtype == DSA_BF16 ? kAttendBf16x64 : kAttendF32x64) + (sh.d == 128), pad};
+            attends = *attended = true;
+        }
+    }
+    auto go = [&](auto kern, const auto &args) -> hipError_t {
+        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds)) return e;
+        hipLaunchKernelGGL(kern, dim3((unsigned)sh.B * sh.H * a.wgs_per_head), dim3(p.W * kWave), lds, st, args);
+        return hipGetLastError();
+    };
+    return attends ? go(predict_split<K, GROUP, UT, NB, NWM, true>, a) : go(predict_split<K, GROUP, UT, NB, NWM, false>, static_cast<const SplitArgs &>(a));
 }
 
 template <int K, bool GROUP>
-hipError_t launch_split_g(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st)
+hipError_t launch_split_g(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, const AttendPtrs *attend,
+                          bool *attended, hipStream_t st)
 {
     constexpr bool pairs = K == 64 || (K == 48 && !GROUP);
     const SplitPlan p = split_plan(sh, pairs);
     if constexpr (pairs) {
-        if (p.UT == 2 && p.NW <= 4) return launch_split_t<K, GROUP, 2, 16, 4>(sh, p, Qt, Kt, idx, st);
-        if (p.UT == 2) return launch_split_t<K, GROUP, 2, 16, 8>(sh, p, Qt, Kt, idx, st);
+        if (p.UT == 2 && p.NW <= 4) return launch_split_t<K, GROUP, 2, 16, 4>(sh, p, Qt, Kt, idx, attend, attended, st);
+        if (p.UT == 2) return launch_split_t<K, GROUP, 2, 16, 8>(sh, p, Qt, Kt, idx, attend, attended, st);
     }
-    if (p.NW == 1) return launch_split_t<K, GROUP, 1, 32, 1>(sh, p, Qt, Kt, idx, st);
-    if (p.NW <= 4) return launch_split_t<K, GROUP, 1, 32, 4>(sh, p, Qt, Kt, idx, st);
-    if (p.NW <= 8) return launch_split_t<K, GROUP, 1, 32, 8>(sh, p, Qt, Kt, idx, st);
-    return launch_split_t<K, GROUP, 1, 32, 16>(sh, p, Qt, Kt, idx, st);
+    if (p.NW == 1) return launch_split_t<K, GROUP, 1, 32, 1>(sh, p, Qt, Kt, idx, attend, attended, st);
+    if (p.NW <= 4) return launch_split_t<K, GROUP, 1, 32, 4>(sh, p, Qt, Kt, idx, attend, attended, st);
+    if (p.NW <= 8) return launch_split_t<K, GROUP, 1, 32, 8>(sh, p, Qt, Kt, idx, attend, attended, st);
+    return launch_split_t<K, GROUP, 1, 32, 16>(sh, p, Qt, Kt, idx, attend, attended, st);
 }
 
 template <int K>
-hipError_t launch_split_k(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st)
+hipError_t launch_split_k(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, const AttendPtrs *attend,
+                          bool *attended, hipStream_t st)
 {
-    if (sh.vec == 1) return launch_split_g<K, false>(sh, Qt, Kt, idx, st);
-    return launch_split_g<K, true>(sh, Qt, Kt, idx, st);
+    if (sh.vec == 1) return launch_split_g<K, false>(sh, Qt, Kt, idx, attend, attended, st);
+    return launch_split_g<K, true>(sh, Qt, Kt, idx, attend, attended, st);
 }
 
 }  // namespace

@@ -3,9 +3,10 @@
 
 namespace dsa {
 
-hipError_t launch_split_k128(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, hipStream_t st)
+hipError_t launch_split_k128(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx,
+                            const AttendPtrs *attend, bool *attended, hipStream_t st)
 {
-    return launch_split_k<128>(sh, Qt, Kt, idx, st);
+    return launch_split_k<128>(sh, Qt, Kt, idx, attend, attended, st);
 }
 
 }  // namespace dsa

@@ -1,0 +1,76 @@
+"""The forward call where the launch that makes the lists also attends over them, on both sides of the line where it does: list
+lengths around the gathers of the row loops (8, 4, 4 and 2 keys per load instruction for bf16 and fp32 at d = 64 and 128, four in
+flight), row counts that leave a workgroup with one unit, groups of rows.  The result has to be that of the two entry points one
+after the other, bit for bit, and the oracle's within the bounds that the other tests use."""
+import numpy as np
+import pytest
+
+import dsa_inputs as di
+
+pytestmark = pytest.mark.gpu
+TOL = {"f32": 1e-4, "bf16": 2e-2}
+
+
+@pytest.fixture(scope="module")
+def dsa():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("these tests need the MI355X: run them with -m gpu on the GPU box")
+    import paper_2110_11299_amd as pkg
+    pkg.binding.lib()
+    return pkg
+
+
+def forward(dsa, dtype, H, L, d, vec, k, keep, scale=0.125, change=None):
+    import torch
+    print(f"[forward] {dtype} H={H} L={L} d={d} vec={vec} k={k} keep={keep} scale={scale}", flush=True)
+    x = di.make_inputs(di.custom_config("fwd", B=1, H=H, L=L, d=d, dtype=dtype, rank=8, k=k, vec=vec, keep=keep, seed=L + keep))
+    qkv = [np.array(a) for a in (x.Q, x.K, x.V)]
+    if change:
+        change(qkv)
+    t, code = (torch.float32, dsa.DSA_F32) if dtype == "f32" else (torch.bfloat16, dsa.DSA_BF16)
+    sh = dsa.make_shape(1, H, L, d, k, keep, vec, code, scale)
+    dev = [torch.from_numpy(a).cuda().to(t) for a in qkv]
+    codes = [torch.from_numpy(a).cuda() for a in (x.Qt, x.Kt)]
+    O, idx = dsa.dsa_attention_fwd(sh, *dev, *codes)
+    idx2 = dsa.dsa_predict_mask(sh, *codes)
+    O2 = dsa.dsa_masked_attention(sh, *dev, idx2)
+    assert torch.equal(idx, idx2)
+    assert torch.equal(O.view(torch.int32), O2.view(torch.int32)) or torch.equal(torch.nan_to_num(O), torch.nan_to_num(O2))
+    return qkv, idx.cpu().numpy().reshape(-1, keep), O.cpu().numpy().reshape(-1, d)
+
+
+def check(dsa, oracle, dtype, H, L, d, vec, k, keep, scale=0.125):
+    qkv, idx, got = forward(dsa, dtype, H, L, d, vec, k, keep, scale)
+    want = oracle.masked_attention(*qkv, idx, scale, vec).reshape(-1, d)
+    assert np.abs(got - want).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("keep", [1, 2, 4, 5, 8, 9, 15, 16, 17, 24, 25, 32, 33, 47, 65, 97])
+def test_list_lengths(dsa, oracle, dtype, d, keep):
+    check(dsa, oracle, dtype, 80, 97, d, 1, 16, keep, scale=0.125 if keep % 2 else -0.125)
+
+
+# few workgroups and short or long lists; groups of rows in fp32; two tiles of units per workgroup; a list that leaves a CU one
+# workgroup; ranges of several groups with a ragged end
+@pytest.mark.parametrize("dtype,H,L,d,vec,k,keep", [
+    ("f32", 2, 256, 64, 1, 16, 4), ("f32", 2, 256, 64, 1, 16, 26), ("bf16", 1, 1000, 64, 1, 32, 10), ("bf16", 1, 1000, 64, 1, 32, 200),
+    ("f32", 130, 200, 64, 4, 32, 20), ("f32", 140, 136, 128, 8, 32, 14), ("f32", 2, 1000, 64, 8, 16, 100), ("bf16", 130, 200, 64, 8, 32, 20),
+    ("bf16", 4, 4100, 64, 1, 64, 60), ("bf16", 3, 4096, 64, 1, 32, 410), ("bf16", 2, 4096, 128, 1, 48, 1300), ("bf16", 16, 777, 128, 1, 96, 39),
+    ("f32", 20, 513, 128, 1, 128, 51), ("bf16", 2, 8200, 64, 1, 32, 82)])
+def test_shapes(dsa, oracle, dtype, H, L, d, vec, k, keep):
+    check(dsa, oracle, dtype, H, L, d, vec, k, keep)
+
+
+@pytest.mark.parametrize("d,keep", [(64, 24), (64, 28), (128, 22), (128, 30)])
+def test_infinite_value_at_the_end_of_a_list(dsa, oracle, d, keep):
+    """Lists that are a whole number of load instructions: no entry beyond the list makes NaN of an infinite value."""
+    def change(qkv):
+        qkv[2][0, :, -30:, 5] = np.inf
+    qkv, idx, got = forward(dsa, "f32", 80, 97, d, 1, 16, keep, change=change)
+    want = oracle.masked_attention(*qkv, idx, 0.125, 1).reshape(-1, d)
+    ok = np.isfinite(want)
+    assert 0 < (~ok).sum() < want.size and not np.isnan(want).any()
+    assert np.array_equal(got[~ok], want[~ok])
+    assert np.abs(got[ok] - want[ok]).max() <= TOL["f32"]
