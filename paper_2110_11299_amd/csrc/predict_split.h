@@ -31,7 +31,7 @@
 #include "dsa_internal.h"
 #include "predict_api.h"
 #include "key_stream.h"
-#include "row_attend.h"
+#include "unit_attend.h"
 
 #include <math.h>
 
@@ -51,7 +51,7 @@ template <bool GROUP, int UT, int NWM> constexpr int band_slots() { return !GROU
 constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
 
 // The attention that a workgroup goes on with, over the lists it has just made (see attend_here).
-enum AttendKind { kAttendBf16x64, kAttendBf16x128, kAttendF32x64, kAttendF32x128 };
+enum AttendKind { kAttendBf16x64, kAttendBf16x128, kAttendF32x64, kAttendF32x128, kAttendUnits64 };
 struct AttendArgs {
     const void *Q, *K, *V;
     float *O;
@@ -144,6 +144,21 @@ __device__ __forceinline__ void attend_block(const AttendArgs &a, const uint16_t
         }
         auto at = [&](int r, int t) { return (unsigned)list[r][t] * (unsigned)(D * sizeof(T)); };
         attend_rows<T, D, NR>(Kh, Vh, q, at, lds, a.pad, keep, a.scale, out, lane);
+    }
+}
+
+// The workgroup's nu units of vec rows, one at a time per wavefront.  lds: room for a tile and the list per wavefront.
+template <int D>
+__device__ __forceinline__ void attend_block_units(const AttendArgs &a, const uint16_t *image, char *lds, int L, int keep, int vec, unsigned n, int u0, int nu)
+{
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), W = blockDim.x / kWave;
+    const size_t head = (size_t)n * L * D;
+    const uint16_t *Q = static_cast<const uint16_t *>(a.Q), *K = static_cast<const uint16_t *>(a.K) + head, *V = static_cast<const uint16_t *>(a.V) + head;
+    for (int u = wv; u < nu; u += W) {
+        const size_t first = head + (size_t)(u0 + u) * vec * D;
+        attend_unit<D>(Q + first, K, V, [&](int t) { return (int)image[u * keep + t]; }, a.O + first, vec, keep, a.pad, a.scale,
+                       lds + wv * (unit_tile_bytes<D>() + a.pad * 4));
+        wave_lds_sync();                   // the next unit overwrites list and tile
     }
 }
 
@@ -754,12 +769,11 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     if constexpr (ATTEND) {
         unsigned *room = reinterpret_cast<unsigned *>(lds + at.attend);     // behind the image: nobody else reads or writes there any more
         const int vec = GROUP ? a.vec : 1;
-        switch (a.attend.kind) {
-        case kAttendBf16x64: attend_block<uint16_t, 64>(a.attend, image, room, L, keep, vec, n, u0, nu); break;
-        case kAttendBf16x128: attend_block<uint16_t, 128>(a.attend, image, room, L, keep, vec, n, u0, nu); break;
-        case kAttendF32x64: attend_block<float, 64>(a.attend, image, room, L, keep, vec, n, u0, nu); break;
-        case kAttendF32x128: attend_block<float, 128>(a.attend, image, room, L, keep, vec, n, u0, nu); break;
-        }
+        if (a.attend.kind == kAttendF32x64) attend_block<float, 64>(a.attend, image, room, L, keep, vec, n, u0, nu);
+        else if (a.attend.kind == kAttendF32x128) attend_block<float, 128>(a.attend, image, room, L, keep, vec, n, u0, nu);
+        else if constexpr (GROUP) attend_block_units<64>(a.attend, image, reinterpret_cast<char *>(room), L, keep, vec, n, u0, nu);
+        else if (a.attend.kind == kAttendBf16x64) attend_block<uint16_t, 64>(a.attend, image, room, L, keep, vec, n, u0, nu);
+        else attend_block<uint16_t, 128>(a.attend, image, room, L, keep, vec, n, u0, nu);
     }
 }
 
@@ -869,6 +883,7 @@ inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
 
 inline size_t attend_lds_bytes(const dsa_shape &sh, int W, int pad)
 {
+    if (sh.vec > 1 && sh.dtype == DSA_BF16) return (size_t)W * (unit_tile_bytes<64>() + pad * sizeof(unsigned));
     return (size_t)W * (sh.dtype == DSA_F32 ? attend_rows_at_once<float>() : attend_rows_at_once<uint16_t>()) * pad * sizeof(unsigned);
 }
 
@@ -881,13 +896,17 @@ inline size_t attend_lds_bytes(const dsa_shape &sh, int W, int pad)
 //     16.6 and 15.3; fp32, groups of 8, N = 16, L = 2048, keep = 102 69.5 and 67.4, but with 1024, N = 64, L = 512, 29.0 and 38.8;
 //   - if a CU does not hold two workgroups: 16 wavefronts, N = 8, L = 16384, keep = 164 1063 and 1106, or long lists, L = 8192,
 //     keep = 1229, N = 2 281 and 294; keep = 614, L = 4096, N = 8 (three workgroups instead of four) 252 and 229.
-// Units of several rows in bf16 have a kernel of their own (attention_units_bf16).
+// Units of several rows in bf16 (attention_units_bf16 by itself): from 2048 wavefronts on, at most four units to a wavefront.  k = 32,
+// groups of 4: N = 32, L = 512, keep = 51 (1024 wavefronts) 16.9 and 19.0 us, N = 128 36.1 and 32.6, N = 32, L = 2048, keep = 205 79.1
+// and 72.0; groups of 8: N = 16, L = 4096, keep = 205 54.6 and 48.1, N = 64, L = 2048, keep = 102 59.4 and 55.1, N = 4, L = 4096, keep = 82
+// (1024) 23.2 and 24.4.  Eight units: N = 512, L = 256, keep = 26, groups of 4, 54.7 and 60.7.  At d = 128 its registers do not fit.
 inline bool attend_here(const dsa_shape &sh, int W, int units, long long wgs, size_t lds)
 {
-    if (sh.vec > 1 && sh.dtype == DSA_BF16) return false;
+    const bool grouped = sh.vec > 1 && sh.dtype == DSA_BF16;
+    if (grouped && (sh.d != 64 || units > 4 * W)) return false;
     if (W > 8 || lds > 80 * 1024) return false;
     const long long work = ((long long)sh.keep * sh.d * (sh.dtype == DSA_F32 ? 4 : 2) + 1536) * ((units * sh.vec + W - 1) / W);
-    return wgs * W >= 2048 || work <= 16 * 1024;
+    return wgs * W >= 2048 || (!grouped && work <= 16 * 1024);
 }
 
 template <int K, bool GROUP, int UT, int NB, int NWM>
@@ -911,7 +930,7 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
         if (attend_here(sh, p.W, kTile * UT, (long long)sh.B * sh.H * a.wgs_per_head, std::max(lds, all))) {
             lds = std::max(lds, all);
             a.attend = AttendArgs{attend->Q, attend->K, attend->V, attend->O, sh.scale,
-                                  (sh.dtype == DSA_BF16 ? kAttendBf16x64 : kAttendF32x64) + (sh.d == 128), pad};
+                                  sh.dtype == DSA_F32 ? kAttendF32x64 + (sh.d == 128) : sh.vec > 1 ? (int)kAttendUnits64 : kAttendBf16x64 + (sh.d == 128), pad};
             attends = *attended = true;
         }
     }

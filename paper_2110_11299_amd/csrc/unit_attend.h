@@ -1,0 +1,203 @@
+// Exact attention of a unit of 8 or 4 query rows that share one list of kept keys (paper section 5.1), by one 64-lane wavefront
+// on the bf16 matrix cores.  What attention_units_bf16 and the predictor that goes on to attend share.
+// Device code only; everything is internal to the translation unit that includes it.
+#pragma once
+
+#include "row_attend.h"
+
+namespace dsa {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// A unit of vec rows (8 or 4) with bfloat16 inputs by one wavefront, in one pass over the unit's keys: key and value rows of a step of 32 keys are gathered together, one step ahead, and pass through one tile in LDS, the
+// keys first.  Scores as in attention_groups_bf16, but they stay in the lane that owns them (query c, keys 4g..4g+3 of both
+// tiles), which is where the second product wants its weights: neither scores nor weights pass through LDS.  The
+// exponentials are taken relative to a running reference that is moved only when a score exceeds it by a factor of
+// 2^kUnitSlack, so that a step needs no reduction across lanes.
+// Every list length fits (4 bytes per key and wavefront; 96 KB of LDS with 4096 keys at D = 128).
+//
+// What bounds it: LDS (145 cycles per step and wavefront, two thirds of them the writes of the gathered rows; active 69 % of
+// the time at N = 64, L = 2000, keep = 200, VEC = 4), next to it the latency of list -> gather -> tile for short lists.
+// Measured (kernel alone): that shape 213 -> 94 us against one row per wavefront (attention_rows), which gathers the four
+// times 3.3 GB; VEC = 8, N = 16, L = 4096, keep = 205: 44.7 -> 29 us, N = 64, L = 2048, keep = 102: 51 -> 35 us, D = 128,
+// N = 16, L = 8192, keep = 82: 72.6 -> 55 us against two passes with the scores in LDS.  A key and a value tile side by side
+// cost occupancy at D = 128 (59 us); rows padded to 16 bytes more instead of swizzled: 96 us at the first shape.
+// The error against 64 bits (two-norm): L = 4096, keep = 205, VEC = 8 4.5e-6, L = 2000, keep = 200, VEC = 4 4.3e-6, D = 128,
+// L = 8192, keep = 82, VEC = 8 4.0e-6; 3.7e-4 to 4.2e-4 there with weights of one bf16.
+constexpr float kUnitSlack = 16.f;
+
+// Where the 16-byte pieces of tile row r are: piece p at p ^ unit_swizzle(r).  Eight rows of one piece (the score operand)
+// and four rows of two neighbouring pieces (a transposing read) both fall on different banks.
+__device__ __forceinline__ unsigned unit_swizzle(unsigned r) { return (r & 3u) << 1 | (r >> 2 & 1u); }
+
+template <int D> constexpr int unit_tile_bytes() { return 32 * 2 * D; }        // key rows, then value rows
+
+// The unit from its list (key(t): entry t) to its rows of O (both Q and O from the unit's first row on), with a reference that may lag the maximum by a factor of 2^slack.  Returns whether
+// every sum was finite.
+template <int D, typename Key>
+__device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, const uint16_t *V, Key &&key, float *O, int vec,
+                                          int keep, int keep_pad, float scale, int lane, char *tile, float slack)
+{
+    constexpr int KS = D / 32, CT = D / 16;
+    constexpr int ROW = D * 2;             // bytes of a row in LDS
+    constexpr int LPR = D / 8, RPI = kWave / LPR, VP = 32 / RPI;
+    const int c = lane & 15, g = lane >> 4;
+    unsigned *sl = reinterpret_cast<unsigned *>(tile + unit_tile_bytes<D>());        // [keep_pad] byte offsets of the rows
+
+    const char *Kh = reinterpret_cast<const char *>(K), *Vh = reinterpret_cast<const char *>(V);
+    for (int t = lane; t < keep_pad; t += kWave) sl[t] = (unsigned)key(min(t, keep - 1)) * (D * 2u);
+
+    // the sign of the scale goes into the query rows, its size into the exponential
+    const float factor = fabsf(scale) * 1.44269504088896340736f;
+    bf16x8 qop[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+        uint4 raw = make_uint4(0, 0, 0, 0);
+        if (c < vec) raw = *reinterpret_cast<const uint4 *>(Q + c * D + 32 * s + 8 * g);
+        if (scale < 0.f) raw = Piece<uint16_t>::negate(raw);
+        qop[s] = __builtin_bit_cast(bf16x8, raw);
+    }
+    wave_lds_sync();
+
+    // gathers: lane (r = lane / LPR, p = lane % LPR) takes piece p of list entries VP r .. VP r + VP - 1 of the step, which
+    // are also the tile's rows: the entries come as one or two 16-byte reads
+    const int first = lane / LPR * VP;
+    const unsigned piece = lane % LPR;
+    v4u kring[VP], vring[VP];
+    auto gather = [&](v4u (&ring)[VP], const char *head, int t0) {
+#pragma unroll
+        for (int r = 0; r < VP; r += 4) {
+            const v4u at = *reinterpret_cast<const v4u *>(sl + t0 + first + r);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ring[r + i] = *reinterpret_cast<const v4u *>(head + (at[i] + 16u * piece));
+        }
+    };
+    auto put = [&](const v4u (&ring)[VP]) {
+#pragma unroll
+        for (int r = 0; r < VP; ++r)
+            *reinterpret_cast<v4u *>(tile + (first + r) * ROW + 16u * (piece ^ unit_swizzle(first + r))) = ring[r];
+    };
+    // operands: row c (and 16 + c) of the key rows; of the value rows, the 4 x 4 block that ds_read_tr16_b64 takes from a lane
+    const unsigned vrow = 4 * g + (c >> 2), vswz = unit_swizzle(vrow);       // the same for row 16 + vrow
+    auto key_piece = [&](int half, int s) {
+        return *reinterpret_cast<const bf16x8 *>(tile + (16 * half + c) * ROW + 16u * ((4 * s + g) ^ unit_swizzle(c)));
+    };
+    auto value_block = [&](int half, int ct) {
+        return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (lds_s16x4 *)(tile + (16 * half + vrow) * ROW + 16u * ((2 * ct + (c >> 1 & 1)) ^ vswz) + 8 * (c & 1)));
+    };
+
+    v4f o[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) o[ct] = v4f{0.f, 0.f, 0.f, 0.f};
+    float m = -INFINITY, z = 0.f;
+    const float share = 1.f / (float)(keep_pad - keep + 1);      // the list is filled up with copies of its last key
+    gather(kring, Kh, 0);
+    gather(vring, Vh, 0);
+    for (int t0 = 0; t0 < keep_pad; t0 += 32) {
+        const int t1 = min(t0 + 32, keep_pad - 32);
+        put(kring);
+        gather(kring, Kh, t1);
+        wave_lds_sync();
+        v4f s2[2];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            s2[half] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                s2[half] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(key_piece(half, s), qop[s], s2[half], 0, 0, 0);
+            }
+        }
+        wave_lds_sync();
+        put(vring);
+        gather(vring, Vh, t1);
+        float mx = fmaxf(s2[0][0], s2[1][0]);
+#pragma unroll
+        for (int i = 1; i < 4; ++i) mx = fmaxf(fmaxf(s2[0][i], s2[1][i]), mx);
+        // (compared with >: nothing moves for scores that are not numbers, they reach the sums by themselves)
+        if (__ballot(m == -INFINITY ? mx > -INFINITY : (mx - m) * factor > slack) != 0) {
+            mx = fmaxf(mx, __shfl_xor(mx, 16, kWave));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, kWave));
+            const float to = fmaxf(m, mx);
+            const float f = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - to) * factor);
+            m = to;
+            z *= f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float fi = __shfl(f, 4 * g + i, kWave);          // lane (query, 0): the sums of query 4 g + i
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) o[ct][i] *= fi;
+            }
+        }
+        const float m0 = m == -INFINITY ? 0.f : m;
+        float p[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f((s2[i / 4][i % 4] - m0) * factor);
+        if (t0 + 32 > keep) {              // the copies of the last key share its weight: 0 would make NaN of an infinite value
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (t0 + 16 * (i / 4) + 4 * g + i % 4 >= keep - 1) p[i] *= share;
+        }
+        // A weight is the sum of two bf16 (relative 2^-16): one alone would be rounded at 2^-8, the largest one too, whose
+        // weight is not 1 here.  hi is p cut off, and lo is not zero where p is not (the factor is 1 + 2^-23), so that both
+        // products with an infinite value have its sign.
+        unsigned cut[8];
+        bf16x8 lo;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            z += p[i];
+            cut[i] = __float_as_uint(p[i]) & 0xffff0000u;
+            lo[i] = (__bf16)fmaf(p[i], 1.00000012f, -__uint_as_float(cut[i]));
+        }
+        const bf16x8 hi = __builtin_bit_cast(bf16x8, v4u{cut[0] >> 16 | cut[1], cut[2] >> 16 | cut[3], cut[4] >> 16 | cut[5], cut[6] >> 16 | cut[7]});
+        wave_lds_sync();
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            union { s16x4 half[2]; bf16x8 all; } vb;
+            vb.half[0] = value_block(0, ct);
+            vb.half[1] = value_block(1, ct);
+            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, vb.all, o[ct], 0, 0, 0);
+            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, vb.all, o[ct], 0, 0, 0);
+        }
+        wave_lds_sync();                  // the next step overwrites the tile
+    }
+    z += __shfl_xor(z, 16, kWave);
+    z += __shfl_xor(z, 32, kWave);
+    // lane (c, g) holds O[query 4g+i][16 ct + c]; the sum of query q sits in the lanes with column q
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float inv = 1.f / __shfl(z, 4 * g + i, kWave);
+        if (4 * g + i < vec) {
+            float *out = O + (4 * g + i) * D + c;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) out[16 * ct] = o[ct][i] * inv;
+        }
+    }
+    float odd = 0.f;                       // NaN if a sum is not finite
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) odd = fmaf(o[ct][i], 0.f, odd);
+    return __ballot(odd != 0.f) == 0;
+}
+
+// Weights above 1 may take large values beyond fp32 (from 2^111 / keep on) that weights of at most 1 would not: then once
+// more with a reference that is the maximum.  (That from the start costs up to 13 % of the kernel.)
+template <int D, typename Key>
+__device__ __forceinline__ void attend_unit(const uint16_t *Q, const uint16_t *K, const uint16_t *V, Key &&key, float *O, int vec,
+                                            int keep, int keep_pad, float scale, char *tile)
+{
+    for (float slack = kUnitSlack;; slack = 0.f) {
+        int lane = threadIdx.x & (kWave - 1);
+        asm volatile("" : "+v"(lane));     // nothing of a round is computed ahead of the loop: that would delay the first gathers
+        if (unit_rows<D>(Q, K, V, key, O, vec, keep, keep_pad, scale, lane, tile, slack) || slack == 0.f) break;
+    }
+}
+
+}  // namespace
+}  // namespace dsa

@@ -57,10 +57,22 @@ def test_list_lengths(dsa, oracle, dtype, d, keep):
 @pytest.mark.parametrize("dtype,H,L,d,vec,k,keep", [
     ("f32", 2, 256, 64, 1, 16, 4), ("f32", 2, 256, 64, 1, 16, 26), ("bf16", 1, 1000, 64, 1, 32, 10), ("bf16", 1, 1000, 64, 1, 32, 200),
     ("f32", 130, 200, 64, 4, 32, 20), ("f32", 140, 136, 128, 8, 32, 14), ("f32", 2, 1000, 64, 8, 16, 100), ("bf16", 130, 200, 64, 8, 32, 20),
+    ("bf16", 130, 520, 64, 4, 32, 52), ("bf16", 140, 264, 64, 8, 16, 33), ("bf16", 17, 4104, 64, 8, 64, 205), ("bf16", 9, 8200, 64, 8, 64, 410),
     ("bf16", 4, 4100, 64, 1, 64, 60), ("bf16", 3, 4096, 64, 1, 32, 410), ("bf16", 2, 4096, 128, 1, 48, 1300), ("bf16", 16, 777, 128, 1, 96, 39),
     ("f32", 20, 513, 128, 1, 128, 51), ("bf16", 2, 8200, 64, 1, 32, 82)])
 def test_shapes(dsa, oracle, dtype, H, L, d, vec, k, keep):
     check(dsa, oracle, dtype, H, L, d, vec, k, keep)
+
+
+@pytest.mark.parametrize("vec", [4, 8])
+def test_large_values_in_groups(dsa, oracle, vec):
+    """Units whose sums leave fp32 on the first round (weights of up to 2^16, values of 2^118): done again within the same launch."""
+    def change(qkv):
+        qkv[0][...] *= 8.0
+        qkv[2][...] = np.where(qkv[2] > 0, 2.0 ** 119, 2.0 ** 118)
+    qkv, idx, got = forward(dsa, "bf16", 130, 520, 64, vec, 32, 75, scale=1.0, change=change)
+    want = oracle.masked_attention(*qkv, idx, 1.0, vec).reshape(-1, 64)
+    assert np.abs(got / want - 1.0).max() <= 2.0 ** -12      # weights 2^-16; scores of up to 2^9 in fp32 on either side
 
 
 @pytest.mark.parametrize("d,keep", [(64, 24), (64, 28), (128, 22), (128, 30)])
