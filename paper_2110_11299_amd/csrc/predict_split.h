@@ -358,7 +358,10 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     // ---- bounds -------------------------------------------------------------------------------------------------------
     // The histogram's range is [smallest maximum, it + 3 * (mean - it)]: high-norm keys put a few maxima far above the
     // others and would otherwise stretch the bins; they go to the last one.
-    const bool full = nv_all == Lr;               // every bucket of the wavefront holds a key
+    // The first group (or the first two, if the parity tells buckets apart) puts a key into every bucket.  In a wavefront where that
+    // fails for a range an empty bucket counts in a bin beyond the others; one beyond L has nothing to count.  (A branch per bucket
+    // instead took the bounds of such a wavefront, for which the others wait, from 6 k to 12 k cycles of 48 k.)
+    const bool full = nv_all >= min(Lr, NWM > 1 && NB == 32 ? 64 : 32), none = 4 * wv * Lr >= L;
     {
         float *s_sum = reinterpret_cast<float *>(s_toth);
 #pragma unroll
@@ -370,7 +373,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                     mn = min(mn, bm[t][b]);
                     all += bm[t][b];
                 }
-            } else {
+            } else if (!none) {
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     const bool real = bm[t][b] != INT32_MIN;
@@ -403,14 +406,13 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             const float range = fminf(fmaxf(3.f * (sum / per_bucket - (float)mn), 1.f), 1.0e9f);
             const int shift = max(0, 25 - (int)__clz((int)((unsigned)range | 1u)));     // range >> shift < kBins
             unsigned *uh = hist + (kTile * t + c) * kBinStride;
-            auto count = [&](int x) { atomicAdd(&uh[min((unsigned)(x - mn) >> shift, (unsigned)(kBins - 1))], 1u); };
+            auto bin = [&](int x) { return min((unsigned)(x - mn) >> shift, (unsigned)(kBins - 1)); };
             if (full) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b) count(bm[t][b]);
-            } else {
+                for (int b = 0; b < NB; ++b) atomicAdd(&uh[bin(bm[t][b])], 1u);
+            } else if (!none) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    if (bm[t][b] != INT32_MIN) count(bm[t][b]);
+                for (int b = 0; b < NB; ++b) atomicAdd(&uh[bm[t][b] != INT32_MIN ? bin(bm[t][b]) : (unsigned)kBins], 1u);
             }
             if (wv == 0 && g == 0) {
                 s_tl[kTile * t + c] = mn;
@@ -645,12 +647,12 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             }
         }
         // The need-th largest of the band: all its scores are >= tl and at least need of them exist.  The interval is cut
-        // where it would be cut for evenly spread scores and in the middle in turn, until a cut leaves exactly need.
+        // where it would be cut for evenly spread scores, every third time in the middle, until a cut leaves exactly need.
         int lo_ = ulo, hi_ = nb ? max(row_max(peak), ulo) : ulo, cnt_lo = nb, cnt_hi = 0;   // counts >= lo_ and > hi_
-        for (bool even = true; __ballot(lo_ < hi_) != 0; even = !even) {
+        for (int cut = 0; __ballot(lo_ < hi_) != 0; cut = cut == 2 ? 0 : cut + 1) {
             const int width = hi_ - lo_;                  // |scores| < 2^27
             int step = (width + 1) >> 1;
-            if (even)
+            if (cut < 2)
                 step = min(max((int)((float)width * (float)(cnt_lo - need) * __builtin_amdgcn_rcpf((float)(cnt_lo - cnt_hi))), 1), width);
             const int mid = lo_ + step;
             int cnt = 0;
@@ -670,6 +672,21 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             }
         }
         const int Tx = lo_;
+        auto keep_key = [&](int i) {
+            const unsigned code = ul[c + 16 * i], hh = code >> kPosBits, pos = code & ((1u << kPosBits) - 1);
+            const unsigned thread = (hh >> 2) * kWave + (hh & 3) * 16 + (u & 15);
+            atomicOr(&sel[((u >> 4) * NW + (pos >> 5)) * T + thread], 1u << (pos & 31));
+        };
+        if (__ballot(nb && cnt_lo != need) == 0) {        // no tie at the threshold is left out: no order among them
+#pragma unroll
+            for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
+                if (16 * i0 >= most) break;
+#pragma unroll
+                for (int i = i0; i < i0 + 4; ++i)
+                    if (sc[i] >= Tx) keep_key(i);
+            }
+            continue;
+        }
         int gt = 0;
 #pragma unroll
         for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
@@ -687,11 +704,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             const unsigned meq = (unsigned)(__ballot(eq) >> (16 * g)) & 0xffffu;
             const bool take = c + 16 * i < nb && (sc[i] > Tx || (eq && eq_before + __popc(meq & below) < need_eq));
             eq_before += __popc(meq);
-            if (take) {
-                const unsigned code = ul[c + 16 * i], hh = code >> kPosBits, pos = code & ((1u << kPosBits) - 1);
-                const unsigned thread = (hh >> 2) * kWave + (hh & 3) * 16 + (u & 15);
-                atomicOr(&sel[((u >> 4) * NW + (pos >> 5)) * T + thread], 1u << (pos & 31));
-            }
+            if (take) keep_key(i);
         }
     }
     __syncthreads();
