@@ -229,26 +229,29 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
 
     // ---- key rows: lane (r = lane % 16, kb = lane / 16) fetches 16 bytes of matrix row r ---------------------------
     const int sub = R == 4 ? g : R == 2 ? g >> 1 : 0, part = R == 4 ? 0 : R == 2 ? g & 1 : g;
-    int poff[STEPS];
+    // (buffer loads: the batch is a scalar offset, the row operand an immediate one, and rows beyond L read zeros without a test)
+    unsigned poff[STEPS], voff[STEPS];
     bool plive[STEPS];
+    const bool crossed = CROSS && (c & 1);
+    const unsigned row0 = (unsigned)((4 * wv + (c >> 2)) * Lr + 4 * sub + (c & 3)) * (unsigned)k;
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
         plive[s] = 64 * s + 16 * part < k;
         poff[s] = plive[s] ? 64 * s + 16 * part : 0;
     }
-    const bool crossed = CROSS && (c & 1);
-    unsigned row0 = (unsigned)((4 * wv + (c >> 2)) * Lr + 4 * sub + (c & 3)) * (unsigned)k;
-    const unsigned row_last = (unsigned)(L - 1) * (unsigned)k;
-    const unsigned slot_step = 4u * R * (unsigned)k;
-    const int batches = NW * BPG;
-    auto request = [&](v4i (&dst)[NSB][STEPS], int b) {          // rows beyond L (and batches beyond the range) read real ones
-        const unsigned first = row0 + (unsigned)(min(b, batches - 1) * NSB) * slot_step;
 #pragma unroll
-        for (int sl = 0; sl < NSB; ++sl) {
-            const unsigned row = min(first + sl * slot_step, row_last);
+    for (int s = 0; s < STEPS; ++s) voff[s] = row0 + poff[crossed ? STEPS - 1 - s : s];
+    const __amdgpu_buffer_rsrc_t keys = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(Kh), 0, L * k, 0x00020000);
+    const int slot_step = 4 * R * k, batches = NW * BPG;
+    auto request = [&](v4i (&dst)[NSB][STEPS], int b) {          // batches beyond the range read its last one
+        const int first = __builtin_amdgcn_readfirstlane(min(b, batches - 1) * NSB * slot_step);
 #pragma unroll
-            for (int s = 0; s < STEPS; ++s) dst[sl][s] = *reinterpret_cast<const v4i *>(Kh + row + poff[crossed ? STEPS - 1 - s : s]);
-        }
+        for (int sl = 0; sl < NSB; ++sl)
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s)
+                dst[sl][s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(keys, K ? voff[s] + sl * slot_step : voff[s],
+                                                                                          K ? first : first + sl * slot_step, 0));
+        __builtin_amdgcn_sched_barrier(0);       // the requests stay ahead of the batch that is used next
     };
     v4i rows[2][NSB][STEPS];
     request(rows[0], 0);
@@ -329,13 +332,12 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                 }
     };
     {
-        auto group = [&](int w, auto par) {
+        auto group = [&](int w, auto par, auto masked) {
             constexpr int PAR = decltype(par)::value;
             auto batch = [&](auto half) {
                 constexpr int HB = decltype(half)::value, P = BPG == 1 ? PAR : HB & 1;
                 request(rows[P ^ 1], w * BPG + HB + 1);
-                if (32 * (w + 1) <= nv_all) maxima(rows[P], w, par, half, std::false_type{});
-                else maxima(rows[P], w, par, half, std::true_type{});
+                maxima(rows[P], w, par, half, masked);
             };
             batch(std::integral_constant<int, 0>{});
             if constexpr (BPG >= 2) batch(std::integral_constant<int, 1>{});
@@ -344,12 +346,22 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                 batch(std::integral_constant<int, 3>{});
             }
         };
+        const std::integral_constant<int, 0> even{};
+        const std::integral_constant<int, 1> odd{};
         if (NWM == 1) {
-            group(0, std::integral_constant<int, 0>{});
+            if (nv_all >= 32) group(0, even, std::false_type{});
+            else group(0, even, std::true_type{});
         } else {
-            for (int w = 0; w < NW; w += 2) {
-                group(w, std::integral_constant<int, 0>{});
-                if (w + 1 < NW) group(w + 1, std::integral_constant<int, 1>{});
+            // (one loop without and one with the test for real keys: with both in one body the buckets changed registers, 32 moves for
+            // every 48 instructions that do something)
+            int w = 0;
+            for (; 32 * (w + 2) <= nv_all; w += 2) {
+                group(w, even, std::false_type{});
+                group(w + 1, odd, std::false_type{});
+            }
+            for (; w < NW; w += 2) {
+                group(w, even, std::true_type{});
+                if (w + 1 < NW) group(w + 1, odd, std::true_type{});
             }
         }
     }
@@ -465,9 +477,9 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
         int cl[UT], ch[UT];
 #pragma unroll
         for (int t = 0; t < UT; ++t) cl[t] = ch[t] = 0;
-        // the sweep's addresses and masks are the same in every round: computed ahead for all words they would fill the
-        // registers, so the compiler is kept from seeing it
-        asm volatile("" : "+v"(row0), "+v"(nv));
+        // the sweep's masks are the same in every round: computed ahead for all words they would fill the registers, so the
+        // compiler is kept from seeing it
+        asm volatile("" : "+v"(nv));
 #pragma unroll
         for (int w = 0; w < NWM; ++w) {
             if (w < NW) {
@@ -494,12 +506,22 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                             if (j % 2 == 1) __builtin_amdgcn_sched_barrier(0);      // else every tile's scores live at once
                         }
                 }
-                const int left = nv - 32 * w;                            // real keys of this word
-                const unsigned real = left >= 32 ? ~0u : left <= 0 ? 0u : (1u << left) - 1u;
 #pragma unroll
                 for (int t = 0; t < UT; ++t) {
-                    wl[t][w] = ~__brev(wl[t][w]) & real;                 // the first key of the word was shifted in first
-                    wh[t][w] = ~__brev(wh[t][w]) & real;
+                    wl[t][w] = ~__brev(wl[t][w]);                        // the first key of the word was shifted in first
+                    wh[t][w] = ~__brev(wh[t][w]);
+                }
+                if (32 * (w + 1) > nv_all) {
+                    const int left = nv - 32 * w;                        // real keys of this word
+                    const unsigned real = left >= 32 ? ~0u : left <= 0 ? 0u : (1u << left) - 1u;
+#pragma unroll
+                    for (int t = 0; t < UT; ++t) {
+                        wl[t][w] &= real;
+                        wh[t][w] &= real;
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < UT; ++t) {
                     cl[t] += __popc(wl[t][w]);
                     ch[t] += __popc(wh[t][w]);
                 }
@@ -573,9 +595,8 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             if (w < NW) {
                 unsigned m = scored[t] ? wl[t][w] & ~wh[t][w] : 0u;
                 const int code1 = (h << kPosBits) + 32 * w - 1;
-                while (__ballot(m != 0u) != 0) {
-                    if (m) ul[pos] = (uint16_t)(code1 + __ffs(m));       // pos < nl - nh <= kBandCap
-                    pos += m != 0u;
+                while (m) {
+                    ul[pos++] = (uint16_t)(code1 + __ffs(m));            // pos < nl - nh <= kBandCap
                     m &= m - 1u;
                 }
             }
@@ -734,7 +755,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
         if (g == 0) s_totl[wv * U + kTile * t + c] = all;
     }
     __syncthreads();
-    uint16_t *image = reinterpret_cast<uint16_t *>(lds + at.hist);      // [U * keep] and a spare slot; everything there is dead
+    uint16_t *image = reinterpret_cast<uint16_t *>(lds + at.hist);      // [U * keep]; everything there is dead
     int32_t *out = a.idx + ((size_t)n * G + u0) * keep;
 #pragma unroll
     for (int t = 0; t < UT; ++t) {
@@ -748,13 +769,9 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                 unsigned m = live ? wl[t][w] : 0u;
                 const int key1 = h * Lr + 32 * w - 1;
                 if (!a.direct) {
-                    while (__ballot(m != 0u) != 0) {
-#pragma unroll
-                        for (int twice = 0; twice < 2; ++twice) {
-                            image[m != 0u ? pos : U * keep] = (uint16_t)(key1 + __ffs(m));
-                            pos += m != 0u;
-                            m &= m - 1u;
-                        }
+                    while (m) {
+                        image[pos++] = (uint16_t)(key1 + __ffs(m));
+                        m &= m - 1u;
                     }
                 } else {
                     while (m) {
