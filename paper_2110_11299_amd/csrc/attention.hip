@@ -71,31 +71,28 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
 // raises the maximum, the sums so far are rescaled by exp(m_old - m_new).  4 KB of LDS per row leave room for eight rows
 // per SIMD, and most lists are one chunk.  N = 16, L = 2048, about 102 keys a row: 91 -> 54 us against tests per key,
 // a conversion per weight and gather, and 8 KB per row.
+// One wavefront per workgroup: with four, their places wait for the longest of four lists (a call with 105 keys a row on average,
+// standard deviation 83: 72.9 and 70.2 us).
 // The weights are summed in fp32 as they are made; only the products take them rounded, if T is bfloat16.
 constexpr int kCsrChunk = 512;
 static_assert(kCsrChunk % kRowPad == 0, "a full chunk needs no padding");
 
 template <typename T, int D>
-__global__ __launch_bounds__(kRowWaves *kWave) void attention_rows_csr(
+__global__ __launch_bounds__(kWave) void attention_rows_csr(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
-    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col, float *__restrict__ O, int L, int vec,
-    float scale, unsigned total_rows)
+    const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col, float *__restrict__ O, int L, int vec, float scale)
 {
     typedef Piece<T> P;
     constexpr int E = P::N;
     constexpr unsigned kRowBytes = D * sizeof(T);
-    __shared__ unsigned lists[kRowWaves][kCsrChunk];
-    __shared__ unsigned weights[kRowWaves][kCsrChunk];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    __shared__ unsigned sl[kCsrChunk], sw[kCsrChunk];      // the list; scores, then weights
+    const int lane = threadIdx.x;
     const int sub = lane % RowShape<T, D>::LPR;
-    const unsigned row = xcd_contiguous(blockIdx.x, gridDim.x) * kRowWaves + wave;
-    if (row >= total_rows) return;                        // the whole wavefront: nothing below is shared
+    const unsigned row = xcd_contiguous(blockIdx.x, gridDim.x);
     const unsigned n = row / (unsigned)L, i = row % (unsigned)L;
     const size_t u = (size_t)n * (L / vec) + i / vec;
     const int beg = row_ptr[u];
     const int cnt = max(row_ptr[u + 1] - beg, 0);
-    unsigned *sl = lists[wave], *sw = weights[wave];      // (scores, then weights)
     // the scores are kept as sign(scale) * q.k and the factor |scale| waits for the exponential
     typename P::raw_t q[1] = {P::load(Q + (size_t)row * D + sub * E)};
     if (scale < 0.f) q[0] = P::negate(q[0]);
@@ -500,9 +497,8 @@ hipError_t launch_attention_csr(const dsa_shape &sh, const void *Q, const void *
                                 const int32_t *row_ptr, const int32_t *col, float *O, hipStream_t st)
 {
     const unsigned rows = (unsigned)sh.B * sh.H * sh.L;
-    const dim3 grid((rows + kRowWaves - 1) / kRowWaves), block(kRowWaves * kWave);
     auto go = [&](auto kern, auto *q, auto *k, auto *v) -> hipError_t {
-        hipLaunchKernelGGL(kern, grid, block, 0, st, q, k, v, row_ptr, col, O, sh.L, sh.vec, sh.scale, rows);
+        hipLaunchKernelGGL(kern, dim3(rows), dim3(kWave), 0, st, q, k, v, row_ptr, col, O, sh.L, sh.vec, sh.scale);
         return hipGetLastError();
     };
     if (sh.dtype == DSA_F32) {
