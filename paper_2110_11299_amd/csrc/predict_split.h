@@ -175,6 +175,12 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     // the L1 takes them one after the other.  Odd rows fetch their second half first, and the halves change places in front
     // of the matrix instruction.  L = 4096, keep = 41, N = 8: 251 -> 143 us (k = 112, whose rows spread by themselves: 111).
     constexpr bool CROSS = K == 128;
+    // Rows of 64 bytes: two of the four rows that neighbouring lanes read 16 bytes of lie at the same place of their cache lines.  In
+    // sweep 1, which waits for the L1, every other pair of rows is fetched with its halves exchanged and multiplied with the units'
+    // halves exchanged: a second matrix instruction per tile, which leaves the right scores in the registers of those rows.  (In
+    // sweep 2 vector and matrix instructions are the longer.)  N = 4, L = 16384: sweep 1 129 -> 84 us, a call 651 -> 615; N = 8, L = 8192,
+    // keep = 82, groups of 8 57.3 -> 54.0.  Two tiles of groups have no registers for it: N = 16, L = 8192, d = 128 120 and 130 us.
+    constexpr bool TWIST = K == 64 && !(GROUP && UT == 2);
     constexpr int NS = 8 / R;                            // row operands of a group of 8 tiles (32 keys per lane range)
     constexpr int NSB = STEPS == 2 ? 2 : NS < 4 ? NS : 4;    // row operands of one batch of requests (8 registers each if two steps)
     constexpr int BPG = NS / NSB;                        // batches per group
@@ -241,20 +247,23 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     }
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) voff[s] = row0 + poff[crossed ? STEPS - 1 - s : s];
+    unsigned twisted[STEPS];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) twisted[s] = TWIST && (c & 2) ? row0 + (poff[s] ^ 32u) : voff[s];
     const __amdgpu_buffer_rsrc_t keys = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(Kh), 0, L * k, 0x00020000);
     const int slot_step = 4 * R * k, batches = NW * BPG;
-    auto request = [&](v4i (&dst)[NSB][STEPS], int b) {          // batches beyond the range read its last one
+    auto request = [&](v4i (&dst)[NSB][STEPS], int b, const unsigned (&at)[STEPS]) {          // batches beyond the range read its last one
         const int first = __builtin_amdgcn_readfirstlane(min(b, batches - 1) * NSB * slot_step);
 #pragma unroll
         for (int sl = 0; sl < NSB; ++sl)
 #pragma unroll
             for (int s = 0; s < STEPS; ++s)
-                dst[sl][s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(keys, K ? voff[s] + sl * slot_step : voff[s],
+                dst[sl][s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(keys, K ? at[s] + sl * slot_step : at[s],
                                                                                           K ? first : first + sl * slot_step, 0));
         __builtin_amdgcn_sched_barrier(0);       // the requests stay ahead of the batch that is used next
     };
     v4i rows[2][NSB][STEPS];
-    request(rows[0], 0);
+    request(rows[0], 0, twisted);
     __syncthreads();
 
     // unit operands: 16 bytes of the unit's query side where this lane's part of the key row is, zero in the tiles of
@@ -271,6 +280,13 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                 for (int i = 0; i < R; ++i) q[t][p][i][s] = (sub == i && plive[s]) ? piece : v4i{0, 0, 0, 0};
             }
 
+    v4i qx[UT][PARTS];                                   // with the halves exchanged, for sweep 1
+#pragma unroll
+    for (int t = 0; t < UT; ++t)
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p)
+            if (TWIST) qx[t][p] = *reinterpret_cast<const v4i *>(s_q + (kTile * t + c) * qstride + p * (k + 16) + (poff[0] ^ 32u));
+
     // scores of tile j of the batch against the units of operand t, each plus b
     auto tile_scores = [&](const v4i (&buf)[NSB][STEPS], int j, int t, int b) -> v4i {
         v4i key[STEPS];
@@ -286,6 +302,18 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) top = __builtin_amdgcn_mfma_i32_16x16x64_i8(key[s], q[t][PARTS - 1][j % R][s], top, 0, 0, 0);
             acc += top << 7;
+        }
+        return acc;
+    };
+
+    // the same without b from rows that were fetched for sweep 1: registers 2 and 3 are the rows with exchanged halves
+    auto tile_scores1 = [&](const v4i (&buf)[NSB][STEPS], int j, int t) -> v4i {
+        v4i acc = tile_scores(buf, j, t, 0);
+        if constexpr (TWIST) {
+            v4i x = __builtin_amdgcn_mfma_i32_16x16x64_i8(buf[j / R][0], qx[t][0], v4i{0, 0, 0, 0}, 0, 0, 0);
+            if (GROUP) x += __builtin_amdgcn_mfma_i32_16x16x64_i8(buf[j / R][0], qx[t][PARTS - 1], v4i{0, 0, 0, 0}, 0, 0, 0) << 7;
+            acc[2] = x[2];
+            acc[3] = x[3];
         }
         return acc;
     };
@@ -310,7 +338,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
 #pragma unroll
                 for (int e = 0; e < PAIR; ++e) {
                     const int j = jb + e;
-                    v4i x = tile_scores(buf, j, t, 0), y = tile_scores(buf, j + PAIR, t, 0);
+                    v4i x = tile_scores1(buf, j, t), y = tile_scores1(buf, j + PAIR, t);
                     if (decltype(masked)::value) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
@@ -336,7 +364,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             constexpr int PAR = decltype(par)::value;
             auto batch = [&](auto half) {
                 constexpr int HB = decltype(half)::value, P = BPG == 1 ? PAR : HB & 1;
-                request(rows[P ^ 1], w * BPG + HB + 1);
+                request(rows[P ^ 1], w * BPG + HB + 1, twisted);
                 maxima(rows[P], w, par, half, masked);
             };
             batch(std::integral_constant<int, 0>{});
@@ -365,7 +393,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             }
         }
     }
-    request(rows[0], 0);         // sweep 2 starts with what is on its way during the bounds
+    request(rows[0], 0, voff);   // sweep 2 starts with what is on its way during the bounds
 
     // ---- bounds -------------------------------------------------------------------------------------------------------
     // The histogram's range is [smallest maximum, it + 3 * (mean - it)]: high-norm keys put a few maxima far above the
@@ -488,7 +516,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
 #pragma unroll
                 for (int hb = 0; hb < BPG; ++hb) {
                     const int P = BPG == 1 ? w & 1 : hb & 1;
-                    request(rows[P ^ 1], w * BPG + hb + 1);
+                    request(rows[P ^ 1], w * BPG + hb + 1, voff);
 #pragma unroll
                     for (int j = 0; j < TB; ++j)
 #pragma unroll
@@ -530,7 +558,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                 for (int t = 0; t < UT; ++t) wl[t][w] = wh[t][w] = 0u;
             }
         }
-        request(rows[0], 0);
+        request(rows[0], 0, voff);
 #pragma unroll
         for (int t = 0; t < UT; ++t) {
             // (count(>= tl) << 16 | count(>= th)) of the unit's ranges in this wavefront: at most 8192 each
