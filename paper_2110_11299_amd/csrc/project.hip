@@ -18,128 +18,144 @@ namespace {
 
 constexpr int kProjThreads = 256;
 
-// 16 bytes of a row widened to fp32.
+// 16 bytes of a row, and element i of them widened to fp32.
 template <typename T> struct Chunk;
 template <> struct Chunk<float> {
     static constexpr int N = 4;
-    static __device__ __forceinline__ void load(const float *p, float (&v)[4])
-    {
-        const float4 x = *reinterpret_cast<const float4 *>(p);
-        v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-    }
+    typedef float raw_t __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ float at(raw_t x, int i) { return x[i]; }
 };
 template <> struct Chunk<uint16_t> {
     static constexpr int N = 8;
-    static __device__ __forceinline__ void load(const uint16_t *p, float (&v)[8])
+    typedef unsigned raw_t __attribute__((ext_vector_type(4)));
+    static __device__ __forceinline__ float at(raw_t x, int i)
     {
-        const uint4 x = *reinterpret_cast<const uint4 *>(p);
-        const unsigned w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[2 * i] = __uint_as_float(w[i] << 16);
-            v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
+        return __uint_as_float(i & 1 ? x[i / 2] & 0xffff0000u : x[i / 2] << 16);
     }
 };
 
-// One lane per row and 16 output columns; a wavefront covers 64 consecutive rows and one chunk of 16
-// columns.  The projection matrix sits in LDS as floats; all lanes of a wavefront read the same 16
-// floats of it (one broadcast read per four multiply-adds), so neither LDS nor memory limits the
-// pass: it runs at the fused multiply-add rate.  Each of the 16 chains takes its terms in
-// increasing c, which fixes the result bit for bit.  A ternary matrix (entries -1, 0, 1: the sparse
-// random projection of equation 5, up to its positive constant sqrt(3/k), which the quantiser's
-// scale absorbs) becomes the floats -1, 0, 1: fma(x, +-1, y) is the exact sum or difference and
-// fma(x, 0, y) leaves y alone, so the chain is the sequence of additions and subtractions itself.
+// A wavefront takes 64 consecutive rows and 16 * NC columns.  v_mfma_f32_16x16x1 adds one term to each of its 4 x 16 x 16 sums as
+// one fma, with numbers below the smallest normal one as they are, so that the chains of the definition above can be given to the
+// matrix cores term by term: twice the rate of the vector units, and no instruction per sum.  Lane l holds row l of the tile (the
+// right operand: block l / 16, column l % 16), and of R the entries (4 s + l / 16, l % 16) of its columns; the left operand of term
+// 4 s + e is broadcast from block e to all four.
+// What bounds it: small tensors the latency of two launches, large ones the rows, 64 cache lines per load instruction, twice from
+// memory.  The rows come in parts of 32 columns, requested as a whole before the first product of the part (fewer registers and
+// more wavefronts than all at once: fp32, d = 128, N = 24, L = 2048, k = 32 20.3 -> 18.7 us; N = 128, L = 4096, d = 64 96 -> 88; left
+// to the compiler each request waits where it is used: 125).  One row per lane on the vector units, R through the scalar cache, ->
+// this, both passes: N = 2, L = 256, k = 16 12.1 -> 9.0 us; N = 96, L = 512, k = 32 15.3 -> 12.8; bf16, N = 16, L = 4096, k = 32, INT4
+// 15.6 -> 11.9; bf16, N = 64, L = 2000, k = 16 19.0 -> 13.2; bf16, d = 128, N = 16, L = 8192, k = 64 81 -> 50.
+// A ternary matrix (entries -1, 0, 1: the sparse random projection of equation 5, up to its positive constant sqrt(3/k), which
+// the quantiser's scale absorbs) becomes the floats -1, 0, 1: fma(x, +-1, y) is the exact sum or difference and fma(x, 0, y)
+// leaves y alone, so the chain is the sequence of additions and subtractions itself.
 // PASS 0: per-workgroup maximum of |Y| to block_max[blockIdx.x].  PASS 1: reduce block_max (the grid
 // of pass 0 is at most kProjMaxBlocks), scale, round to nearest even, clip, pack BITS-wide codes.
 constexpr int kProjCols = 16;
 constexpr int kProjMaxBlocks = 1024;
 
-template <typename T, int PASS, int BITS, bool TERNARY>
-__global__ __launch_bounds__(kProjThreads) void project_lanes(const T *__restrict__ X, const float *__restrict__ R,
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+template <typename T, int D, int NC, int PASS, int BITS, bool TERNARY>
+__global__ __launch_bounds__(kProjThreads) void project_tiles(const T *__restrict__ X, const float *__restrict__ R,
                                                               const int8_t *__restrict__ P3,
                                                               float *__restrict__ block_max, int n_block_max,
                                                               uint8_t *__restrict__ Xt, float *__restrict__ amax_out,
-                                                              unsigned rows, int d, int k, unsigned items)
+                                                              unsigned rows, int k, unsigned items)
 {
     constexpr int E = Chunk<T>::N;
-    extern __shared__ float sR[];                  // [d][k], then one float per wavefront
-    float *red = sR + d * k;
-    // a dense matrix is read straight from memory through the scalar cache (the address is the same for
-    // all lanes); only the ternary one is widened to floats in LDS
-    if (TERNARY)
-        for (int i = threadIdx.x; i < d * k; i += kProjThreads) sR[i] = (float)P3[i];
-    float amax = 0.f;
-    if (PASS == 1) {
-        float m = 0.f;
-        for (int i = threadIdx.x; i < n_block_max; i += kProjThreads) m = fmaxf(m, block_max[i]);
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
-        if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = m;
-    }
-    __syncthreads();
-    if (PASS == 1) {
-#pragma unroll
-        for (int w = 0; w < kProjThreads / kWave; ++w) amax = fmaxf(amax, red[w]);
-        if (amax_out && blockIdx.x == 0 && threadIdx.x == 0) *amax_out = amax;
-    }
-    constexpr float kQmax = (float)((1 << (BITS - 1)) - 1);
-    const float scale = amax > 0.f ? __fdiv_rn(kQmax, amax) : 0.f;
-    const int chunks = k / kProjCols;
+    constexpr int PART = 32;                          // columns of X requested at a time
+    typedef typename Chunk<T>::raw_t raw_t;
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int c = lane & 15, g = lane >> 4;
+    const unsigned chunks = (unsigned)k / (kProjCols * NC);
+    constexpr float kQmax = (float)((1 << (BITS - 1)) - 1);
+    float amax = 0.f;
+    if (PASS == 1) {                                   // every wavefront by itself: no barrier
+#pragma unroll
+        for (int i = 0; i < kProjMaxBlocks; i += 4 * kWave) {
+            if (i >= n_block_max) break;
+#pragma unroll
+            for (int j = i; j < i + 4 * kWave; j += kWave) amax = fmaxf(amax, block_max[min(j + lane, n_block_max - 1)]);
+        }
+    }
     float seen = 0.f;
-    // work item = (tile of 64 rows, chunk of 16 columns); a wavefront takes items wave, wave + stride, ...
+    // work item = (tile of 64 rows, chunk of columns); a wavefront takes items wave, wave + stride, ...
     for (unsigned item = blockIdx.x * (kProjThreads / kWave) + wave; item < items;
          item += gridDim.x * (kProjThreads / kWave)) {
         const unsigned tile = item / chunks;
-        const int j0 = (int)(item % chunks) * kProjCols;
-        const unsigned r = tile * kWave + lane;
-        const bool live = r < rows;
-        const T *x = X + (size_t)(live ? r : rows - 1) * d;
-        float y[kProjCols];
+        const int j0 = (int)(item % chunks) * (kProjCols * NC);
+        const raw_t *xp = reinterpret_cast<const raw_t *>(X + (size_t)min(tile * kWave + lane, rows - 1) * D);       // (the last row again beyond it)
+        v16f y[NC];
 #pragma unroll
-        for (int j = 0; j < kProjCols; ++j) y[j] = 0.f;
-        for (int c0 = 0; c0 < d; c0 += E) {
-            float xv[E];
-            Chunk<T>::load(x + c0, xv);
+        for (int n = 0; n < NC; ++n)
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-                if (TERNARY) {
-                    const float *rc = sR + (c0 + e) * k + j0;
+            for (int i = 0; i < 16; ++i) y[n][i] = 0.f;
 #pragma unroll
-                    for (int j = 0; j < kProjCols; ++j) y[j] = __fmaf_rn(xv[e], rc[j], y[j]);
-                } else {
-                    const float *rc = R + (c0 + e) * k + j0;     // wavefront-uniform: scalar loads
+        for (int p = 0; p < D / PART; ++p) {
+            float ra[NC][PART / 4];
 #pragma unroll
-                    for (int j = 0; j < kProjCols; ++j) y[j] = __fmaf_rn(xv[e], rc[j], y[j]);
+            for (int s = 0; s < PART / 4; ++s)
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+                    const int e = (p * PART + 4 * s + g) * k + j0 + kProjCols * n + c;
+                    ra[n][s] = TERNARY ? (float)P3[e] : R[e];
+                }
+            raw_t xv[PART / E];
+#pragma unroll
+            for (int i = 0; i < PART / E; ++i) xv[i] = xp[p * (PART / E) + i];
+            __builtin_amdgcn_sched_barrier(0);       // (else every request moves down to where it is used)
+#pragma unroll
+            for (int s = 0; s < PART / 4; ++s) {
+                auto term = [&](auto block) {
+                    constexpr int B = decltype(block)::value;
+                    const float xe = Chunk<T>::at(xv[(4 * s + B) / E], (4 * s + B) % E);
+#pragma unroll
+                    for (int n = 0; n < NC; ++n) y[n] = __builtin_amdgcn_mfma_f32_16x16x1f32(ra[n][s], xe, y[n], 2, B, 0);
+                };
+                term(std::integral_constant<int, 0>{});
+                term(std::integral_constant<int, 1>{});
+                term(std::integral_constant<int, 2>{});
+                term(std::integral_constant<int, 3>{});
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // y[n][4 b + i]: row 16 b + c of the tile, column 16 n + 4 g + i of the chunk
+        if (PASS == 0) {
+#pragma unroll
+            for (int n = 0; n < NC; ++n)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) seen = fmaxf(seen, fabsf(y[n][i]));
+        } else {
+            float all = amax;
+#pragma unroll
+            for (int off = 1; off < kWave; off <<= 1) all = fmaxf(all, __shfl_xor(all, off, kWave));
+            if (amax_out && item == 0 && lane == 0) *amax_out = all;
+            const float scale = all > 0.f ? __fdiv_rn(kQmax, all) : 0.f;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const unsigned r = tile * kWave + 16 * b + c;
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+                    unsigned packed = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float v = fminf(fmaxf(rintf(__fmul_rn(y[n][4 * b + i], scale)), -kQmax), kQmax);
+                        packed |= ((unsigned)(int)v & ((1u << BITS) - 1u)) << (i * BITS);
+                    }
+                    // four codes: 4, 2 or 1 bytes
+                    uint8_t *dst = Xt + ((size_t)r * k + j0 + kProjCols * n + 4 * g) * BITS / 8;
+                    if (r >= rows) continue;
+                    if (BITS == 8) *reinterpret_cast<unsigned *>(dst) = packed;
+                    else if (BITS == 4) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)packed;
+                    else *dst = (uint8_t)packed;
                 }
             }
         }
-        if (PASS == 0) {
-            if (live) {
-#pragma unroll
-                for (int j = 0; j < kProjCols; ++j) seen = fmaxf(seen, fabsf(y[j]));
-            }
-        } else if (live) {
-            unsigned packed[kProjCols * BITS / 32 > 0 ? kProjCols * BITS / 32 : 1];
-#pragma unroll
-            for (int i = 0; i < (int)(sizeof(packed) / sizeof(unsigned)); ++i) packed[i] = 0;
-#pragma unroll
-            for (int j = 0; j < kProjCols; ++j) {
-                const float v = fminf(fmaxf(rintf(__fmul_rn(y[j], scale)), -kQmax), kQmax);
-                packed[j * BITS / 32] |= ((unsigned)(int)v & ((1u << BITS) - 1u)) << ((j * BITS) % 32);
-            }
-            // codes j0 .. j0+15 of row r: 16, 8 or 4 bytes at byte (r * k + j0) * BITS / 8
-            uint8_t *dst = Xt + ((size_t)r * k + j0) * BITS / 8;
-            if (BITS == 8) *reinterpret_cast<uint4 *>(dst) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
-            else if (BITS == 4) *reinterpret_cast<uint2 *>(dst) = make_uint2(packed[0], packed[1]);
-            else *reinterpret_cast<unsigned *>(dst) = packed[0];
-        }
     }
     if (PASS == 0) {
+        __shared__ float red[kProjThreads / kWave];
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) seen = fmaxf(seen, __shfl_xor(seen, off, kWave));
-        __syncthreads();
         if (lane == 0) red[wave] = seen;
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -185,39 +201,57 @@ __global__ __launch_bounds__(kProjThreads) void unpack_codes(const unsigned *__r
 
 size_t project_workspace_bytes(const dsa_shape &) { return kProjMaxBlocks * sizeof(float); }
 
-template <typename T>
+// Wavefronts of 16 columns above which half as many with 32 each are better: more than the chip has SIMDs, so that two of them
+// would share one and fetch the same rows.  Both ways, a call: 512 (N = 16, L = 1024, k = 32, bf16) 9.7 and 11.7 us, 1024 (fp32,
+// N = 16, L = 2048, d = 128) 15.5 and 19.9; 1536 (fp32, N = 96, L = 512) 15.5 and 12.0, 2048 (N = 16, L = 4096, bf16) 12.8 and 12.1.
+// 64 columns: N = 64, L = 4096, k = 64, bf16 48.0 and 55.6; fp32, d = 128, N = 16, L = 8192 72.2 and 63.9: not kept.
+constexpr unsigned kProjWide = 1024;
+
+template <typename T, int D, int NC>
 hipError_t launch_project_t(const dsa_shape &sh, int bits, const T *X, const float *R, const int8_t *P3, void *Xt,
                             float *amax_out, void *ws, hipStream_t st)
 {
     const unsigned rows = (unsigned)sh.B * sh.H * sh.L;
-    const unsigned items = ((rows + kWave - 1) / kWave) * (unsigned)(sh.k / kProjCols);
+    const unsigned items = ((rows + kWave - 1) / kWave) * (unsigned)(sh.k / (kProjCols * NC));
     const unsigned per_block = kProjThreads / kWave;
     const unsigned grid = std::min<unsigned>((items + per_block - 1) / per_block, kProjMaxBlocks);
-    const size_t lds = ((size_t)sh.d * sh.k + kProjThreads / kWave) * sizeof(float);
     float *block_max = static_cast<float *>(ws);
     uint8_t *out = static_cast<uint8_t *>(Xt);
     auto go = [&](auto kern) -> hipError_t {
-        if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kern), lds)) return e;
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(kProjThreads), lds, st, X, R, P3, block_max, (int)grid, out, amax_out,
-                           rows, sh.d, sh.k, items);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kProjThreads), 0, st, X, R, P3, block_max, (int)grid, out, amax_out, rows, sh.k,
+                           items);
         return hipGetLastError();
     };
     auto both = [&](auto ternary_tag) -> hipError_t {
         constexpr bool TERNARY = decltype(ternary_tag)::value;
-        if (hipError_t e = go(project_lanes<T, 0, 8, TERNARY>)) return e;
-        if (bits == 8) return go(project_lanes<T, 1, 8, TERNARY>);
-        if (bits == 4) return go(project_lanes<T, 1, 4, TERNARY>);
-        return go(project_lanes<T, 1, 2, TERNARY>);
+        if (hipError_t e = go(project_tiles<T, D, NC, 0, 8, TERNARY>)) return e;
+        if (bits == 8) return go(project_tiles<T, D, NC, 1, 8, TERNARY>);
+        if (bits == 4) return go(project_tiles<T, D, NC, 1, 4, TERNARY>);
+        return go(project_tiles<T, D, NC, 1, 2, TERNARY>);
     };
     return P3 ? both(std::true_type{}) : both(std::false_type{});
+}
+
+template <typename T>
+hipError_t launch_project_dtype(const dsa_shape &sh, int bits, const T *X, const float *R, const int8_t *P3, void *Xt,
+                                float *amax_out, void *ws, hipStream_t st)
+{
+    const unsigned long long narrow = ((unsigned long long)sh.B * sh.H * sh.L + kWave - 1) / kWave * (sh.k / kProjCols);
+    const bool wide = sh.k % (2 * kProjCols) == 0 && narrow > kProjWide;
+    auto go = [&](auto d) {
+        constexpr int D = decltype(d)::value;
+        return wide ? launch_project_t<T, D, 2>(sh, bits, X, R, P3, Xt, amax_out, ws, st)
+                    : launch_project_t<T, D, 1>(sh, bits, X, R, P3, Xt, amax_out, ws, st);
+    };
+    return sh.d == 64 ? go(std::integral_constant<int, 64>{}) : go(std::integral_constant<int, 128>{});
 }
 
 hipError_t launch_project_quantize(const dsa_shape &sh, int bits, const void *X, const float *R, const int8_t *P3,
                                    void *Xt, float *amax_out, void *ws, hipStream_t st)
 {
     if (sh.dtype == DSA_F32)
-        return launch_project_t<float>(sh, bits, static_cast<const float *>(X), R, P3, Xt, amax_out, ws, st);
-    return launch_project_t<uint16_t>(sh, bits, static_cast<const uint16_t *>(X), R, P3, Xt, amax_out, ws, st);
+        return launch_project_dtype<float>(sh, bits, static_cast<const float *>(X), R, P3, Xt, amax_out, ws, st);
+    return launch_project_dtype<uint16_t>(sh, bits, static_cast<const uint16_t *>(X), R, P3, Xt, amax_out, ws, st);
 }
 
 hipError_t launch_unpack_codes(int bits, const void *packed_a, const void *packed_b, int8_t *codes_a, int8_t *codes_b,

@@ -1,0 +1,77 @@
+"""The projection on the matrix cores: tiles of 64 rows that are not full, 16 and 32 columns per wavefront (and 48, which takes the
+16), more tiles than wavefronts, terms and sums below the smallest normal number, infinities.  Codes and maximum bit for bit
+those of the oracle's chain of fmas."""
+import numpy as np
+import pytest
+
+import dsa_inputs as di
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dsa():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("these tests need the MI355X: run them with -m gpu on the GPU box")
+    import paper_2110_11299_amd as pkg
+    pkg.binding.lib()
+    return pkg
+
+
+def check(dsa, oracle, X, R, dtype, bits, ternary=False):
+    import torch
+    H, L, d = X.shape
+    k = R.shape[1]
+    print(f"[project] {dtype} H={H} L={L} d={d} k={k} bits={bits} ternary={ternary}", flush=True)
+    x = torch.from_numpy(X).view(1, H, L, d).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    sh = dsa.make_shape(1, H, L, d, k, 1, 1, dsa.DSA_F32 if dtype == "f32" else dsa.DSA_BF16, 1.0)
+    Rd = torch.from_numpy(R).cuda()
+    got, amax = (dsa.dsa_project_quantize_ternary if ternary else dsa.dsa_project_quantize_bits)(sh, bits, x.cuda(), Rd)
+    want, want_amax = (oracle.project_quantize_ternary if ternary else oracle.project_quantize)(x.float().numpy(), R, bits=bits)
+    assert np.float32(amax.item()) == np.float32(want_amax)
+    want = np.asarray(want).reshape(-1, k)
+    packed = got.cpu().numpy().view(np.uint8).reshape(H * L, -1)
+    fields = np.stack([(packed >> s) & ((1 << bits) - 1) for s in range(0, 8, bits)], axis=-1).reshape(H * L, k).astype(np.int32)
+    codes = np.where(fields >= 1 << (bits - 1), fields - (1 << bits), fields)
+    assert np.array_equal(codes, want)
+    return codes
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,L,d,k,bits", [
+    (1, 1, 64, 16, 8), (1, 63, 64, 32, 4), (3, 43, 128, 16, 2), (5, 64, 64, 48, 8), (2, 65, 128, 64, 4), (8, 4096, 64, 32, 8),
+    (9, 4099, 64, 32, 2), (8, 4095, 64, 32, 4), (7, 2345, 128, 64, 8), (3, 3001, 128, 128, 4), (67, 4100, 64, 16, 8), (35, 4101, 128, 48, 2)])
+def test_shapes(dsa, oracle, dtype, H, L, d, k, bits):
+    rng = np.random.default_rng(L + k)
+    check(dsa, oracle, rng.standard_normal((H, L, d), np.float32), rng.standard_normal((d, k), np.float32), dtype, bits)
+
+
+@pytest.mark.parametrize("H,L,d,k", [(2, 77, 64, 32), (8, 4097, 64, 32), (3, 100, 128, 48)])
+def test_ternary(dsa, oracle, H, L, d, k):
+    rng = np.random.default_rng(L)
+    check(dsa, oracle, rng.standard_normal((H, L, d), np.float32), rng.integers(-1, 2, (d, k)).astype(np.int8), "f32", 8, True)
+
+
+# the largest sum is about 1e-36, so that a code is a step of about 1e-38: most terms, many partial sums and a third of the inputs lie
+# below 2^-126
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,L,d,k", [(2, 200, 64, 16), (8, 4096, 64, 32), (2, 300, 128, 64)])
+def test_denormal(dsa, oracle, dtype, H, L, d, k):
+    rng = np.random.default_rng(d)
+    X = rng.standard_normal((H, L, d), np.float32) * np.float32(2.0 ** -126) * rng.choice(np.array([0.25, 1, 4], np.float32), (H, L, d))
+    codes = check(dsa, oracle, X, rng.standard_normal((d, k), np.float32), dtype, 8)
+    assert len(np.unique(codes)) > 100
+    check(dsa, oracle, X * np.float32(2.0 ** 60), rng.standard_normal((d, k), np.float32) * np.float32(2.0 ** -60), dtype, 8)
+
+
+def test_infinity(dsa, oracle):
+    """An infinite entry makes its row's sums infinite or NaN; the maximum takes the infinity, the scale is 0."""
+    import torch
+    X = np.random.default_rng(1).standard_normal((1, 100, 64), np.float32)
+    X[0, 70, 5] = np.inf
+    sh = dsa.make_shape(1, 1, 100, 64, 16, 1, 1, dsa.DSA_F32, 1.0)
+    codes, amax = dsa.dsa_project_quantize(sh, torch.from_numpy(X).cuda().view(1, 1, 100, 64), torch.ones((64, 16), device="cuda"))
+    codes = codes.cpu().numpy().reshape(100, 16)
+    assert np.isinf(amax.item())
+    assert not codes[:70].any() and not codes[71:].any() and (codes[70] == -127).all()      # inf * 0 is NaN, which is clipped to the lower end
