@@ -30,6 +30,7 @@
 
 #include "dsa_internal.h"
 #include "predict_api.h"
+#include "key_rows.h"
 #include "key_stream.h"
 #include "unit_attend.h"
 
@@ -233,33 +234,37 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     }
     for (int e = tid; e < U * kBinStride / 4; e += T) reinterpret_cast<v4i *>(hist)[e] = v4i{0, 0, 0, 0};
 
-    // ---- key rows: lane (r = lane % 16, kb = lane / 16) fetches 16 bytes of matrix row r ---------------------------
-    const int sub = R == 4 ? g : R == 2 ? g >> 1 : 0, part = R == 4 ? 0 : R == 2 ? g & 1 : g;
-    // (buffer loads: the batch is a scalar offset, the row operand an immediate one, and rows beyond L read zeros without a test)
+    // ---- key rows: lane (r = lane % 16, kb = lane / 16) fetches 16 bytes of matrix row r (key_rows.h) ---------------
+    // (buffer loads: the batch is in the base and the length of the descriptor, scalar work, the row operand an immediate offset;
+    // rows beyond L read zeros without a test)
+    const int sub = R == 4 ? g : R == 2 ? g >> 1 : 0;
     unsigned poff[STEPS], voff[STEPS];
     bool plive[STEPS];
     const bool crossed = CROSS && (c & 1);
-    const unsigned row0 = (unsigned)((4 * wv + (c >> 2)) * Lr + 4 * sub + (c & 3)) * (unsigned)k;
+    const unsigned row0 = key_row_offset(wv, lane, Lr, k, R);
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
-        plive[s] = 64 * s + 16 * part < k;
-        poff[s] = plive[s] ? 64 * s + 16 * part : 0;
+        plive[s] = key_piece_offset(lane, k, R, s) >= 0;
+        poff[s] = max(key_piece_offset(lane, k, R, s), 0);
     }
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) voff[s] = row0 + poff[crossed ? STEPS - 1 - s : s];
     unsigned twisted[STEPS];
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) twisted[s] = TWIST && (c & 2) ? row0 + (poff[s] ^ 32u) : voff[s];
-    const __amdgpu_buffer_rsrc_t keys = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(Kh), 0, L * k, 0x00020000);
-    const int slot_step = 4 * R * k, batches = NW * BPG;
+    const int slot_step = key_slot_step(k, R);
+    int batches = NW * BPG;
     auto request = [&](v4i (&dst)[NSB][STEPS], int b, const unsigned (&at)[STEPS]) {          // batches beyond the range read its last one
-        const int first = __builtin_amdgcn_readfirstlane(min(b, batches - 1) * NSB * slot_step);
+        const int first = __builtin_amdgcn_readfirstlane(key_batch_offset(b, batches, NSB, slot_step));
 #pragma unroll
-        for (int sl = 0; sl < NSB; ++sl)
+        for (int sl = 0; sl < NSB; ++sl) {
+            const int from = K ? first : first + sl * slot_step;
+            const __amdgpu_buffer_rsrc_t keys =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(Kh) + from, 0, key_bytes_left(L, k, from), 0x00020000);
 #pragma unroll
             for (int s = 0; s < STEPS; ++s)
-                dst[sl][s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(keys, K ? at[s] + sl * slot_step : at[s],
-                                                                                          K ? first : first + sl * slot_step, 0));
+                dst[sl][s] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(keys, K ? at[s] + sl * slot_step : at[s], 0, 0));
+        }
         __builtin_amdgcn_sched_barrier(0);       // the requests stay ahead of the batch that is used next
     };
     v4i rows[2][NSB][STEPS];
@@ -505,9 +510,9 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
         int cl[UT], ch[UT];
 #pragma unroll
         for (int t = 0; t < UT; ++t) cl[t] = ch[t] = 0;
-        // the sweep's masks are the same in every round: computed ahead for all words they would fill the registers, so the
+        // the sweep's masks and addresses are the same in every round: computed ahead for all words they would fill the registers, so the
         // compiler is kept from seeing it
-        asm volatile("" : "+v"(nv));
+        asm volatile("" : "+v"(nv), "+s"(batches));
 #pragma unroll
         for (int w = 0; w < NWM; ++w) {
             if (w < NW) {

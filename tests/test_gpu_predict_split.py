@@ -141,3 +141,14 @@ def test_two_steps(dsa, oracle, H, L, k):
     for vec in (1, 4, 8):
         Lv = L // vec * vec
         check(dsa, oracle, np.ascontiguousarray(Qt[:, :, :Lv]), np.ascontiguousarray(Kt[:, :, :Lv]), max(1, L // 50), vec, "two steps")
+
+
+# heads shorter than what a lane range's later batches of key rows start at (28 rows), where every one of them lies beyond the head
+@pytest.mark.parametrize("k", [16, 48, 64, 80, 112, 128])
+def test_short_heads(dsa, oracle, k):
+    for L in (1, 2, 3, 7, 8, 12, 15, 16, 17, 23, 24, 27, 28, 31, 32):
+        Qt, Kt = di.random_int8_case(L + k, 1, 3, L, k)
+        for vec in (1, 4, 8):
+            if L % vec == 0:
+                for keep in sorted({1, (L + 1) // 2, L}):
+                    check(dsa, oracle, Qt, Kt, keep, vec, "short")
