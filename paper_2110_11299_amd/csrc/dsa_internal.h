@@ -33,7 +33,7 @@ inline hipError_t allow_dynamic_lds(const void *kern, size_t bytes)
 {
     if (bytes <= 48 * 1024) return hipSuccess;
     struct Entry { const void *kern; int dev; };
-    static Entry done[128];
+    static Entry done[512];
     static int used = 0;
     static std::mutex mu;
     int dev = 0;
@@ -45,7 +45,7 @@ inline hipError_t allow_dynamic_lds(const void *kern, size_t bytes)
     if (hipError_t e = hipDeviceGetAttribute(&limit, hipDeviceAttributeMaxSharedMemoryPerBlock, dev)) return e;
     if ((size_t)limit < bytes) return hipErrorInvalidValue;
     if (hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, limit)) return e;
-    if (used < 128) done[used++] = Entry{kern, dev};
+    if (used < 512) done[used++] = Entry{kern, dev};
     return hipSuccess;
 }
 

@@ -51,13 +51,14 @@ constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' b
 template <bool GROUP, int UT, int NWM> constexpr int band_slots() { return !GROUP && UT == 1 && NWM >= 4 ? 32 : 24; }
 constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
 
-// The attention that a workgroup goes on with, over the lists it has just made (see attend_here).
-enum AttendKind { kAttendBf16x64, kAttendBf16x128, kAttendF32x64, kAttendF32x128, kAttendUnits64 };
+// The attention that a workgroup goes on with, over the lists it has just made (see attend_here): fp32 rows, or bf16 rows (of units
+// of several rows: the units on the matrix cores).
+enum AttendKind { kNoAttend, kAttendF32, kAttendBf16 };
 struct AttendArgs {
     const void *Q, *K, *V;
     float *O;
     float scale;
-    int kind, pad;                      // list length rounded up to kRowPad
+    int d, pad;                         // list length rounded up to kRowPad
 };
 
 struct SplitArgs {
@@ -166,9 +167,10 @@ __device__ __forceinline__ void attend_block_units(const AttendArgs &a, const ui
 // K: the projection dimension (16, 32, 48, 64, 128), or 0 for any other (up to 112, two contraction steps).
 // GROUP: units are groups of vec rows.  UT: tiles of 16 units per workgroup.  NB: buckets per lane and unit (32, or 16 if a
 // range has several groups).  NWM: most bitmap words per lane.
-// ATTEND: goes on with the attention (an instance of its own: the other one is up to 3 % faster without that code).
-template <int K, bool GROUP, int UT, int NB, int NWM, bool ATTEND>
-__global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::conditional_t<ATTEND, SplitAttendArgs, SplitArgs> a)
+// ATTEND: the attention that it goes on with, an instance of its own for each kind (the one without is up to 3 % faster for it; fp32
+// rows and bf16 units in one instance kept 103 registers in scratch: groups of 8, k = 32, N = 32, L = 8192, keep = 82 198 us, now 146).
+template <int K, bool GROUP, int UT, int NB, int NWM, int ATTEND>
+__global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::conditional_t<ATTEND != kNoAttend, SplitAttendArgs, SplitArgs> a)
 {
     constexpr int R = K == 16 ? 4 : K == 32 ? 2 : 1;     // keys side by side in a matrix row = tiles per row operand
     constexpr int STEPS = K && K <= 64 ? 1 : 2;          // contraction steps of 64
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     // keep = 82, groups of 8 57.3 -> 54.0.  Two tiles of groups have no registers for it: N = 16, L = 8192, d = 128 120 and 130 us.
     constexpr bool TWIST = K == 64 && !(GROUP && UT == 2);
     constexpr int NS = 8 / R;                            // row operands of a group of 8 tiles (32 keys per lane range)
-    constexpr int NSB = STEPS == 2 ? 2 : NS < 4 ? NS : 4;    // row operands of one batch of requests (8 registers each if two steps)
+    constexpr int NSB = key_batch_slots(NS, STEPS, GROUP && UT == 1);    // row operands of one batch of requests (8 registers each if two steps)
     constexpr int BPG = NS / NSB;                        // batches per group
     constexpr int TB = NSB * R;                          // tiles per batch
     constexpr int PAIR = TB >= 4 ? 2 : 1;                // tiles j and j + PAIR share a bucket
@@ -829,14 +831,16 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     }
 
     // ---- attention over the lists -------------------------------------------------------------------------------------
-    if constexpr (ATTEND) {
+    if constexpr (ATTEND != kNoAttend) {
         unsigned *room = reinterpret_cast<unsigned *>(lds + at.attend);     // behind the image: nobody else reads or writes there any more
         const int vec = GROUP ? a.vec : 1;
-        if (a.attend.kind == kAttendF32x64) attend_block<float, 64>(a.attend, image, room, L, keep, vec, n, u0, nu);
-        else if (a.attend.kind == kAttendF32x128) attend_block<float, 128>(a.attend, image, room, L, keep, vec, n, u0, nu);
-        else if constexpr (GROUP) attend_block_units<64>(a.attend, image, reinterpret_cast<char *>(room), L, keep, vec, n, u0, nu);
-        else if (a.attend.kind == kAttendBf16x64) attend_block<uint16_t, 64>(a.attend, image, room, L, keep, vec, n, u0, nu);
-        else attend_block<uint16_t, 128>(a.attend, image, room, L, keep, vec, n, u0, nu);
+        if constexpr (GROUP && ATTEND == kAttendBf16) {
+            attend_block_units<64>(a.attend, image, reinterpret_cast<char *>(room), L, keep, vec, n, u0, nu);
+        } else {
+            typedef std::conditional_t<ATTEND == kAttendF32, float, uint16_t> T;
+            if (a.attend.d == 64) attend_block<T, 64>(a.attend, image, room, L, keep, vec, n, u0, nu);
+            else attend_block<T, 128>(a.attend, image, room, L, keep, vec, n, u0, nu);
+        }
     }
 }
 
@@ -961,7 +965,8 @@ inline size_t attend_lds_bytes(const dsa_shape &sh, int W, int pad)
 //     keep = 1229, N = 2 281 and 294; keep = 614, L = 4096, N = 8 (three workgroups instead of four) 252 and 229.
 // Units of several rows in bf16 (attention_units_bf16 by itself): from 2048 wavefronts on, at most four units to a wavefront.  k = 32,
 // groups of 4: N = 32, L = 512, keep = 51 (1024 wavefronts) 16.9 and 19.0 us, N = 128 36.1 and 32.6, N = 32, L = 2048, keep = 205 79.1
-// and 72.0; groups of 8: N = 16, L = 4096, keep = 205 54.6 and 48.1, N = 64, L = 2048, keep = 102 59.4 and 55.1, N = 4, L = 4096, keep = 82
+// and 72.0; groups of 8: N = 32, L = 5120, keep = 256 134.0 and 128.1, N = 32, L = 8192, keep = 82 159.7 and 149.0, N = 8, L = 16384, keep = 164
+// 147.8 and 145.1; N = 16, L = 4096, keep = 205 54.6 and 48.1, N = 64, L = 2048, keep = 102 59.4 and 55.1, N = 4, L = 4096, keep = 82
 // (1024) 23.2 and 24.4.  Eight units: N = 512, L = 256, keep = 26, groups of 4, 54.7 and 60.7.  At d = 128 its registers do not fit.
 inline bool attend_here(const dsa_shape &sh, int W, int units, long long wgs, size_t lds)
 {
@@ -992,8 +997,7 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
         const size_t all = at.attend + attend_lds_bytes(sh, p.W, pad);
         if (attend_here(sh, p.W, kTile * UT, (long long)sh.B * sh.H * a.wgs_per_head, std::max(lds, all))) {
             lds = std::max(lds, all);
-            a.attend = AttendArgs{attend->Q, attend->K, attend->V, attend->O, sh.scale,
-                                  sh.dtype == DSA_F32 ? kAttendF32x64 + (sh.d == 128) : sh.vec > 1 ? (int)kAttendUnits64 : kAttendBf16x64 + (sh.d == 128), pad};
+            a.attend = AttendArgs{attend->Q, attend->K, attend->V, attend->O, sh.scale, sh.d, pad};
             attends = *attended = true;
         }
     }
@@ -1002,7 +1006,9 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
         hipLaunchKernelGGL(kern, dim3((unsigned)sh.B * sh.H * a.wgs_per_head), dim3(p.W * kWave), lds, st, args);
         return hipGetLastError();
     };
-    return attends ? go(predict_split<K, GROUP, UT, NB, NWM, true>, a) : go(predict_split<K, GROUP, UT, NB, NWM, false>, static_cast<const SplitArgs &>(a));
+    if (!attends) return go(predict_split<K, GROUP, UT, NB, NWM, kNoAttend>, static_cast<const SplitArgs &>(a));
+    if (sh.dtype == DSA_F32) return go(predict_split<K, GROUP, UT, NB, NWM, kAttendF32>, a);
+    return go(predict_split<K, GROUP, UT, NB, NWM, kAttendBf16>, a);
 }
 
 template <int K, bool GROUP>

@@ -15,12 +15,12 @@ PROGRAM = r"""
 #include <vector>
 using namespace dsa;
 
-// every request of a workgroup of W wavefronts; `twist` and `crossed` as predict_split has them for k
-static void check(int k, int L, int W)
+// every request of a workgroup of W wavefronts
+static void check(int k, int L, int W, bool half)
 {
     const int NW = (L + 128 * W - 1) / (128 * W), Lr = 32 * NW;
     const int R = k == 16 ? 4 : k == 32 ? 2 : 1, STEPS = k <= 64 ? 1 : 2, NS = 8 / R;
-    const int NSB = STEPS == 2 ? 2 : NS < 4 ? NS : 4, BPG = NS / NSB, batches = NW * BPG, step = key_slot_step(k, R);
+    const int NSB = key_batch_slots(NS, STEPS, half), BPG = NS / NSB, batches = NW * BPG, step = key_slot_step(k, R);
     const bool constant = k == 16 || k == 32 || k == 48 || k == 64 || k == 128;
     std::vector<char> seen((size_t)L * (k / 16), 0);
     for (int wv = 0; wv < W; ++wv)
@@ -54,13 +54,15 @@ static void check(int k, int L, int W)
 
 int main()
 {
-    for (int k = 16; k <= 128; k += 16) {
-        for (int W : {1, 2, 4, 8, 16}) {
-            for (int L = 1; L <= 132; ++L) check(k, L, W);
-            for (int L : {255, 256, 257, 511, 513, 777, 2000, 2049, 4100}) check(k, L, W);
+    for (int k = 16; k <= 128; k += 16)
+        for (bool half : {false, true}) {
+            for (int W : {1, 2, 4, 8, 16}) {
+                for (int L = 1; L <= 132; ++L) check(k, L, W, half);
+                for (int L : {255, 256, 257, 511, 513, 777, 2000, 2049, 4100}) check(k, L, W, half);
+            }
+            check(k, 8199, 8, half);
+            for (int L : {16384, 16385, 32767, 32768}) check(k, L, 16, half);
         }
-        check(k, 8199, 8); check(k, 16384, 16); check(k, 16385, 16); check(k, 32767, 16); check(k, 32768, 16);
-    }
     puts("ok");
 }
 """
