@@ -1,7 +1,10 @@
 """The forward call where the launch that makes the lists also attends over them, on both sides of the line where it does: list
 lengths around the gathers of the row loops (8, 4, 4 and 2 keys per load instruction for bf16 and fp32 at d = 64 and 128, four in
 flight), row counts that leave a workgroup with one unit, groups of rows.  The result has to be that of the two entry points one
-after the other, bit for bit, and the oracle's within the bounds that the other tests use."""
+after the other, bit for bit, and the oracle's within the bounds that the other tests use.  Which of the two routes a call took is
+told by the number of kernels that it leaves in a captured graph, and every case says which one it stands for."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -21,7 +24,31 @@ def dsa():
     return pkg
 
 
-def forward(dsa, dtype, H, L, d, vec, k, keep, scale=0.125, change=None):
+def captured_kernels(call):
+    """Kernels that `call`, which allocates nothing, enqueues on the current stream: it is captured and not run."""
+    import torch
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)      # the runtime that torch loaded
+    hip = ctypes.CDLL(path)
+    stream = torch.cuda.Stream()
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        assert hip.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), 1) == 0
+        try:
+            call()
+        finally:
+            ended = hip.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph))
+    assert ended == 0 and hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    for node in nodes:
+        kind = ctypes.c_int(-1)
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0      # a kernel
+    assert hip.hipGraphDestroy(graph) == 0
+    return n.value
+
+
+def forward(dsa, launches, dtype, H, L, d, vec, k, keep, scale=0.125, change=None):
     import torch
     print(f"[forward] {dtype} H={H} L={L} d={d} vec={vec} k={k} keep={keep} scale={scale}", flush=True)
     x = di.make_inputs(di.custom_config("fwd", B=1, H=H, L=L, d=d, dtype=dtype, rank=8, k=k, vec=vec, keep=keep, seed=L + keep))
@@ -33,15 +60,17 @@ def forward(dsa, dtype, H, L, d, vec, k, keep, scale=0.125, change=None):
     dev = [torch.from_numpy(a).cuda().to(t) for a in qkv]
     codes = [torch.from_numpy(a).cuda() for a in (x.Qt, x.Kt)]
     O, idx = dsa.dsa_attention_fwd(sh, *dev, *codes)
+    again, ws = (torch.empty_like(O), torch.empty_like(idx)), torch.empty(dsa.workspace_bytes(sh), dtype=torch.uint8, device="cuda")
+    assert captured_kernels(lambda: dsa.dsa_attention_fwd(sh, *dev, *codes, O=again[0], idx_out=again[1], ws=ws)) == launches
     idx2 = dsa.dsa_predict_mask(sh, *codes)
     O2 = dsa.dsa_masked_attention(sh, *dev, idx2)
     assert torch.equal(idx, idx2)
-    assert torch.equal(O.view(torch.int32), O2.view(torch.int32)) or torch.equal(torch.nan_to_num(O), torch.nan_to_num(O2))
+    assert torch.equal(O.view(torch.int32), O2.view(torch.int32))
     return qkv, idx.cpu().numpy().reshape(-1, keep), O.cpu().numpy().reshape(-1, d)
 
 
-def check(dsa, oracle, dtype, H, L, d, vec, k, keep, scale=0.125):
-    qkv, idx, got = forward(dsa, dtype, H, L, d, vec, k, keep, scale)
+def check(dsa, oracle, launches, dtype, H, L, d, vec, k, keep, scale=0.125):
+    qkv, idx, got = forward(dsa, launches, dtype, H, L, d, vec, k, keep, scale)
     want = oracle.masked_attention(*qkv, idx, scale, vec).reshape(-1, d)
     assert np.abs(got - want).max() <= TOL[dtype]
 
@@ -49,19 +78,30 @@ def check(dsa, oracle, dtype, H, L, d, vec, k, keep, scale=0.125):
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
 @pytest.mark.parametrize("keep", [1, 2, 4, 5, 8, 9, 15, 16, 17, 24, 25, 32, 33, 47, 65, 97])
 def test_list_lengths(dsa, oracle, dtype, d, keep):
-    check(dsa, oracle, dtype, 80, 97, d, 1, 16, keep, scale=0.125 if keep % 2 else -0.125)
+    check(dsa, oracle, 1, dtype, 80, 97, d, 1, 16, keep, scale=0.125 if keep % 2 else -0.125)
 
 
-# few workgroups and short or long lists; groups of rows in fp32; two tiles of units per workgroup; a list that leaves a CU one
-# workgroup; ranges of several groups with a ragged end
+# few workgroups and short or long lists; groups of rows in fp32; more than four units to a wavefront; two tiles of units per workgroup;
+# a list that leaves a CU one workgroup; ranges of several groups with a ragged end
+@pytest.mark.parametrize("launches,dtype,H,L,d,vec,k,keep", [
+    (1, "f32", 2, 256, 64, 1, 16, 4), (2, "f32", 2, 256, 64, 1, 16, 26), (1, "bf16", 1, 1000, 64, 1, 32, 10), (2, "bf16", 1, 1000, 64, 1, 32, 200),
+    (1, "f32", 130, 200, 64, 4, 32, 20), (2, "f32", 140, 136, 128, 8, 32, 14), (2, "f32", 2, 1000, 64, 8, 16, 100), (2, "bf16", 130, 200, 64, 8, 32, 20),
+    (1, "bf16", 130, 520, 64, 4, 32, 52), (2, "bf16", 140, 264, 64, 8, 16, 33), (1, "bf16", 17, 4104, 64, 8, 64, 205), (1, "bf16", 9, 8200, 64, 8, 64, 410),
+    (1, "bf16", 4, 4100, 64, 1, 64, 60), (1, "bf16", 3, 4096, 64, 1, 32, 410), (2, "bf16", 2, 4096, 128, 1, 48, 1300), (1, "bf16", 16, 777, 128, 1, 96, 39),
+    (1, "f32", 20, 513, 128, 1, 128, 51), (1, "bf16", 2, 8200, 64, 1, 32, 82)])
+def test_shapes(dsa, oracle, launches, dtype, H, L, d, vec, k, keep):
+    check(dsa, oracle, launches, dtype, H, L, d, vec, k, keep)
+
+
+# units of several rows in the kernels of every range length: fp32 of both widths, bf16, 9 to 16 groups per range (four and eight
+# wavefronts), two tiles of units per workgroup
 @pytest.mark.parametrize("dtype,H,L,d,vec,k,keep", [
-    ("f32", 2, 256, 64, 1, 16, 4), ("f32", 2, 256, 64, 1, 16, 26), ("bf16", 1, 1000, 64, 1, 32, 10), ("bf16", 1, 1000, 64, 1, 32, 200),
-    ("f32", 130, 200, 64, 4, 32, 20), ("f32", 140, 136, 128, 8, 32, 14), ("f32", 2, 1000, 64, 8, 16, 100), ("bf16", 130, 200, 64, 8, 32, 20),
-    ("bf16", 130, 520, 64, 4, 32, 52), ("bf16", 140, 264, 64, 8, 16, 33), ("bf16", 17, 4104, 64, 8, 64, 205), ("bf16", 9, 8200, 64, 8, 64, 410),
-    ("bf16", 4, 4100, 64, 1, 64, 60), ("bf16", 3, 4096, 64, 1, 32, 410), ("bf16", 2, 4096, 128, 1, 48, 1300), ("bf16", 16, 777, 128, 1, 96, 39),
-    ("f32", 20, 513, 128, 1, 128, 51), ("bf16", 2, 8200, 64, 1, 32, 82)])
-def test_shapes(dsa, oracle, dtype, H, L, d, vec, k, keep):
-    check(dsa, oracle, dtype, H, L, d, vec, k, keep)
+    ("f32", 140, 512, 64, 8, 32, 20), ("f32", 140, 512, 128, 8, 32, 20), ("f32", 65, 1000, 128, 4, 16, 40), ("bf16", 65, 2008, 64, 4, 16, 150),
+    ("bf16", 65, 2008, 64, 8, 32, 60), ("bf16", 17, 5120, 64, 8, 32, 256), ("bf16", 17, 8192, 64, 8, 32, 80), ("f32", 9, 8192, 128, 4, 32, 80),
+    ("bf16", 4, 8200, 64, 8, 32, 80), ("f32", 4, 8200, 64, 8, 32, 80), ("bf16", 4, 8200, 64, 8, 16, 80), ("bf16", 17, 4104, 64, 8, 48, 100),
+    ("bf16", 5, 5000, 64, 4, 112, 100), ("bf16", 2, 16384, 64, 8, 128, 120), ("bf16", 17, 8192, 64, 8, 64, 80), ("f32", 17, 8192, 128, 8, 64, 80)])
+def test_groups_in_one_launch(dsa, oracle, dtype, H, L, d, vec, k, keep):
+    check(dsa, oracle, 1, dtype, H, L, d, vec, k, keep)
 
 
 @pytest.mark.parametrize("vec", [4, 8])
@@ -70,7 +110,7 @@ def test_large_values_in_groups(dsa, oracle, vec):
     def change(qkv):
         qkv[0][...] *= 8.0
         qkv[2][...] = np.where(qkv[2] > 0, 2.0 ** 119, 2.0 ** 118)
-    qkv, idx, got = forward(dsa, "bf16", 130, 520, 64, vec, 32, 75, scale=1.0, change=change)
+    qkv, idx, got = forward(dsa, 1, "bf16", 130, 520, 64, vec, 32, 75, scale=1.0, change=change)
     want = oracle.masked_attention(*qkv, idx, 1.0, vec).reshape(-1, 64)
     assert np.abs(got / want - 1.0).max() <= 2.0 ** -12      # weights 2^-16; scores of up to 2^9 in fp32 on either side
 
@@ -80,7 +120,7 @@ def test_infinite_value_at_the_end_of_a_list(dsa, oracle, d, keep):
     """Lists that are a whole number of load instructions: no entry beyond the list makes NaN of an infinite value."""
     def change(qkv):
         qkv[2][0, :, -30:, 5] = np.inf
-    qkv, idx, got = forward(dsa, "f32", 80, 97, d, 1, 16, keep, change=change)
+    qkv, idx, got = forward(dsa, 1, "f32", 80, 97, d, 1, 16, keep, change=change)
     want = oracle.masked_attention(*qkv, idx, 0.125, 1).reshape(-1, d)
     ok = np.isfinite(want)
     assert 0 < (~ok).sum() < want.size and not np.isnan(want).any()
