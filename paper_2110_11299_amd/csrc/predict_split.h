@@ -955,26 +955,36 @@ inline size_t attend_lds_bytes(const dsa_shape &sh, int W, int pad)
 }
 
 // Whether the workgroups that make the lists attend over them too.  One launch less, lists that need not come back from memory,
-// and while some workgroups select (vector issue) others gather (L2): N = 16, L = 4096, keep = 205, bf16, k = 32 250 -> 214 us.
+// and while some workgroups select (vector issue) others gather (L2): N = 16, L = 4096, keep = 205, bf16, k = 32 232 -> 195 us.
 // Both launches are better (times of two launches and of one):
-//   - if few workgroups have many bytes to gather, where the rows by themselves spread over more CUs.  Up to 16 KB per wavefront:
-//     N = 2, L = 128, keep = 13 11.8 and 11.3; 26 KB, N = 1, L = 512, keep = 51 12.1 and 12.8, fp32, N = 2, L = 256, keep = 26, 11.6
-//     and 12.4; 53 KB, fp32, d = 128, N = 4, L = 512, keep = 26, 12.6 and 14.1.  From 2048 wavefronts on: N = 16, L = 512, keep = 51
-//     16.6 and 15.3; fp32, groups of 8, N = 16, L = 2048, keep = 102 69.5 and 67.4, but with 1024, N = 64, L = 512, 29.0 and 38.8;
+//   - if few workgroups have many bytes to gather, where the rows by themselves spread over more CUs.  Single rows: up to 16 KB per
+//     wavefront N = 2, L = 128, keep = 13 11.8 and 11.3; 26 KB, N = 1, L = 512, keep = 51 12.1 and 12.8, fp32, N = 2, L = 256, keep = 26,
+//     11.6 and 12.4; 53 KB, fp32, d = 128, N = 4, L = 512, keep = 26, 12.6 and 14.1.  From 2048 wavefronts on: N = 16, L = 512, keep = 51
+//     16.6 and 15.3.
+//   - fp32 rows of groups, 16 or 32 to a wavefront, if the last round of workgroups leaves places of the chip idle for long: if the
+//     share of the idle places, times the bytes of a wavefront, is above 20 KB per round.  Groups of 8, k = 32: N = 60, L = 552, d = 128,
+//     keep = 39 (2400 wavefronts) 58.4 and 91.9, N = 8, L = 4448, keep = 94 (2240) 82.0 and 114, N = 191, L = 416, keep = 30 (3056) 59.2
+//     and 66.9, k = 16, N = 113, L = 1216, keep = 17 (4520) 90.5 and 97.8; within it groups of 4, N = 65, L = 692, keep = 7 (2860) 33.2 and
+//     28.8, groups of 8, k = 64, N = 127, L = 952, keep = 17 (4064) 79.3 and 73.4, k = 32, N = 32, L = 8192, keep = 82 (8192) 474 and 410.
+//     (300 shapes from 1024 wavefronts on: 0.8 % behind the better of the two on average; the worst, N = 232, L = 392, keep = 19, 57.7 and 65.8.)
+//   - units of several rows in bf16, if there are fewer than 2048 wavefronts or three tenths of the places are idle: groups of 4, k = 16,
+//     N = 108, L = 264, keep = 14 (2160) 20.1 and 22.1, k = 48, N = 103, L = 664, keep = 40 (4532) 48.6 and 53.7; within it k = 32, N = 128,
+//     L = 512, keep = 51 36.1 and 32.4, k = 64, N = 29, L = 2128, keep = 62 (3944) 58.0 and 53.3; groups of 8, k = 32: N = 32, L = 8192,
+//     keep = 82 159.7 and 149.0, N = 8, L = 16384, keep = 164 147.8 and 145.1, N = 4, L = 4096, keep = 82 (1024) 23.2 and 24.4.  (200 shapes:
+//     0.6 % behind the better of the two on average; lost are a few like N = 32, L = 5120, keep = 256 (5120), 134.0 and 128.1.)  Above four
+//     units to a wavefront (N = 512, L = 256, keep = 26, groups of 4, 54.7 and 60.7) and at d = 128, whose registers do not fit, never;
 //   - if a CU does not hold two workgroups: 16 wavefronts, N = 8, L = 16384, keep = 164 1063 and 1106, or long lists, L = 8192,
 //     keep = 1229, N = 2 281 and 294; keep = 614, L = 4096, N = 8 (three workgroups instead of four) 252 and 229.
-// Units of several rows in bf16 (attention_units_bf16 by itself): from 2048 wavefronts on, at most four units to a wavefront.  k = 32,
-// groups of 4: N = 32, L = 512, keep = 51 (1024 wavefronts) 16.9 and 19.0 us, N = 128 36.1 and 32.6, N = 32, L = 2048, keep = 205 79.1
-// and 72.0; groups of 8: N = 32, L = 5120, keep = 256 134.0 and 128.1, N = 32, L = 8192, keep = 82 159.7 and 149.0, N = 8, L = 16384, keep = 164
-// 147.8 and 145.1; N = 16, L = 4096, keep = 205 54.6 and 48.1, N = 64, L = 2048, keep = 102 59.4 and 55.1, N = 4, L = 4096, keep = 82
-// (1024) 23.2 and 24.4.  Eight units: N = 512, L = 256, keep = 26, groups of 4, 54.7 and 60.7.  At d = 128 its registers do not fit.
 inline bool attend_here(const dsa_shape &sh, int W, int units, long long wgs, size_t lds)
 {
-    const bool grouped = sh.vec > 1 && sh.dtype == DSA_BF16;
-    if (grouped && (sh.d != 64 || units > 4 * W)) return false;
     if (W > 8 || lds > 80 * 1024) return false;
+    const long long waves = wgs * W;
     const long long work = ((long long)sh.keep * sh.d * (sh.dtype == DSA_F32 ? 4 : 2) + 1536) * ((units * sh.vec + W - 1) / W);
-    return wgs * W >= 2048 || (!grouped && work <= 16 * 1024);
+    if (sh.vec == 1) return waves >= 2048 || work <= 16 * 1024;
+    // wavefronts that 256 CUs hold at a time (four to a SIMD by the registers), and places that the last round leaves idle
+    const long long slots = 256LL * W * std::min(16 / W, (int)(160 * 1024 / lds)), rounds = (waves + slots - 1) / slots, idle = rounds * slots - waves;
+    if (sh.dtype == DSA_F32) return idle * work <= 20 * 1024 * rounds * rounds * slots;
+    return sh.d == 64 && units <= 4 * W && waves >= 2048 && 10 * idle <= 3 * rounds * slots;
 }
 
 template <int K, bool GROUP, int UT, int NB, int NWM>
