@@ -21,7 +21,8 @@ constexpr int key_piece_offset(int lane, int k, int R, int s)
 // need a second unit operand and the sums of two matrix instructions: with four, 6 to 33 of their registers went through scratch.
 // Groups of 8, four and two: k = 32, N = 32, L = 8192, keep = 82 102.4 and 99.8 us, k = 64, N = 4, L = 12288, keep = 246 60.0 and 57.5.
 // Two tiles of groups use what they fetch twice and want the four: k = 64, N = 16, L = 8192, keep = 82 66.2 and 71.8.  (k = 16 has
-// two in all: one at a time 95.1 and 96.2, N = 32, L = 8192.)
+// two in all: one at a time 95.1 and 96.2, N = 32, L = 8192.  k = 48 has the registers for four, and with few wavefronts two are waited
+// for: N = 14, L = 1976, keep = 66, groups of 4, 18.8 and 21.0.)
 constexpr int key_batch_slots(int all, int steps, bool fewer) { return steps == 2 || fewer || all < 4 ? 2 : 4; }
 // Bytes from row operand to row operand, and from the head to batch b of them (beyond the range: to its last batch).
 constexpr int key_slot_step(int k, int R) { return 4 * R * k; }

@@ -185,7 +185,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     // keep = 82, groups of 8 57.3 -> 54.0.  Two tiles of groups have no registers for it: N = 16, L = 8192, d = 128 120 and 130 us.
     constexpr bool TWIST = K == 64 && !(GROUP && UT == 2);
     constexpr int NS = 8 / R;                            // row operands of a group of 8 tiles (32 keys per lane range)
-    constexpr int NSB = key_batch_slots(NS, STEPS, GROUP && UT == 1);    // row operands of one batch of requests (8 registers each if two steps)
+    constexpr int NSB = key_batch_slots(NS, STEPS, GROUP && UT == 1 && K != 48);    // row operands of one batch of requests (8 registers each if two steps)
     constexpr int BPG = NS / NSB;                        // batches per group
     constexpr int TB = NSB * R;                          // tiles per batch
     constexpr int PAIR = TB >= 4 ? 2 : 1;                // tiles j and j + PAIR share a bucket
