@@ -13,6 +13,13 @@ namespace {
 constexpr int kRowWaves = 4;          // query rows (wavefronts) per workgroup
 constexpr int kMaxKeep = 4096;        // list and scores of a row in LDS: 4 waves * 4096 * 8 B = 128 KB
 
+// The unit that row i of head n belongs to; vec is 1, 4 or 8.  (Two divisions were 60 of the 330 instructions of a row of 3 keys.)
+__device__ __forceinline__ size_t unit_of(unsigned n, unsigned i, int L, int vec)
+{
+    const int shift = __builtin_ctz(vec);
+    return (size_t)n * (L >> shift) + (i >> shift);
+}
+
 // MODE kFused: Q,K,V,idx -> O.  kSddmm: Q,K,idx -> S.  kSpmm: Pin,V,idx -> O.
 template <typename T, int D, int MODE>
 __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
@@ -32,7 +39,7 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
     const unsigned row = vblock * kRowWaves + wave;                 // wavefront-uniform from here on
     if (row >= total_rows) return;                        // the whole wavefront: nothing below is shared
     const unsigned n = row / (unsigned)L, i = row % (unsigned)L;
-    const int32_t *list = idx + ((size_t)n * (L / vec) + i / vec) * keep;
+    const int32_t *list = idx + unit_of(n, i, L, vec) * keep;
     // per wavefront in LDS: the row's key list, as the byte offset of every key row inside its head
     // (keys clamped into [0, L), so that no idx can send a gather outside K / V), filled up with its last key, and its scores,
     // later (or from the start, when the weights are given) its weights
@@ -71,26 +78,31 @@ __global__ __launch_bounds__(kRowWaves *kWave) void attention_rows(
 // raises the maximum, the sums so far are rescaled by exp(m_old - m_new).  4 KB of LDS per row leave room for eight rows
 // per SIMD, and most lists are one chunk.  N = 16, L = 2048, about 102 keys a row: 91 -> 54 us against tests per key,
 // a conversion per weight and gather, and 8 KB per row.
-// One wavefront per workgroup: with four, their places wait for the longest of four lists (a call with 105 keys a row on average,
-// standard deviation 83: 72.9 and 70.2 us).
+// WAVES: rows of a workgroup.  With four, their places wait for the longest of four lists, with one, neighbours that share a list do not
+// share an L1.  One and four (the kernel alone): single rows, fp32, N = 77, L = 2056, 27 keys a row (standard deviation 42) 105.9 and
+// 117.7 us, bf16, N = 16, L = 2048, 109 (95) 42.4 and 43.9; groups of 4, bf16, d = 128, N = 148, L = 520, 23 (23) 49.8 and 51.5, but fp32,
+// N = 44, L = 1048, 27 (31) 61.6 and 60.5; groups of 8, fp32, N = 15, L = 5032, 145 (180) 251.5 and 237.2, bf16, N = 124, L = 1296, 103 (81)
+// 170.3 and 167.4, but d = 128, N = 21, L = 2336, 36 (50) 51.2 and 52.2.  Groups of 8 take four (their rows are a multiple of it).
 // The weights are summed in fp32 as they are made; only the products take them rounded, if T is bfloat16.
 constexpr int kCsrChunk = 512;
 static_assert(kCsrChunk % kRowPad == 0, "a full chunk needs no padding");
 
-template <typename T, int D>
-__global__ __launch_bounds__(kWave) void attention_rows_csr(
+template <typename T, int D, int WAVES>
+__global__ __launch_bounds__(WAVES *kWave) void attention_rows_csr(
     const T *__restrict__ Q, const T *__restrict__ K, const T *__restrict__ V,
     const int32_t *__restrict__ row_ptr, const int32_t *__restrict__ col, float *__restrict__ O, int L, int vec, float scale)
 {
     typedef Piece<T> P;
     constexpr int E = P::N;
     constexpr unsigned kRowBytes = D * sizeof(T);
-    __shared__ unsigned sl[kCsrChunk], sw[kCsrChunk];      // the list; scores, then weights
-    const int lane = threadIdx.x;
+    __shared__ unsigned lists[WAVES][kCsrChunk], weights[WAVES][kCsrChunk];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int sub = lane % RowShape<T, D>::LPR;
-    const unsigned row = xcd_contiguous(blockIdx.x, gridDim.x);
+    unsigned *sl = lists[wave], *sw = weights[wave];       // the list; scores, then weights
+    const unsigned row = xcd_contiguous(blockIdx.x, gridDim.x) * WAVES + wave;
     const unsigned n = row / (unsigned)L, i = row % (unsigned)L;
-    const size_t u = (size_t)n * (L / vec) + i / vec;
+    const size_t u = unit_of(n, i, L, vec);
     const int beg = row_ptr[u];
     const int cnt = max(row_ptr[u + 1] - beg, 0);
     // the scores are kept as sign(scale) * q.k and the factor |scale| waits for the exponential
@@ -148,7 +160,7 @@ __global__ __launch_bounds__(kRowWaves *kWave) void gather_probe(const T *__rest
     const bool live = row < total_rows;
     const unsigned r = live ? row : total_rows - 1;
     const unsigned n = r / (unsigned)L, i = r % (unsigned)L;
-    const int32_t *list = idx + ((size_t)n * (L / vec) + i / vec) * keep;
+    const int32_t *list = idx + unit_of(n, i, L, vec) * keep;
     // the same padded list of byte offsets as in attention_rows, the same address arithmetic
     unsigned *sl = reinterpret_cast<unsigned *>(lds_scores) + wave * keep_pad;
     for (int t = lane; t < keep_pad; t += kWave) sl[t] = (unsigned)min(max(list[min(t, keep - 1)], 0), L - 1) * kRowBytes;
@@ -497,17 +509,18 @@ hipError_t launch_attention_csr(const dsa_shape &sh, const void *Q, const void *
                                 const int32_t *row_ptr, const int32_t *col, float *O, hipStream_t st)
 {
     const unsigned rows = (unsigned)sh.B * sh.H * sh.L;
-    auto go = [&](auto kern, auto *q, auto *k, auto *v) -> hipError_t {
-        hipLaunchKernelGGL(kern, dim3(rows), dim3(kWave), 0, st, q, k, v, row_ptr, col, O, sh.L, sh.vec, sh.scale);
+    auto launch = [&](auto *q, auto *k, auto *v, auto d, auto waves) -> hipError_t {
+        constexpr int D = decltype(d)::value, W = decltype(waves)::value;
+        hipLaunchKernelGGL((attention_rows_csr<std::remove_const_t<std::remove_pointer_t<decltype(q)>>, D, W>), dim3(rows / W), dim3(W * kWave), 0, st,
+                           q, k, v, row_ptr, col, O, sh.L, sh.vec, sh.scale);
         return hipGetLastError();
     };
-    if (sh.dtype == DSA_F32) {
-        const float *q = static_cast<const float *>(Q), *k = static_cast<const float *>(K), *v = static_cast<const float *>(V);
-        return sh.d == 64 ? go(attention_rows_csr<float, 64>, q, k, v) : go(attention_rows_csr<float, 128>, q, k, v);
-    }
-    const uint16_t *q = static_cast<const uint16_t *>(Q), *k = static_cast<const uint16_t *>(K),
-                   *v = static_cast<const uint16_t *>(V);
-    return sh.d == 64 ? go(attention_rows_csr<uint16_t, 64>, q, k, v) : go(attention_rows_csr<uint16_t, 128>, q, k, v);
+    auto go = [&](auto *q, auto *k, auto *v) -> hipError_t {
+        auto width = [&](auto d) { return sh.vec == 8 ? launch(q, k, v, d, std::integral_constant<int, 4>{}) : launch(q, k, v, d, std::integral_constant<int, 1>{}); };
+        return sh.d == 64 ? width(std::integral_constant<int, 64>{}) : width(std::integral_constant<int, 128>{});
+    };
+    if (sh.dtype == DSA_F32) return go(static_cast<const float *>(Q), static_cast<const float *>(K), static_cast<const float *>(V));
+    return go(static_cast<const uint16_t *>(Q), static_cast<const uint16_t *>(K), static_cast<const uint16_t *>(V));
 }
 
 hipError_t launch_gather_probe(const dsa_shape &sh, const void *K, const void *V, const int32_t *idx, unsigned *sink,

@@ -193,7 +193,8 @@ __device__ __forceinline__ void row_gather(typename Piece<T>::raw_t (&x)[NR][kRo
     }
 }
 
-// q . k of the first n entries of NR lists to sc[r * pad + t], and something to the entries up to the end of the last trip.  at(r, t): byte offset of the key row of entry t inside the head.  m[r]: this lane's share of the maximum.
+// q . k of the first n entries of NR lists to sc[r * pad + t], and something to entries behind them, up to the end of the last trip at
+// most.  at(r, t): byte offset of the key row of entry t inside the head.  m[r]: this lane's share of the maximum.
 template <typename T, int D, int NR, typename At>
 __device__ __forceinline__ void row_scores(const T *Kh, const typename Piece<T>::raw_t (&q)[NR], At &&at, float *sc, int pad, int n,
                                            int lane, float (&m)[NR])
@@ -202,22 +203,22 @@ __device__ __forceinline__ void row_scores(const T *Kh, const typename Piece<T>:
 #pragma unroll
     for (int r = 0; r < NR; ++r) m[r] = -INFINITY;
     row_trips<T, D>(n, [&](int t0, auto tail) {
-        constexpr int TAIL = decltype(tail)::value;
+        constexpr int TAIL = decltype(tail)::value, NS = NR == 1 && (TAIL == 1 || TAIL == 2) ? TAIL : kRowGathers;     // sums that are taken
         typename Piece<T>::raw_t kv[NR][kRowGathers];
         if (TAIL) {
 #pragma unroll
             for (int r = 0; r < NR; ++r)
 #pragma unroll
-                for (int u = TAIL; u < kRowGathers; ++u) kv[r][u] = q[r];
+                for (int u = TAIL; u < NS; ++u) kv[r][u] = q[r];
         }
         row_gather<T, D, NR, TAIL>(kv, Kh, at, t0, n, lane);
-        const int t = t0 + piece_slot<G::LPR, kRowGathers>(lane) * G::RPI + lane / G::LPR;
+        const int t = t0 + piece_slot<G::LPR, NS>(lane) * G::RPI + lane / G::LPR;
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-            float part[kRowGathers];
+            float part[NS];
 #pragma unroll
-            for (int u = 0; u < kRowGathers; ++u) part[u] = Piece<T>::dot(q[r], kv[r][u]);
-            const float s = piece_sums<G::LPR, kRowGathers>(part, lane);
+            for (int u = 0; u < NS; ++u) part[u] = Piece<T>::dot(q[r], kv[r][u]);
+            const float s = piece_sums<G::LPR, NS>(part, lane);
             if (!TAIL || t < n) m[r] = fmaxf(m[r], s);
             sc[r * pad + t] = s;                      // lanes with the same entry write the same value
         }
