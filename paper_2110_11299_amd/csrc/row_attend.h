@@ -225,7 +225,7 @@ __device__ __forceinline__ void row_scores(const T *Kh, const typename Piece<T>:
     });
 }
 
-// o[r] += weight * value row over the entries of this lane group.  sw: the weights; entries beyond n weigh 0.
+// o[r] += weight * value row over the entries of this lane group.  sw: the weights.
 template <typename T, int D, int NR, typename At>
 __device__ __forceinline__ void row_values(const T *Vh, At &&at, const unsigned *sw, int pad, int n, int lane,
                                            float (&o)[NR][Piece<T>::N])
@@ -242,7 +242,9 @@ __device__ __forceinline__ void row_values(const T *Vh, At &&at, const unsigned 
             for (int u = 0; u < kRowGathers; ++u) w[r][u] = sw[r * pad + t0 + u * G::RPI + lane / G::LPR];
 #pragma unroll
         for (int u = 0; u < kRowGathers; ++u) {
-            if (TAIL && u >= TAIL) continue;      // (0 times an infinite value would not be 0)
+            // nothing is added for what lies behind the list, not a weight of 0 either: times an infinite value that is not 0
+            if (TAIL && u >= TAIL) continue;
+            if (TAIL && u == TAIL - 1 && t0 + u * G::RPI + lane / G::LPR >= n) continue;
 #pragma unroll
             for (int r = 0; r < NR; ++r) Piece<T>::axpy(o[r], w[r][u], vv[r][u]);
         }

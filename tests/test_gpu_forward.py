@@ -129,3 +129,26 @@ def test_infinite_value_at_the_end_of_a_list(dsa, oracle, d, keep):
     assert 0 < (~ok).sum() < want.size and not np.isnan(want).any()
     assert np.array_equal(got[~ok], want[~ok])
     assert np.abs(got[ok] - want[ok]).max() <= TOL["f32"]
+
+
+@pytest.mark.parametrize("d,keep", [(64, 1), (64, 25), (64, 27), (128, 23), (128, 31)])
+def test_infinite_value_inside_a_load(dsa, oracle, d, keep):
+    """Lists that end inside a load instruction: the lanes behind the end add nothing, in the forward, from ELL and from CSR lists.
+    (fp32: in bf16 a row's products pair a weight with a zero, which an infinite value in the neighbouring column makes NaN.)"""
+    import torch
+
+    def change(qkv):
+        qkv[2][0, :, -30:, 5] = np.inf
+    qkv, idx, got = forward(dsa, 1, "f32", 80, 97, d, 1, 16, keep, change=change)
+    want = oracle.masked_attention(*qkv, idx, 0.125, 1).reshape(-1, d)
+    sh = dsa.make_shape(1, 80, 97, d, 16, keep, 1, dsa.DSA_F32, 0.125)
+    dev = [torch.from_numpy(a).cuda() for a in qkv]
+    lists = torch.from_numpy(np.ascontiguousarray(idx)).cuda()
+    csr = dsa.dsa_masked_attention_csr(sh, *dev, torch.arange(80 * 97 + 1, device="cuda", dtype=torch.int32) * keep, lists.flatten())
+    S = dsa.dsa_sddmm(sh, *dev[:2], lists.view(1, 80, 97, keep))
+    staged = dsa.dsa_spmm(sh, dsa.dsa_sparse_softmax(sh, S), lists.view(1, 80, 97, keep), dev[2])
+    ok = np.isfinite(want)
+    assert 0 < (~ok).sum() < want.size and not np.isnan(want).any()
+    for out in (got, csr.cpu().numpy().reshape(-1, d), staged.cpu().numpy().reshape(-1, d)):
+        assert np.array_equal(out[~ok], want[~ok])
+        assert np.abs(out[ok] - want[ok]).max() <= TOL["f32"]
