@@ -97,13 +97,22 @@ struct Codes {
     }
 };
 
-// Mask and attention over it, from int8 codes: one launch, or two.
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + b_bytes && y < x + a_bytes;
+}
+
+// Mask and attention over it, from int8 codes: one launch, or two.  Two where O lies over the codes (a workspace that becomes the
+// output): in one launch some workgroups would write O while others still read them.
 dsa_status launch_forward(const dsa_shape &sh, const void *Q, const void *K, const void *V, const int8_t *Qt, const int8_t *Kt,
                           float *O, int32_t *idx, void *pws, hipStream_t st)
 {
     const dsa::AttendPtrs attend{Q, K, V, O};
+    const size_t rows = (size_t)sh.B * sh.H * sh.L, out = rows * sh.d * sizeof(float), codes = rows * sh.k;
+    const bool apart = !overlap(O, out, Qt, codes) && !overlap(O, out, Kt, codes);
     bool attended = false;
-    if (hipError_t e = dsa::launch_predict(sh, Qt, Kt, idx, pws, &attend, &attended, st)) return from_hip(e);
+    if (hipError_t e = dsa::launch_predict(sh, Qt, Kt, idx, pws, apart ? &attend : nullptr, &attended, st)) return from_hip(e);
     return attended ? DSA_OK : from_hip(dsa::launch_attention(dsa::kFused, sh, Q, K, V, idx, nullptr, nullptr, O, st));
 }
 

@@ -152,3 +152,42 @@ def test_infinite_value_inside_a_load(dsa, oracle, d, keep):
     for out in (got, csr.cpu().numpy().reshape(-1, d), staged.cpu().numpy().reshape(-1, d)):
         assert np.array_equal(out[~ok], want[~ok])
         assert np.abs(out[ok] - want[ok]).max() <= TOL["f32"]
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+def test_output_over_the_codes(dsa, bits):
+    """Codes (or, packed, the workspace that they are widened in) in the memory that becomes the output: two launches, since the codes
+    of a head are read by all of its workgroups."""
+    import torch
+    H, L, d, k, keep = 64, 513, 64, 32, 20
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(bits)
+    Q, K, V = (torch.randn((1, H, L, d), generator=gen, device="cuda") for _ in range(3))
+    top = 2 ** (bits - 1)
+    Qt, Kt = (torch.randint(1 - top, top, (1, H, L, k), generator=gen, device="cuda", dtype=torch.int8) for _ in range(2))
+    sh = dsa.make_shape(1, H, L, d, k, keep, 1, dsa.DSA_F32, 0.125)
+    idx = torch.empty((1, H, L, keep), dtype=torch.int32, device="cuda")
+    memory = torch.zeros(H * L * d, dtype=torch.float32, device="cuda")
+    O, raw = memory.view(1, H, L, d), memory.view(torch.int8)
+    if bits == 8:
+        over = [raw[i * H * L * k:][:H * L * k].view(1, H, L, k) for i in range(2)]
+        ws = torch.empty(dsa.workspace_bytes(sh), dtype=torch.uint8, device="cuda")
+        want = [x.clone() for x in dsa.dsa_attention_fwd(sh, Q, K, V, Qt, Kt)]
+        apart = lambda: dsa.dsa_attention_fwd(sh, Q, K, V, Qt, Kt, O=O, idx_out=idx, ws=ws)  # noqa: E731
+        call = lambda: dsa.dsa_attention_fwd(sh, Q, K, V, *over, O=O, idx_out=idx, ws=ws)  # noqa: E731
+        launches = (1, 2)
+    else:
+        packed = [((x[..., ::2] & 15) | (x[..., 1::2] << 4)).view(torch.uint8).contiguous() for x in (Qt, Kt)]
+        ws = torch.empty(dsa.binding.workspace_bytes_bits(sh, bits), dtype=torch.uint8, device="cuda")
+        want = [x.clone() for x in dsa.dsa_attention_fwd_bits(sh, bits, Q, K, V, *packed)]
+        apart = lambda: dsa.dsa_attention_fwd_bits(sh, bits, Q, K, V, *packed, O=O, idx_out=idx, ws=ws)  # noqa: E731
+        call = lambda: dsa.dsa_attention_fwd_bits(sh, bits, Q, K, V, *packed, O=O, idx_out=idx, ws=memory.view(torch.uint8))  # noqa: E731
+        launches = (2, 3)             # one for the packed codes
+    print(f"[over] bits={bits}", flush=True)
+    assert captured_kernels(apart) == launches[0] and captured_kernels(call) == launches[1]
+    if bits == 8:
+        for place, codes in zip(over, (Qt, Kt)):
+            place.copy_(codes)
+    call()
+    torch.cuda.synchronize()
+    assert torch.equal(idx, want[1].view_as(idx)) and torch.equal(O, want[0])
