@@ -909,24 +909,28 @@ inline int split_waves(const dsa_shape &sh, long long tiles)
 }
 
 // Two tiles per workgroup halve the key rows that come from L2 per unit.  They take the unit operands of both in registers, which
-// only a contraction that fills its 64 slots leaves room for (k = 32 keeps two half-empty copies of each: 139 -> 171 us), 16
-// buckets per lane instead of 32, whose bounds are worse the longer the list is, and a grid that is not left with half a round at
-// its end (waves between one and two per slot: L = 12288, N = 1, 88.6 us with one tile, 91.0 with two).  k = 64, N L^2 = 2^28,
-// one tile and two at 1, 2, 4, 8 %:
-//   rows         L = 1536 155 and 174, 161/182, 168/196, 195/232; 2048 158/148, 164/159, 174/177, 215/232; 3072 150/127, 153/139,
-//                173/165, 212/213; 4096 140/113, 148/127, 176/161, 211/209; 8192 139/107, 156/129, 181/157; 16384 145/116, 158/132,
-//                188/197.  Half a round is enough: L = 4096, N = 2, 27.1 and 23.4; L = 8192, N = 1, 47.1 and 37.7.
-//   groups of 8  (the operands do not fit: 31 and 50 registers go through scratch) 4096 123/126, 132/136, 148/160; 6144 153/157,
-//                164/177; 8192 146/136, 168/166, 200/218; 16384 157/144, 164/160, 197/195.  A quarter of a round: 49.2 and 67.5.
-//   k = 48 rows  4096 110/103, 120/114, 132/137; 7000, 5 % 194/167; 8192 96/90, 109/111, 134/129; 16384 99/96, 113/110, 134/135.
-//                In groups never (59 registers).
+// only a contraction that fills its 64 slots leaves room for (k = 32 keeps two half-empty copies of each: 28 registers through
+// scratch, N = 16, L = 4096, 5 % 103 -> 115 us), 16 buckets per lane instead of 32, whose bounds are worse the longer the list is,
+// more wavefronts per workgroup, whose ranges may not end far beyond the head, and a grid that is not left with half a round at its end
+// (waves between one and two per slot: L = 12288, N = 1, 80.6 us with one tile, 90.5 with two).  One tile and two at 1, 2, 4, 8 %:
+//   rows, k = 64, N L^2 = 2^28: L = 2048 137 and 141, 144/149, 157/166, 196/213; 3072 123/126, 130/136, 151/162, 191/209; 4096 115/103,
+//                126/116, 156/148, 195/194; 8192 119/93, 129/112, 162/142, 202/198; 16384 123/115, 132/133, 163/149, 240/234.  At 1 and 3 %:
+//                6144 119/104, 147/139, 7168 115/110, 158/137, 10240 157/150, 182/184, 12288 140/125, 165/160; with ranges that end 2 %
+//                beyond the head 5000 126/124, 155/162, 6000 118/117, 150/154, 14000 204/197, 244/244, with 14 % 4500 125/139, 150/179,
+//                9000 139/156, 163/191.  Half a round is enough: L = 4096, N = 2, 24.4 and 23.3; L = 8192, N = 1, 41.4 and 38.1.
+//   groups of 8, k = 64, N L^2 = 2^31, at 1, 2, 3, 4, 8 %: 8192 140/118, 155/138, 174/153, 185/190, 228/243; 12288 152/148, 168/165, 181/182,
+//                194/195, 254/272; 16384 139/130, 153/144, 192/161, 178/223, 297/309.  A quarter of a round: 46.0 and 60.2.  (4096 146/134,
+//                155/146, 166/159, 183/179, but 5000, 2 % 87/99: left at one.)
+//   k = 48 rows, at 1, 2, 4 %: 4096 94/92, 101/103, 121/128; 8192 88/82, 102/96, 130/125; 16384 93/92, 104/103, 126/127; others 1 to 9 %
+//                slower (10240, 1 % 120/131).  In groups never (59 registers through scratch).
 inline bool split_pairs(const dsa_shape &sh, int W2, long long waves)
 {
-    if (sh.L < 2048 || sh.L > 16384) return false;
-    if (sh.vec > 1) return sh.L >= 8192 && 32LL * sh.keep <= sh.L && waves >= 4096;
+    const int NW2 = (sh.L + 128 * W2 - 1) / (128 * W2), spare = 128 * W2 * NW2 - sh.L;
+    if (sh.L > 16384 || NW2 < 4 || 64 * spare > sh.L) return false;
+    if (sh.vec > 1) return sh.L > 7168 && 32LL * sh.keep <= sh.L && waves >= 4096;
     if (waves < 2048 || (W2 == 16 && waves > 4096 && waves < 8192)) return false;
-    if (sh.k == 48 && (sh.L < 4096 || (sh.L <= 5120 && 50LL * sh.keep > sh.L))) return false;
-    return 5 * sh.keep <= 4 * 64 * W2 && sh.keep <= sh.L / (sh.L < 4096 ? 32 : 20) + 1;
+    if (sh.k == 48 && NW2 < 8) return false;
+    return 5 * sh.keep <= 4 * 64 * W2 && sh.keep <= sh.L / 20 + 1;
 }
 
 inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
@@ -1028,7 +1032,8 @@ hipError_t launch_split_g(const dsa_shape &sh, const int8_t *Qt, const int8_t *K
     constexpr bool pairs = K == 64 || (K == 48 && !GROUP);
     const SplitPlan p = split_plan(sh, pairs);
     if constexpr (pairs) {
-        if (p.UT == 2 && p.NW <= 4) return launch_split_t<K, GROUP, 2, 16, 4>(sh, p, Qt, Kt, idx, attend, attended, st);
+        if constexpr (K == 64 && !GROUP)     // (the others take two tiles from five words on)
+            if (p.UT == 2 && p.NW <= 4) return launch_split_t<K, GROUP, 2, 16, 4>(sh, p, Qt, Kt, idx, attend, attended, st);
         if (p.UT == 2) return launch_split_t<K, GROUP, 2, 16, 8>(sh, p, Qt, Kt, idx, attend, attended, st);
     }
     if (p.NW == 1) return launch_split_t<K, GROUP, 1, 32, 1>(sh, p, Qt, Kt, idx, attend, attended, st);

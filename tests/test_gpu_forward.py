@@ -87,7 +87,7 @@ def test_list_lengths(dsa, oracle, dtype, d, keep):
     (1, "f32", 2, 256, 64, 1, 16, 4), (2, "f32", 2, 256, 64, 1, 16, 26), (1, "bf16", 1, 1000, 64, 1, 32, 10), (2, "bf16", 1, 1000, 64, 1, 32, 200),
     (2, "f32", 130, 200, 64, 4, 32, 20), (2, "f32", 140, 136, 128, 8, 32, 14), (2, "f32", 2, 1000, 64, 8, 16, 100), (2, "bf16", 130, 200, 64, 8, 32, 20),
     (2, "bf16", 130, 520, 64, 4, 32, 52), (2, "bf16", 140, 264, 64, 8, 16, 33), (2, "bf16", 17, 4104, 64, 8, 64, 205), (2, "bf16", 9, 8200, 64, 8, 64, 410),
-    (1, "bf16", 4, 4100, 64, 1, 64, 60), (1, "bf16", 3, 4096, 64, 1, 32, 410), (2, "bf16", 2, 4096, 128, 1, 48, 1300), (1, "bf16", 16, 777, 128, 1, 96, 39),
+    (1, "bf16", 4, 4100, 64, 1, 64, 60), (1, "bf16", 4, 4090, 64, 1, 64, 60), (1, "f32", 3, 8150, 128, 1, 64, 100), (1, "bf16", 3, 4096, 64, 1, 32, 410), (2, "bf16", 2, 4096, 128, 1, 48, 1300), (1, "bf16", 16, 777, 128, 1, 96, 39),
     (1, "f32", 20, 513, 128, 1, 128, 51), (1, "bf16", 2, 8200, 64, 1, 32, 82),
     (2, "f32", 60, 552, 128, 8, 32, 39), (2, "f32", 8, 4448, 64, 8, 32, 94), (2, "f32", 113, 1216, 64, 8, 16, 17), (1, "f32", 65, 692, 64, 4, 32, 7),
     (1, "f32", 127, 952, 64, 8, 64, 17), (2, "bf16", 108, 264, 64, 4, 16, 14), (2, "bf16", 103, 664, 64, 4, 48, 40), (1, "bf16", 29, 2128, 64, 4, 64, 62)])

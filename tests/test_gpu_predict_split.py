@@ -80,7 +80,8 @@ def test_score_orders(dsa, oracle, L, keep):
 @pytest.mark.parametrize("H,L,vec,k,keep", [
     (2, 512, 1, 16, 30), (2, 512, 8, 48, 30), (2, 512, 1, 128, 30), (2, 1600, 1, 48, 90), (2, 1600, 4, 64, 90), (2, 1600, 8, 96, 90),
     (4, 4096, 1, 16, 205), (5, 4096, 1, 32, 205), (5, 4096, 8, 64, 205), (5, 4096, 1, 112, 205), (1, 12000, 1, 64, 600), (1, 12000, 4, 16, 120),
-    (1, 12000, 8, 128, 120), (16, 2050, 1, 64, 60), (2, 4100, 1, 48, 80), (1, 16384, 1, 64, 500), (16, 8192, 8, 64, 250)])
+    (1, 12000, 8, 128, 120), (16, 2050, 1, 64, 60), (2, 4100, 1, 48, 80), (1, 16384, 1, 64, 500), (16, 8192, 8, 64, 250),
+    (3, 4040, 1, 64, 60), (2, 6100, 1, 64, 60), (2, 8100, 1, 48, 80), (16, 8072, 8, 64, 250)])
 def test_score_orders_in_every_kernel(dsa, oracle, H, L, vec, k, keep):
     """As above, and tiles of 16 units that need no second sweep next to tiles that do (of a workgroup with two tiles one is good
     while the other is swept again)."""
@@ -115,11 +116,14 @@ def test_pairs_of_tiles(dsa, oracle, H, L, vec, k):
         check(dsa, oracle, Qt, Kt, keep, vec, "pairs")
 
 
-# the same where the plan takes two tiles now: half a round of wavefronts, two rounds, long lists of a middling length, the two
-# lengths of a row that differ in wavefronts; and shapes on both sides of every line of the plan
+# the same where the plan takes two tiles now, and on both sides of its lines: ranges that end at the head, 1 to 1/64 of it beyond and
+# farther, four and five words, half a round of wavefronts, two rounds, the longest list, the two lengths that differ in wavefronts
 @pytest.mark.parametrize("H,L,vec,k,keep", [(2, 4100, 1, 64, 409), (2, 4100, 1, 48, 82), (16, 2050, 1, 64, 64), (1, 16384, 1, 64, 512),
                                             (1, 16384, 1, 48, 327), (16, 8192, 8, 64, 256), (8, 8200, 4, 64, 256), (16, 8192, 8, 64, 257),
-                                            (4, 4100, 1, 64, 409), (64, 1040, 1, 64, 10), (16, 8192, 8, 48, 82)])
+                                            (4, 4100, 1, 64, 409), (64, 1040, 1, 64, 10), (16, 8192, 8, 48, 82),
+                                            (2, 4096, 1, 64, 205), (2, 4095, 1, 64, 1), (3, 4033, 1, 64, 200), (3, 4032, 1, 64, 200), (2, 5041, 1, 64, 253), (2, 5042, 1, 64, 253),
+                                            (1, 8192, 1, 64, 409), (1, 8066, 1, 48, 400), (2, 16133, 1, 64, 512), (2, 16161, 1, 48, 160),
+                                            (17, 8064, 8, 64, 252), (17, 8072, 8, 64, 1), (9, 12280, 8, 64, 300), (5, 16136, 4, 64, 500)])
 def test_pairs_of_tiles_in_the_plan(dsa, oracle, H, L, vec, k, keep):
     Qt, Kt = di.random_int8_case(L + H + keep, 1, H, L, k)
     check(dsa, oracle, Qt, Kt, keep, vec, "pairs in the plan")
