@@ -44,10 +44,10 @@ namespace {
 constexpr int kTile = 16;               // units of one matrix instruction
 constexpr int kBins = 128;              // histogram bins per unit
 constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' bins start in different banks
-// Keys of one unit's band that are scored, 16 per slot.  Few-level codes make bands of whole plateaus of equal scores: with 24
-// slots INT4 codes at L = 4096, keep = 205 sweep 1.47 times on average, with 32 the kernel takes 154 us instead of 168.  Where
-// that does not pay (short ranges, whose bands are one bucket, and units of several rows, which have many levels) or the
-// registers are short (two tiles), it is 24: L = 256, 9.5 us against 10.4.
+// Keys of one unit's band that are scored, 16 per slot.  Few-level codes make bands of whole plateaus of equal scores, which are swept
+// again where they do not fit: INT4 codes at L = 4096, keep = 205, 16 high-norm keys per head, with 24 slots 146.7 us (unpacking
+// included), with 32 138.4.  Where that does not pay (short ranges, whose bands are one bucket, and units of several rows, which
+// have many levels) or the registers are short (two tiles), it is 24.
 template <bool GROUP, int UT, int NWM> constexpr int band_slots() { return !GROUP && UT == 1 && NWM >= 4 ? 32 : 24; }
 constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
 
@@ -891,13 +891,16 @@ inline void split_targets(int L, int keep, int NW, int NB, int *target_l, int *t
 // Wavefronts.  A lane's range holds at most 512 keys, which four wavefronts reach up to L = 8192 and eight up to 16384.  More
 // than that pay where they fill an empty chip, and for long lists in long ranges, whose words are then too many for the
 // registers (times of both sides; k = 32 and 5 % unless said):
-//   4 or 8   L = 4608, N = 12: 112 and 166 us; 6144, N = 7: 111 and 129; 6000, N = 3, 10 %: 89 and 85; 8192, N = 4, 2 %: 92 and 101,
-//            N = 2, 10 %, k = 16: 81 and 76; k = 128, 8192: 398 and 362.
-//            Few tiles: L = 777, 294 tiles 12.7 and 11.8, 1024, 256 tiles 9.9 and 9.2, 512 12.2 and 13.3, 768, 672 tiles 15.4 and
-//            18.6; 1536, 96 tiles, k = 16, 7 %: 14.2 and 12.7, 288 tiles 13.5 and 16.6; 2048, 256 tiles 13.5 and 12.7, 512 15.7
-//            and 16.1; 3072, 336 tiles 27.2 and 28.5; 4096, 512 tiles 23.3 and 22.5, 1024 36.1 and 40.9; 8192, 512 38.9 and 36.1.
-//   1 or 4   L = 128, 10 %: 1024 tiles 14.3 and 13.1, 2048 24.1 and 23.4, 4096 36.7 and 40.9.
-//   2 or 4   L = 256, 10 %: 512 tiles 11.1 and 10.1, 1024 11.5 and 13.0; L = 192, 672 tiles 12.0 and 11.8, 1356 15.6 and 19.5.
+//   4 or 8   L = 4608, N = 12: 101 and 153 us; 6144, N = 7: 98 and 117; 8192, N = 4, 2 %: 82 and 94; 8192, N = 2, 10 %, k = 16: 66.9
+//            and 65.1; k = 128, 8192: 367 and 360; groups of 8, 8192, N = 32, 10 %: 183 and 165.  (Four have come to be better beyond
+//            the line too, with lists of up to 5 %, for the mask by itself 8 %: 7000, N = 5, 5 %: 101 and 132, 8192, N = 4: 95 and 108, a
+//            forward 185 and 200, at 8 % 287 and 267.)
+//            Few tiles: L = 777, 294 tiles 12.1 and 11.3, 1024, 256 tiles 10.0 and 9.3, 512 11.1 and 11.6, 768, 672 tiles 13.3 and
+//            16.5; 1536, 96 tiles, k = 16, 7 %: 12.2 and 12.2, 288 tiles 12.9 and 14.6; 2048, 256 tiles 12.4 and 12.0, 512 14.6
+//            and 15.0; 3072, 192 tiles 16.3 and 14.7, 384 18.0 and 18.8; 4096, 512 tiles 22.1 and 21.8, 1024 32.8 and 37.9; 8192, 2 %,
+//            512 29.8 and 28.0, 1024 46.8 and 50.0.
+//   1 or 4   L = 128, 10 %: 1024 tiles 13.3 and 11.2, 2048 22.8 and 19.7, 4096 34.7 and 34.9.
+//   2 or 4   L = 256, 10 %: 512 tiles 10.5 and 9.0, 1024 11.4 and 11.5; L = 192, 672 tiles 11.4 and 10.5, 1356 15.0 and 17.1.
 inline int split_waves(const dsa_shape &sh, long long tiles)
 {
     if (sh.L <= 128) return tiles <= 2048 ? 4 : 1;

@@ -225,7 +225,9 @@ __device__ __forceinline__ void row_scores(const T *Kh, const typename Piece<T>:
     });
 }
 
-// o[r] += weight * value row over the entries of this lane group.  sw: the weights.
+// o[r] += weight * value row over the entries of this lane group.  sw: the weights; entries beyond n weigh 0, and their values are 0 in
+// fp32, since 0 times an infinite value would not be.  (In bf16 an infinite value makes NaN of the neighbouring column anyway, whose
+// product with the weight's zero is NaN.)
 template <typename T, int D, int NR, typename At>
 __device__ __forceinline__ void row_values(const T *Vh, At &&at, const unsigned *sw, int pad, int n, int lane,
                                            float (&o)[NR][Piece<T>::N])
@@ -235,6 +237,17 @@ __device__ __forceinline__ void row_values(const T *Vh, At &&at, const unsigned 
         constexpr int TAIL = decltype(tail)::value;
         typename Piece<T>::raw_t vv[NR][kRowGathers];
         row_gather<T, D, NR, TAIL>(vv, Vh, at, t0, n, lane);
+        if constexpr (TAIL != 0 && sizeof(T) == 4) {
+            const bool in = t0 + (TAIL - 1) * G::RPI + lane / G::LPR < n;
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                typename Piece<T>::raw_t &x = vv[r][TAIL - 1];
+                x.x = in ? x.x : 0;
+                x.y = in ? x.y : 0;
+                x.z = in ? x.z : 0;
+                x.w = in ? x.w : 0;
+            }
+        }
         unsigned w[NR][kRowGathers];
 #pragma unroll
         for (int r = 0; r < NR; ++r)
@@ -242,9 +255,7 @@ __device__ __forceinline__ void row_values(const T *Vh, At &&at, const unsigned 
             for (int u = 0; u < kRowGathers; ++u) w[r][u] = sw[r * pad + t0 + u * G::RPI + lane / G::LPR];
 #pragma unroll
         for (int u = 0; u < kRowGathers; ++u) {
-            // nothing is added for what lies behind the list, not a weight of 0 either: times an infinite value that is not 0
-            if (TAIL && u >= TAIL) continue;
-            if (TAIL && u == TAIL - 1 && t0 + u * G::RPI + lane / G::LPR >= n) continue;
+            if (TAIL && u >= TAIL) continue;      // (0 times an infinite value would not be 0)
 #pragma unroll
             for (int r = 0; r < NR; ++r) Piece<T>::axpy(o[r], w[r][u], vv[r][u]);
         }

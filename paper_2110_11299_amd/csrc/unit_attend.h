@@ -14,11 +14,11 @@ typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-// A unit of vec rows (8 or 4) with bfloat16 inputs by one wavefront, in one pass over the unit's keys: key and value rows of a step of 32 keys are gathered together, one step ahead, and pass through one tile in LDS, the
-// keys first.  Scores as in attention_groups_bf16, but they stay in the lane that owns them (query c, keys 4g..4g+3 of both
-// tiles), which is where the second product wants its weights: neither scores nor weights pass through LDS.  The
-// exponentials are taken relative to a running reference that is moved only when a score exceeds it by a factor of
-// 2^kUnitSlack, so that a step needs no reduction across lanes.
+// A unit of vec rows (8 or 4) with bfloat16 inputs by one wavefront, in one pass over the unit's keys: key and value rows of a step
+// of 32 keys are gathered together, one step ahead, and pass through one tile in LDS, the keys first.  Scores as in
+// attention_groups_bf16, but they stay in the lane that owns them (query c, keys 4g..4g+3 of both tiles), which is where the second
+// product wants its weights: neither scores nor weights pass through LDS.  The exponentials are taken relative to a running
+// reference that is moved only when a score exceeds it by a factor of 2^kUnitSlack, so that a step needs no reduction across lanes.
 // Every list length fits (4 bytes per key and wavefront; 96 KB of LDS with 4096 keys at D = 128).
 //
 // What bounds it: LDS (145 cycles per step and wavefront, two thirds of them the writes of the gathered rows; active 69 % of
@@ -37,8 +37,8 @@ __device__ __forceinline__ unsigned unit_swizzle(unsigned r) { return (r & 3u) <
 
 template <int D> constexpr int unit_tile_bytes() { return 32 * 2 * D; }        // key rows, then value rows
 
-// The unit from its list (key(t): entry t) to its rows of O (both Q and O from the unit's first row on), with a reference that may lag the maximum by a factor of 2^slack.  Returns whether
-// every sum was finite.
+// The unit from its list (key(t): entry t) to its rows of O (both Q and O from the unit's first row on), with a reference that may
+// lag the maximum by a factor of 2^slack.  Returns whether every sum was finite.
 template <int D, typename Key>
 __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, const uint16_t *V, Key &&key, float *O, int vec,
                                           int keep, int keep_pad, float scale, int lane, char *tile, float slack)
