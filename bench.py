@@ -43,8 +43,8 @@ TRAFFIC_SUMMARY = ROOT / "profiles" / "bench_C4_hbm_traffic.md"
 COUNTER_SUMMARY = ROOT / "profiles" / "bench_C4_pmc_counters.md"
 
 # The fine-grained mask prediction by itself; within the forward call its workgroups go on with the attention
-# (the same template with `true`), so that the two stages are timed and counted on the calls that run them alone.
-PREDICTOR = "predict_split<32, false, 1, 32, 8, false>"
+# (the same template with 2 or, in fp32, 1), so that the two stages are timed and counted on the calls that run them alone.
+PREDICTOR = "predict_split<32, false, 1, 32, 8, 0>"
 
 
 def profiled_ratio(row_prefix: str, kernel_prefix: str):
