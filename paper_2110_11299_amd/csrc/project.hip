@@ -40,9 +40,11 @@ template <> struct Chunk<uint16_t> {
 // right operand: block l / 16, column l % 16), and of R the entries (4 s + l / 16, l % 16) of its columns; the left operand of term
 // 4 s + e is broadcast from block e to all four.
 // What bounds it: small tensors the latency of two launches, large ones the rows, 64 cache lines per load instruction, twice from
-// memory.  The rows come in parts of 32 columns, requested as a whole before the first product of the part (fewer registers and
-// more wavefronts than all at once: fp32, d = 128, N = 24, L = 2048, k = 32 20.3 -> 18.7 us; N = 128, L = 4096, d = 64 96 -> 88; left
-// to the compiler each request waits where it is used: 125).  One row per lane on the vector units, R through the scalar cache, ->
+// memory.  The rows come in parts of 64 bytes, requested as a whole before the first product of the part (fewer registers and more
+// wavefronts than all at once; left to the compiler each request waits where it is used: 88 -> 125 us, N = 128, L = 4096, d = 64).  Of
+// 128 bytes, the L1 does not keep the lines of two wavefronts per SIMD: fp32, parts of 32 and of 16 columns, d = 64, k = 64: N = 40,
+// L = 1024 21.7 and 19.0, N = 64, L = 4096 83.9 and 72.7, k = 128 156.9 and 130.7; d = 128, k = 64 141.9 and 130.3, but N = 16, L = 1024
+// 16.8 and 17.3.  One row per lane on the vector units, R through the scalar cache, ->
 // this, both passes: N = 2, L = 256, k = 16 12.1 -> 9.0 us; N = 96, L = 512, k = 32 15.3 -> 12.8; bf16, N = 16, L = 4096, k = 32, INT4
 // 15.6 -> 11.9; bf16, N = 64, L = 2000, k = 16 19.0 -> 13.2; bf16, d = 128, N = 16, L = 8192, k = 64 81 -> 50.
 // A ternary matrix (entries -1, 0, 1: the sparse random projection of equation 5, up to its positive constant sqrt(3/k), which
@@ -63,7 +65,7 @@ __global__ __launch_bounds__(kProjThreads) void project_tiles(const T *__restric
                                                               unsigned rows, int k, unsigned items)
 {
     constexpr int E = Chunk<T>::N;
-    constexpr int PART = 32;                          // columns of X requested at a time
+    constexpr int PART = 64 / sizeof(T);              // columns of X requested at a time
     typedef typename Chunk<T>::raw_t raw_t;
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int c = lane & 15, g = lane >> 4;
@@ -203,8 +205,9 @@ size_t project_workspace_bytes(const dsa_shape &) { return kProjMaxBlocks * size
 
 // Wavefronts of 16 columns above which half as many with 32 each are better: more than the chip has SIMDs, so that two of them
 // would share one and fetch the same rows.  Both ways, a call: 512 (N = 16, L = 1024, k = 32, bf16) 9.7 and 11.7 us, 1024 (fp32,
-// N = 16, L = 2048, d = 128) 15.5 and 19.9; 1536 (fp32, N = 96, L = 512) 15.5 and 12.0, 2048 (N = 16, L = 4096, bf16) 12.8 and 12.1.
-// 64 columns: N = 64, L = 4096, k = 64, bf16 48.0 and 55.6; fp32, d = 128, N = 16, L = 8192 72.2 and 63.9: not kept.
+// N = 16, L = 1024, k = 64) 10.1 and 11.7; 1280 (fp32, N = 40, L = 1024, k = 32) 14.1 and 11.8, 2048 (N = 16, L = 4096, bf16) 12.8 and
+// 12.1, 2250 and 3072 (fp32, N = 64, L = 1125 and N = 96, L = 1024, k = 32) 19.4 and 21.4, 19.8 and 22.3, 4096 25.3 and 21.6.
+// 64 columns: N = 64, L = 4096, k = 64, bf16 48.0 and 55.6; fp32 72.7 and 66.7, but N = 64, L = 1125 28.8 and 32.1: not kept.
 constexpr unsigned kProjWide = 1024;
 
 template <typename T, int D, int NC>
