@@ -40,8 +40,8 @@ template <> struct Chunk<uint16_t> {
 // right operand: block l / 16, column l % 16), and of R the entries (4 s + l / 16, l % 16) of its columns; the left operand of term
 // 4 s + e is broadcast from block e to all four.
 // What bounds it: small tensors the latency of two launches, large ones the rows, 64 cache lines per load instruction, twice from
-// memory.  The rows come in parts of 64 bytes, requested as a whole before the first product of the part (fewer registers and more
-// wavefronts than all at once; left to the compiler each request waits where it is used: 88 -> 125 us, N = 128, L = 4096, d = 64).  Of
+// memory.  The rows come in parts of 64 bytes, requested as a whole before the first product of the part, or of the part before it
+// (kProjAhead) (fewer registers and more wavefronts than all at once; left to the compiler each request waits where it is used: 88 -> 125 us, N = 128, L = 4096, d = 64).  Of
 // 128 bytes, the L1 does not keep the lines of two wavefronts per SIMD: fp32, parts of 32 and of 16 columns, d = 64, k = 64: N = 40,
 // L = 1024 21.7 and 19.0, N = 64, L = 4096 83.9 and 72.7, k = 128 156.9 and 130.7; d = 128, k = 64 141.9 and 130.3, but N = 16, L = 1024
 // 16.8 and 17.3.  One row per lane on the vector units, R through the scalar cache, ->
@@ -57,7 +57,7 @@ constexpr int kProjMaxBlocks = 1024;
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-template <typename T, int D, int NC, int PASS, int BITS, bool TERNARY>
+template <typename T, int D, int NC, int PASS, int BITS, bool TERNARY, bool AHEAD>
 __global__ __launch_bounds__(kProjThreads) void project_tiles(const T *__restrict__ X, const float *__restrict__ R,
                                                               const int8_t *__restrict__ P3,
                                                               float *__restrict__ block_max, int n_block_max,
@@ -81,38 +81,50 @@ __global__ __launch_bounds__(kProjThreads) void project_tiles(const T *__restric
         }
     }
     float seen = 0.f;
+    // A part of a work item: 64 bytes of every row and what they are multiplied with.  AHEAD: one is on its way while another is used.
+    constexpr int PARTS = D / PART, BUFFERS = AHEAD ? 2 : 1;
+    static_assert(PARTS % 2 == 0, "the last part of an item is not in the buffer of the next item's first");
+    struct Part { raw_t x[PART / E]; float r[NC][PART / 4]; };
+    Part part[BUFFERS];
     // work item = (tile of 64 rows, chunk of columns); a wavefront takes items wave, wave + stride, ...
-    for (unsigned item = blockIdx.x * (kProjThreads / kWave) + wave; item < items;
-         item += gridDim.x * (kProjThreads / kWave)) {
+    auto request = [&](Part &to, unsigned item, int p) {
         const unsigned tile = item / chunks;
         const int j0 = (int)(item % chunks) * (kProjCols * NC);
         const raw_t *xp = reinterpret_cast<const raw_t *>(X + (size_t)min(tile * kWave + lane, rows - 1) * D);       // (the last row again beyond it)
+#pragma unroll
+        for (int s = 0; s < PART / 4; ++s)
+#pragma unroll
+            for (int n = 0; n < NC; ++n) {
+                const int e = (p * PART + 4 * s + g) * k + j0 + kProjCols * n + c;
+                to.r[n][s] = TERNARY ? (float)P3[e] : R[e];
+            }
+#pragma unroll
+        for (int i = 0; i < PART / E; ++i) to.x[i] = xp[p * (PART / E) + i];
+        __builtin_amdgcn_sched_barrier(0);       // (else every request moves down to where it is used)
+    };
+    const unsigned stride = gridDim.x * (kProjThreads / kWave), first = blockIdx.x * (kProjThreads / kWave) + wave;
+    if (AHEAD && first < items) request(part[0], first, 0);
+    for (unsigned item = first; item < items; item += stride) {
+        const unsigned tile = item / chunks;
+        const int j0 = (int)(item % chunks) * (kProjCols * NC);
         v16f y[NC];
 #pragma unroll
         for (int n = 0; n < NC; ++n)
 #pragma unroll
             for (int i = 0; i < 16; ++i) y[n][i] = 0.f;
 #pragma unroll
-        for (int p = 0; p < D / PART; ++p) {
-            float ra[NC][PART / 4];
-#pragma unroll
-            for (int s = 0; s < PART / 4; ++s)
-#pragma unroll
-                for (int n = 0; n < NC; ++n) {
-                    const int e = (p * PART + 4 * s + g) * k + j0 + kProjCols * n + c;
-                    ra[n][s] = TERNARY ? (float)P3[e] : R[e];
-                }
-            raw_t xv[PART / E];
-#pragma unroll
-            for (int i = 0; i < PART / E; ++i) xv[i] = xp[p * (PART / E) + i];
-            __builtin_amdgcn_sched_barrier(0);       // (else every request moves down to where it is used)
+        for (int p = 0; p < PARTS; ++p) {
+            if (!AHEAD) request(part[0], item, p);
+            else if (p + 1 < PARTS) request(part[(p + 1) % BUFFERS], item, p + 1);
+            else if (item + stride < items) request(part[0], item + stride, 0);
+            const Part &now = part[p % BUFFERS];
 #pragma unroll
             for (int s = 0; s < PART / 4; ++s) {
                 auto term = [&](auto block) {
                     constexpr int B = decltype(block)::value;
-                    const float xe = Chunk<T>::at(xv[(4 * s + B) / E], (4 * s + B) % E);
+                    const float xe = Chunk<T>::at(now.x[(4 * s + B) / E], (4 * s + B) % E);
 #pragma unroll
-                    for (int n = 0; n < NC; ++n) y[n] = __builtin_amdgcn_mfma_f32_16x16x1f32(ra[n][s], xe, y[n], 2, B, 0);
+                    for (int n = 0; n < NC; ++n) y[n] = __builtin_amdgcn_mfma_f32_16x16x1f32(now.r[n][s], xe, y[n], 2, B, 0);
                 };
                 term(std::integral_constant<int, 0>{});
                 term(std::integral_constant<int, 1>{});
@@ -210,6 +222,14 @@ size_t project_workspace_bytes(const dsa_shape &) { return kProjMaxBlocks * size
 // 64 columns: N = 64, L = 4096, k = 64, bf16 48.0 and 55.6; fp32 72.7 and 66.7, but N = 64, L = 1125 28.8 and 32.1: not kept.
 constexpr unsigned kProjWide = 1024;
 
+// Work items up to which (per 64 columns of X; at d = 128 any number of 32 columns each) a part is requested while the one before it is used.  The registers of two parts leave room for three
+// wavefronts per SIMD instead of four, which counts where that many come: without and with, a call: 768 items (N = 96, L = 512,
+// k = 32, fp32) 12.3 and 11.2 us, 1024 (N = 16, L = 4096, bf16) 12.9 and 12.0, 2000 (N = 64, L = 2000, k = 16, bf16) 13.7 and 12.8, 2250
+// (N = 64, L = 1125, k = 64, fp32) 28.7 and 28.3; 3516 (N = 50, L = 1125, k = 128, fp32) 36.7 and 38.2, 8192 (N = 64, L = 4096, k = 64, bf16) 48.4
+// and 51.0.  At d = 128 (twice the parts) 2048 items (N = 4, L = 16384, k = 64, bf16) 27.1 and 26.2, 4096 (N = 16, L = 8192) 49.6 and 46.6, 8192
+// (N = 64, L = 4096, fp32) 128.7 and 120.3; 16 columns each 2304 (N = 96, L = 512, k = 48, fp32) 34.7 and 31.1, but 4608 (N = 192, bf16) 37.2 and 39.1.
+constexpr unsigned kProjAhead = 2048;
+
 template <typename T, int D, int NC>
 hipError_t launch_project_t(const dsa_shape &sh, int bits, const T *X, const float *R, const int8_t *P3, void *Xt,
                             float *amax_out, void *ws, hipStream_t st)
@@ -225,14 +245,18 @@ hipError_t launch_project_t(const dsa_shape &sh, int bits, const T *X, const flo
                            items);
         return hipGetLastError();
     };
-    auto both = [&](auto ternary_tag) -> hipError_t {
-        constexpr bool TERNARY = decltype(ternary_tag)::value;
-        if (hipError_t e = go(project_tiles<T, D, NC, 0, 8, TERNARY>)) return e;
-        if (bits == 8) return go(project_tiles<T, D, NC, 1, 8, TERNARY>);
-        if (bits == 4) return go(project_tiles<T, D, NC, 1, 4, TERNARY>);
-        return go(project_tiles<T, D, NC, 1, 2, TERNARY>);
+    auto both = [&](auto ternary_tag, auto ahead_tag) -> hipError_t {
+        constexpr bool TERNARY = decltype(ternary_tag)::value, AHEAD = decltype(ahead_tag)::value;
+        if (hipError_t e = go(project_tiles<T, D, NC, 0, 8, TERNARY, AHEAD>)) return e;
+        if (bits == 8) return go(project_tiles<T, D, NC, 1, 8, TERNARY, AHEAD>);
+        if (bits == 4) return go(project_tiles<T, D, NC, 1, 4, TERNARY, AHEAD>);
+        return go(project_tiles<T, D, NC, 1, 2, TERNARY, AHEAD>);
     };
-    return P3 ? both(std::true_type{}) : both(std::false_type{});
+    auto either = [&](auto ternary_tag) -> hipError_t {
+        if constexpr (D == 128 && NC == 2) return both(ternary_tag, std::true_type{});
+        else return items <= kProjAhead * (D / 64) ? both(ternary_tag, std::true_type{}) : both(ternary_tag, std::false_type{});
+    };
+    return P3 ? either(std::true_type{}) : either(std::false_type{});
 }
 
 template <typename T>
