@@ -429,10 +429,11 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                 }
             }
             float sum = (float)all;
-            mn = min(mn, __shfl_xor(mn, 16, kWave));
-            mn = min(mn, __shfl_xor(mn, 32, kWave));
-            sum += __shfl_xor(sum, 16, kWave);
-            sum += __shfl_xor(sum, 32, kWave);
+            Halves a = row_halves(mn), b = wave_halves(min(a.lower, a.upper));
+            mn = min(b.lower, b.upper);
+            a = row_halves(__float_as_int(sum));
+            b = wave_halves(__float_as_int(__int_as_float(a.lower) + __int_as_float(a.upper)));
+            sum = __int_as_float(b.lower) + __int_as_float(b.upper);
             if (g == 0) {
                 s_totl[wv * U + kTile * t + c] = mn;
                 s_sum[wv * U + kTile * t + c] = sum;
@@ -657,10 +658,8 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
         const uint16_t *ul = list + u * kBandCap;
         const unsigned char *uq = s_q + u * qstride;
         // (the loops over slots leave where the band ends: one taken branch, not one per slot that is skipped)
-        int sc[kBandSlots];
+        int sc[kBandSlots];                        // (those behind the last slots that the band reaches are not looked at)
         int peak = INT32_MIN;
-#pragma unroll
-        for (int i = 0; i < kBandSlots; ++i) sc[i] = INT32_MIN;
 #pragma unroll
         for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
             if (16 * i0 >= most) break;

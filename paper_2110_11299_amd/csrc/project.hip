@@ -9,6 +9,7 @@
 // never stored.
 #include "dsa_internal.h"
 #include "project_api.h"
+#include "wave_select.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -140,9 +141,7 @@ __global__ __launch_bounds__(kProjThreads) void project_tiles(const T *__restric
 #pragma unroll
                 for (int i = 0; i < 16; ++i) seen = fmaxf(seen, fabsf(y[n][i]));
         } else {
-            float all = amax;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) all = fmaxf(all, __shfl_xor(all, off, kWave));
+            const float all = wave_all_max(amax);
             if (amax_out && item == 0 && lane == 0) *amax_out = all;
             const float scale = all > 0.f ? __fdiv_rn(kQmax, all) : 0.f;
 #pragma unroll
@@ -168,8 +167,7 @@ __global__ __launch_bounds__(kProjThreads) void project_tiles(const T *__restric
     }
     if (PASS == 0) {
         __shared__ float red[kProjThreads / kWave];
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) seen = fmaxf(seen, __shfl_xor(seen, off, kWave));
+        seen = wave_all_max(seen);
         if (lane == 0) red[wave] = seen;
         __syncthreads();
         if (threadIdx.x == 0) {

@@ -70,52 +70,6 @@ template <> struct Piece<uint16_t> {
     }
 };
 
-// x from the lane that differs in bit log2(OFF) of its number; for OFF = 4 from the mirror image in the lane's 8 (which lies in the
-// other half of them: as good where all 8 are summed).
-template <int OFF> __device__ __forceinline__ float other_half(float x)
-{
-    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8, "DPP reaches a row of 16 lanes");
-    constexpr int CTRL = OFF == 1 ? kDppXor1 : OFF == 2 ? kDppXor2 : OFF == 4 ? kDppHalfMirror : 0x128 /* row_ror:8 */;
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
-}
-// Lanes whose bit log2(OFF) is clear get x summed over both halves, the others y.  v_permlane32_swap exchanges the upper half of
-// x with the lower half of y, v_permlane16_swap the odd rows of 16 of x with the even ones of y.
-template <int OFF> __device__ __forceinline__ float halves_sum(float x, float y, int lane)
-{
-    if constexpr (OFF >= 16) {
-        const unsigned a = __float_as_uint(x), b = __float_as_uint(y);
-        const auto s = OFF == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false) : __builtin_amdgcn_permlane16_swap(a, b, false, false);
-        return __uint_as_float(s[0]) + __uint_as_float(s[1]);
-    } else {
-        const float sx = x + other_half<OFF>(x), sy = y + other_half<OFF>(y);
-        return (lane & OFF) ? sy : sx;
-    }
-}
-// x summed over both halves, in all lanes.
-template <int OFF> __device__ __forceinline__ float halves_sum(float x)
-{
-    if constexpr (OFF >= 16) return halves_sum<OFF>(x, x, 0);
-    else return x + other_half<OFF>(x);
-}
-template <int OFF> __device__ __forceinline__ float halves_max(float x)
-{
-    if constexpr (OFF >= 16) {
-        const unsigned a = __float_as_uint(x);
-        const auto s = OFF == 32 ? __builtin_amdgcn_permlane32_swap(a, a, false, false) : __builtin_amdgcn_permlane16_swap(a, a, false, false);
-        return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
-    } else {
-        return fmaxf(x, other_half<OFF>(x));
-    }
-}
-__device__ __forceinline__ float wave_all_sum(float x)
-{
-    return halves_sum<32>(halves_sum<16>(halves_sum<8>(halves_sum<4>(halves_sum<2>(halves_sum<1>(x))))));
-}
-__device__ __forceinline__ float wave_all_max(float x)
-{
-    return halves_max<32>(halves_max<16>(halves_max<8>(halves_max<4>(halves_max<2>(halves_max<1>(x))))));
-}
-
 // Sums of N values (1, 2 or 4) over the LPR neighbouring lanes that hold a row: a step towards fewer lanes also halves the number
 // of values, so four take 10 instructions instead of 12 (LPR = 8) and their results are in one register: lane l has that of
 // value piece_slot<LPR, N>(l).

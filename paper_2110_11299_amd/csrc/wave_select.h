@@ -1,4 +1,4 @@
-// Wavefront-level selection primitives shared by the predictor kernels: DPP reductions and scans, the
+// Wavefront-level primitives shared by the kernels: reductions and scans without LDS, the
 // lowest set bits of a word, and the exact int8 score of one (unit, key) pair.  Device code only; everything is
 // internal to the translation unit that includes it.
 #pragma once
@@ -14,9 +14,11 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 // Wavefront reductions without LDS traffic: butterfly inside each row of 16 lanes with DPP
 // (quad permutes, then the two mirrors), then the four row results through v_readlane into
 // scalar registers.  The result is wavefront-uniform and lives in an SGPR.
+// (every lane has a source, so that what stands in for a missing one does not matter; with 0 the compiler makes one instruction of the
+// move and what is done with it)
 template <int CTRL> __device__ __forceinline__ int dpp_move(int x)
 {
-    return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
+    return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, true);
 }
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
 
@@ -45,16 +47,74 @@ __device__ __forceinline__ int wave_incl_scan(int x, int lane, int *total)
     return x;
 }
 
+// x of the even and of the odd row of 16 in every pair of rows, and of the lower and the upper 32 lanes: both in all lanes.
+// v_permlane16_swap exchanges the odd rows of its first operand with the even ones of its second, v_permlane32_swap the upper half of
+// the first with the lower half of the second.
+struct Halves { int lower, upper; };
+__device__ __forceinline__ Halves row_halves(int x)
+{
+    const auto s = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
+    return Halves{(int)s[0], (int)s[1]};
+}
+__device__ __forceinline__ Halves wave_halves(int x)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
+    return Halves{(int)s[0], (int)s[1]};
+}
+
 // Exclusive prefix and total of a per-lane count over the four lanes (c, 0..3) of a unit, in lane
 // order g = 0..3.
 __device__ __forceinline__ int unit_excl_scan(int x, int g, int *total)
 {
-    const int s1 = __shfl_xor(x, 16, kWave);      // lane g ^ 1
-    const int s2 = __shfl_xor(x, 32, kWave);      // lane g ^ 2
-    const int s3 = __shfl_xor(s1, 32, kWave);     // lane g ^ 3
-    *total = x + s1 + s2 + s3;
-    // g ^ 1 < g iff bit 0 of g is set; g ^ 2 < g and g ^ 3 < g iff bit 1 is set
-    return ((g & 1) ? s1 : 0) + ((g & 2) ? s2 + s3 : 0);
+    const Halves a = row_halves(x), b = wave_halves(a.lower + a.upper);
+    *total = b.lower + b.upper;
+    return ((g & 1) ? a.lower : 0) + ((g & 2) ? b.lower : 0);
+}
+
+// x from the lane that differs in bit log2(OFF) of its number; for OFF = 4 from the mirror image in the lane's 8 (which lies in the
+// other half of them: as good where all 8 are summed).
+template <int OFF> __device__ __forceinline__ float other_half(float x)
+{
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8, "DPP reaches a row of 16 lanes");
+    constexpr int CTRL = OFF == 1 ? kDppXor1 : OFF == 2 ? kDppXor2 : OFF == 4 ? kDppHalfMirror : 0x128 /* row_ror:8 */;
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+// Lanes whose bit log2(OFF) is clear get x summed over both halves, the others y.  v_permlane32_swap exchanges the upper half of
+// x with the lower half of y, v_permlane16_swap the odd rows of 16 of x with the even ones of y.
+template <int OFF> __device__ __forceinline__ float halves_sum(float x, float y, int lane)
+{
+    if constexpr (OFF >= 16) {
+        const unsigned a = __float_as_uint(x), b = __float_as_uint(y);
+        const auto s = OFF == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false) : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    } else {
+        const float sx = x + other_half<OFF>(x), sy = y + other_half<OFF>(y);
+        return (lane & OFF) ? sy : sx;
+    }
+}
+// x summed over both halves, in all lanes.
+template <int OFF> __device__ __forceinline__ float halves_sum(float x)
+{
+    if constexpr (OFF >= 16) return halves_sum<OFF>(x, x, 0);
+    else return x + other_half<OFF>(x);
+}
+template <int OFF> __device__ __forceinline__ float halves_max(float x)
+{
+    if constexpr (OFF >= 16) {
+        const unsigned a = __float_as_uint(x);
+        const auto s = OFF == 32 ? __builtin_amdgcn_permlane32_swap(a, a, false, false) : __builtin_amdgcn_permlane16_swap(a, a, false, false);
+        return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+    } else {
+        return fmaxf(x, other_half<OFF>(x));
+    }
+}
+__device__ __forceinline__ float wave_all_sum(float x)
+{
+    return halves_sum<32>(halves_sum<16>(halves_sum<8>(halves_sum<4>(halves_sum<2>(halves_sum<1>(x))))));
+}
+__device__ __forceinline__ float wave_all_max(float x)
+{
+    return halves_max<32>(halves_max<16>(halves_max<8>(halves_max<4>(halves_max<2>(halves_max<1>(x))))));
 }
 
 // Makes LDS writes of some lanes of a wavefront visible to reads of its other lanes.
