@@ -5,7 +5,10 @@
 // (about 1 flop per byte), so everything else stays on chip: S and P never reach HBM in the fused mode.
 #include "dsa_internal.h"
 #include "attention_api.h"
-#include "unit_attend.h"
+#include "predict_api.h"
+#include "tile_attend.h"
+
+#include <algorithm>
 
 namespace dsa {
 namespace {
@@ -358,6 +361,74 @@ __global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
     attend_unit<D>(Q + first, K + head, V + head, [&](int t) { return min(max(list[t], 0), L - 1); }, O + first, VEC, keep, keep_pad, scale, tile);
 }
 
+// Fine-grained rows in bfloat16, 16 to a workgroup, over the union of their lists (tile_attend.h): what predict_split does with lists that
+// it has made, for lists that are given.  The union comes from a word of LDS per two keys (which needs their 2 L bytes to fit what the
+// tiles take later).  Rows that have a key twice, as entries outside of [0, L) may when they are clamped, and sums that are not
+// finite go to the loops of attention_rows.
+__global__ __launch_bounds__(512, 4) void attention_tiles_bf16(AttendArgs a, const int32_t *__restrict__ idx, int L, int keep, int tiles_per_head)
+{
+    extern __shared__ __align__(16) char lds_raw[];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(tid / kWave), T = blockDim.x, W = T / kWave;
+    const unsigned wg = xcd_contiguous(blockIdx.x, gridDim.x), n = wg / (unsigned)tiles_per_head;
+    const int u0 = (int)(wg % (unsigned)tiles_per_head) * kTileRows, nu = min(kTileRows, L - u0);
+    char *room = lds_raw;
+    const TileLds at(W, a.most);
+    unsigned *masks = reinterpret_cast<unsigned *>(room + at.work), *entries = reinterpret_cast<unsigned *>(room + at.list);
+    const int words = (L + 1) / 2;
+    for (int e = tid; 4 * e < words; e += T) reinterpret_cast<v4u *>(masks)[e] = v4u{0, 0, 0, 0};
+    const int32_t *lists = idx + ((size_t)n * L + u0) * keep;
+    __syncthreads();
+    for (int e = tid, r = tid / keep, t = tid % keep; e < nu * keep; e += T) {      // entry t of row r
+        const unsigned key = min(max(lists[e], 0), L - 1);
+        atomicOr(&masks[key >> 1], 1u << (r + 16 * (key & 1)));
+        r += T / keep;
+        t += T % keep;
+        if (t >= keep) {
+            t -= keep;
+            ++r;
+        }
+    }
+    __syncthreads();
+    const int share = (words + T - 1) / T * kWave, first = wv * share;          // words of a wavefront
+    int mine = 0, kept = 0;
+    for (int e = first + lane; e - lane < first + share; e += kWave) {
+        const unsigned m = e < words ? masks[e] : 0u;
+        mine += __popcll(__ballot((m & 0xffffu) != 0)) + __popcll(__ballot((m >> 16) != 0));
+        kept += __popc(m);
+    }
+    kept = wave_sum(kept);
+    int *counts = reinterpret_cast<int *>(room);
+    if (lane == 0) {
+        counts[2 * wv] = mine;
+        counts[2 * wv + 1] = kept;
+    }
+    __syncthreads();
+    int total = 0, pos = 0, all = 0;
+    for (int w = 0; w < W; ++w) {
+        pos += w < wv ? counts[2 * w] : 0;
+        total += counts[2 * w];
+        all += counts[2 * w + 1];
+    }
+    total = __builtin_amdgcn_readfirstlane(total);
+    if (__builtin_amdgcn_readfirstlane(all) == nu * keep) {
+        if (wv == 0) tile_fill(entries, total, lane);
+        for (int e = first + lane; e - lane < first + share; e += kWave) {
+            const unsigned m = e < words ? masks[e] : 0u, lo = m & 0xffffu, hi = m >> 16;
+            const unsigned long long blo = __ballot(lo != 0), bhi = __ballot(hi != 0), below = (1ull << lane) - 1;
+            int to = pos + __popcll(blo & below) + __popcll(bhi & below);
+            if (lo) entries[to++] = (unsigned)(2 * e) << 16 | lo;
+            if (hi) entries[to] = (unsigned)(2 * e + 1) << 16 | hi;
+            pos += __popcll(blo) + __popcll(bhi);
+        }
+        __syncthreads();
+        const size_t head = (size_t)n * L * 64, row = head + (size_t)u0 * 64;
+        if (attend_tile(static_cast<const uint16_t *>(a.Q) + row, static_cast<const uint16_t *>(a.K) + head, static_cast<const uint16_t *>(a.V) + head,
+                        a.O + row, nu, total, a.scale, a.most, room))
+            return;
+    }
+    attend_listed(a, lists, room, L, keep, n, u0, nu);
+}
+
 // Softmax over the `keep` scores of each row: one wavefront per row.
 __global__ __launch_bounds__(kRowWaves *kWave) void softmax_rows(const float *S, float *P, int keep,
                                                                   unsigned total_rows)
@@ -469,6 +540,18 @@ hipError_t launch_units(const dsa_shape &sh, const void *Q, const void *K, const
     return hipGetLastError();
 }
 
+hipError_t launch_tiles(const dsa_shape &sh, int W, int most, const void *Q, const void *K, const void *V, const int32_t *idx, float *O,
+                        hipStream_t st)
+{
+    const int tiles_per_head = (sh.L + kTileRows - 1) / kTileRows;
+    const int keep_pad = (sh.keep + kRowPad - 1) / kRowPad * kRowPad;
+    const size_t lds = tile_lds_bytes(sh, W, most);
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(attention_tiles_bf16), lds)) return e;
+    hipLaunchKernelGGL(attention_tiles_bf16, dim3((unsigned)sh.B * sh.H * tiles_per_head), dim3(W * kWave), lds, st,
+                       AttendArgs{Q, K, V, O, sh.scale, sh.d, keep_pad, most, (unsigned)lds}, idx, sh.L, sh.keep, tiles_per_head);
+    return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_groups_d(AttnMode mode, const dsa_shape &sh, const void *Q, const void *K, const void *V,
                            const int32_t *idx, const float *Pin, float *S, float *O, hipStream_t st)
@@ -496,6 +579,10 @@ hipError_t launch_attention(AttnMode mode, const dsa_shape &sh, const void *Q, c
         if (sh.vec == 8)
             return sh.d == 64 ? launch_units<64, 8>(sh, Q, K, V, idx, O, st) : launch_units<128, 8>(sh, Q, K, V, idx, O, st);
         return sh.d == 64 ? launch_units<64, 4>(sh, Q, K, V, idx, O, st) : launch_units<128, 4>(sh, Q, K, V, idx, O, st);
+    }
+    if (mode == kFused) {
+        const int W = predict_waves(sh);
+        if (const int most = tile_most(sh, W)) return launch_tiles(sh, W, most, Q, K, V, idx, O, st);
     }
     if (sh.vec == 8 && groups_lds_bytes(sh) <= 144 * 1024) {
         if (sh.d == 64) return launch_groups_d<64>(mode, sh, Q, K, V, idx, Pin, S, O, st);

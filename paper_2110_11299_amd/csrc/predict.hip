@@ -2,6 +2,7 @@
 // section 3.1 by itself: row maxima of S~ = Q~ K~^T, and the int8 matrix-core yardstick.
 #include "dsa_internal.h"
 #include "predict_api.h"
+#include "split_plan.h"
 #include "wave_select.h"
 
 namespace dsa {
@@ -134,6 +135,12 @@ __global__ __launch_bounds__(512) void rowmax_mfma(
 }  // namespace
 
 int predict_max_L() { return 32768; }
+
+int predict_waves(const dsa_shape &sh)
+{
+    const SplitPlan p = split_plan(sh, split_pairs_exist(sh.k, sh.vec > 1));
+    return p.UT == 1 ? p.W : 0;
+}
 
 size_t predict_workspace_bytes(const dsa_shape &) { return 0; }
 

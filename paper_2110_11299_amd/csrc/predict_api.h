@@ -11,6 +11,9 @@ struct AttendPtrs { const void *Q, *K, *V; float *O; };
 hipError_t launch_predict(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, void *ws,
                           const AttendPtrs *attend, bool *attended, hipStream_t st);
 size_t predict_workspace_bytes(const dsa_shape &sh);
+// Wavefronts of the workgroups of a launch_predict that have one tile of units (the attention of a tile by itself takes as many, and sums
+// in the same order), 0 where they have two.
+int predict_waves(const dsa_shape &sh);
 hipError_t launch_rowmax(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *rowmax,
                          hipStream_t st);
 hipError_t launch_mfma_i8_stream(int blocks, int iters, int32_t *sink, hipStream_t st);

@@ -21,7 +21,8 @@
 //              lanes per unit; the exact threshold is found by interpolation and bisection in turn, ties go to the lower key.
 //   emission   every lane turns its words into key indices at its place in the unit's row, in LDS; the rows leave as
 //              one contiguous block.
-//   attention  where it pays, over the lists while they are in LDS (row_attend.h).
+//   attention  where it pays, over the lists while they are in LDS (row_attend.h, unit_attend.h), or over their union, which comes from the
+//              bitmaps in the registers (tile_attend.h).
 //
 // What bounds it: vector-ALU issue (half an operation per score in sweep 1, two in sweep 2, about 25 per candidate).
 // Splitting the keys rather than giving a wavefront whole units keeps the bitmaps in registers, needs a quarter of the
@@ -30,9 +31,10 @@
 
 #include "dsa_internal.h"
 #include "predict_api.h"
+#include "split_plan.h"
 #include "key_rows.h"
 #include "key_stream.h"
-#include "unit_attend.h"
+#include "tile_attend.h"
 
 #include <math.h>
 
@@ -41,7 +43,6 @@
 namespace dsa {
 namespace {
 
-constexpr int kTile = 16;               // units of one matrix instruction
 constexpr int kBins = 128;              // histogram bins per unit
 constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' bins start in different banks
 // Keys of one unit's band that are scored, 16 per slot.  Few-level codes make bands of whole plateaus of equal scores, which are swept
@@ -51,15 +52,9 @@ constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' b
 template <bool GROUP, int UT, int NWM> constexpr int band_slots() { return !GROUP && UT == 1 && NWM >= 4 ? 32 : 24; }
 constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
 
-// The attention that a workgroup goes on with, over the lists it has just made (see attend_here): fp32 rows, or bf16 rows (of units
-// of several rows: the units on the matrix cores).
-enum AttendKind { kNoAttend, kAttendF32, kAttendBf16 };
-struct AttendArgs {
-    const void *Q, *K, *V;
-    float *O;
-    float scale;
-    int d, pad;                         // list length rounded up to kRowPad
-};
+// The attention that a workgroup goes on with, over the lists it has just made (see attend_here): fp32 rows, bf16 rows (of units
+// of several rows: the units on the matrix cores), or bf16 rows over the union of their lists, on the matrix cores.
+enum AttendKind { kNoAttend, kAttendF32, kAttendBf16, kAttendTile };
 
 struct SplitArgs {
     const int8_t *Qt, *Kt;
@@ -117,38 +112,6 @@ __device__ __forceinline__ int row_sum_above(int x)
     return s - x;
 }
 
-// Rows a wavefront attends to at a time: a gather of each is as good as another gather of one, and the steps between the gathers
-// overlap.  bf16 1, 2, 4 rows, k = 32: N = 16, L = 4096, keep = 205 211.7, 202.2, 210.4 us, keep = 410 323, 307, 356; fp32 (a
-// quarter of the sums per row) 2 and 4, k = 16: N = 512, L = 256, keep = 26 113.7 and 103.8, N = 128, L = 1024, keep = 102 256 and 249.
-template <typename T> constexpr int attend_rows_at_once() { return sizeof(T) == 2 ? 2 : 4; }
-
-// The rows of the workgroup's nu units.  image: the units' lists; lds: room for attend_rows_at_once() * pad words per wavefront.
-template <typename T, int D>
-__device__ __forceinline__ void attend_block(const AttendArgs &a, const uint16_t *image, unsigned *lds, int L, int keep, int vec, unsigned n, int u0, int nu)
-{
-    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), W = blockDim.x / kWave;
-    constexpr int NR = attend_rows_at_once<T>(), LPR = RowShape<T, D>::LPR, E = Piece<T>::N;
-    const size_t head = (size_t)n * L * D;
-    const T *Kh = static_cast<const T *>(a.K) + head, *Vh = static_cast<const T *>(a.V) + head, *Qh = static_cast<const T *>(a.Q) + head;
-    lds += wv * NR * a.pad;
-    const int total = nu * vec;
-    for (int p = wv; NR * p < total; p += W) {
-        typename Piece<T>::raw_t q[NR];
-        const uint16_t *list[NR];
-        float *out[NR];
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int j = min(NR * p + r, total - 1);          // (a row that is there twice is written twice)
-            const size_t row = (size_t)(u0 * vec + j) * D;
-            q[r] = Piece<T>::load(Qh + row + lane % LPR * E);
-            list[r] = image + (vec == 1 ? j : j / vec) * keep;
-            out[r] = a.O + head + row;
-        }
-        auto at = [&](int r, int t) { return (unsigned)list[r][t] * (unsigned)(D * sizeof(T)); };
-        attend_rows<T, D, NR>(Kh, Vh, q, at, lds, a.pad, keep, a.scale, out, lane);
-    }
-}
-
 // The workgroup's nu units of vec rows, one at a time per wavefront.  lds: room for a tile and the list per wavefront.
 template <int D>
 __device__ __forceinline__ void attend_block_units(const AttendArgs &a, const uint16_t *image, char *lds, int L, int keep, int vec, unsigned n, int u0, int nu)
@@ -162,6 +125,81 @@ __device__ __forceinline__ void attend_block_units(const AttendArgs &a, const ui
                        lds + wv * (unit_tile_bytes<D>() + a.pad * 4));
         wave_lds_sync();                   // the next unit overwrites list and tile
     }
+}
+
+// Bits of a square of 16 x 16, twice: lane c of a row of 16 has row c in its lower half word (and another square's in the upper one) and
+// gets column c.
+struct Transpose16 {
+    unsigned amount[4], stays[4];
+    __device__ __forceinline__ explicit Transpose16(int c)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const unsigned s = 1u << i, low = i == 0 ? 0x55555555u : i == 1 ? 0x33333333u : i == 2 ? 0x0f0f0f0fu : 0x00ff00ffu;
+            amount[i] = c & s ? s : 32 - s;            // what comes from the other lane goes s down or up
+            stays[i] = c & s ? ~low : low;
+        }
+    }
+    __device__ __forceinline__ unsigned step(unsigned x, unsigned other, int i) const
+    {
+        return (x & stays[i]) | (__builtin_amdgcn_alignbit(other, other, amount[i]) & ~stays[i]);
+    }
+    __device__ __forceinline__ unsigned operator()(unsigned x) const
+    {
+        x = step(x, (unsigned)dpp_move<0x128>((int)x), 3);                                     // lane ^ 8 (row_ror:8)
+        x = step(x, (unsigned)dpp_move<0x1B>(dpp_move<kDppHalfMirror>((int)x)), 2);            // lane ^ 4: ^ 7, then ^ 3
+        x = step(x, (unsigned)dpp_move<kDppXor2>((int)x), 1);
+        return step(x, (unsigned)dpp_move<kDppXor1>((int)x), 0);
+    }
+};
+
+// The union of the lists of a tile's units from their bitmaps: word w of a lane holds the keys first + 32 w .. of unit c that are kept
+// (live: the unit exists).  Entries as in tile_attend.h, keys ascending.  Returns their number.  counts: a word per wavefront.  What was at
+// `entries` may be read until the barrier in here.
+template <int NWM>
+__device__ __forceinline__ int union_entries(const unsigned (&words)[NWM], int NW, int first, bool live, unsigned *entries, int *counts)
+{
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), W = blockDim.x / kWave;
+    const int c = lane & 15, g = lane >> 4;
+    const Transpose16 transpose(c);
+    unsigned m[NWM];                       // keys first + 32 w + c and 16 more: the units that keep them, 16 bits each
+    int mine = 0;
+#pragma unroll
+    for (int w = 0; w < NWM; ++w) {
+        m[w] = 0;
+        if (w < NW) {
+            m[w] = transpose(live ? words[w] : 0u);
+            mine += ((m[w] & 0xffffu) != 0) + ((m[w] >> 16) != 0);
+        }
+    }
+    int all;
+    int pos = unit_excl_scan(row_sum(mine), g, &all);
+    if (lane == 0) counts[wv] = all;
+    __syncthreads();
+    int total = 0;
+    for (int w = 0; w < W; ++w) {
+        pos += w < wv ? counts[w] : 0;
+        total += counts[w];
+    }
+    total = __builtin_amdgcn_readfirstlane(total);
+    if (wv == 0) tile_fill(entries, total, lane);
+    const unsigned below = (1u << c) - 1u, shift = 16 * (g & 1);
+#pragma unroll
+    for (int w = 0; w < NWM; ++w) {
+        if (w < NW) {
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const bool kept = half ? m[w] >> 16 : m[w] & 0xffffu;
+                const unsigned long long b = __ballot(kept);
+                const unsigned row = ((g & 2 ? (unsigned)(b >> 32) : (unsigned)b) >> shift) & 0xffffu;      // of the keys that this row of lanes has
+                const unsigned key = first + 32 * w + 16 * half + c;
+                if (kept) entries[pos + __popc(row & below)] = half ? __builtin_amdgcn_alignbit(key, m[w], 16) : (key << 16) | (m[w] & 0xffffu);
+                pos += __popc(row);
+            }
+        }
+    }
+    __syncthreads();
+    return total;
 }
 
 // K: the projection dimension (16, 32, 48, 64, 128), or 0 for any other (up to 112, two contraction steps).
@@ -833,126 +871,27 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     if constexpr (ATTEND != kNoAttend) {
         unsigned *room = reinterpret_cast<unsigned *>(lds + at.attend);     // behind the image: nobody else reads or writes there any more
         const int vec = GROUP ? a.vec : 1;
-        if constexpr (GROUP && ATTEND == kAttendBf16) {
+        if constexpr (ATTEND == kAttendTile) {
+            static_assert(UT == 1, "one tile of units");
+            const size_t head = (size_t)n * L * 64;
+            const uint16_t *Q = static_cast<const uint16_t *>(a.attend.Q) + head, *Kx = static_cast<const uint16_t *>(a.attend.K) + head,
+                           *V = static_cast<const uint16_t *>(a.attend.V) + head;
+            // (from where the image was: the lists are in memory, and the bitmaps still in the registers)
+            char *tile = reinterpret_cast<char *>(image);
+            const int total = union_entries<NWM>(wl[0], NW, h * Lr, c < nu, reinterpret_cast<unsigned *>(tile + TileLds(W, a.attend.most).list), s_totl);
+            if (!attend_tile(Q + (size_t)u0 * 64, Kx, V, a.attend.O + head + (size_t)u0 * 64, nu, total, a.attend.scale, a.attend.most, tile))
+                attend_listed(a.attend, out, tile, L, keep, n, u0, nu);
+        } else if constexpr (GROUP && ATTEND == kAttendBf16) {
             attend_block_units<64>(a.attend, image, reinterpret_cast<char *>(room), L, keep, vec, n, u0, nu);
         } else {
             typedef std::conditional_t<ATTEND == kAttendF32, float, uint16_t> T;
-            if (a.attend.d == 64) attend_block<T, 64>(a.attend, image, room, L, keep, vec, n, u0, nu);
-            else attend_block<T, 128>(a.attend, image, room, L, keep, vec, n, u0, nu);
+            if (a.attend.d == 64) attend_block<T, 64>(a.attend, image, room, L, keep, vec, n, u0, nu, W);
+            else attend_block<T, 128>(a.attend, image, room, L, keep, vec, n, u0, nu, W);
         }
     }
 }
 
 // ---- host side -----------------------------------------------------------------------------------------------------------
-
-struct SplitPlan { int W, NW, UT, NB, target_l, target_h; };
-
-// Targets.  If a share p of a unit's keys lies above a threshold, a bucket of s keys reaches it with probability
-// 1 - (1 - p)^s; the number of buckets that reach it, given the number x of keys that do, has the mean D(x) below and a
-// variance that is the binomial one less what x explains.  tl is put where keep + z sigma keys are expected above it,
-// th where keep - z sigma are: with z = 3.5 a unit misses in about one case of 2000 (and is then swept again).
-inline void split_targets(int L, int keep, int NW, int NB, int *target_l, int *target_h)
-{
-    if (NW == 1) {                       // every key is its own bucket
-        *target_l = keep;
-        *target_h = keep - 1;
-        return;
-    }
-    const int Lr = 32 * NW;
-    const double p = (double)keep / L, vx = L * p * (1.0 - p);
-    // one bucket size, or two (group parity), 16 of each in `ranges` full lane ranges
-    const double ranges = (double)L / Lr;
-    const double size[2] = {NB == 32 ? 2.0 * ((NW + 1) / 2) : 2.0 * NW, NB == 32 ? 2.0 * (NW / 2) : 0.0}, count = 16.0 * ranges;
-    double binomial = 0, cov = 0;
-    for (double s : size) {
-        const double miss = pow(1.0 - p, s);
-        binomial += count * miss * (1.0 - miss);
-        cov += count * s * p * miss;
-    }
-    auto buckets = [&](double x) {
-        const double share = fmin(fmax(x / L, 0.0), 1.0);
-        double d = 0;
-        for (double s : size) d += count * (1.0 - pow(1.0 - share, s));
-        return d;
-    };
-    const double slope = vx > 0 ? fmax(cov / vx, 1e-6) : 1.0;
-    const double sigma = sqrt(fmax(binomial - (vx > 0 ? cov * cov / vx : 0.0), 0.0)) / slope;
-    const double reach = 3.5 * sigma + 1.0;
-    int l = (int)ceil(buckets(keep + reach)), h = (int)floor(buckets(keep - reach));
-    if (keep - reach < 1.0) h = 0;
-    const int most = (int)(count * NB / 16);
-    l = l > most ? most : l < 1 ? 1 : l;
-    h = h > l - 1 ? l - 1 : h;
-    *target_l = l;
-    *target_h = h;
-}
-
-// Wavefronts.  A lane's range holds at most 512 keys, which four wavefronts reach up to L = 8192 and eight up to 16384.  More
-// than that pay where they fill an empty chip, and for long lists in long ranges, whose words are then too many for the
-// registers (times of both sides; k = 32 and 5 % unless said):
-//   4 or 8   L = 4608, N = 12: 101 and 153 us; 6144, N = 7: 98 and 117; 8192, N = 4, 2 %: 82 and 94; 8192, N = 2, 10 %, k = 16: 66.9
-//            and 65.1; k = 128, 8192: 367 and 360; groups of 8, 8192, N = 32, 10 %: 183 and 165.  (Four have come to be better beyond
-//            the line too, with lists of up to 5 %, for the mask by itself 8 %: 7000, N = 5, 5 %: 101 and 132, 8192, N = 4: 95 and 108, a
-//            forward 185 and 200, at 8 % 287 and 267.)
-//            Few tiles: L = 777, 294 tiles 12.1 and 11.3, 1024, 256 tiles 10.0 and 9.3, 512 11.1 and 11.6, 768, 672 tiles 13.3 and
-//            16.5; 1536, 96 tiles, k = 16, 7 %: 12.2 and 12.2, 288 tiles 12.9 and 14.6; 2048, 256 tiles 12.4 and 12.0, 512 14.6
-//            and 15.0; 3072, 192 tiles 16.3 and 14.7, 384 18.0 and 18.8; 4096, 512 tiles 22.1 and 21.8, 1024 32.8 and 37.9; 8192, 2 %,
-//            512 29.8 and 28.0, 1024 46.8 and 50.0.
-//   1 or 4   L = 128, 10 %: 1024 tiles 13.3 and 11.2, 2048 22.8 and 19.7, 4096 34.7 and 34.9.
-//   2 or 4   L = 256, 10 %: 512 tiles 10.5 and 9.0, 1024 11.4 and 11.5; L = 192, 672 tiles 11.4 and 10.5, 1356 15.0 and 17.1.
-inline int split_waves(const dsa_shape &sh, long long tiles)
-{
-    if (sh.L <= 128) return tiles <= 2048 ? 4 : 1;
-    if (sh.L <= 256) return tiles <= 768 ? 4 : 2;
-    if (sh.L <= 512) return 4;
-    const bool four = sh.L <= 5120 || (sh.L <= 6144 && 16LL * sh.keep <= sh.L) || (sh.L <= 8192 && sh.k <= 64 && 40LL * sh.keep <= sh.L);
-    if (!four) return sh.L <= 16384 ? 8 : 16;
-    return tiles <= (sh.L <= 1024 ? 400 : sh.L < 2048 ? 128 : sh.L < 4096 ? 256 : sh.L / 8) ? 8 : 4;
-}
-
-// Two tiles per workgroup halve the key rows that come from L2 per unit.  They take the unit operands of both in registers, which
-// only a contraction that fills its 64 slots leaves room for (k = 32 keeps two half-empty copies of each: 28 registers through
-// scratch, N = 16, L = 4096, 5 % 103 -> 115 us), 16 buckets per lane instead of 32, whose bounds are worse the longer the list is,
-// more wavefronts per workgroup, whose ranges may not end far beyond the head, and a grid that is not left with half a round at its end
-// (waves between one and two per slot: L = 12288, N = 1, 80.6 us with one tile, 90.5 with two).  One tile and two at 1, 2, 4, 8 %:
-//   rows, k = 64, N L^2 = 2^28: L = 2048 137 and 141, 144/149, 157/166, 196/213; 3072 123/126, 130/136, 151/162, 191/209; 4096 115/103,
-//                126/116, 156/148, 195/194; 8192 119/93, 129/112, 162/142, 202/198; 16384 123/115, 132/133, 163/149, 240/234.  At 1 and 3 %:
-//                6144 119/104, 147/139, 7168 115/110, 158/137, 10240 157/150, 182/184, 12288 140/125, 165/160; with ranges that end 2 %
-//                beyond the head 5000 126/124, 155/162, 6000 118/117, 150/154, 14000 204/197, 244/244, with 14 % 4500 125/139, 150/179,
-//                9000 139/156, 163/191.  Half a round is enough: L = 4096, N = 2, 24.4 and 23.3; L = 8192, N = 1, 41.4 and 38.1.
-//   groups of 8, k = 64, N L^2 = 2^31, at 1, 2, 3, 4, 8 %: 8192 140/118, 155/138, 174/153, 185/190, 228/243; 12288 152/148, 168/165, 181/182,
-//                194/195, 254/272; 16384 139/130, 153/144, 192/161, 178/223, 297/309.  A quarter of a round: 46.0 and 60.2.  (4096 146/134,
-//                155/146, 166/159, 183/179, but 5000, 2 % 87/99: left at one.)
-//   k = 48 rows, at 1, 2, 4 %: 4096 94/92, 101/103, 121/128; 8192 88/82, 102/96, 130/125; 16384 93/92, 104/103, 126/127; others 1 to 9 %
-//                slower (10240, 1 % 120/131).  In groups never (59 registers through scratch).
-inline bool split_pairs(const dsa_shape &sh, int W2, long long waves)
-{
-    const int NW2 = (sh.L + 128 * W2 - 1) / (128 * W2), spare = 128 * W2 * NW2 - sh.L;
-    if (sh.L > 16384 || NW2 < 4 || 64 * spare > sh.L) return false;
-    if (sh.vec > 1) return sh.L > 7168 && 32LL * sh.keep <= sh.L && waves >= 4096;
-    if (waves < 2048 || (W2 == 16 && waves > 4096 && waves < 8192)) return false;
-    if (sh.k == 48 && NW2 < 8) return false;
-    return 5 * sh.keep <= 4 * 64 * W2 && sh.keep <= sh.L / 20 + 1;
-}
-
-inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
-{
-    SplitPlan p{};
-    const long long units = sh.L / sh.vec, heads = (long long)sh.B * sh.H;
-    const long long tiles = heads * ((units + kTile - 1) / kTile);
-    p.UT = 1;
-    p.NB = 32;
-    p.W = split_waves(sh, tiles);
-    const int W2 = sh.L <= 8192 ? 8 : 16;
-    if (pairs && split_pairs(sh, W2, heads * ((units + 2 * kTile - 1) / (2 * kTile)) * W2)) {
-        p.UT = 2;
-        p.NB = 16;
-        p.W = W2;
-    }
-    p.NW = (sh.L + 128 * p.W - 1) / (128 * p.W);
-    split_targets(sh.L, sh.keep, p.NW, p.NB, &p.target_l, &p.target_h);
-    return p;
-}
 
 inline size_t attend_lds_bytes(const dsa_shape &sh, int W, int pad)
 {
@@ -1010,10 +949,11 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
     bool attends = false;
     if (attend && !a.direct) {
         const int pad = (sh.keep + kRowPad - 1) / kRowPad * kRowPad;
-        const size_t all = at.attend + attend_lds_bytes(sh, p.W, pad);
+        const int most = !GROUP && UT == 1 ? tile_most(sh, p.W) : 0;
+        const size_t all = most ? at.hist + tile_lds_bytes(sh, p.W, most) : at.attend + attend_lds_bytes(sh, p.W, pad);
         if (attend_here(sh, p.W, kTile * UT, (long long)sh.B * sh.H * a.wgs_per_head, std::max(lds, all))) {
             lds = std::max(lds, all);
-            a.attend = AttendArgs{attend->Q, attend->K, attend->V, attend->O, sh.scale, sh.d, pad};
+            a.attend = AttendArgs{attend->Q, attend->K, attend->V, attend->O, sh.scale, sh.d, pad, most, (unsigned)(lds - at.hist)};
             attends = *attended = true;
         }
     }
@@ -1024,6 +964,8 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
     };
     if (!attends) return go(predict_split<K, GROUP, UT, NB, NWM, kNoAttend>, static_cast<const SplitArgs &>(a));
     if (sh.dtype == DSA_F32) return go(predict_split<K, GROUP, UT, NB, NWM, kAttendF32>, a);
+    if constexpr (!GROUP && UT == 1)
+        if (a.attend.most) return go(predict_split<K, GROUP, UT, NB, NWM, kAttendTile>, a);
     return go(predict_split<K, GROUP, UT, NB, NWM, kAttendBf16>, a);
 }
 
@@ -1031,7 +973,7 @@ template <int K, bool GROUP>
 hipError_t launch_split_g(const dsa_shape &sh, const int8_t *Qt, const int8_t *Kt, int32_t *idx, const AttendPtrs *attend,
                           bool *attended, hipStream_t st)
 {
-    constexpr bool pairs = K == 64 || (K == 48 && !GROUP);
+    constexpr bool pairs = split_pairs_exist(K, GROUP);
     const SplitPlan p = split_plan(sh, pairs);
     if constexpr (pairs) {
         if constexpr (K == 64 && !GROUP)     // (the others take two tiles from five words on)

@@ -289,5 +289,50 @@ __device__ __forceinline__ void attend_rows(const T *Kh, const T *Vh, typename P
     for (int r = 0; r < NR; ++r) row_store<T, D>(out[r], o[r], 1.f / wave_all_sum(z[r]), lane);
 }
 
+// What a workgroup attends with.
+struct AttendArgs {
+    const void *Q, *K, *V;
+    float *O;
+    float scale;
+    int d, pad;                         // list length rounded up to kRowPad
+    int most;                           // tile_attend.h: keys of the longest union
+    unsigned lds;                       // and bytes of LDS
+};
+
+// Rows a wavefront attends to at a time: a gather of each is as good as another gather of one, and the steps between the gathers
+// overlap.  bf16 1, 2, 4 rows, k = 32: N = 16, L = 4096, keep = 205 211.7, 202.2, 210.4 us, keep = 410 323, 307, 356; fp32 (a
+// quarter of the sums per row) 2 and 4, k = 16: N = 512, L = 256, keep = 26 113.7 and 103.8, N = 128, L = 1024, keep = 102 256 and 249.
+template <typename T> constexpr int attend_rows_at_once() { return sizeof(T) == 2 ? 2 : 4; }
+
+// The rows of the workgroup's nu units, by `waves` of its wavefronts (at most all).  image: the units' lists; lds: room for
+// attend_rows_at_once() * pad words for each of them.
+template <typename T, int D>
+__device__ __forceinline__ void attend_block(const AttendArgs &a, const uint16_t *image, unsigned *lds, int L, int keep, int vec, unsigned n, int u0, int nu,
+                                             int waves)
+{
+    const int lane = threadIdx.x & (kWave - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), W = min(waves, (int)(blockDim.x / kWave));
+    if (wv >= W) return;
+    constexpr int NR = attend_rows_at_once<T>(), LPR = RowShape<T, D>::LPR, E = Piece<T>::N;
+    const size_t head = (size_t)n * L * D;
+    const T *Kh = static_cast<const T *>(a.K) + head, *Vh = static_cast<const T *>(a.V) + head, *Qh = static_cast<const T *>(a.Q) + head;
+    lds += wv * NR * a.pad;
+    const int total = nu * vec;
+    for (int p = wv; NR * p < total; p += W) {
+        typename Piece<T>::raw_t q[NR];
+        const uint16_t *list[NR];
+        float *out[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int j = min(NR * p + r, total - 1);          // (a row that is there twice is written twice)
+            const size_t row = (size_t)(u0 * vec + j) * D;
+            q[r] = Piece<T>::load(Qh + row + lane % LPR * E);
+            list[r] = image + (vec == 1 ? j : j / vec) * keep;
+            out[r] = a.O + head + row;
+        }
+        auto at = [&](int r, int t) { return (unsigned)list[r][t] * (unsigned)(D * sizeof(T)); };
+        attend_rows<T, D, NR>(Kh, Vh, q, at, lds, a.pad, keep, a.scale, out, lane);
+    }
+}
+
 }  // namespace
 }  // namespace dsa

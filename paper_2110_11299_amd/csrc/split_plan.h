@@ -1,0 +1,126 @@
+// How predict_split cuts a shape: wavefronts per workgroup, tiles of units per workgroup, bitmap words per lane.  Host code.
+#pragma once
+
+#include "dsa_internal.h"
+
+#include <math.h>
+
+namespace dsa {
+namespace {
+
+constexpr int kTile = 16;               // units of one matrix instruction
+
+// Projection dimensions that have a kernel for two tiles.
+constexpr bool split_pairs_exist(int k, bool group) { return k == 64 || (k == 48 && !group); }
+
+struct SplitPlan { int W, NW, UT, NB, target_l, target_h; };
+
+// Targets.  If a share p of a unit's keys lies above a threshold, a bucket of s keys reaches it with probability
+// 1 - (1 - p)^s; the number of buckets that reach it, given the number x of keys that do, has the mean D(x) below and a
+// variance that is the binomial one less what x explains.  tl is put where keep + z sigma keys are expected above it,
+// th where keep - z sigma are: with z = 3.5 a unit misses in about one case of 2000 (and is then swept again).
+inline void split_targets(int L, int keep, int NW, int NB, int *target_l, int *target_h)
+{
+    if (NW == 1) {                       // every key is its own bucket
+        *target_l = keep;
+        *target_h = keep - 1;
+        return;
+    }
+    const int Lr = 32 * NW;
+    const double p = (double)keep / L, vx = L * p * (1.0 - p);
+    // one bucket size, or two (group parity), 16 of each in `ranges` full lane ranges
+    const double ranges = (double)L / Lr;
+    const double size[2] = {NB == 32 ? 2.0 * ((NW + 1) / 2) : 2.0 * NW, NB == 32 ? 2.0 * (NW / 2) : 0.0}, count = 16.0 * ranges;
+    double binomial = 0, cov = 0;
+    for (double s : size) {
+        const double miss = pow(1.0 - p, s);
+        binomial += count * miss * (1.0 - miss);
+        cov += count * s * p * miss;
+    }
+    auto buckets = [&](double x) {
+        const double share = fmin(fmax(x / L, 0.0), 1.0);
+        double d = 0;
+        for (double s : size) d += count * (1.0 - pow(1.0 - share, s));
+        return d;
+    };
+    const double slope = vx > 0 ? fmax(cov / vx, 1e-6) : 1.0;
+    const double sigma = sqrt(fmax(binomial - (vx > 0 ? cov * cov / vx : 0.0), 0.0)) / slope;
+    const double reach = 3.5 * sigma + 1.0;
+    int l = (int)ceil(buckets(keep + reach)), h = (int)floor(buckets(keep - reach));
+    if (keep - reach < 1.0) h = 0;
+    const int most = (int)(count * NB / 16);
+    l = l > most ? most : l < 1 ? 1 : l;
+    h = h > l - 1 ? l - 1 : h;
+    *target_l = l;
+    *target_h = h;
+}
+
+// Wavefronts.  A lane's range holds at most 512 keys, which four wavefronts reach up to L = 8192 and eight up to 16384.  More
+// than that pay where they fill an empty chip, and for long lists in long ranges, whose words are then too many for the
+// registers (times of both sides; k = 32 and 5 % unless said):
+//   4 or 8   L = 4608, N = 12: 101 and 153 us; 6144, N = 7: 98 and 117; 8192, N = 4, 2 %: 82 and 94; 8192, N = 2, 10 %, k = 16: 66.9
+//            and 65.1; k = 128, 8192: 367 and 360; groups of 8, 8192, N = 32, 10 %: 183 and 165.  (Four have come to be better beyond
+//            the line too, with lists of up to 5 %, for the mask by itself 8 %: 7000, N = 5, 5 %: 101 and 132, 8192, N = 4: 95 and 108, a
+//            forward 185 and 200, at 8 % 287 and 267.)
+//            Few tiles: L = 777, 294 tiles 12.1 and 11.3, 1024, 256 tiles 10.0 and 9.3, 512 11.1 and 11.6, 768, 672 tiles 13.3 and
+//            16.5; 1536, 96 tiles, k = 16, 7 %: 12.2 and 12.2, 288 tiles 12.9 and 14.6; 2048, 256 tiles 12.4 and 12.0, 512 14.6
+//            and 15.0; 3072, 192 tiles 16.3 and 14.7, 384 18.0 and 18.8; 4096, 512 tiles 22.1 and 21.8, 1024 32.8 and 37.9; 8192, 2 %,
+//            512 29.8 and 28.0, 1024 46.8 and 50.0.
+//   1 or 4   L = 128, 10 %: 1024 tiles 13.3 and 11.2, 2048 22.8 and 19.7, 4096 34.7 and 34.9.
+//   2 or 4   L = 256, 10 %: 512 tiles 10.5 and 9.0, 1024 11.4 and 11.5; L = 192, 672 tiles 11.4 and 10.5, 1356 15.0 and 17.1.
+inline int split_waves(const dsa_shape &sh, long long tiles)
+{
+    if (sh.L <= 128) return tiles <= 2048 ? 4 : 1;
+    if (sh.L <= 256) return tiles <= 768 ? 4 : 2;
+    if (sh.L <= 512) return 4;
+    const bool four = sh.L <= 5120 || (sh.L <= 6144 && 16LL * sh.keep <= sh.L) || (sh.L <= 8192 && sh.k <= 64 && 40LL * sh.keep <= sh.L);
+    if (!four) return sh.L <= 16384 ? 8 : 16;
+    return tiles <= (sh.L <= 1024 ? 400 : sh.L < 2048 ? 128 : sh.L < 4096 ? 256 : sh.L / 8) ? 8 : 4;
+}
+
+// Two tiles per workgroup halve the key rows that come from L2 per unit.  They take the unit operands of both in registers, which
+// only a contraction that fills its 64 slots leaves room for (k = 32 keeps two half-empty copies of each: 28 registers through
+// scratch, N = 16, L = 4096, 5 % 103 -> 115 us), 16 buckets per lane instead of 32, whose bounds are worse the longer the list is,
+// more wavefronts per workgroup, whose ranges may not end far beyond the head, and a grid that is not left with half a round at its end
+// (waves between one and two per slot: L = 12288, N = 1, 80.6 us with one tile, 90.5 with two).  One tile and two at 1, 2, 4, 8 %:
+//   rows, k = 64, N L^2 = 2^28: L = 2048 137 and 141, 144/149, 157/166, 196/213; 3072 123/126, 130/136, 151/162, 191/209; 4096 115/103,
+//                126/116, 156/148, 195/194; 8192 119/93, 129/112, 162/142, 202/198; 16384 123/115, 132/133, 163/149, 240/234.  At 1 and 3 %:
+//                6144 119/104, 147/139, 7168 115/110, 158/137, 10240 157/150, 182/184, 12288 140/125, 165/160; with ranges that end 2 %
+//                beyond the head 5000 126/124, 155/162, 6000 118/117, 150/154, 14000 204/197, 244/244, with 14 % 4500 125/139, 150/179,
+//                9000 139/156, 163/191.  Half a round is enough: L = 4096, N = 2, 24.4 and 23.3; L = 8192, N = 1, 41.4 and 38.1.
+//   groups of 8, k = 64, N L^2 = 2^31, at 1, 2, 3, 4, 8 %: 8192 140/118, 155/138, 174/153, 185/190, 228/243; 12288 152/148, 168/165, 181/182,
+//                194/195, 254/272; 16384 139/130, 153/144, 192/161, 178/223, 297/309.  A quarter of a round: 46.0 and 60.2.  (4096 146/134,
+//                155/146, 166/159, 183/179, but 5000, 2 % 87/99: left at one.)
+//   k = 48 rows, at 1, 2, 4 %: 4096 94/92, 101/103, 121/128; 8192 88/82, 102/96, 130/125; 16384 93/92, 104/103, 126/127; others 1 to 9 %
+//                slower (10240, 1 % 120/131).  In groups never (59 registers through scratch).
+inline bool split_pairs(const dsa_shape &sh, int W2, long long waves)
+{
+    const int NW2 = (sh.L + 128 * W2 - 1) / (128 * W2), spare = 128 * W2 * NW2 - sh.L;
+    if (sh.L > 16384 || NW2 < 4 || 64 * spare > sh.L) return false;
+    if (sh.vec > 1) return sh.L > 7168 && 32LL * sh.keep <= sh.L && waves >= 4096;
+    if (waves < 2048 || (W2 == 16 && waves > 4096 && waves < 8192)) return false;
+    if (sh.k == 48 && NW2 < 8) return false;
+    return 5 * sh.keep <= 4 * 64 * W2 && sh.keep <= sh.L / 20 + 1;
+}
+
+inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
+{
+    SplitPlan p{};
+    const long long units = sh.L / sh.vec, heads = (long long)sh.B * sh.H;
+    const long long tiles = heads * ((units + kTile - 1) / kTile);
+    p.UT = 1;
+    p.NB = 32;
+    p.W = split_waves(sh, tiles);
+    const int W2 = sh.L <= 8192 ? 8 : 16;
+    if (pairs && split_pairs(sh, W2, heads * ((units + 2 * kTile - 1) / (2 * kTile)) * W2)) {
+        p.UT = 2;
+        p.NB = 16;
+        p.W = W2;
+    }
+    p.NW = (sh.L + 128 * p.W - 1) / (128 * p.W);
+    split_targets(sh.L, sh.keep, p.NW, p.NB, &p.target_l, &p.target_h);
+    return p;
+}
+
+}  // namespace
+}  // namespace dsa

@@ -1,0 +1,144 @@
+"""Fine-grained attention over the union of 16 rows' lists (bfloat16, d = 64): in the launch that makes the lists and from given ones, on every
+side of the rule that takes it, at the edges of its tiles of 16 rows and its steps of 32 keys.  Which route a call took is told by its
+error: weights that are the sum of two bf16 are off by up to 2^-17 each (2e-6 to 5e-6 in the two-norm), weights of one bf16 by 2^-9
+(3e-4 to 2e-3)."""
+import numpy as np
+import pytest
+
+import dsa_inputs as di
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2
+TWO_NORM = 5e-5         # 6.6 * 2^-17: the largest error of a weight, and those of fp32 exponentials and sums beside it
+
+
+@pytest.fixture(scope="module")
+def dsa():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("these tests need the MI355X: run them with -m gpu on the GPU box")
+    import paper_2110_11299_amd as pkg
+    pkg.binding.lib()
+    return pkg
+
+
+def inputs(H, L, k, keep, change=None):
+    x = di.make_inputs(di.custom_config("tiles", B=1, H=H, L=L, d=64, dtype="bf16", rank=8, k=k, vec=1, keep=keep, seed=L + keep))
+    qkv = [np.array(a) for a in (x.Q, x.K, x.V)]
+    if change:
+        change(qkv)
+    return qkv, x
+
+
+def device(dsa, qkv, k, keep, scale):
+    import torch
+    _, H, L, _ = qkv[0].shape
+    print(f"[tiles] H={H} L={L} k={k} keep={keep} scale={scale}", flush=True)
+    return dsa.make_shape(1, H, L, 64, k, keep, 1, dsa.DSA_BF16, scale), [torch.from_numpy(a).cuda().bfloat16() for a in qkv]
+
+
+def forward(dsa, qkv, x, k, keep, scale):
+    """The forward, which has to be the two entry points one after the other, bit for bit."""
+    import torch
+    sh, dev = device(dsa, qkv, k, keep, scale)
+    codes = [torch.from_numpy(a).cuda() for a in (x.Qt, x.Kt)]
+    O, idx = dsa.dsa_attention_fwd(sh, *dev, *codes)
+    idx2 = dsa.dsa_predict_mask(sh, *codes)
+    assert torch.equal(idx, idx2)
+    assert torch.equal(O.view(torch.int32), dsa.dsa_masked_attention(sh, *dev, idx2).view(torch.int32))
+    return idx.cpu().numpy().reshape(-1, keep), O.cpu().numpy().reshape(-1, 64)
+
+
+def attention(dsa, qkv, idx, scale):
+    import torch
+    _, H, L, _ = qkv[0].shape
+    keep = idx.shape[-1]
+    sh, dev = device(dsa, qkv, 16, keep, scale)
+    return dsa.dsa_masked_attention(sh, *dev, torch.from_numpy(idx.astype(np.int32)).cuda().view(1, H, L, keep)).cpu().numpy().reshape(-1, 64)
+
+
+def check(oracle, qkv, idx, got, scale, tile=True, bound=TWO_NORM):
+    want = oracle.masked_attention(*qkv, idx, scale, 1).reshape(-1, 64)
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print(f"    two-norm {err:.2e}", flush=True)
+    assert np.abs(got - want).max() <= TOL
+    assert (err <= bound) == tile
+
+
+# two wavefronts per tile, lengths up to 256: last tiles of 1, 10 and 16 rows, from one key to all of them
+@pytest.mark.parametrize("H,L,keep", [(114, 129, 1), (114, 129, 2), (64, 250, 26), (64, 250, 31), (64, 256, 32), (64, 256, 33), (64, 241, 97), (64, 250, 250)])
+def test_short(dsa, oracle, H, L, keep):
+    for scale in (0.125, -0.125):
+        qkv, x = inputs(H, L, 16, keep)
+        idx, got = forward(dsa, qkv, x, 16, keep, scale)
+        check(oracle, qkv, idx, got, scale)
+
+
+# the lines of the rule on the side that takes the union (one key less does not), bitmaps of one to sixteen words per lane, eight
+# wavefronts; every projection dimension with a kernel of its own
+@pytest.mark.parametrize("H,L,k,keep", [(8, 2049, 32, 171), (27, 650, 48, 82), (54, 300, 64, 75), (17, 1025, 112, 114), (8, 1024, 128, 205), (1, 8200, 32, 684),
+                                        (4, 4100, 16, 342), (2, 8200, 16, 684)])
+def test_lines(dsa, oracle, H, L, k, keep):
+    for now in (keep, keep - 1):
+        qkv, x = inputs(H, L, k, now)
+        idx, got = forward(dsa, qkv, x, k, now, 0.125)
+        check(oracle, qkv, idx, got, 0.125, tile=now == keep)
+
+
+def test_scores_that_outgrow_the_reference(dsa, oracle):
+    def change(qkv):
+        qkv[0][...] *= 4.0
+        qkv[1][0, :, ::7] *= 4.0
+    qkv, x = inputs(64, 250, 16, 60, change)
+    idx, got = forward(dsa, qkv, x, 16, 60, 1.0)
+    # a score of s is off by a few 2^-24 s in fp32, and so is its weight, relatively
+    check(oracle, qkv, idx, got, 1.0, bound=TWO_NORM + 2.0 ** -22 * np.abs(qkv[0][0] @ qkv[1][0].transpose(0, 2, 1)).max())
+
+
+@pytest.mark.parametrize("H,L,keep", [(64, 250, 30), (8, 2049, 180)])
+def test_given_lists(dsa, oracle, H, L, keep):
+    """Lists in any order; scales that make every score the same or the exponents overflow; keys that are there twice or lie outside
+    (clamped), which the loops of the rows take, a tile at a time."""
+    rng = np.random.default_rng(L)
+    qkv, _ = inputs(H, L, 16, keep)
+    idx = np.argsort(rng.random((H * L, L)), axis=1)[:, :keep] if L < 1000 else np.stack([rng.choice(L, keep, replace=False) for _ in range(H * L)])
+    check(oracle, qkv, idx, attention(dsa, qkv, idx, 0.125), 0.125)
+    for scale in (0.0, 1e38):
+        want = oracle.masked_attention(*qkv, idx, scale, 1).reshape(-1, 64)
+        assert np.abs(attention(dsa, qkv, idx, scale) - want).max() <= TOL
+    odd = idx.copy()
+    odd[3, 1] = odd[3, 0]
+    odd[40, :2] = (L + 5, -3)
+    odd[40, 2:][(odd[40, 2:] == 0) | (odd[40, 2:] == L - 1)] = 1
+    odd[41, :2] = (L + 5, L + 7)
+    got = attention(dsa, qkv, odd, 0.125)
+    want = oracle.masked_attention(*qkv, np.clip(odd, 0, L - 1), 0.125, 1).reshape(-1, 64)
+    assert np.abs(got - want).max() <= TOL
+    # the tiles of rows 3 and 41 are the rows' own, the others as before
+    assert np.array_equal(got[48:].view(np.int32), attention(dsa, qkv, idx, 0.125)[48:].view(np.int32))
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("which", [1, 2])
+def test_rows_without_a_key_do_not_see_it(dsa, oracle, which, value):
+    """A key or value row that is not finite belongs to the union of a tile, but not to every row of it."""
+    def change(qkv):
+        qkv[which][0, :, 100, 7] = value
+    qkv, x = inputs(64, 250, 16, 26, change)
+    idx, got = forward(dsa, qkv, x, 16, 26, 0.125)
+    clean = [np.where(np.isfinite(a), a, 0.0).astype(np.float32) for a in qkv]
+    want = oracle.masked_attention(*clean, idx, 0.125, 1).reshape(-1, 64)
+    without = ~(idx == 100).any(axis=1)
+    assert 0 < without.sum() < len(idx)
+    assert np.abs(got[without] - want[without]).max() <= TOL
+
+
+def test_values_that_leave_fp32(dsa, oracle):
+    """Weights of up to 2^16 times values of 2^118: sums that only the rows by themselves can hold."""
+    def change(qkv):
+        qkv[0][...] *= 8.0
+        qkv[2][...] = np.where(qkv[2] > 0, 2.0 ** 119, 2.0 ** 118)
+    qkv, x = inputs(64, 250, 16, 75, change)
+    idx, got = forward(dsa, qkv, x, 16, 75, 1.0)
+    want = oracle.masked_attention(*qkv, idx, 1.0, 1).reshape(-1, 64)
+    assert np.abs(got / want - 1.0).max() <= 2.0 ** -7       # weights of one bf16
