@@ -50,6 +50,10 @@ constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' b
 // included), with 32 138.4.  Where that does not pay (short ranges, whose bands are one bucket, and units of several rows, which
 // have many levels) or the registers are short (two tiles), it is 24.
 template <bool GROUP, int UT, int NWM> constexpr int band_slots() { return !GROUP && UT == 1 && NWM >= 4 ? 32 : 24; }
+// Slots that are looked at together: their requests are on their way at the same time.  Where every key is its own bucket a band is
+// one bin of the histogram, a few keys: N = 96, L = 512, keep = 51, fp32 with one slot 86.1 us, two 83.9, four 84.9, bf16 50.7, 49.9, 53.8;
+// N = 192, L = 128 20.0, 20.3, 23.3.  Longer ranges with two: N = 16, L = 4096, keep = 205 195.6 and 190.9.
+template <int NWM> constexpr int band_step() { return NWM == 1 ? 2 : 4; }
 constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
 
 // The attention that a workgroup goes on with, over the lists it has just made (see attend_here): fp32 rows, bf16 rows (of units
@@ -230,6 +234,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
     constexpr int PARTS = GROUP ? 2 : 1;
     constexpr int U = kTile * UT;
     constexpr int kBandSlots = band_slots<GROUP, UT, NWM>(), kBandCap = 16 * kBandSlots;
+    constexpr int SG = band_step<NWM>();
     extern __shared__ __align__(16) unsigned char lds[];
 
     const int k = K ? K : a.k;
@@ -699,25 +704,25 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
         int sc[kBandSlots];                        // (those behind the last slots that the band reaches are not looked at)
         int peak = INT32_MIN;
 #pragma unroll
-        for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
+        for (int i0 = 0; i0 < kBandSlots; i0 += SG) {
             if (16 * i0 >= most) break;
-            const int8_t *kr[4];
-            int s[4], sh[4];
+            const int8_t *kr[SG];
+            int s[SG], sh[SG];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < SG; ++i) {
                 const unsigned code = ul[max(min(c + 16 * (i0 + i), nb - 1), 0)];
                 const int key = (int)(code >> kPosBits) * Lr + (int)(code & ((1u << kPosBits) - 1));
                 kr[i] = Kh + (size_t)((unsigned)min(key, L - 1) * (unsigned)k);
                 s[i] = sh[i] = 0;
             }
             auto piece = [&](int p) {
-                v4i kk[4];
+                v4i kk[SG];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) kk[i] = *reinterpret_cast<const v4i *>(kr[i] + 16 * p);
+                for (int i = 0; i < SG; ++i) kk[i] = *reinterpret_cast<const v4i *>(kr[i] + 16 * p);
                 const v4i ql = *reinterpret_cast<const v4i *>(uq + 16 * p);
                 const v4i qh = *reinterpret_cast<const v4i *>(uq + (GROUP ? k + 16 : 0) + 16 * p);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < SG; ++i)
 #pragma unroll
                     for (int x = 0; x < 4; ++x) {
                         s[i] = __builtin_amdgcn_sdot4(ql[x], kk[i][x], s[i], false);
@@ -733,10 +738,32 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
                 for (int p = 0; p < k / 16; ++p) piece(p);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < SG; ++i) {
                 const int v = s[i] + 128 * sh[i];
                 sc[i0 + i] = c + 16 * (i0 + i) < nb ? v : INT32_MIN;
                 peak = max(peak, sc[i0 + i]);
+            }
+        }
+        auto keep_key = [&](int i) {
+            const unsigned code = ul[c + 16 * i], hh = code >> kPosBits, pos = code & ((1u << kPosBits) - 1);
+            const unsigned thread = (hh >> 2) * kWave + (hh & 3) * 16 + (u & 15);
+            atomicOr(&sel[((u >> 4) * NW + (pos >> 5)) * T + thread], 1u << (pos & 31));
+        };
+        if constexpr (NWM == 1) {                  // (bands of single keys: a few of them, mostly)
+            if (most <= 16) {
+                // One key to a lane: kept if fewer than `need` others come before it (|scores| < 2^25; the lower key first among equals).
+                // No search, whose cuts wait for each other: N = 2, L = 256, keep = 26, attention included 11.3 -> 10.2 us with one slot
+                // for every key, N = 192, L = 256, keep = 20 41.9 -> 38.1.
+                const int mine = c < nb ? 16 * sc[0] + 15 - c : INT32_MIN;
+                int before = 0;
+                auto against = [&](auto r) { before += __builtin_amdgcn_update_dpp(0, mine, 0x120 + decltype(r)::value /* row_ror */, 0xF, 0xF, true) > mine; };
+                against(std::integral_constant<int, 1>{}); against(std::integral_constant<int, 2>{}); against(std::integral_constant<int, 3>{});
+                against(std::integral_constant<int, 4>{}); against(std::integral_constant<int, 5>{}); against(std::integral_constant<int, 6>{});
+                against(std::integral_constant<int, 7>{}); against(std::integral_constant<int, 8>{}); against(std::integral_constant<int, 9>{});
+                against(std::integral_constant<int, 10>{}); against(std::integral_constant<int, 11>{}); against(std::integral_constant<int, 12>{});
+                against(std::integral_constant<int, 13>{}); against(std::integral_constant<int, 14>{}); against(std::integral_constant<int, 15>{});
+                if (c < nb && before < need) keep_key(0);
+                continue;
             }
         }
         // The need-th largest of the band: all its scores are >= tl and at least need of them exist.  The interval is cut
@@ -750,10 +777,10 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             const int mid = lo_ + step;
             int cnt = 0;
 #pragma unroll
-            for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
+            for (int i0 = 0; i0 < kBandSlots; i0 += SG) {
                 if (16 * i0 >= most) break;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) cnt += sc[i0 + i] >= mid;
+                for (int i = 0; i < SG; ++i) cnt += sc[i0 + i] >= mid;
             }
             cnt = row_sum(cnt);
             if (lo_ < hi_) {
@@ -765,27 +792,22 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, 4) void predict_split(std::c
             }
         }
         const int Tx = lo_;
-        auto keep_key = [&](int i) {
-            const unsigned code = ul[c + 16 * i], hh = code >> kPosBits, pos = code & ((1u << kPosBits) - 1);
-            const unsigned thread = (hh >> 2) * kWave + (hh & 3) * 16 + (u & 15);
-            atomicOr(&sel[((u >> 4) * NW + (pos >> 5)) * T + thread], 1u << (pos & 31));
-        };
         if (__ballot(nb && cnt_lo != need) == 0) {        // no tie at the threshold is left out: no order among them
 #pragma unroll
-            for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
+            for (int i0 = 0; i0 < kBandSlots; i0 += SG) {
                 if (16 * i0 >= most) break;
 #pragma unroll
-                for (int i = i0; i < i0 + 4; ++i)
+                for (int i = i0; i < i0 + SG; ++i)
                     if (sc[i] >= Tx) keep_key(i);
             }
             continue;
         }
         int gt = 0;
 #pragma unroll
-        for (int i0 = 0; i0 < kBandSlots; i0 += 4) {
+        for (int i0 = 0; i0 < kBandSlots; i0 += SG) {
             if (16 * i0 >= most) break;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) gt += sc[i0 + i] > Tx;
+            for (int i = 0; i < SG; ++i) gt += sc[i0 + i] > Tx;
         }
         const int need_eq = need - row_sum(gt);
         int eq_before = 0;
