@@ -580,7 +580,7 @@ hipError_t launch_attention(AttnMode mode, const dsa_shape &sh, const void *Q, c
             return sh.d == 64 ? launch_units<64, 8>(sh, Q, K, V, idx, O, st) : launch_units<128, 8>(sh, Q, K, V, idx, O, st);
         return sh.d == 64 ? launch_units<64, 4>(sh, Q, K, V, idx, O, st) : launch_units<128, 4>(sh, Q, K, V, idx, O, st);
     }
-    if (mode == kFused) {
+    if (mode == kFused && sh.vec == 1 && sh.d == 64) {
         const int W = predict_waves(sh);
         if (const int most = tile_most(sh, W)) return launch_tiles(sh, W, most, Q, K, V, idx, O, st);
     }

@@ -21,8 +21,8 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 // reference that is moved only when a score exceeds it by a factor of 2^kUnitSlack, so that a step needs no reduction across lanes.
 // Every list length fits (4 bytes per key and wavefront; 96 KB of LDS with 4096 keys at D = 128).
 //
-// What bounds it: LDS (145 cycles per step and wavefront, two thirds of them the writes of the gathered rows; active 69 % of
-// the time at N = 64, L = 2000, keep = 200, VEC = 4), next to it the latency of list -> gather -> tile for short lists.
+// What bounds it: LDS (8 writes of 14.3 cycles, 4 reads of 4.7 and 8 of 2.8 per step and CU) and vector issue (62 % of the time at
+// N = 64, L = 2000, keep = 200, VEC = 4), next to them the latency of list -> gather -> tile for short lists.
 // Measured (kernel alone): that shape 213 -> 94 us against one row per wavefront (attention_rows), which gathers the four
 // times 3.3 GB; VEC = 8, N = 16, L = 4096, keep = 205: 44.7 -> 29 us, N = 64, L = 2048, keep = 102: 51 -> 35 us, D = 128,
 // N = 16, L = 8192, keep = 82: 72.6 -> 55 us against two passes with the scores in LDS.  A key and a value tile side by side
