@@ -8,12 +8,12 @@
 // 32 * NW keys, and lane (c = lane % 16, g = lane / 16) of wavefront w holds, for unit c, the scores of range 4 w + g.
 //
 //   sweep 1    every lane keeps up to NB = 32 or 16 maxima over disjoint key sets ("buckets").
-//   bounds     from a histogram of a unit's maxima in LDS two thresholds tl < th are read off, such that the keep-th
+//   bounds     from a histogram of the upper part of a unit's maxima in LDS two thresholds tl < th are read off, such that the keep-th
 //              largest score lies between them almost surely: the number of buckets that the x largest keys fall into
 //              is known to a few per cent (section "targets" on the host side).  For short ranges a bucket is one key
 //              and the bounds are certain.
-//   sweep 2    the keys are swept again with -tl and with -th as accumulator inputs: the signs that come out are two
-//              bitmaps, which stay in registers (NW words per lane and bitmap), and their counts.
+//   sweep 2    the keys are swept again with -tl as accumulator input: the signs of what comes out and of that less th - tl are two
+//              bitmaps (of NW words per lane; the band between them stays in registers, the other goes to LDS), and their counts.
 //   check      count(>= th) <= keep <= count(>= tl), and few enough keys between (the "band"): else the bracket is
 //              moved or cut in three and swept again.  This ends for any scores: the bracket shrinks until it holds a
 //              single score value, and a plateau of equal scores needs no score at all (its first keys are taken).
@@ -24,7 +24,9 @@
 //   attention  where it pays, over the lists while they are in LDS (row_attend.h, unit_attend.h), or over their union, which comes from the
 //              bitmaps in the registers (tile_attend.h).
 //
-// What bounds it: vector-ALU issue (half an operation per score in sweep 1, two in sweep 2, about 25 per candidate).
+// What bounds it: vector-ALU issue (half an operation per score in sweep 1, three of half the cycles in sweep 2, about 25 per candidate).
+// Add, and, three-way logic and fma take two cycles per wavefront here, everything with a scalar operand, shifts to the left, compares, minima and
+// most of what has three operands four.
 // Splitting the keys rather than giving a wavefront whole units keeps the bitmaps in registers, needs a quarter of the
 // bucket registers per lane and gives every shape, the shortest included, four times the wavefronts.
 #pragma once
@@ -44,7 +46,8 @@ namespace dsa {
 namespace {
 
 constexpr int kBins = 128;              // histogram bins per unit
-constexpr int kBinStride = kBins + 4;   // words from unit to unit: the units' bins start in different banks
+constexpr int kBelow = 4;               // words before them, one for each lane of a unit in a wavefront: what lies below the bins, mostly, goes there without a conflict
+constexpr int kBinStride = kBins + kBelow;      // words from unit to unit: the units' bins start in different banks
 // Keys of one unit's band that are scored, 16 per slot.  Few-level codes make bands of whole plateaus of equal scores, which are swept
 // again where they do not fit: INT4 codes at L = 4096, keep = 205, 16 high-norm keys per head, with 24 slots 146.7 us (unpacking
 // included), with 32 138.4.  Where that does not pay (short ranges, whose bands are one bucket, and units of several rows, which
@@ -53,7 +56,6 @@ template <bool GROUP, int UT, int NWM> constexpr int band_slots() { return !GROU
 // Slots that are looked at together: their requests are on their way at the same time.  Of two instead of four, bands of more than 32 keys
 // wait twice as often: N = 4, L = 1024, k = 32, keep = 204 and 341 12.6 and 14.1 us, 14.5 and 17.0; N = 16, L = 4096, keep = 205 190.9 and 195.6.
 constexpr int kBandStep = 4;
-constexpr int kPosBits = 9;             // list entry: lane range (at most 64) << 9 | key inside the range (at most 512)
 
 // The attention that a workgroup goes on with, over the lists it has just made (see attend_here): fp32 rows, bf16 rows (of units
 // of several rows: the units on the matrix cores), or bf16 rows over the union of their lists, on the matrix cores.
@@ -66,6 +68,7 @@ struct SplitArgs {
     int NW;                             // bitmap words per lane: a lane range is 32 * NW keys
     int wgs_per_head;
     int target_l, target_h;             // buckets that reach tl / th
+    float low, high;                    // the histogram's window (SplitPlan)
     int direct;                         // the rows do not fit LDS: indices go straight to memory
 };
 struct SplitAttendArgs : SplitArgs { AttendArgs attend; };
@@ -73,19 +76,63 @@ struct SplitAttendArgs : SplitArgs { AttendArgs attend; };
 // LDS of a workgroup, in bytes from the start (every part a multiple of 16).
 struct SplitLds {
     unsigned tot, q, hist, list, bytes;
+    unsigned sel;                                               // words from unit to unit of the bitmaps at `hist`, one more than they have: other banks
     unsigned attend;                                            // what the attention needs, behind the image of the rows
     __host__ __device__ SplitLds(int W, int UT, int NW, int k, bool group, int keep, bool direct, int slots)
     {
         const unsigned U = kTile * UT;
-        tot = 6 * U * 4;                                        // [6][U]: tl, th, need, band count, and two spare
+        tot = 6 * U * 4;                                        // [6][U]: tl, th, need (smallest maximum before), band count, and two spare
         q = tot + 2 * W * U * 4;                                // [2][W][U]
         hist = q + U * (group ? 2 : 1) * (k + 16);              // [U][parts][k + 16]
-        const unsigned h = U * kBinStride * 4, s = UT * NW * W * kWave * 4;
-        list = hist + (h > s ? h : s);                          // [U][bins], later the selected band bits [UT][NW][threads]
+        sel = 4 * W * NW + 1;
+        const unsigned h = U * kBinStride * 4, s = (U * sel * 4 + 15) / 16 * 16;
+        list = hist + (h > s ? h : s);                          // [U][bins], later the bitmaps of kept keys [U][sel]
         bytes = list + U * slots * 16 * 2;                      // [U][16 slots]
         const unsigned rows = hist + (direct ? 0 : (U * keep * 2 + 16 + 15) / 16 * 16);   // image of the index rows, last
         if (rows > bytes) bytes = rows;
         attend = rows;
+    }
+};
+
+// x from the lane whose number differs by `bit`.
+template <int bit> __device__ __forceinline__ int dpp_xor(int x)
+{
+    if constexpr (bit == 1) return dpp_move<kDppXor1>(x);
+    else if constexpr (bit == 2) return dpp_move<kDppXor2>(x);
+    else return dpp_move<0x1B>(dpp_move<kDppHalfMirror>(x));         // 4: ^ 7, then ^ 3
+}
+// Words from the signs of 32 numbers below 2^24, whose upper eight bits are all alike: number i puts its sign at bit 24 + i % 8 of part i / 8, in this
+// order but for 7 before 6.  The first fills the part, and the masks of the others reach over bits that the ones behind them take, so that
+// four of them are constants of the instruction and four are in registers: v_bitop3 takes two cycles per wavefront (a funnel shift or v_bfi
+// four), but not with a scalar operand.  Sweep 2 with it and with y = x - (th - tl) instead of a second matrix instruction (19 cycles for
+// four scores, as long as all else): mask, N = 16, L = 2048, k = 64, keep = 102 46.6 -> 41.2 us, N = 4, L = 16384, k = 64 390 -> 371, N = 16, L = 4096, k = 32,
+// keep = 205 94.6 -> 91.6.
+struct SignMasks {
+    unsigned reg[4];
+    __device__ __forceinline__ SignMasks()
+    {
+        reg[0] = 0x3c000000u; reg[1] = 0x38000000u; reg[2] = 0x30000000u; reg[3] = 0x20000000u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(reg[i]));
+    }
+    __device__ __forceinline__ void put(unsigned &part, int i, int x) const
+    {
+        const unsigned mask = i == 1 ? 0x3e22f983u /* 1 / (2 pi) */ : i == 7 ? 0xc0000000u /* -2.0 */ : i == 6 ? 0x40000000u /* 2.0 */ : reg[(i - 2) & 3];
+        part = i == 0 ? (unsigned)x : __builtin_amdgcn_bitop3_b32(mask, (unsigned)x, part, 0xCA);         // (mask & x) | (~mask & part)
+    }
+    // numbers first, first + 1, .. of the 32
+    template <typename V> __device__ __forceinline__ void tile(unsigned (&part)[4], int first, const V &x) const
+    {
+        constexpr int N = sizeof(V) / sizeof(int);
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            const int i = (first + r) % 8, now = i == 6 ? r + 1 : i == 7 ? r - 1 : r;
+            put(part[(first + now) / 8], (first + now) % 8, x[now]);
+        }
+    }
+    static __device__ __forceinline__ unsigned word(const unsigned (&part)[4])
+    {
+        return __builtin_amdgcn_perm(part[1], part[0], 0x0c0c0703u) | __builtin_amdgcn_perm(part[3], part[2], 0x07030c0cu);
     }
 };
 
@@ -103,6 +150,22 @@ __device__ __forceinline__ int row_max(int x)
     x = max(x, dpp_move<kDppXor2>(x));
     x = max(x, dpp_move<kDppHalfMirror>(x));
     return max(x, dpp_move<kDppMirror>(x));
+}
+// Sums of N values over N neighbouring lanes: lane l gets that of value l % N.
+template <int N> __device__ __forceinline__ int key_sums(const int (&x)[N], int lane)
+{
+    if constexpr (N == 1) {
+        return x[0];
+    } else {
+        constexpr int H = N / 2;
+        int y[H];
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const int lower = x[i] + dpp_xor<H>(x[i]), upper = x[i + H] + dpp_xor<H>(x[i + H]);
+            y[i] = lane & H ? upper : lower;
+        }
+        return key_sums<H>(y, lane);
+    }
 }
 // Sum of x over the lanes above this one in its row of 16.
 __device__ __forceinline__ int row_sum_above(int x)
@@ -243,6 +306,11 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
     constexpr int U = kTile * UT;
     constexpr int kBandSlots = band_slots<GROUP, UT, NWM>(), kBandCap = 16 * kBandSlots;
     constexpr int SG = kBandStep;
+    constexpr bool COPIES = !((K == 0 || K == 128) && GROUP);            // |score - threshold| < 2^24 (SignMasks)
+    // Lanes that fetch a key row of the band, 16 bytes each: the L1 looks a row up once, not once for every 16 bytes.  N = 4, L = 16384, k = 64,
+    // keep = 164 band scores and search 51 -> 29 us; N = 16, L = 4096, k = 32, keep = 205 96.8 -> 94.6 in all.  (k = 128: 100 to 800 registers through
+    // scratch; single keys as buckets, k = 64: 49, and bands are a few keys.)
+    constexpr int LPK = NWM > 1 && (K == 32 || K == 64) ? K / 16 : 1;
     extern __shared__ __align__(16) unsigned char lds[];
 
     const int k = K ? K : a.k;
@@ -377,7 +445,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
     };
 
     int nv = max(0, min(L - h * Lr, Lr));                          // real keys of this lane's range
-    const int nv_all = max(0, min(L - (4 * wv + 3) * Lr, Lr));           // of the wavefront's last range: the fewest
+    const int nv_all = max(0, min(L - (4 * wv + 3) * Lr, Lr));     // of the wavefront's last range: the fewest
 
     // ---- sweep 1: bucket maxima --------------------------------------------------------------------------------------
     // A range of one group (NWM == 1) keeps every score; else tiles j and j + PAIR share a bucket, and so do all groups (of
@@ -454,22 +522,30 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
     request(rows[0], 0, voff);   // sweep 2 starts with what is on its way during the bounds
 
     // ---- bounds -------------------------------------------------------------------------------------------------------
-    // The histogram's range is [smallest maximum, it + 3 * (mean - it)]: high-norm keys put a few maxima far above the
-    // others and would otherwise stretch the bins; they go to the last one.
-    // The first group (or the first two, if the parity tells buckets apart) puts a key into every bucket.  In a wavefront where that
-    // fails for a range an empty bucket counts in a bin beyond the others; one beyond L has nothing to count.  (A branch per bucket
-    // instead took the bounds of such a wavefront, for which the others wait, from 6 k to 12 k cycles of 48 k.)
-    const bool full = nv_all >= min(Lr, NWM > 1 && NB == 32 ? 64 : 32), none = 4 * wv * Lr >= L;
+    // The histogram's bins lie in a window around the thresholds (split_window); what is above goes to the last bin, what is below it, an empty
+    // bucket too, to a word of the lane before the bins (mostly: most maxima are, and would otherwise meet in one).  Bins over all
+    // maxima, three times the distance from the smallest to the mean, were two to six times as wide and the band half as long again:
+    // N = 16, L = 4096, k = 32, keep = 205 72 keys of a unit instead of 52, the mask 103 -> 97 us.
+    // (Empty buckets without a branch each: that took the bounds of a wavefront that has some, for which the others wait, from 6 k to 12 k
+    // cycles of 48 k.)
+    const bool full = nv_all >= 32, none = 4 * wv * Lr >= L;
     {
         float *s_sum = reinterpret_cast<float *>(s_toth);
 #pragma unroll
         for (int t = 0; t < UT; ++t) {
             int mn = INT32_MAX, all = 0;                 // 32 scores below 2^24 each
-            if (full) {
+            if (NWM > 1 || full) {
+                unsigned sum_of = 0;
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                     mn = min(mn, bm[t][b]);
-                    all += bm[t][b];
+                    sum_of += (unsigned)bm[t][b];
+                }
+                all = (int)sum_of;
+                // (a range that ends beyond the head has buckets of fewer keys or of none: their maxima are lower)
+                if (NWM > 1 && nv < Lr) {
+                    mn = INT32_MAX;
+                    all = 0;
                 }
             } else if (!none) {
 #pragma unroll
@@ -491,8 +567,8 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
             }
         }
         __syncthreads();
-        // buckets that hold a key: NB (or min(nv, 32) single keys) per full range; the mean only places the range's end
-        const float per_bucket = NWM == 1 ? (float)min(L, 32 * 4 * W) : (float)NB * fminf((float)(4 * W), (float)L / (float)Lr);
+        // maxima that were added up: NB per full range, or every key
+        const float per_bucket = NWM == 1 ? (float)min(L, 32 * 4 * W) : (float)(NB * (L / Lr));
 #pragma unroll
         for (int t = 0; t < UT; ++t) {
             int mn = INT32_MAX;
@@ -502,20 +578,21 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
                 mn = min(mn, s_totl[x * U + kTile * t + c]);
                 sum += s_sum[x * U + kTile * t + c];
             }
-            const float range = fminf(fmaxf(3.f * (sum / per_bucket - (float)mn), 1.f), 1.0e9f);
+            const float mean = sum / per_bucket, reach = fmaxf(mean - (float)mn, 0.f);
+            const float range = fminf(fmaxf((a.high - a.low) * reach, 1.f), 1.0e9f);
             const int shift = max(0, 25 - (int)__clz((int)((unsigned)range | 1u)));     // range >> shift < kBins
-            unsigned *uh = hist + (kTile * t + c) * kBinStride;
-            auto bin = [&](int x) { return min((unsigned)(x - mn) >> shift, (unsigned)(kBins - 1)); };
-            if (full) {
+            // (the bins are a power of two wide: what they cover beyond the window lies on both sides of it)
+            const int base = max((int)floorf(mean + a.low * reach) - (((kBins << shift) - (int)range) >> 1), mn);
+            unsigned *uh = hist + (kTile * t + c) * kBinStride + kBelow;
+            if (!none) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b) atomicAdd(&uh[bin(bm[t][b])], 1u);
-            } else if (!none) {
-#pragma unroll
-                for (int b = 0; b < NB; ++b) atomicAdd(&uh[bm[t][b] != INT32_MIN ? bin(bm[t][b]) : (unsigned)kBins], 1u);
+                for (int b = 0; b < NB; ++b)
+                    atomicAdd(&uh[min(max(__builtin_elementwise_sub_sat(bm[t][b], base) >> shift, -1 - g), kBins - 1)], 1u);
             }
             if (wv == 0 && g == 0) {
-                s_tl[kTile * t + c] = mn;
+                s_tl[kTile * t + c] = base;
                 s_th[kTile * t + c] = shift;
+                s_need[kTile * t + c] = mn;
             }
         }
         __syncthreads();
@@ -523,7 +600,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
         // that at least target_l reach
         for (int b4 = wv; b4 < 4 * UT; b4 += W) {
             const int u = 4 * b4 + g;
-            const unsigned *uh = hist + u * kBinStride + 8 * c;
+            const unsigned *uh = hist + u * kBinStride + kBelow + 8 * c;
             const v4i x = *reinterpret_cast<const v4i *>(uh), y = *reinterpret_cast<const v4i *>(uh + 4);
             const int bins[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
             int suffix = row_sum_above(((bins[0] + bins[1]) + (bins[2] + bins[3])) + ((bins[4] + bins[5]) + (bins[6] + bins[7])));
@@ -539,7 +616,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
             const int base = s_tl[u], sh = s_th[u];
             const int top = (GROUP ? a.vec : 1) * k * 16384 + 1;             // above every score
             if (c == 0) {
-                s_tl[u] = base + (max(edge_l, 0) << sh);
+                s_tl[u] = edge_l > 0 ? base + (edge_l << sh) : s_need[u];        // (not in the bins: the smallest maximum)
                 s_th[u] = edge_h == kBins ? top : base + (edge_h << sh);
             }
         }
@@ -558,8 +635,15 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
         bhi[t] = smax + 1;
         nbhi[t] = 0;
     }
-    unsigned wl[UT][NWM], wh[UT][NWM];
+    // The keys at or above th go to LDS, where the histogram was, and those that are kept of the band, which the registers have, join them there:
+    // half the registers of two bitmaps, and nothing to clear or to merge.
+    unsigned *sel = hist;                          // [U][at.sel]
+    unsigned *mine_at[UT];
+#pragma unroll
+    for (int t = 0; t < UT; ++t) mine_at[t] = sel + (kTile * t + c) * at.sel + h * NW;
+    unsigned band[UT][NWM];
     int nl[UT], nh[UT], band0[UT];                 // counts of the unit; band keys in the ranges before this lane's
+    const SignMasks signs;
     for (int tries = 0;; ++tries) {
         int cl[UT], ch[UT];
 #pragma unroll
@@ -569,9 +653,12 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
         asm volatile("" : "+v"(nv), "+s"(batches));
 #pragma unroll
         for (int w = 0; w < NWM; ++w) {
-            if (w < NW) {
 #pragma unroll
-                for (int t = 0; t < UT; ++t) wl[t][w] = wh[t][w] = 0u;
+            for (int t = 0; t < UT; ++t) band[t][w] = 0u;
+            if (w < NW) {
+                unsigned wl[UT], wh[UT], sl[UT][4], sh[UT][4];
+#pragma unroll
+                for (int t = 0; t < UT; ++t) wl[t] = wh[t] = 0u;
 #pragma unroll
                 for (int hb = 0; hb < BPG; ++hb) {
                     const int P = BPG == 1 ? w & 1 : hb & 1;
@@ -582,39 +669,39 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
                         for (int t = 0; t < UT; ++t) {
                             const v4i x = tile_scores(rows[P], j, t, -tl[t]);
                             v4i y;
-                            if (GROUP) {
 #pragma unroll
-                                for (int i = 0; i < 4; ++i) y[i] = x[i] - (th[t] - tl[t]);
+                            for (int i = 0; i < 4; ++i) y[i] = x[i] - (th[t] - tl[t]);
+                            if constexpr (COPIES) {
+                                signs.tile(sl[t], 4 * (hb * TB + j), x);
+                                signs.tile(sh[t], 4 * (hb * TB + j), y);
                             } else {
-                                y = tile_scores(rows[P], j, t, -th[t]);
+                                shift_in_signs(wl[t], x);
+                                shift_in_signs(wh[t], y);
                             }
-                            shift_in_signs(wl[t][w], x);
-                            shift_in_signs(wh[t][w], y);
                             if (j % 2 == 1) __builtin_amdgcn_sched_barrier(0);      // else every tile's scores live at once
                         }
                 }
 #pragma unroll
                 for (int t = 0; t < UT; ++t) {
-                    wl[t][w] = ~__brev(wl[t][w]);                        // the first key of the word was shifted in first
-                    wh[t][w] = ~__brev(wh[t][w]);
+                    wl[t] = ~(COPIES ? SignMasks::word(sl[t]) : __brev(wl[t]));             // (shifted in: the first key of the word first)
+                    wh[t] = ~(COPIES ? SignMasks::word(sh[t]) : __brev(wh[t]));
                 }
                 if (32 * (w + 1) > nv_all) {
                     const int left = nv - 32 * w;                        // real keys of this word
                     const unsigned real = left >= 32 ? ~0u : left <= 0 ? 0u : (1u << left) - 1u;
 #pragma unroll
                     for (int t = 0; t < UT; ++t) {
-                        wl[t][w] &= real;
-                        wh[t][w] &= real;
+                        wl[t] &= real;
+                        wh[t] &= real;
                     }
                 }
 #pragma unroll
                 for (int t = 0; t < UT; ++t) {
-                    cl[t] += __popc(wl[t][w]);
-                    ch[t] += __popc(wh[t][w]);
+                    cl[t] += __popc(wl[t]);
+                    ch[t] += __popc(wh[t]);
+                    band[t][w] = wl[t] & ~wh[t];
+                    mine_at[t][w] = wh[t];
                 }
-            } else {
-#pragma unroll
-                for (int t = 0; t < UT; ++t) wl[t][w] = wh[t][w] = 0u;
             }
         }
         request(rows[0], 0, voff);
@@ -680,10 +767,10 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
 #pragma unroll
         for (int w = 0; w < NWM; ++w) {
             if (w < NW) {
-                unsigned m = scored[t] ? wl[t][w] & ~wh[t][w] : 0u;
-                const int code1 = (h << kPosBits) + 32 * w - 1;
+                unsigned m = scored[t] ? band[t][w] : 0u;
+                const int key1 = h * Lr + 32 * w - 1;
                 while (m) {
-                    ul[pos++] = (uint16_t)(code1 + __ffs(m));            // pos < nl - nh <= kBandCap
+                    ul[pos++] = (uint16_t)(key1 + __ffs(m));             // pos < nl - nh <= kBandCap
                     m &= m - 1u;
                 }
             }
@@ -695,13 +782,11 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
             s_nb[kTile * t + c] = scored[t] ? nl[t] - nh[t] : 0;
         }
     }
-    unsigned *sel = hist;                          // [UT][NW][T] band keys that are kept: the histogram is dead
-    for (int e = tid; e < UT * NW * T / 4; e += T) reinterpret_cast<v4i *>(sel)[e] = v4i{0, 0, 0, 0};
     __syncthreads();
 
     // ---- band scores and exact threshold: 16 lanes per unit, four units at a time per wavefront -------------------------
     for (int b4 = wv; b4 < 4 * UT; b4 += W) {
-        const int u = 4 * b4 + g;                  // this lane's unit here; c is its place in the row of 16
+        const int u = 4 * b4 + g;                 // this lane's unit here
         const int nb = s_nb[u], need = s_need[u], ulo = s_tl[u];
         const int most = max(max(__builtin_amdgcn_readlane(nb, 0), __builtin_amdgcn_readlane(nb, 16)),
                              max(__builtin_amdgcn_readlane(nb, 32), __builtin_amdgcn_readlane(nb, 48)));
@@ -722,38 +807,76 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
 #pragma unroll
         for (int i0 = 0; i0 < kBandSlots; i0 += SG) {
             if (16 * i0 >= most) break;
-            const int8_t *kr[SG];
             int s[SG], sh[SG];
+            if constexpr (LPK > 1) {
+                // a row's pieces by neighbouring lanes, whose sums for the LPK entries of their group change places in the end
+                const int8_t *kr[SG][LPK];
+                const int p = 16 * (c & (LPK - 1));
 #pragma unroll
-            for (int i = 0; i < SG; ++i) {
-                if (i >= 2 && two) continue;
-                const unsigned code = ul[max(min(c + 16 * (i0 + i), nb - 1), 0)];
-                const int key = (int)(code >> kPosBits) * Lr + (int)(code & ((1u << kPosBits) - 1));
-                kr[i] = Kh + (size_t)((unsigned)min(key, L - 1) * (unsigned)k);
-                s[i] = sh[i] = 0;
-            }
-            auto piece = [&](int p) {
-                v4i kk[SG];
+                for (int i = 0; i < SG; ++i) {
+                    const uint16_t *entries = ul + (c & ~(LPK - 1)) + 16 * (i0 + i);      // (behind the band: some key, whose score is not used)
 #pragma unroll
-                for (int i = 0; i < SG; ++i) if (i < 2 || !two) kk[i] = *reinterpret_cast<const v4i *>(kr[i] + 16 * p);
-                const v4i ql = *reinterpret_cast<const v4i *>(uq + 16 * p);
-                const v4i qh = *reinterpret_cast<const v4i *>(uq + (GROUP ? k + 16 : 0) + 16 * p);
+                    for (int j = 0; j < LPK; ++j) kr[i][j] = Kh + min((unsigned)entries[j], (unsigned)(L - 1)) * (unsigned)k + p;
+                }
+                const v4i ql = *reinterpret_cast<const v4i *>(uq + p), qh = *reinterpret_cast<const v4i *>(uq + (GROUP ? k + 16 : 0) + p);
+                constexpr int AT = LPK == 2 ? SG : 2;            // slots whose rows are requested together: 32 registers
 #pragma unroll
-                for (int i = 0; i < SG; ++i)
+                for (int i1 = 0; i1 < SG; i1 += AT) {
+                    v4i kk[AT][LPK];
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        if (i >= 2 && two) continue;
-                        s[i] = __builtin_amdgcn_sdot4(ql[x], kk[i][x], s[i], false);
-                        if (GROUP) sh[i] = __builtin_amdgcn_sdot4(qh[x], kk[i][x], sh[i], false);
+                    for (int i = 0; i < AT; ++i)
+#pragma unroll
+                        for (int j = 0; j < LPK; ++j) kk[i][j] = *reinterpret_cast<const v4i *>(kr[i1 + i][j]);
+#pragma unroll
+                    for (int i = 0; i < AT; ++i) {
+                        int part[LPK];
+#pragma unroll
+                        for (int j = 0; j < LPK; ++j) {
+                            int top = 0;
+                            part[j] = 0;
+#pragma unroll
+                            for (int x = 0; x < 4; ++x) {
+                                part[j] = __builtin_amdgcn_sdot4(ql[x], kk[i][j][x], part[j], false);
+                                if (GROUP) top = __builtin_amdgcn_sdot4(qh[x], kk[i][j][x], top, false);
+                            }
+                            if (GROUP) part[j] += 128 * top;
+                        }
+                        s[i1 + i] = key_sums<LPK>(part, lane);
+                        sh[i1 + i] = 0;
                     }
-                if (NWM == 1 || K == 0 || K > 32) __builtin_amdgcn_sched_barrier(0);       // the rows of four keys do not fit the registers
-            };
-            if constexpr (K != 0 && (NWM > 1 || K <= 64)) {        // (128 in a row: 80 to 504 registers through scratch)
-#pragma unroll
-                for (int p = 0; p < K / 16; ++p) piece(p);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             } else {
+                const int8_t *kr[SG];
+#pragma unroll
+                for (int i = 0; i < SG; ++i) {
+                    if (i >= 2 && two) continue;
+                    kr[i] = Kh + min((unsigned)ul[c + 16 * (i0 + i)], (unsigned)(L - 1)) * (unsigned)k;      // (behind the band: some key, whose score is not used)
+                    s[i] = sh[i] = 0;
+                }
+                auto piece = [&](int p) {
+                    v4i kk[SG];
+#pragma unroll
+                    for (int i = 0; i < SG; ++i) if (i < 2 || !two) kk[i] = *reinterpret_cast<const v4i *>(kr[i] + 16 * p);
+                    const v4i ql = *reinterpret_cast<const v4i *>(uq + 16 * p);
+                    const v4i qh = *reinterpret_cast<const v4i *>(uq + (GROUP ? k + 16 : 0) + 16 * p);
+#pragma unroll
+                    for (int i = 0; i < SG; ++i)
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) {
+                            if (i >= 2 && two) continue;
+                            s[i] = __builtin_amdgcn_sdot4(ql[x], kk[i][x], s[i], false);
+                            if (GROUP) sh[i] = __builtin_amdgcn_sdot4(qh[x], kk[i][x], sh[i], false);
+                        }
+                    if (NWM == 1 || K == 0 || K > 32) __builtin_amdgcn_sched_barrier(0);       // the rows of four keys do not fit the registers
+                };
+                if constexpr (K != 0 && (NWM > 1 || K <= 64)) {        // (128 in a row: 80 to 504 registers through scratch)
+#pragma unroll
+                    for (int p = 0; p < K / 16; ++p) piece(p);
+                } else {
 #pragma unroll 1
-                for (int p = 0; p < k / 16; ++p) piece(p);
+                    for (int p = 0; p < k / 16; ++p) piece(p);
+                }
             }
 #pragma unroll
             for (int i = 0; i < SG; ++i) {
@@ -766,11 +889,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
                 peak = max(peak, sc[i0 + i]);
             }
         }
-        auto keep_key = [&](int i) {
-            const unsigned code = ul[c + 16 * i], hh = code >> kPosBits, pos = code & ((1u << kPosBits) - 1);
-            const unsigned thread = (hh >> 2) * kWave + (hh & 3) * 16 + (u & 15);
-            atomicOr(&sel[((u >> 4) * NW + (pos >> 5)) * T + thread], 1u << (pos & 31));
-        };
+        auto keep_key = [&](unsigned key) { atomicOr(&sel[u * at.sel + (key >> 5)], 1u << (key & 31)); };
         if constexpr (NWM == 1) {                  // (bands of single keys: a few of them, mostly)
             if (most <= 16) {
                 // One key to a lane: kept if fewer than `need` others come before it (|scores| < 2^25; the lower key first among equals).
@@ -784,7 +903,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
                 against(std::integral_constant<int, 7>{}); against(std::integral_constant<int, 8>{}); against(std::integral_constant<int, 9>{});
                 against(std::integral_constant<int, 10>{}); against(std::integral_constant<int, 11>{}); against(std::integral_constant<int, 12>{});
                 against(std::integral_constant<int, 13>{}); against(std::integral_constant<int, 14>{}); against(std::integral_constant<int, 15>{});
-                if (c < nb && before < need) keep_key(0);
+                if (c < nb && before < need) keep_key(ul[c]);
                 continue;
             }
         }
@@ -818,9 +937,12 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
 #pragma unroll
             for (int i0 = 0; i0 < kBandSlots; i0 += SG) {
                 if (16 * i0 >= most) break;
+                unsigned key[SG];
 #pragma unroll
-                for (int i = i0; i < i0 + SG; ++i)
-                    if (sc[i] >= Tx) keep_key(i);
+                for (int i = 0; i < SG; ++i) key[i] = ul[c + 16 * (i0 + i)];
+#pragma unroll
+                for (int i = 0; i < SG; ++i)
+                    if (sc[i0 + i] >= Tx) keep_key(key[i]);
             }
             continue;
         }
@@ -841,12 +963,13 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
             const unsigned meq = (unsigned)(__ballot(eq) >> (16 * g)) & 0xffffu;
             const bool take = c + 16 * i < nb && (sc[i] > Tx || (eq && eq_before + __popc(meq & below) < need_eq));
             eq_before += __popc(meq);
-            if (take) keep_key(i);
+            if (take) keep_key(ul[c + 16 * i]);
         }
     }
     __syncthreads();
 
     // ---- emission -----------------------------------------------------------------------------------------------------
+    unsigned words[UT][NWM];                       // the lists as bitmaps
     int out0[UT];
 #pragma unroll
     for (int t = 0; t < UT; ++t) {
@@ -855,15 +978,15 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
         int mine = 0;
 #pragma unroll
         for (int w = 0; w < NWM; ++w) {
+            words[t][w] = 0u;
             if (w < NW) {
-                const unsigned band = wl[t][w] & ~wh[t][w];
-                unsigned more = sel[(t * NW + w) * T + tid];
+                words[t][w] = mine_at[t][w];
                 if (tie) {
-                    more = lowest_set_bits(band, quota);
+                    const unsigned more = lowest_set_bits(band[t][w], quota);
                     quota -= __popc(more);
+                    words[t][w] |= more;
                 }
-                wl[t][w] = wh[t][w] | more;
-                mine += __popc(wl[t][w]);
+                mine += __popc(words[t][w]);
             }
         }
         int all;
@@ -882,7 +1005,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
 #pragma unroll
         for (int w = 0; w < NWM; ++w) {
             if (w < NW) {
-                unsigned m = live ? wl[t][w] : 0u;
+                unsigned m = live ? words[t][w] : 0u;
                 const int key1 = h * Lr + 32 * w - 1;
                 if (!a.direct) {
                     while (m) {
@@ -922,7 +1045,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
                            *V = static_cast<const uint16_t *>(a.attend.V) + head;
             // (from where the image was: the lists are in memory, and the bitmaps still in the registers)
             char *tile = reinterpret_cast<char *>(image);
-            const int total = union_entries<NWM>(wl[0], NW, h * Lr, c < nu, reinterpret_cast<unsigned *>(tile + TileLds(W, a.attend.most).list), s_totl);
+            const int total = union_entries<NWM>(words[0], NW, h * Lr, c < nu, reinterpret_cast<unsigned *>(tile + TileLds(W, a.attend.most).list), s_totl);
             if (!attend_tile(Q + (size_t)u0 * 64, Kx, V, a.attend.O + head + (size_t)u0 * 64, nu, total, a.attend.scale, a.attend.most, tile))
                 attend_listed(a.attend, out, tile, L, keep, n, u0, nu);
         } else if constexpr (GROUP && ATTEND == kAttendBf16) {
@@ -989,6 +1112,8 @@ hipError_t launch_split_t(const dsa_shape &sh, const SplitPlan &p, const int8_t 
     a.wgs_per_head = (sh.L / sh.vec + kTile * UT - 1) / (kTile * UT);
     a.target_l = p.target_l;
     a.target_h = p.target_h;
+    a.low = p.low;
+    a.high = p.high;
     a.direct = (size_t)kTile * UT * sh.keep * 2 > 128 * 1024;
     const SplitLds at(p.W, UT, p.NW, sh.k, GROUP, sh.keep, a.direct != 0, band_slots<GROUP, UT, NWM>());
     size_t lds = at.bytes;

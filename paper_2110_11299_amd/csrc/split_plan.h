@@ -13,13 +13,15 @@ constexpr int kTile = 16;               // units of one matrix instruction
 // Projection dimensions that have a kernel for two tiles.
 constexpr bool split_pairs_exist(int k, bool group) { return k == 64 || (k == 48 && !group); }
 
-struct SplitPlan { int W, NW, UT, NB, target_l, target_h; };
+struct SplitPlan { int W, NW, UT, NB, target_l, target_h; float low, high; };
 
 // Targets.  If a share p of a unit's keys lies above a threshold, a bucket of s keys reaches it with probability
 // 1 - (1 - p)^s; the number of buckets that reach it, given the number x of keys that do, has the mean D(x) below and a
 // variance that is the binomial one less what x explains.  tl is put where keep + z sigma keys are expected above it,
-// th where keep - z sigma are: with z = 3.5 a unit misses in about one case of 2000 (and is then swept again).
-inline void split_targets(int L, int keep, int NW, int NB, int *target_l, int *target_h)
+// th where keep - z sigma are: with z = 3.5 a unit misses in about one case of 4000 (and is then swept again, with its workgroup).
+// In up to two rounds of workgroups nothing makes up for one that takes longer, and z is 4.2: N = 16, L = 4096, keep = 205, groups of 8 28.5 and
+// 24.2 us (2 of 8192 units missed); with more rounds longer bands cost more.
+inline void split_targets(int L, int keep, int NW, int NB, double z, int *target_l, int *target_h)
 {
     if (NW == 1) {                       // every key is its own bucket
         *target_l = keep;
@@ -45,7 +47,7 @@ inline void split_targets(int L, int keep, int NW, int NB, int *target_l, int *t
     };
     const double slope = vx > 0 ? fmax(cov / vx, 1e-6) : 1.0;
     const double sigma = sqrt(fmax(binomial - (vx > 0 ? cov * cov / vx : 0.0), 0.0)) / slope;
-    const double reach = 3.5 * sigma + 1.0;
+    const double reach = z * sigma + 1.0;
     int l = (int)ceil(buckets(keep + reach)), h = (int)floor(buckets(keep - reach));
     if (keep - reach < 1.0) h = 0;
     const int most = (int)(count * NB / 16);
@@ -53,6 +55,25 @@ inline void split_targets(int L, int keep, int NW, int NB, int *target_l, int *t
     h = h > l - 1 ? l - 1 : h;
     *target_l = l;
     *target_h = h;
+}
+
+// Where the histogram of a unit's bucket maxima has its bins: from mean + low * reach to mean + high * reach, reach being the distance from the
+// smallest maximum to the mean.  The place of the maximum that a given share of them reaches depends on little else than the share: the
+// tables are its 0.2 and 99.8 % quantiles over units, the lowest and highest of them over heads of low-rank codes (rank 8 to 64, k = 16 to 64,
+// L = 256 to 16384, with and without high-norm keys, single rows and groups of 8), and a little beyond.  A unit outside of them is swept again.
+inline void split_window(int buckets, int target_l, int target_h, float *low, float *high)
+{
+    constexpr int N = 17;
+    constexpr double share[N] = {0.0, 0.005, 0.015, 0.03, 0.05, 0.08, 0.125, 0.175, 0.25, 0.35, 0.45, 0.55, 0.65, 0.75, 0.85, 0.93, 1.0};
+    constexpr double lowest[N] = {0.40, 0.40, 0.40, 0.36, 0.30, 0.24, 0.20, 0.14, 0.06, -0.07, -0.13, -0.30, -0.46, -0.55, -0.75, -1.0, -1.0};
+    constexpr double highest[N] = {1.9, 1.6, 1.5, 1.5, 1.15, 0.95, 0.82, 0.62, 0.50, 0.30, 0.20, 0.06, -0.03, -0.10, -0.15, -0.25, -0.35};
+    auto at = [&](const double (&y)[N], double x) {
+        int i = 1;
+        while (i < N - 1 && share[i] < x) ++i;
+        return y[i - 1] + (y[i] - y[i - 1]) * fmin((x - share[i - 1]) / (share[i] - share[i - 1]), 1.0);
+    };
+    *low = (float)at(lowest, (double)target_l / buckets);
+    *high = (float)at(highest, (double)target_h / buckets);
 }
 
 // Wavefronts.  A lane's range holds at most 512 keys, which four wavefronts reach up to L = 8192 and eight up to 16384.  More
@@ -118,7 +139,10 @@ inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
         p.W = W2;
     }
     p.NW = (sh.L + 128 * p.W - 1) / (128 * p.W);
-    split_targets(sh.L, sh.keep, p.NW, p.NB, &p.target_l, &p.target_h);
+    const long long waves = heads * ((units + kTile * p.UT - 1) / (kTile * p.UT)) * p.W;
+    split_targets(sh.L, sh.keep, p.NW, p.NB, waves <= 8192 ? 4.2 : 3.5, &p.target_l, &p.target_h);
+    const double ranges = (double)sh.L / (32 * p.NW);
+    split_window(p.NW == 1 ? sh.L : (int)(ranges * p.NB), p.target_l, p.target_h, &p.low, &p.high);
     return p;
 }
 
