@@ -346,7 +346,7 @@ __global__ __launch_bounds__(2 * kGroupWaves *kWave) void attention_groups_bf16(
 }
 
 template <int D, int VEC>
-__global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
+__global__ __launch_bounds__(kGroupWaves *kWave, 4) void attention_units_bf16(
     const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K, const uint16_t *__restrict__ V,
     const int32_t *__restrict__ idx, float *__restrict__ O, int L, int keep, int keep_pad, float scale, unsigned total_units)
 {
@@ -358,7 +358,7 @@ __global__ __launch_bounds__(kGroupWaves *kWave, 3) void attention_units_bf16(
     const unsigned G = L / VEC, n = unit / G, u = unit % G;
     const int32_t *list = idx + (size_t)unit * keep;
     const size_t head = (size_t)n * L * D, first = head + (size_t)u * VEC * D;
-    attend_unit<D>(Q + first, K + head, V + head, [&](int t) { return min(max(list[t], 0), L - 1); }, O + first, VEC, keep, keep_pad, scale, tile);
+    attend_unit<D, true>(Q + first, K + head, V + head, [&](int t) { return min(max(list[t], 0), L - 1); }, O + first, VEC, keep, keep_pad, scale, tile);
 }
 
 // Fine-grained rows in bfloat16, 16 to a workgroup, over the union of their lists (tile_attend.h): what predict_split does with lists that

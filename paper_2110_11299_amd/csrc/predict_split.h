@@ -187,7 +187,7 @@ __device__ __forceinline__ void attend_block_units(const AttendArgs &a, const ui
     const uint16_t *Q = static_cast<const uint16_t *>(a.Q), *K = static_cast<const uint16_t *>(a.K) + head, *V = static_cast<const uint16_t *>(a.V) + head;
     for (int u = wv; u < nu; u += W) {
         const size_t first = head + (size_t)(u0 + u) * vec * D;
-        attend_unit<D>(Q + first, K, V, [&](int t) { return (int)image[u * keep + t]; }, a.O + first, vec, keep, a.pad, a.scale,
+        attend_unit<D, false>(Q + first, K, V, [&](int t) { return (int)image[u * keep + t]; }, a.O + first, vec, keep, a.pad, a.scale,
                        lds + wv * (unit_tile_bytes<D>() + a.pad * 4));
         wave_lds_sync();                   // the next unit overwrites list and tile
     }
@@ -624,13 +624,14 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
     }
 
     // ---- sweep 2: bitmaps of score >= tl and score >= th, until every unit's bracket is good ---------------------------
-    const int smax = (GROUP ? a.vec : 1) * k * 16384;
+    // (the largest product of two codes is -128 * -128, the smallest -128 * 127: with thresholds between these ends no difference reaches 2^24)
+    const int smax = (GROUP ? a.vec : 1) * k * 16384, smin = -(GROUP ? a.vec : 1) * k * 16256;
     int tl[UT], th[UT], blo[UT], bhi[UT], nblo[UT], nbhi[UT];
 #pragma unroll
     for (int t = 0; t < UT; ++t) {
         tl[t] = s_tl[kTile * t + c];
-        th[t] = max(s_th[kTile * t + c], tl[t] + 1);
-        blo[t] = -smax;
+        th[t] = min(max(s_th[kTile * t + c], tl[t] + 1), smax + 1);
+        blo[t] = smin;
         nblo[t] = L;
         bhi[t] = smax + 1;
         nbhi[t] = 0;

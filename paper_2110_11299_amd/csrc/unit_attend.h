@@ -40,7 +40,14 @@ template <int D> constexpr int unit_tile_bytes() { return 32 * 2 * D; }        /
 
 // The unit from its list (key(t): entry t) to its rows of O (both Q and O from the unit's first row on), with a reference that may
 // lag the maximum by a factor of 2^slack.  Returns whether every sum was finite.
-template <int D, typename Key>
+// DIRECT: the gathered rows go straight to LDS, a tile of keys and then one of values, each requested as soon as the operands of the one before it
+// are in registers.  Nothing is on its way while they are waited for, but a KB takes 18 cycles of a CU instead of 25 (L1 and LDS write one after
+// the other), and 22 (D = 64) to 38 registers less leave five and four wavefronts per SIMD instead of four and three, which cover for each other.  Kernel by
+// itself, through registers and so: D = 64, VEC = 4, N = 64, L = 2000, keep = 200 91.5 and 80.1 us (23 TB/s of gathers), VEC = 8, N = 16, L = 4096, keep = 205 28.1 and
+// 26.7, D = 128, N = 16, L = 8192, keep = 82 55.2 and 48.2, VEC = 4, N = 4, L = 4096, keep = 400 44.0 and 35.3.  In the predictor's launch, whose
+// registers leave four wavefronts per SIMD either way, groups of 8 lose (N = 16, L = 4096, keep = 205 44.7 and 49.1 us) and groups of 4 win 2 %: left.
+// Tiles for keys and values, one step ahead: occupancy (87.6, 26.6, 70.5 us).
+template <int D, bool DIRECT, typename Key>
 __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, const uint16_t *V, Key &&key, float *O, int vec,
                                           int keep, int keep_pad, float scale, int lane, char *tile, float slack)
 {
@@ -69,8 +76,8 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
     // are also the tile's rows: the entries come as one or two 16-byte reads
     const int first = lane / LPR * VP;
     const unsigned piece = lane % LPR;
-    v4u kring[VP], vring[VP];
-    auto gather = [&](v4u (&ring)[VP], const char *head, int t0) {
+    v4u kring[DIRECT ? 1 : VP], vring[DIRECT ? 1 : VP];
+    auto gather = [&](auto &ring, const char *head, int t0) {
 #pragma unroll
         for (int r = 0; r < VP; r += 4) {
             const v4u at = *reinterpret_cast<const v4u *>(sl + t0 + first + r);
@@ -78,11 +85,29 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
             for (int i = 0; i < 4; ++i) ring[r + i] = *reinterpret_cast<const v4u *>(head + (at[i] + 16u * piece));
         }
     };
-    auto put = [&](const v4u (&ring)[VP]) {
+    auto put = [&](const auto &ring) {
 #pragma unroll
         for (int r = 0; r < VP; ++r)
             *reinterpret_cast<v4u *>(tile + (first + r) * ROW + 16u * (piece ^ unit_swizzle<D>(first + r))) = ring[r];
     };
+    // DIRECT: request r fills the tile's rows RPI r .. RPI r + RPI - 1 with list entries in order, lane after lane 16 bytes, so that the lane of
+    // place p in a row asks for piece p ^ unit_swizzle of the row (D = 128: another one in even and in odd requests)
+    const unsigned group = lane / LPR, swizzled[2] = {16u * ((lane % LPR) ^ unit_swizzle<D>(group)), 16u * ((lane % LPR) ^ unit_swizzle<D>(RPI + group))};
+    const unsigned base = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) char *)tile);
+    unsigned off[DIRECT ? VP : 1];
+    auto find = [&](int t0) {
+#pragma unroll
+        for (int r = 0; r < VP; ++r) off[r] = sl[t0 + RPI * r + group] + swizzled[r & 1];
+    };
+    auto fetch = [&](const char *head) {
+#pragma unroll
+        for (int r = 0; r < VP; ++r)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(head + off[r]),
+                                             (__attribute__((address_space(3))) void *)(size_t)(base + 1024u * r), 16, 0, 0);
+    };
+    // what was requested is in LDS; what was read from there is in registers, and may be overwritten
+    auto fetched = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+    auto taken = [] { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
     // operands: row c (and 16 + c) of the key rows; of the value rows, the 4 x 4 block that ds_read_tr16_b64 takes from a lane
     const unsigned vrow = 4 * g + (c >> 2), vswz = unit_swizzle<D>(vrow);       // the same for row 16 + vrow
     auto key_piece = [&](int half, int s) {
@@ -98,25 +123,48 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
     for (int ct = 0; ct < CT; ++ct) o[ct] = v4f{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, z = 0.f;
     const float share = 1.f / (float)(keep_pad - keep + 1);      // the list is filled up with copies of its last key
-    gather(kring, Kh, 0);
-    gather(vring, Vh, 0);
+    if constexpr (DIRECT) {
+        find(0);
+        fetch(Kh);
+    } else {
+        gather(kring, Kh, 0);
+        gather(vring, Vh, 0);
+    }
     for (int t0 = 0; t0 < keep_pad; t0 += 32) {
         const int t1 = min(t0 + 32, keep_pad - 32);
-        put(kring);
-        gather(kring, Kh, t1);
-        wave_lds_sync();
+        bf16x8 keys[2][DIRECT ? KS : 1];
+        if constexpr (DIRECT) {
+            fetched();
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+#pragma unroll
+                for (int s = 0; s < KS; ++s) keys[half][s] = key_piece(half, s);
+            taken();
+            fetch(Vh);
+            find(t1);
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            put(kring);
+            gather(kring, Kh, t1);
+            wave_lds_sync();
+        }
         v4f s2[2];
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             s2[half] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                s2[half] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(key_piece(half, s), qop[s], s2[half], 0, 0, 0);
+                bf16x8 key;
+                if constexpr (DIRECT) key = keys[half][s];
+                else key = key_piece(half, s);
+                s2[half] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(key, qop[s], s2[half], 0, 0, 0);
             }
         }
-        wave_lds_sync();
-        put(vring);
-        gather(vring, Vh, t1);
+        if constexpr (!DIRECT) {
+            wave_lds_sync();
+            put(vring);
+            gather(vring, Vh, t1);
+        }
         float mx = fmaxf(s2[0][0], s2[1][0]);
 #pragma unroll
         for (int i = 1; i < 4; ++i) mx = fmaxf(fmaxf(s2[0][i], s2[1][i]), mx);
@@ -156,16 +204,35 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
             lo[i] = (__bf16)fmaf(p[i], 1.00000012f, -__uint_as_float(cut[i]));
         }
         const bf16x8 hi = __builtin_bit_cast(bf16x8, v4u{cut[0] >> 16 | cut[1], cut[2] >> 16 | cut[3], cut[4] >> 16 | cut[5], cut[6] >> 16 | cut[7]});
-        wave_lds_sync();
+        union ValueBlock { s16x4 half[2]; bf16x8 all; };
+        if constexpr (DIRECT) {
+            fetched();
+            ValueBlock vb[CT];
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            union { s16x4 half[2]; bf16x8 all; } vb;
-            vb.half[0] = value_block(0, ct);
-            vb.half[1] = value_block(1, ct);
-            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, vb.all, o[ct], 0, 0, 0);
-            o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, vb.all, o[ct], 0, 0, 0);
+            for (int ct = 0; ct < CT; ++ct) {
+                vb[ct].half[0] = value_block(0, ct);
+                vb[ct].half[1] = value_block(1, ct);
+            }
+            taken();
+            if (t0 + 32 < keep_pad) fetch(Kh);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, vb[ct].all, o[ct], 0, 0, 0);
+                o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, vb[ct].all, o[ct], 0, 0, 0);
+            }
+        } else {
+            wave_lds_sync();
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                ValueBlock vb;
+                vb.half[0] = value_block(0, ct);
+                vb.half[1] = value_block(1, ct);
+                o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, vb.all, o[ct], 0, 0, 0);
+                o[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, vb.all, o[ct], 0, 0, 0);
+            }
+            wave_lds_sync();                  // the next step overwrites the tile
         }
-        wave_lds_sync();                  // the next step overwrites the tile
     }
     z += __shfl_xor(z, 16, kWave);
     z += __shfl_xor(z, 32, kWave);
@@ -189,14 +256,14 @@ __device__ __forceinline__ bool unit_rows(const uint16_t *Q, const uint16_t *K, 
 
 // Weights above 1 may take large values beyond fp32 (from 2^111 / keep on) that weights of at most 1 would not: then once
 // more with a reference that is the maximum.  (That from the start costs up to 13 % of the kernel.)
-template <int D, typename Key>
+template <int D, bool DIRECT, typename Key>
 __device__ __forceinline__ void attend_unit(const uint16_t *Q, const uint16_t *K, const uint16_t *V, Key &&key, float *O, int vec,
                                             int keep, int keep_pad, float scale, char *tile)
 {
     for (float slack = kUnitSlack;; slack = 0.f) {
         int lane = threadIdx.x & (kWave - 1);
         asm volatile("" : "+v"(lane));     // nothing of a round is computed ahead of the loop: that would delay the first gathers
-        if (unit_rows<D>(Q, K, V, key, O, vec, keep, keep_pad, scale, lane, tile, slack) || slack == 0.f) break;
+        if (unit_rows<D, DIRECT>(Q, K, V, key, O, vec, keep, keep_pad, scale, lane, tile, slack) || slack == 0.f) break;
     }
 }
 

@@ -76,6 +76,29 @@ def test_score_orders(dsa, oracle, L, keep):
             check(dsa, oracle, np.ascontiguousarray(Qt[:, :, :Lv]), np.ascontiguousarray(Kt[:, :, :Lv]), keep, vec, name)
 
 
+# where a threshold and a score are as far apart as they get: a group of 8 rows at k = 64 has scores from -8 * 64 * 16256 to 8 * 64 * 16384, and the
+# signs of differences are taken from eight bits that are copies of it below 2^24 only (k = 128: from the sign itself)
+@pytest.mark.parametrize("L", [520, 1040, 4104])
+@pytest.mark.parametrize("k,vec", [(16, 1), (32, 8), (48, 8), (64, 1), (64, 4), (64, 8), (128, 8)])
+def test_extreme_codes(dsa, oracle, L, k, vec):
+    rng = np.random.Generator(np.random.Philox(L + k + vec))
+    Qt = np.full((1, 2, L, k), -128, np.int8)
+    Qt[:, 1] = rng.integers(-128, 128, size=(L, k))
+    Qt[:, :, ::24] = 127
+    Kt = np.where(rng.random((1, 2, L, 1)) < 0.5, -128, 127).astype(np.int8) * np.ones((1, 1, 1, k), np.int8)
+    Kt[:, :, 5::7] = rng.integers(-128, 128, size=Kt[:, :, 5::7].shape)
+    Kt[:, :, 3::11, : k // 2] = 127
+    for keep in (1, L // 50, L // 12, L // 2, L - 3):
+        check(dsa, oracle, Qt, np.ascontiguousarray(Kt), keep, vec, "extreme")
+
+
+# heads that end inside a lane range: the bins' window must not follow buckets that have fewer keys than the others
+@pytest.mark.parametrize("L,k,vec,keep", [(2104, 32, 1, 32), (3680, 16, 1, 40), (7792, 32, 8, 145), (896, 32, 1, 36), (1032, 64, 1, 20)])
+def test_ragged_ranges(dsa, oracle, L, k, vec, keep):
+    x = di.make_inputs(di.custom_config("ragged", B=1, H=2, L=L, d=64, dtype="bf16", rank=32, k=k, vec=vec, keep=keep, seed=L))
+    check(dsa, oracle, x.Qt, x.Kt, keep, vec, "ragged")
+
+
 # the same orders in every kernel: all projection dimensions, 1, 4, 8 and 16 groups per range with one tile, 4 and 8 with two
 @pytest.mark.parametrize("H,L,vec,k,keep", [
     (2, 512, 1, 16, 30), (2, 512, 8, 48, 30), (2, 512, 1, 128, 30), (2, 1600, 1, 48, 90), (2, 1600, 4, 64, 90), (2, 1600, 8, 96, 90),
