@@ -124,6 +124,17 @@ inline bool split_pairs(const dsa_shape &sh, int W2, long long waves)
     return 5 * sh.keep <= 4 * 64 * W2 && sh.keep <= sh.L / 20 + 1;
 }
 
+// Rows go over the union of their lists (tile_most, with the times) if they keep one key in so many, at least; 0: in no case.
+inline int tile_part(const dsa_shape &sh, long long waves)
+{
+    if (sh.vec != 1 || sh.dtype != DSA_BF16 || sh.d != 64 || sh.scale == 0.f || sh.L <= 128 || waves < 2048) return 0;
+    if (sh.L < 640) return 4;
+    if (sh.L < 1024) return waves >= 12288 ? 10 : 8;
+    if (sh.L < 2048) return waves >= 16384 ? 13 : 9;
+    if (sh.L > 5120 || waves < 8192) return 12;
+    return sh.L < 3000 ? 15 : sh.L < 3584 || waves < 12288 ? 16 : 20;
+}
+
 inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
 {
     SplitPlan p{};
@@ -133,7 +144,9 @@ inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
     p.NB = 32;
     p.W = split_waves(sh, tiles);
     const int W2 = sh.L <= 8192 ? 8 : 16;
-    if (pairs && split_pairs(sh, W2, heads * ((units + 2 * kTile - 1) / (2 * kTile)) * W2)) {
+    // (where lists are dense enough for their union, for every k: the attention by itself has no use for k)
+    const bool united = (long long)sh.keep * tile_part(sh, tiles * p.W) >= sh.L;
+    if (pairs && !united && split_pairs(sh, W2, heads * ((units + 2 * kTile - 1) / (2 * kTile)) * W2)) {
         p.UT = 2;
         p.NB = 16;
         p.W = W2;

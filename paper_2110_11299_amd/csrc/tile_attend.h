@@ -3,6 +3,7 @@
 // Device code only; everything is internal to the translation unit that includes it.
 #pragma once
 
+#include "split_plan.h"
 #include "unit_attend.h"
 
 #include <algorithm>
@@ -308,23 +309,34 @@ inline size_t tile_lds_bytes(const dsa_shape &sh, int W, int most)
 //   per CU          N = 1, L = 12600 262 and 278 (147 and 159), N = 2, L = 13000 489 and 506 (274 and 285), N = 4, L = 14500 1260 and 1290
 //                   (742 and 761), L = 15500 1532 and 1435 (966 and 867); a tenth 1008 and 1013 (637 and 619) with N = 4, L = 12600, N = 2,
 //                   L = 13000 606 and 559 (375 and 320).
+//   rounds of      (two wavefronts in turn for every place, and codes of low rank, rank 32, with and without high-norm keys: the unions of uniformly
+//   4096 waves     random codes are longer, and lose 1 to 5 % at 5 %, 0 to 4 % at a sixteenth) 5 %: N = 16, L = 4096 187 to 192 and 179 to 185 (118 and
+//                  114), INT4, both passes of the projection included, 242 and 230, N = 12 140 to 146 and 139 to 147 (92 and 88), N = 32 375 and 361
+//                  (238 and 228), N = 20, L = 3600 208 to 215 and 203 to 205 (117 and 115), N = 16, L = 5000 290 and 275 (181 and 164); a sixteenth: N = 8,
+//                  L = 4096 112 and 106 to 112 (73 and 71), N = 8, L = 5000 181 and 175 (109 and 101), N = 40, L = 3000 318 and 300 (199 and 181), N = 64,
+//                  L = 2048 242 and 226 (150 and 146), N = 20 81 to 87 and 81 to 83 (49 and 51; 7 % 87 and 83, 57 and 53); 5 %, N = 8, L = 4096 99.6 and 101 (58.8 and
+//                  62.2), N = 40, L = 3000 274 and 274 (156 and 161), N = 8, L = 8000 365 and 386 (211 and 213), 6 %, N = 12, L = 6000 340 and 361; a thirteenth: N = 128,
+//                  L = 1024 173 and 164 (102 and 100), N = 100, L = 1500 262 and 244 (163 and 145), but N = 40, L = 1024 62.2 and 62.4 (33.5 and 34.7); a
+//                  tenth: N = 80, L = 700 82.8 and 77.8 (43.3 and 42.5), N = 100, L = 900 139 and 128 (80 and 75); an eighth: N = 96, L = 512 48.2 and 49.4
+//                  (32.4 and 33.0).
 // Wider rows of K and V (d = 128) do not leave the registers, fp32 has no matrix instruction of that rate.
 // A scale of 0 makes 0 * -infinity, no number, of the exponent of a key that a row does not keep: every tile would be done again row by row
 // (N = 16, L = 4096, keep = 410 299 and 431 us, by itself 224 and 349).
 inline int tile_most(const dsa_shape &sh, int W)
 {
-    if (sh.vec != 1 || sh.dtype != DSA_BF16 || sh.d != 64 || sh.scale == 0.f || W < 1 || W > 8 || 2 * sh.L > W * unit_tile_bytes<64>()) return 0;
+    if (W < 1 || W > 8 || 2 * sh.L > W * unit_tile_bytes<64>()) return 0;
     const long long waves = (long long)sh.B * sh.H * ((sh.L + kTileRows - 1) / kTileRows) * W;
-    if (sh.L <= 128 || waves < 2048) return 0;
+    const int part = tile_part(sh, waves);
+    if (!part) return 0;
     const int most = (std::min((long long)sh.L, (long long)kTileRows * sh.keep) + 31) / 32 * 32;
     const size_t lds = tile_lds_bytes(sh, W, most);
     if (lds > 128 * 1024) return 0;
     if (sh.L <= 256) return W == 2 ? most : 0;
-    int part = sh.L < 640 ? 4 : sh.L < 1024 ? 8 : sh.L < 2048 ? 9 : 12;         // of the keys, at least
-    if (waves < 4096) part = std::min(part, W < 8 || sh.L > 1024 ? 5 : sh.L < 768 ? 3 : sh.L < 960 ? 4 : 5);
-    else if (waves > 4096 && waves < 6144 && sh.L < 800) part = std::min(part, 7);
-    if (lds > 80 * 1024 && sh.L < 15000) part = std::min(part, 10);
-    return (long long)sh.keep * part >= sh.L ? most : 0;
+    int share = part;
+    if (waves < 4096) share = std::min(share, W < 8 || sh.L > 1024 ? 5 : sh.L < 768 ? 3 : sh.L < 960 ? 4 : 5);
+    else if (waves > 4096 && waves < 6144 && sh.L < 800) share = std::min(share, 7);
+    if (lds > 80 * 1024 && sh.L < 15000) share = std::min(share, 10);
+    return (long long)sh.keep * share >= sh.L ? most : 0;
 }
 
 }  // namespace
