@@ -58,6 +58,15 @@ def test_lines(ask):
         assert on[2] <= 128 * 1024
 
 
+# from two and three rounds of wavefronts on, (N, L, k, keep): the line, with one key less row by row; and with fewer wavefronts
+@pytest.mark.parametrize("shape,fewer", [((70, 700, 32, 70), 69), ((64, 1024, 16, 79), 63), ((16, 2048, 64, 137), 15), ((11, 3000, 32, 188), 10), ((8, 4096, 32, 256), 7),
+                                         ((12, 4096, 48, 205), 11), ((16, 4096, 32, 205), 11), ((10, 5120, 32, 256), 9)])
+def test_lines_of_several_rounds(ask, shape, fewer):
+    n, L, k, keep = shape
+    on, off, short = ask([shape, (n, L, k, keep - 1), (fewer, L, k, keep)])
+    assert on[1] >= min(L, 16 * keep) and off[1] == 0 and short[1] == 0
+
+
 # where the union is slower by itself than the rows and one launch does not make up for it, (N, L, k, keep): eight wavefronts per tile of a
 # short head, a second round that is mostly empty, one workgroup per CU
 @pytest.mark.parametrize("shape", [(7, 640, 32, 128), (6, 768, 32, 154), (5, 900, 32, 180), (27, 640, 32, 80), (24, 700, 32, 88), (22, 768, 32, 96), (1, 12600, 32, 1050),
