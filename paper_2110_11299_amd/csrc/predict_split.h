@@ -33,6 +33,7 @@
 
 #include "dsa_internal.h"
 #include "predict_api.h"
+#include "split_bounds.h"
 #include "split_plan.h"
 #include "key_rows.h"
 #include "key_stream.h"
@@ -45,7 +46,6 @@
 namespace dsa {
 namespace {
 
-constexpr int kBins = 128;              // histogram bins per unit
 constexpr int kBelow = 4;               // words before them, one for each lane of a unit in a wavefront: what lies below the bins, mostly, goes there without a conflict
 constexpr int kBinStride = kBins + kBelow;      // words from unit to unit: the units' bins start in different banks
 // Keys of one unit's band that are scored, 16 per slot.  Few-level codes make bands of whole plateaus of equal scores, which are swept
@@ -81,7 +81,7 @@ struct SplitLds {
     __host__ __device__ SplitLds(int W, int UT, int NW, int k, bool group, int keep, bool direct, int slots)
     {
         const unsigned U = kTile * UT;
-        tot = 6 * U * 4;                                        // [6][U]: tl, th, need (smallest maximum before), band count, and two spare
+        tot = 6 * U * 4;                                        // [6][U]: tl, th, need (smallest maximum before), band count (flags before), base and shift of the bins
         q = tot + 2 * W * U * 4;                                // [2][W][U]
         hist = q + U * (group ? 2 : 1) * (k + 16);              // [U][parts][k + 16]
         sel = 4 * W * NW + 1;
@@ -306,6 +306,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
     constexpr int U = kTile * UT;
     constexpr int kBandSlots = band_slots<GROUP, UT, NWM>(), kBandCap = 16 * kBandSlots;
     constexpr int SG = kBandStep;
+    constexpr bool AGAIN = split_bins_again(K, GROUP, NWM);              // (K = 0 is no multiple of 16 up to 64)
     constexpr bool COPIES = !((K == 0 || K == 128) && GROUP);            // |score - threshold| < 2^24 (SignMasks)
     // Lanes that fetch a key row of the band, 16 bytes each: the L1 looks a row up once, not once for every 16 bytes.  N = 4, L = 16384, k = 64,
     // keep = 164 band scores and search 51 -> 29 us; N = 16, L = 4096, k = 32, keep = 205 96.8 -> 94.6 in all.  (k = 128: 100 to 800 registers through
@@ -320,7 +321,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int c = lane & 15, g = lane >> 4, h = 4 * wv + g;
     const SplitLds at(W, UT, NW, k, GROUP, keep, a.direct, kBandSlots);
-    int *s_tl = reinterpret_cast<int *>(lds), *s_th = s_tl + U, *s_need = s_th + U, *s_nb = s_need + U;
+    int *s_tl = reinterpret_cast<int *>(lds), *s_th = s_tl + U, *s_need = s_th + U, *s_nb = s_need + U, *s_base = s_nb + U, *s_shift = s_base + U;
     int *s_totl = reinterpret_cast<int *>(lds + at.tot), *s_toth = s_totl + W * U;       // [W][U] each
     unsigned char *s_q = lds + at.q;
     const int qstride = PARTS * (k + 16);
@@ -525,7 +526,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
     // The histogram's bins lie in a window around the thresholds (split_window); what is above goes to the last bin, what is below it, an empty
     // bucket too, to a word of the lane before the bins (mostly: most maxima are, and would otherwise meet in one).  Bins over all
     // maxima, three times the distance from the smallest to the mean, were two to six times as wide and the band half as long again:
-    // N = 16, L = 4096, k = 32, keep = 205 72 keys of a unit instead of 52, the mask 103 -> 97 us.
+    // N = 16, L = 4096, k = 32, keep = 205 72 keys of a unit instead of 54, the mask 103 -> 97 us.
     // (Empty buckets without a branch each: that took the bounds of a wavefront that has some, for which the others wait, from 6 k to 12 k
     // cycles of 48 k.)
     const bool full = nv_all >= 32, none = 4 * wv * Lr >= L;
@@ -568,7 +569,9 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
         }
         __syncthreads();
         // maxima that were added up: NB per full range, or every key
-        const float per_bucket = NWM == 1 ? (float)min(L, 32 * 4 * W) : (float)(NB * (L / Lr));
+        const int added = NWM == 1 ? min(L, 32 * 4 * W) : NB * (L / Lr);
+        SplitBins bins[UT];
+        bool open[UT];                                   // thresholds to be looked for
 #pragma unroll
         for (int t = 0; t < UT; ++t) {
             int mn = INT32_MAX;
@@ -578,63 +581,145 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
                 mn = min(mn, s_totl[x * U + kTile * t + c]);
                 sum += s_sum[x * U + kTile * t + c];
             }
-            const float mean = sum / per_bucket, reach = fmaxf(mean - (float)mn, 0.f);
-            const float range = fminf(fmaxf((a.high - a.low) * reach, 1.f), 1.0e9f);
-            const int shift = max(0, 25 - (int)__clz((int)((unsigned)range | 1u)));     // range >> shift < kBins
-            // (the bins are a power of two wide: what they cover beyond the window lies on both sides of it)
-            const int base = max((int)floorf(mean + a.low * reach) - (((kBins << shift) - (int)range) >> 1), mn);
-            unsigned *uh = hist + (kTile * t + c) * kBinStride + kBelow;
-            if (!none) {
+            bins[t] = window_bins(sum / (float)added, mn, a.low, a.high, !AGAIN);
+            open[t] = true;
+            if (wv == 0 && g == 0) s_need[kTile * t + c] = mn;
+        }
+        // A threshold that lies outside of the window (SplitPlan) is looked for on the other side of it, in another histogram over what is left between
+        // the ends of all maxima and the threshold that was found.  That takes a workgroup 2 to 3 us; sweeps of the keys, which would find it too: keys in eight
+        // clusters, N = 16, L = 8192, k = 64, keep = 82, groups of 8 156 -> 57 us, N = 4, L = 16384, keep = 164 1080 -> 376 (with bins over all maxima, which have
+        // long bands there, 73 and 520), log-normal norms, N = 16, L = 4096, k = 32, keep = 410 138 -> 111 (121).
+        for (int round = 1;; ++round) {
 #pragma unroll
-                for (int b = 0; b < NB; ++b)
-                    atomicAdd(&uh[min(max(__builtin_elementwise_sub_sat(bm[t][b], base) >> shift, -1 - g), kBins - 1)], 1u);
+            for (int t = 0; t < UT; ++t) {
+                unsigned *uh = hist + (kTile * t + c) * kBinStride + kBelow;
+                if (!none && open[t]) {
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) atomicAdd(&uh[max(split_bin(bins[t], bm[t][b]), -1 - g)], 1u);
+                }
+                if (wv == 0 && g == 0) {
+                    s_base[kTile * t + c] = bins[t].base;
+                    s_shift[kTile * t + c] = bins[t].shift;
+                }
             }
-            if (wv == 0 && g == 0) {
-                s_tl[kTile * t + c] = base;
-                s_th[kTile * t + c] = shift;
-                s_need[kTile * t + c] = mn;
+            __syncthreads();
+            // 16 lanes per unit, 8 bins each: th is the lowest bin edge that at most target_h maxima reach, tl the highest
+            // that at least target_l reach
+            for (int b4 = wv; b4 < 4 * UT; b4 += W) {
+                const int u = 4 * b4 + g;
+                v4i *uh = reinterpret_cast<v4i *>(hist + u * kBinStride + kBelow + 8 * c);
+                const v4i x = uh[0], y = uh[1];
+                const int in[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+                const int beyond = row_sum_above(((in[0] + in[1]) + (in[2] + in[3])) + ((in[4] + in[5]) + (in[6] + in[7])));
+                int edge_h = kBins, edge_l = -1;         // in this lane: lowest edge with suffix <= target_h, highest with >= target_l
+                int suffix = beyond;
+#pragma unroll
+                for (int e = 7; e >= 0; --e) {
+                    suffix += in[e];                      // maxima in bins >= 8 c + e
+                    if (suffix <= a.target_h) edge_h = 8 * c + e;
+                    if (suffix >= a.target_l && edge_l < 0) edge_l = 8 * c + e;
+                }
+                // how many of them reach the edges
+                auto reach_low = [&] {
+                    int n = INT32_MAX, s = beyond;
+#pragma unroll
+                    for (int e = 7; e >= 0; --e) {
+                        s += in[e];
+                        n = s >= a.target_l ? min(n, s) : n;
+                    }
+                    return -row_max(-n);
+                };
+                auto reach_high = [&] {
+                    int n = 0, s = beyond;
+#pragma unroll
+                    for (int e = 7; e >= 0; --e) {
+                        s += in[e];
+                        n = s <= a.target_h ? s : n;
+                    }
+                    return row_max(n);
+                };
+                edge_h = -row_max(-edge_h);
+                edge_l = row_max(edge_l);
+                const SplitBins now = {s_base[u], s_shift[u]};
+                const bool below = edge_l < 0, above = edge_h == kBins;
+                int tl = now.base + (max(edge_l, 0) << now.shift), th = now.base + (edge_h << now.shift), flags = 0;
+                if (round == 1) {
+                    if (below) tl = s_need[u];                                                // the smallest maximum
+                    if (above) th = (GROUP ? a.vec : 1) * k * 16384 + 1;                      // above every score
+                    if (AGAIN && __ballot(below || above) != 0) {
+                        const int low = reach_low(), between = (below ? added : low) - reach_high();
+                        if (split_crowded(between, a.target_l, a.target_h)) flags = (below ? 1 : 0) | (above ? 2 : 0);
+                    }
+                } else {
+                    // (as long as it helps: the bracket gets shorter, and has bins of more than one score)
+                    const bool shorter = now.shift > 0 && th - tl <= kBins / 4 << now.shift, was = s_nb[u] != 0;
+                    const int between = reach_low() - reach_high();
+                    if (was && !below && round < kBinRounds && shorter && split_crowded(between, a.target_l, a.target_h)) flags = 4;
+                    if (!was) { tl = s_tl[u]; th = s_th[u]; }
+                }
+                if (AGAIN && __ballot(flags != 0) != 0) {          // (all 16 lanes of a unit have read; the other units are not looked at again)
+                    uh[0] = uh[1] = v4i{0, 0, 0, 0};
+                }
+                if (c == 0) {
+                    s_tl[u] = tl;
+                    s_th[u] = th;
+                    if (AGAIN) s_nb[u] = flags;
+                }
+            }
+            __syncthreads();
+            if constexpr (!AGAIN) break;
+            int flags[UT], any = 0;
+#pragma unroll
+            for (int t = 0; t < UT; ++t) any |= flags[t] = s_nb[kTile * t + c];
+            // every wavefront sees all units: the same outcome everywhere
+            if (__ballot(any != 0) == 0) break;
+            if (round == 1) {
+                // the ends of all maxima, those of ranges that end beyond the head too
+#pragma unroll
+                for (int t = 0; t < UT; ++t) {
+                    int least = INT32_MAX, most = INT32_MIN;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        asm volatile("" : "+v"(bm[t][b]));           // (not computed ahead of the loop)
+                        least = min(least, bm[t][b] != INT32_MIN ? bm[t][b] : INT32_MAX);
+                        most = max(most, bm[t][b]);
+                    }
+                    Halves x = row_halves(least), y = wave_halves(min(x.lower, x.upper));
+                    least = min(y.lower, y.upper);
+                    x = row_halves(most), y = wave_halves(max(x.lower, x.upper));
+                    most = max(y.lower, y.upper);
+                    if (g == 0) {
+                        s_totl[wv * U + kTile * t + c] = least;
+                        s_toth[wv * U + kTile * t + c] = most;
+                    }
+                }
+                __syncthreads();
+            }
+#pragma unroll
+            for (int t = 0; t < UT; ++t) {
+                int lo = s_tl[kTile * t + c], hi = s_th[kTile * t + c];
+                open[t] = flags[t] != 0;
+                if (flags[t] & 1) {
+                    lo = INT32_MAX;
+                    for (int x = 0; x < W; ++x) lo = min(lo, s_totl[x * U + kTile * t + c]);
+                }
+                if (flags[t] & 2) {
+                    hi = INT32_MIN;
+                    for (int x = 0; x < W; ++x) hi = max(hi, s_toth[x * U + kTile * t + c] + 1);
+                }
+                bins[t] = bracket_bins(lo, hi);
             }
         }
-        __syncthreads();
-        // 16 lanes per unit, 8 bins each: th is the lowest bin edge that at most target_h maxima reach, tl the highest
-        // that at least target_l reach
-        for (int b4 = wv; b4 < 4 * UT; b4 += W) {
-            const int u = 4 * b4 + g;
-            const unsigned *uh = hist + u * kBinStride + kBelow + 8 * c;
-            const v4i x = *reinterpret_cast<const v4i *>(uh), y = *reinterpret_cast<const v4i *>(uh + 4);
-            const int bins[8] = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-            int suffix = row_sum_above(((bins[0] + bins[1]) + (bins[2] + bins[3])) + ((bins[4] + bins[5]) + (bins[6] + bins[7])));
-            int edge_h = kBins, edge_l = -1;             // in this lane: lowest edge with suffix <= target_h, highest with >= target_l
-#pragma unroll
-            for (int e = 7; e >= 0; --e) {
-                suffix += bins[e];                        // maxima in bins >= 8 c + e
-                if (suffix <= a.target_h) edge_h = 8 * c + e;
-                if (suffix >= a.target_l && edge_l < 0) edge_l = 8 * c + e;
-            }
-            edge_h = -row_max(-edge_h);
-            edge_l = row_max(edge_l);
-            const int base = s_tl[u], sh = s_th[u];
-            const int top = (GROUP ? a.vec : 1) * k * 16384 + 1;             // above every score
-            if (c == 0) {
-                s_tl[u] = edge_l > 0 ? base + (edge_l << sh) : s_need[u];        // (not in the bins: the smallest maximum)
-                s_th[u] = edge_h == kBins ? top : base + (edge_h << sh);
-            }
-        }
-        __syncthreads();
     }
 
     // ---- sweep 2: bitmaps of score >= tl and score >= th, until every unit's bracket is good ---------------------------
     // (the largest product of two codes is -128 * -128, the smallest -128 * 127: with thresholds between these ends no difference reaches 2^24)
     const int smax = (GROUP ? a.vec : 1) * k * 16384, smin = -(GROUP ? a.vec : 1) * k * 16256;
-    int tl[UT], th[UT], blo[UT], bhi[UT], nblo[UT], nbhi[UT];
+    SplitBracket br[UT];
 #pragma unroll
     for (int t = 0; t < UT; ++t) {
-        tl[t] = s_tl[kTile * t + c];
-        th[t] = min(max(s_th[kTile * t + c], tl[t] + 1), smax + 1);
-        blo[t] = smin;
-        nblo[t] = L;
-        bhi[t] = smax + 1;
-        nbhi[t] = 0;
+        const int tl = s_tl[kTile * t + c];
+        br[t] = {tl, min(max(s_th[kTile * t + c], tl + 1), smax + 1), smin, smax + 1, L, 0};
     }
     // The keys at or above th go to LDS, where the histogram was, and those that are kept of the band, which the registers have, join them there:
     // half the registers of two bitmaps, and nothing to clear or to merge.
@@ -668,10 +753,10 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
                     for (int j = 0; j < TB; ++j)
 #pragma unroll
                         for (int t = 0; t < UT; ++t) {
-                            const v4i x = tile_scores(rows[P], j, t, -tl[t]);
+                            const v4i x = tile_scores(rows[P], j, t, -br[t].tl);
                             v4i y;
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) y[i] = x[i] - (th[t] - tl[t]);
+                            for (int i = 0; i < 4; ++i) y[i] = x[i] - (br[t].th - br[t].tl);
                             if constexpr (COPIES) {
                                 signs.tile(sl[t], 4 * (hb * TB + j), x);
                                 signs.tile(sh[t], 4 * (hb * TB + j), y);
@@ -728,28 +813,9 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
                 nh[t] += vh;
                 band0[t] += x < wv ? vl - vh : 0;
             }
-            const bool good = nh[t] == keep || (nh[t] < keep && nl[t] >= keep && (nl[t] - nh[t] <= kBandCap || th[t] - tl[t] == 1));
-            if (!good) {
+            if (!br[t].good(nl[t], nh[t], keep, kBandCap)) {
                 again = true;
-                const int width = th[t] - tl[t];
-                const bool low = nl[t] < keep, high = nh[t] > keep;      // T lies below tl / at or above th
-                if (low) { bhi[t] = tl[t]; nbhi[t] = nl[t]; }
-                else if (high) { blo[t] = th[t]; nblo[t] = nh[t]; }
-                else { blo[t] = tl[t]; nblo[t] = nl[t]; bhi[t] = th[t]; nbhi[t] = nh[t]; }
-                const int span = bhi[t] - blo[t];
-                if (span == 1 || nblo[t] - nbhi[t] <= kBandCap) {
-                    tl[t] = blo[t];
-                    th[t] = bhi[t];
-                } else if (tries < 2 && low) {           // just missed: a bracket of four times the width beside it
-                    th[t] = bhi[t];
-                    tl[t] = max(blo[t], th[t] - 4 * min(width, 1 << 24));
-                } else if (tries < 2 && high) {
-                    tl[t] = blo[t];
-                    th[t] = min(bhi[t], tl[t] + 4 * min(width, 1 << 24));
-                } else {                                 // the middle third (at least one value): T's bracket shrinks whatever comes out
-                    tl[t] = blo[t] + span / 3;
-                    th[t] = tl[t] + max(1, span / 3);
-                }
+                br[t].move(nl[t], nh[t], keep, kBandCap, tries);
             }
         }
         // every wavefront sees all units: the same outcome everywhere
@@ -762,7 +828,7 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
     bool scored[UT];
 #pragma unroll
     for (int t = 0; t < UT; ++t) {
-        scored[t] = nh[t] < keep && th[t] - tl[t] != 1;
+        scored[t] = nh[t] < keep && br[t].th - br[t].tl != 1;
         uint16_t *ul = list + (kTile * t + c) * kBandCap;
         int pos = band0[t];
 #pragma unroll
@@ -777,8 +843,8 @@ __global__ __launch_bounds__(NWM >= 8 ? 1024 : 512, (split_waves_per_simd<NWM, G
             }
         }
         if (wv == 0 && g == 0) {
-            s_tl[kTile * t + c] = tl[t];
-            s_th[kTile * t + c] = th[t];
+            s_tl[kTile * t + c] = br[t].tl;
+            s_th[kTile * t + c] = br[t].th;
             s_need[kTile * t + c] = keep - nh[t];
             s_nb[kTile * t + c] = scored[t] ? nl[t] - nh[t] : 0;
         }

@@ -13,6 +13,11 @@ constexpr int kTile = 16;               // units of one matrix instruction
 // Projection dimensions that have a kernel for two tiles.
 constexpr bool split_pairs_exist(int k, bool group) { return k == 64 || (k == 48 && !group); }
 
+// Whether a threshold that the first histogram does not have is looked for in a second one.  The maxima stay in registers for it, which ranges of
+// one word, five wavefronts per SIMD, do not have (L = 512, k = 32, 15 more through scratch, mask 21.9 -> 27.0 us), nor groups at k = 16, with four copies of the
+// unit operands (4 more, N = 64, L = 2000, groups of 4 125.3 -> 128.8 in all).
+constexpr bool split_bins_again(int k, bool group, int words) { return words > 1 && !(k == 16 && group); }
+
 struct SplitPlan { int W, NW, UT, NB, target_l, target_h; float low, high; };
 
 // Targets.  If a share p of a unit's keys lies above a threshold, a bucket of s keys reaches it with probability
@@ -58,10 +63,16 @@ inline void split_targets(int L, int keep, int NW, int NB, double z, int *target
 }
 
 // Where the histogram of a unit's bucket maxima has its bins: from mean + low * reach to mean + high * reach, reach being the distance from the
-// smallest maximum to the mean.  The place of the maximum that a given share of them reaches depends on little else than the share: the
-// tables are its 0.2 and 99.8 % quantiles over units, the lowest and highest of them over heads of low-rank codes (rank 8 to 64, k = 16 to 64,
-// L = 256 to 16384, with and without high-norm keys, single rows and groups of 8), and a little beyond.  A unit outside of them is swept again.
-inline void split_window(int buckets, int target_l, int target_h, float *low, float *high)
+// smallest maximum to the mean.  The place of the maximum that a given share of them reaches lies within the tables, if the codes are of low
+// rank: they are its 0.2 and 99.8 % quantiles over units, the lowest and highest of them over heads (rank 8 to 64, k = 16 to 64, L = 256 to 16384,
+// single rows and groups of 8, high-norm keys from L = 1024 on), and a little beyond.  Keys whose norms vary more, or that lie in clusters, put it
+// elsewhere: a few of them move the smallest maximum or the mean.
+//   Otherwise the window is three quarters of the reach wide at least, and where a threshold lies outside of it, a second histogram
+//   has it (predict_split).  Keys of a band, by the tables alone, so, and with bins over all maxima: L = 4096, keep = 205 52, 54 and 71.
+//   No second histogram (once): the window is 1.75 wide, a little more than half of all maxima, and starts a third of the reach below the tables.  The longest band of four
+//   units at L = 512, keep = 51, by the tables alone, so, and over all maxima: 4.7, 9.3 and 14.4 keys (up to 16 are put in order without a search), 5 % of keys with four times
+//   the norm 169, 19 and 32, log-normal norms 254, 15 and 28, keys in eight clusters 35, 13 and 21.
+inline void split_window(int buckets, bool once, int target_l, int target_h, float *low, float *high)
 {
     constexpr int N = 17;
     constexpr double share[N] = {0.0, 0.005, 0.015, 0.03, 0.05, 0.08, 0.125, 0.175, 0.25, 0.35, 0.45, 0.55, 0.65, 0.75, 0.85, 0.93, 1.0};
@@ -72,8 +83,16 @@ inline void split_window(int buckets, int target_l, int target_h, float *low, fl
         while (i < N - 1 && share[i] < x) ++i;
         return y[i - 1] + (y[i] - y[i - 1]) * fmin((x - share[i - 1]) / (share[i] - share[i - 1]), 1.0);
     };
-    *low = (float)at(lowest, (double)target_l / buckets);
-    *high = (float)at(highest, (double)target_h / buckets);
+    double lo = at(lowest, (double)target_l / buckets), hi = at(highest, (double)target_h / buckets);
+    if (once) {
+        lo = fmax(lo - 0.35, -1.0);
+        hi = lo + 1.75;
+    } else if (hi - lo < 0.75) {
+        lo = fmax((lo + hi) / 2 - 0.4, -1.0);
+        hi = lo + 0.75;
+    }
+    *low = (float)lo;
+    *high = (float)hi;
 }
 
 // Wavefronts.  A lane's range holds at most 512 keys, which four wavefronts reach up to L = 8192 and eight up to 16384.  More
@@ -158,7 +177,7 @@ inline SplitPlan split_plan(const dsa_shape &sh, bool pairs)
     const long long waves = heads * ((units + kTile * p.UT - 1) / (kTile * p.UT)) * p.W;
     split_targets(sh.L, sh.keep, p.NW, p.NB, waves <= 8192 ? 4.2 : 3.5, &p.target_l, &p.target_h);
     const double ranges = (double)sh.L / (32 * p.NW);
-    split_window(p.NW == 1 ? sh.L : (int)(ranges * p.NB), p.target_l, p.target_h, &p.low, &p.high);
+    split_window(p.NW == 1 ? sh.L : (int)(ranges * p.NB), !split_bins_again(sh.k, sh.vec > 1, p.NW), p.target_l, p.target_h, &p.low, &p.high);
     return p;
 }
 

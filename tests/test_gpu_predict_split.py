@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import dsa_inputs as di
+from test_split_window_host import codes_of
 
 pytestmark = pytest.mark.gpu
 
@@ -97,6 +98,19 @@ def test_extreme_codes(dsa, oracle, L, k, vec):
 def test_ragged_ranges(dsa, oracle, L, k, vec, keep):
     x = di.make_inputs(di.custom_config("ragged", B=1, H=2, L=L, d=64, dtype="bf16", rank=32, k=k, vec=vec, keep=keep, seed=L))
     check(dsa, oracle, x.Qt, x.Kt, keep, vec, "ragged")
+
+
+# thresholds that the first histogram does not have, below it and above it: in every kernel with a second one (2 to 16 words per lane, one tile and two, ranges
+# that end beyond the head) and in those without (one word; groups at k = 16)
+@pytest.mark.parametrize("H,L,vec,k,keep", [
+    (2, 500, 1, 32, 50), (2, 504, 8, 16, 30), (4, 1600, 1, 16, 90), (4, 1604, 4, 16, 90), (4, 1600, 8, 32, 90), (2, 2104, 1, 48, 32), (2, 2048, 8, 64, 102), (2, 2050, 1, 112, 100),
+    (2, 2048, 4, 128, 60), (4, 4096, 1, 32, 410), (4, 4104, 8, 48, 205), (2, 4096, 1, 64, 82), (1, 4500, 1, 96, 220), (2, 8192, 1, 32, 410), (1, 8200, 8, 64, 400), (1, 12000, 1, 16, 120),
+    (16, 8192, 8, 64, 82), (1, 16384, 1, 64, 164), (1, 16384, 8, 128, 164)])
+def test_thresholds_outside_of_the_window(dsa, oracle, H, L, vec, k, keep):
+    rng = np.random.Generator(np.random.Philox(L + keep + k))
+    for kind in ("5 %", "log-normal", "clusters", "sinks"):
+        Qt, Kt = (np.stack(x)[None].astype(np.int8) for x in zip(*[codes_of(rng, L, k, kind, L) for _ in range(H)]))
+        check(dsa, oracle, Qt, Kt, keep, vec, kind)
 
 
 # the same orders in every kernel: all projection dimensions, 1, 4, 8 and 16 groups per range with one tile, 4 and 8 with two
