@@ -130,7 +130,10 @@ inline int split_waves(const dsa_shape &sh, long long tiles)
 //                9000 139/156, 163/191.  Half a round is enough: L = 4096, N = 2, 24.4 and 23.3; L = 8192, N = 1, 41.4 and 38.1.
 //                (These are of kernels before the bins' window and the gathered signs, which two tiles gain more from: N = 16, L = 4096, 1, 4, 6, 8, 10 % now
 //                118/96, 117/107, 130/123, 137/131, 142/140; 8192, N = 4, 1 and 4 % 105/83, 129/114; 16384, N = 4, 1 % 428/372; a forward, N = 16, L = 4096, 8 %, bf16,
-//                d = 128 457/445, N = 8, fp32, 6 % 312/298.  Beyond four fifths of the buckets of a lane range, 5 to 8 % from L = 5000 on, it stays at one.)
+//                d = 128 457/445, N = 8, fp32, 6 % 312/298.  Beyond four fifths of the buckets of a lane range, 5 to 8 % from L = 5000 on, it stays at one.
+//                So it does beyond 5 % with less than a round of wavefronts, whose attention in the same launch has half the workgroups, L = 4096, N = 3, 7.5 %, fp32, bf16
+//                at d = 128 and at 64 89/102, 92/110 and 62.6/70.5, N = 2, 5.5 % 49.6/52.8, 49.7/53.2, 36.9/40.9 (N = 4 87.2/84.9, 91.8/88.5, 67.4/61.8), and for fp32 lists of more than
+//                384 keys, whose attention does not fit the launch: 9.5 %, N = 4, 8, 16 140/145, 258/276, 509/547; 7.5 % 107/105, 210/200, 411/394.)
 //   groups of 8, k = 64, N L^2 = 2^31, at 1, 2, 3, 4, 8 %: 8192 140/118, 155/138, 174/153, 185/190, 228/243; 12288 152/148, 168/165, 181/182,
 //                194/195, 254/272; 16384 139/130, 153/144, 192/161, 178/223, 297/309.  A quarter of a round: 46.0 and 60.2.  (4096 146/134,
 //                155/146, 166/159, 183/179, but 5000, 2 % 87/99: left at one.)
@@ -143,7 +146,8 @@ inline bool split_pairs(const dsa_shape &sh, int W2, long long waves)
     if (sh.vec > 1) return sh.L > 7168 && 32LL * sh.keep <= sh.L && waves >= 4096;
     if (waves < 2048 || (W2 == 16 && waves > 4096 && waves < 8192)) return false;
     if (sh.k == 48 && NW2 < 8) return false;
-    return 5 * sh.keep <= 4 * 64 * W2 && sh.keep <= sh.L / (sh.k == 64 ? 10 : 20) + 1;
+    const bool dense = sh.k == 64 && waves >= 4096 && (sh.dtype != DSA_F32 || sh.keep <= 384);
+    return 5 * sh.keep <= 4 * 64 * W2 && sh.keep <= sh.L / (dense ? 10 : 20) + 1;
 }
 
 // Rows go over the union of their lists (tile_most, with the times) if they keep one key in so many, at least; 0: in no case.

@@ -97,6 +97,13 @@ def test_shapes(dsa, oracle, launches, dtype, H, L, d, vec, k, keep):
 
 # units of several rows in the kernels of every range length: fp32 of both widths, bf16, 9 to 16 groups per range (four and eight
 # wavefronts), two tiles of units per workgroup
+# two tiles of units per workgroup with lists of 5 to 10 % (k = 64): the longest that fp32 rows have in one launch, one key more, 8 % at d = 128, less than a round
+@pytest.mark.parametrize("launches,dtype,H,d,keep", [(1, "f32", 4, 64, 384), (1, "f32", 4, 128, 384), (1, "f32", 4, 64, 385), (1, "bf16", 4, 128, 330), (1, "bf16", 4, 64, 250),
+                                                     (1, "f32", 3, 64, 206), (1, "bf16", 3, 64, 380)])
+def test_two_tiles(dsa, oracle, launches, dtype, H, d, keep):
+    check(dsa, oracle, launches, dtype, H, 4096, d, 1, 64, keep)
+
+
 @pytest.mark.parametrize("dtype,H,L,d,vec,k,keep", [
     ("f32", 250, 504, 64, 8, 32, 20), ("f32", 256, 512, 128, 8, 32, 20), ("f32", 64, 2044, 128, 4, 16, 40), ("f32", 32, 4088, 64, 8, 16, 40),
     ("f32", 16, 8184, 128, 4, 32, 80), ("f32", 4, 16376, 64, 8, 32, 160), ("f32", 16, 8192, 128, 8, 64, 80), ("bf16", 64, 2004, 64, 4, 16, 150),

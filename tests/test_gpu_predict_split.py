@@ -171,6 +171,7 @@ def test_pairs_of_tiles(dsa, oracle, H, L, vec, k):
                                             (1, 16384, 1, 48, 327), (16, 8192, 8, 64, 256), (8, 8200, 4, 64, 256), (16, 8192, 8, 64, 257),
                                             (4, 4100, 1, 64, 409), (64, 1040, 1, 64, 10), (16, 8192, 8, 48, 82),
                                             (2, 4096, 1, 64, 205), (2, 4095, 1, 64, 1), (3, 4033, 1, 64, 200), (3, 4032, 1, 64, 200), (2, 5041, 1, 64, 253), (2, 5042, 1, 64, 253),
+                                            (4, 4096, 1, 64, 206), (4, 4096, 1, 64, 384), (5, 4040, 1, 64, 300), (4, 5110, 1, 64, 384), (4, 4096, 1, 64, 385), (3, 4096, 1, 64, 206),
                                             (1, 8192, 1, 64, 409), (1, 8066, 1, 48, 400), (2, 16133, 1, 64, 512), (2, 16161, 1, 48, 160),
                                             (17, 8064, 8, 64, 252), (17, 8072, 8, 64, 1), (9, 12280, 8, 64, 300), (5, 16136, 4, 64, 500)])
 def test_pairs_of_tiles_in_the_plan(dsa, oracle, H, L, vec, k, keep):

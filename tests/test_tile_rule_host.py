@@ -35,8 +35,9 @@ def ask(tmp_path_factory):
                     "-o", str(at / "rule")], check=True)
 
     def run(shapes):
-        """shapes: (N, L, k, keep) or with the scale behind it -> (wavefronts, longest union, LDS bytes) of each"""
-        lines = "".join(f"1 {s[0]} {s[1]} 64 {s[2]} {s[3]} 1 1 {s[4] if len(s) > 4 else 0.125}\n" for s in shapes)
+        """shapes: (N, L, k, keep), or with the scale, or scale, type and d behind it -> (wavefronts or, of two tiles, 0, longest union, LDS bytes) of each"""
+        full = [(*s, *(0.125, 1, 64)[len(s) - 4:]) for s in shapes]
+        lines = "".join(f"1 {n} {L} {d} {k} {keep} 1 {dtype} {scale}\n" for n, L, k, keep, scale, dtype, d in full)
         out = subprocess.run([str(at / "rule")], input=lines, capture_output=True, text=True, check=True).stdout.split()
         return [tuple(map(int, out[i:i + 3])) for i in range(0, len(out), 3)]
     return run
@@ -87,3 +88,30 @@ def test_the_route_does_not_depend_on_the_projection(ask):
             taken += 1
             assert len(set(each)) == 1, shape              # and the same wavefronts
     assert taken > 100
+
+
+F32, BF16 = 0, 1
+
+
+def test_two_tiles_at_5_to_10_percent(ask):
+    """At k = 64 the predictor has two tiles of units per workgroup up to 10 %, from a round of wavefronts on, and for fp32 where the attention fits the launch."""
+    def wavefronts(n, keep, dtype, d):
+        return ask([(n, 4096, 64, keep, 0.125, dtype, d)])[0][0]
+    for dtype, d in ((F32, 64), (F32, 128), (BF16, 128), (BF16, 64)):
+        assert wavefronts(3, 205, dtype, d) == 0 and wavefronts(3, 206, dtype, d) > 0 and wavefronts(4, 206, dtype, d) == 0
+    for dtype, d in ((F32, 64), (F32, 128)):
+        assert wavefronts(4, 384, dtype, d) == 0 and wavefronts(4, 385, dtype, d) > 0
+    assert wavefronts(4, 409, BF16, 128) == 0
+
+
+def test_one_tile_for_the_sake_of_the_union(ask):
+    """A shape that would have two tiles of units per workgroup if it were of d = 128, whose rows know no union, has one only if it takes the union."""
+    shapes = [(n, L, keep) for n in (1, 2, 3, 4, 5, 8, 12, 16, 64) for L in (2048, 3584, 4096, 5120, 6144, 7168, 8192, 12288, 16384)
+              for keep in range(L // 25, L // 8, 13)]
+    narrow, wide = (ask([(n, L, 64, keep, 0.125, BF16, d) for n, L, keep in shapes]) for d in (64, 128))
+    ones = 0
+    for shape, (W, most, _), (W128, _, _) in zip(shapes, narrow, wide):
+        if W128 == 0 and W:
+            assert most > 0, shape
+            ones += 1
+    assert ones > 100
