@@ -93,7 +93,8 @@ def test_extreme_codes(dsa, oracle, L, k, vec):
         check(dsa, oracle, Qt, np.ascontiguousarray(Kt), keep, vec, "extreme")
 
 
-# heads that end inside a lane range: the bins' window must not follow buckets that have fewer keys than the others
+# heads that end inside a lane range, whose buckets have fewer keys than the others (the masks; that the thresholds do not follow such buckets, which would
+# cost sweeps, is asked in test_split_window_host.py, at lengths like these)
 @pytest.mark.parametrize("L,k,vec,keep", [(2104, 32, 1, 32), (3680, 16, 1, 40), (7792, 32, 8, 145), (896, 32, 1, 36), (1032, 64, 1, 20)])
 def test_ragged_ranges(dsa, oracle, L, k, vec, keep):
     x = di.make_inputs(di.custom_config("ragged", B=1, H=2, L=L, d=64, dtype="bf16", rank=32, k=k, vec=vec, keep=keep, seed=L))

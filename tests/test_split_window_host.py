@@ -185,11 +185,11 @@ def codes_of(rng, L, k, kind, queries):
 
 # ranges of one word (1, 4 and 8 wavefronts), of 2 to 16, that end at the head and beyond, with one tile and two, groups at k = 16
 @pytest.mark.parametrize("N,L,k,keep,vec", [(2, 128, 16, 13, 1), (2, 256, 16, 26, 1), (96, 384, 32, 38, 1), (96, 512, 32, 26, 1), (96, 512, 32, 51, 1), (200, 500, 32, 25, 4),
-                                            (96, 512, 64, 256, 8), (16, 777, 32, 39, 1), (48, 1000, 32, 50, 4), (64, 2000, 16, 200, 4), (2, 2104, 32, 32, 1), (64, 2048, 32, 102, 8),
+                                            (96, 512, 64, 256, 8), (16, 777, 32, 39, 1), (48, 1000, 32, 50, 4), (64, 2000, 16, 200, 4), (2, 2104, 32, 32, 1), (2, 896, 32, 36, 1), (2, 1032, 64, 20, 1), (2, 3680, 16, 40, 1), (64, 2048, 32, 102, 8),
                                             (16, 4096, 32, 41, 1), (16, 4096, 32, 205, 1), (16, 4096, 32, 205, 8), (16, 4096, 32, 410, 1), (16, 4096, 64, 82, 1), (2, 7792, 32, 145, 8),
                                             (4, 8192, 32, 410, 1), (16, 8192, 64, 82, 8), (4, 16384, 64, 164, 1)])
 def test_sweeps(replay, N, L, k, keep, vec):
-    """No workgroup sweeps its keys more often than with bins over all maxima, and no band gets longer but within what is scored at once."""
+    """Workgroups sweep their keys no more often than with bins over all maxima, and bands get no longer but within what is scored at once."""
     rng = np.random.Generator(np.random.Philox(L + keep))
     for kind in ("plain", "one", "1 %", "5 %", "log-normal", "clusters", "sinks"):
         Qt, Kt = codes_of(rng, L, k, kind, 96 * vec)
