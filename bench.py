@@ -291,7 +291,8 @@ def main() -> int:
                     traffic_source="profiles/bench_C4_hbm_traffic.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, not measured in this run)",
                     valu_busy=profiled_ratio("vector ALU busy", PREDICTOR),
                     mfma_busy=profiled_ratio("matrix-core busy", PREDICTOR),
-                    busy_source="profiles/bench_C4_pmc_counters.md (share of the launch in which the vector ALUs / the matrix cores issue; not measured in this run)",
+                    busy_source="profiles/bench_C4_pmc_counters.md (share of the launch in which the vector ALUs, at four cycles for every instruction, "
+                                "an upper bound since some take two, / the matrix cores issue; not measured in this run)",
                     algorithmic_ops=scores_per_launch, algorithmic_unit="score inspections (N*L*L), one lane operation each",
                     avg_launch_ms=dom["predict_ms"], int8_TOPS=dom["predict_int8_TOPS"],
                     frac_int8=dom["predict_frac_int8"], share_of_step=dom["predict_ms"] / ms_per_step)
@@ -310,7 +311,8 @@ def main() -> int:
     kv_GBs = united / (dom["attention_ms"] * 1e-3) / 1e9
     roofline_attention = dict(kernel="attention_tiles_bf16 (fine-grained SDDMM+softmax+SpMM at C4 over the union of 16 rows' lists: c1-c3)",
                               bound="l2-gather and LDS, one after the other", achieved=kv_GBs, peak=roof_GBs, unit="GB/s", frac=kv_GBs / roof_GBs,
-                              peak_source="dsa_gather_roof timed in this run: same launch shape and 16-byte gathers, no arithmetic",
+                              peak_source="dsa_gather_roof timed in this run: 16-byte gathers row by row through the lists, a wavefront per row, no arithmetic; "
+                                          "another launch shape than the kernel's, compared as bytes per second",
                               gathered_kv_bytes=united, row_by_row_kv_bytes=gathered, gather_probe_ms=gather_ms, avg_launch_ms=dom["attention_ms"],
                               algorithmic_bytes=gather_bytes(cf), compulsory_bytes=compulsory_bytes(cf),
                               compulsory_GBs=dom["attention_compulsory_GBs"],
@@ -365,8 +367,7 @@ def main() -> int:
                                     "one fine-grained pass + one vector-wise 8x1 pass per step",
                            storage="Q,K,V bf16; Q~,K~ int8; idx int32; O fp32",
                            arithmetic="int8 x int8 -> int32 approximate scores (exact); bf16 products with fp32 "
-                                      "accumulation for q.k and p.v (softmax weights for p.v: one bf16 in the fine-grained "
-                                      "pass at this density, the sum of two in the vector-wise one); "
+                                      "accumulation for q.k and p.v (softmax weights for p.v: the sum of two bf16 in both passes); "
                                       "softmax statistics in fp32",
                            heads_seqs_per_step=heads_seqs, seed=cf.seed),
                roofline=roofline, roofline_attention=roofline_attention, cpu_baseline=cpu_baseline, stages=stages, contraction=contraction,

@@ -10,8 +10,8 @@
 //   sweep 1    every lane keeps up to NB = 32 or 16 maxima over disjoint key sets ("buckets").
 //   bounds     from a histogram of the upper part of a unit's maxima in LDS two thresholds tl < th are read off, such that the keep-th
 //              largest score lies between them almost surely: the number of buckets that the x largest keys fall into
-//              is known to a few per cent (section "targets" on the host side).  For short ranges a bucket is one key
-//              and the bounds are certain.
+//              is known to a few per cent (section "targets" on the host side).  What lies outside of the part has a second
+//              histogram.  For short ranges a bucket is one key.
 //   sweep 2    the keys are swept again with -tl as accumulator input: the signs of what comes out and of that less th - tl are two
 //              bitmaps (of NW words per lane; the band between them stays in registers, the other goes to LDS), and their counts.
 //   check      count(>= th) <= keep <= count(>= tl), and few enough keys between (the "band"): else the bracket is
@@ -1137,8 +1137,8 @@ inline size_t attend_lds_bytes(const dsa_shape &sh, int W, int pad)
 // and while some workgroups select (vector issue) others gather (L2): N = 16, L = 4096, keep = 205, bf16, k = 32 232 -> 195 us.
 // Both launches are better (times of two launches and of one):
 //   - if few workgroups have many bytes to gather, where the rows by themselves spread over more CUs.  Single rows: up to 16 KB per
-//     wavefront N = 2, L = 128, keep = 13 11.8 and 11.3; 26 KB, N = 1, L = 512, keep = 51 12.1 and 12.8, fp32, N = 2, L = 256, keep = 26,
-//     11.6 and 12.4; 53 KB, fp32, d = 128, N = 4, L = 512, keep = 26, 12.6 and 14.1.  From 2048 wavefronts on: N = 16, L = 512, keep = 51
+//     wavefront N = 2, L = 128, keep = 13 11.8 and 11.3; 26 KB, N = 1, L = 512, keep = 51 9.0 and 10.4, fp32, N = 2, L = 256, keep = 26, 9.2 and 9.5, N = 4, L = 256 9.2 and
+//     9.6 (in a graph; N = 3, L = 200, keep = 20 10.0 and 9.8, N = 12, L = 128, keep = 13 8.9 and 8.7); 53 KB, fp32, d = 128, N = 4, L = 512, keep = 26, 12.6 and 14.1.  From 2048 wavefronts on: N = 16, L = 512, keep = 51
 //     16.6 and 15.3.
 //   - fp32 rows of groups, 16 or 32 to a wavefront, if the last round of workgroups leaves places of the chip idle for long: if the
 //     share of the idle places, times the bytes of a wavefront, is above 20 KB per round.  Groups of 8, k = 32: N = 60, L = 552, d = 128,
@@ -1150,7 +1150,10 @@ inline size_t attend_lds_bytes(const dsa_shape &sh, int W, int pad)
 //     N = 108, L = 264, keep = 14 (2160) 20.1 and 22.1, k = 48, N = 103, L = 664, keep = 40 (4532) 48.6 and 53.7; within it k = 32, N = 128,
 //     L = 512, keep = 51 36.1 and 32.4, k = 64, N = 29, L = 2128, keep = 62 (3944) 58.0 and 53.3; groups of 8, k = 32: N = 32, L = 8192,
 //     keep = 82 159.7 and 149.0, N = 8, L = 16384, keep = 164 147.8 and 145.1, N = 4, L = 4096, keep = 82 (1024) 23.2 and 24.4.  (200 shapes:
-//     0.6 % behind the better of the two on average; lost are a few like N = 32, L = 5120, keep = 256 (5120), 134.0 and 128.1.)  Above four
+//     0.6 % behind the better of the two on average; lost are a few like N = 32, L = 5120, keep = 256 (5120), 134.0 and 128.1.)  These are of an attention kernel whose
+//     rows went through registers; it takes 5 to 20 % less by itself now, and long lists, of groups of 4 above all, have come to be better in two launches: N = 64, L = 2000, k = 16,
+//     keep = 200, groups of 4 129 and 136, N = 96, L = 1024, keep = 102, groups of 4 67.9 and 69.5, groups of 8, N = 64, L = 4096, keep = 205 165 and 167; the others still in one: N = 64,
+//     L = 2048, keep = 102 59.8 and 58.1, N = 16, L = 4096, keep = 205 51.7 and 49.2, N = 32, L = 8192 154 and 152, groups of 4, N = 128, L = 512 31.9 and 31.1.  Above four
 //     units to a wavefront (N = 512, L = 256, keep = 26, groups of 4, 54.7 and 60.7) and at d = 128, whose registers do not fit, never;
 //   - if a CU does not hold two workgroups: 16 wavefronts, N = 8, L = 16384, keep = 164 1063 and 1106, long lists, bf16, d = 128, N = 2,
 //     L = 8192, keep = 1229 420 and 424, or unions of long lists, d = 64, N = 2, L = 11600, keep = 1200 373 and 469 (but N = 2, L = 16384,

@@ -23,9 +23,10 @@ struct SplitPlan { int W, NW, UT, NB, target_l, target_h; float low, high; };
 // Targets.  If a share p of a unit's keys lies above a threshold, a bucket of s keys reaches it with probability
 // 1 - (1 - p)^s; the number of buckets that reach it, given the number x of keys that do, has the mean D(x) below and a
 // variance that is the binomial one less what x explains.  tl is put where keep + z sigma keys are expected above it,
-// th where keep - z sigma are: with z = 3.5 a unit misses in about one case of 4000 (and is then swept again, with its workgroup).
-// In up to two rounds of workgroups nothing makes up for one that takes longer, and z is 4.2: N = 16, L = 4096, keep = 205, groups of 8 28.5 and
-// 24.2 us (2 of 8192 units missed); with more rounds longer bands cost more.
+// th where keep - z sigma are.  A unit that misses is swept again, with its workgroup.  With z = 3.5 from 8193 wavefronts on, that was one of 4000 workgroups of 16
+// units, replayed on the CPU (L = 2048 to 16384, 1 to 10 %, low-rank codes, with high-norm keys, in clusters).  In up to two rounds of workgroups nothing makes up for
+// one that takes longer, and z is 4.2.  Mask, 3.5 and 4.2: N = 1, L = 16384, k = 64, keep = 164 112 and 95.6 us, N = 2, L = 8192, keep = 410 57.4 and 52.2, N = 4, L = 4096, keep = 41
+// 27.0 and 24.6, N = 64, L = 2048, keep = 102, groups of 8 24.2 and 23.6; 24 others are up to 2 % slower for the longer bands (N = 64, L = 2000, k = 16, groups of 4 46.0 and 46.9).
 inline void split_targets(int L, int keep, int NW, int NB, double z, int *target_l, int *target_h)
 {
     if (NW == 1) {                       // every key is its own bucket

@@ -319,6 +319,12 @@ inline size_t tile_lds_bytes(const dsa_shape &sh, int W, int most)
 //                  L = 1024 173 and 164 (102 and 100), N = 100, L = 1500 262 and 244 (163 and 145), but N = 40, L = 1024 62.2 and 62.4 (33.5 and 34.7); a
 //                  tenth: N = 80, L = 700 82.8 and 77.8 (43.3 and 42.5), N = 100, L = 900 139 and 128 (80 and 75); an eighth: N = 96, L = 512 48.2 and 49.4
 //                  (32.4 and 33.0).
+//   the line at    codes of low rank cross at 4 to 5 %, uniformly random ones at 5.5 to 6 %, and it lies between.  In one launch, low rank and random:
+//   5 %            N = 16, L = 4096 4 % 184/184 and 183/191, 4.5 % 188/180 and 181/192, 5 % 192/186 and 193/199, 5.5 % 212/196 and 210/211; N = 32 4 % 348/337 and 348/360,
+//                  5 % 390/375 and 386/388; N = 12 4 % 135/134 and 130/139, 5 % 153/147 and 147/152; N = 16, L = 3600 4.5 % 168/166 and 167/175, 5 % 172/171 and 173/181, 5.5 %
+//                  183/179 and 182/186; N = 20, L = 4500 4.5 % 285/286 and 288/298, 5 % 309/299 and 312/318; N = 16, L = 5000 4 % 265/260 and 257/271, 5 % 291/281 and 292/300.
+//                  (Norms that vary and clusters make unions shorter: N = 16, L = 4096, 5 %, log-normal norms 204/170, 5 % of the keys with four times the norm 190/175, eight
+//                  clusters 203/196.)
 // Wider rows of K and V (d = 128) do not leave the registers, fp32 has no matrix instruction of that rate.
 // A scale of 0 makes 0 * -infinity, no number, of the exponent of a key that a row does not keep: every tile would be done again row by row
 // (N = 16, L = 4096, keep = 410 299 and 431 us, by itself 224 and 349).

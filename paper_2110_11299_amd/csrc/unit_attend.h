@@ -15,15 +15,16 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // A unit of vec rows (8 or 4) with bfloat16 inputs by one wavefront, in one pass over the unit's keys: key and value rows of a step
-// of 32 keys are gathered together, one step ahead, and pass through one tile in LDS, the keys first.  Scores as in
+// of 32 keys pass through one tile in LDS, the keys first, gathered together and one step ahead, or (DIRECT, below) each in turn.  Scores as in
 // attention_groups_bf16, but they stay in the lane that owns them (query c, keys 4g..4g+3 of both tiles), which is where the second
 // product wants its weights: neither scores nor weights pass through LDS.  The exponentials are taken relative to a running
 // reference that is moved only when a score exceeds it by a factor of 2^kUnitSlack, so that a step needs no reduction across lanes.
 // Every list length fits (4 bytes per key and wavefront; 96 KB of LDS with 4096 keys at D = 128).
 //
-// What bounds it: LDS (8 writes of 14.3 cycles, 4 reads of 4.7 and 8 of 2.8 per step and CU) and vector issue (62 % of the time at
-// N = 64, L = 2000, keep = 200, VEC = 4), next to them the latency of list -> gather -> tile for short lists.
-// Measured (kernel alone): that shape 213 -> 94 us against one row per wavefront (attention_rows), which gathers the four
+// What bounds it, in the predictor's launch: LDS (8 writes of 14.3 cycles, 4 reads of 4.7 and 8 of 2.8 per step and CU) and vector issue (62 % of the time at
+// N = 64, L = 2000, keep = 200, VEC = 4), next to them the latency of list -> gather -> tile for short lists.  By itself (DIRECT): the L1, and the latency of a
+// gather that nothing of the same wavefront hides.
+// Measured (kernel alone, rows through registers): that shape 213 -> 94 us against one row per wavefront (attention_rows), which gathers the four
 // times 3.3 GB; VEC = 8, N = 16, L = 4096, keep = 205: 44.7 -> 29 us, N = 64, L = 2048, keep = 102: 51 -> 35 us, D = 128,
 // N = 16, L = 8192, keep = 82: 72.6 -> 55 us against two passes with the scores in LDS.  A key and a value tile side by side
 // cost occupancy at D = 128 (59 us); rows padded to 16 bytes more instead of swizzled: 96 us at the first shape.
@@ -43,7 +44,7 @@ template <int D> constexpr int unit_tile_bytes() { return 32 * 2 * D; }        /
 // DIRECT: the gathered rows go straight to LDS, a tile of keys and then one of values, each requested as soon as the operands of the one before it
 // are in registers.  Nothing is on its way while they are waited for, but a KB takes 18 cycles of a CU instead of 25 (L1 and LDS write one after
 // the other), and 22 (D = 64) to 38 registers less leave five and four wavefronts per SIMD instead of four and three, which cover for each other.  Kernel by
-// itself, through registers and so: D = 64, VEC = 4, N = 64, L = 2000, keep = 200 91.5 and 80.1 us (23 TB/s of gathers), VEC = 8, N = 16, L = 4096, keep = 205 28.1 and
+// itself, through registers and so: D = 64, VEC = 4, N = 64, L = 2000, keep = 200 92 to 94 and 80 to 84 us (by box; up to 23 TB/s of gathers), VEC = 8, N = 16, L = 4096, keep = 205 28.1 and
 // 26.7, D = 128, N = 16, L = 8192, keep = 82 55.2 and 48.2, VEC = 4, N = 4, L = 4096, keep = 400 44.0 and 35.3.  In the predictor's launch, whose
 // registers leave four wavefronts per SIMD either way, groups of 8 lose (N = 16, L = 4096, keep = 205 44.7 and 49.1 us) and groups of 4 win 2 %: left.
 // Tiles for keys and values, one step ahead: occupancy (87.6, 26.6, 70.5 us).
