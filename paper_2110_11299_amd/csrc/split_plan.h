@@ -70,7 +70,7 @@ inline void split_targets(int L, int keep, int NW, int NB, double z, int *target
 // elsewhere: a few of them move the smallest maximum or the mean.
 //   Otherwise the window is three quarters of the reach wide at least, and where a threshold lies outside of it, a second histogram
 //   has it (predict_split).  Keys of a band, by the tables alone, so, and with bins over all maxima: L = 4096, keep = 205 52, 54 and 71.
-//   No second histogram (once): the window is 1.75 wide, a little more than half of all maxima, and starts a third of the reach below the tables.  The longest band of four
+//   No second histogram (once): the window is 1.75 times the reach wide, where 3 cover nearly all maxima, and starts a third of it below the tables.  The longest band of four
 //   units at L = 512, keep = 51, by the tables alone, so, and over all maxima: 4.7, 9.3 and 14.4 keys (up to 16 are put in order without a search), 5 % of keys with four times
 //   the norm 169, 19 and 32, log-normal norms 254, 15 and 28, keys in eight clusters 35, 13 and 21.
 inline void split_window(int buckets, bool once, int target_l, int target_h, float *low, float *high)
